@@ -107,14 +107,113 @@ __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __r
 }
 
 // ------------------------------------------------------------------------
-// RMSNorm -> 1x128 FP8.  A team of kTeam threads owns a row and keeps it in registers
-// between the two phases (a thread holds 16-element pieces, one per 16 kTeam columns):
-//   1. sum of squares in binary64 (the square of a bf16 value is exact there), reduced over
-//      the team; mean rounded once to binary32; r = 1 / sqrt(mean + eps) in binary32;
+// RMSNorm -> 1x128 FP8.
+//   1. sum of squares in binary64 (the square of a bf16 value is exact there); mean rounded once
+//      to binary32; r = 1 / sqrt(mean + eps) in binary32;
 //   2. n = bf16(x r), h = bf16(gamma n), quantized per 128-group.
-// kTeam = 64 (a wave per row, four rows per workgroup, no barrier, up to 128 bytes per lane in
-// flight) for rows up to 8192 columns; kTeam = 256 (the workgroup, one barrier) beyond.
+// Rows up to 8192 columns add their squares in one order whatever kernel runs, so that a row's bytes do not
+// depend on the batch it is in: a piece = 8 columns, ascending; lane i of 64 takes the pieces 2i and 2i+1 of
+// every 1024 columns, ascending; then the 64 lanes by wave_sum.
 // ------------------------------------------------------------------------
+__device__ __forceinline__ double double_of(uint32_t lo, uint32_t hi) {
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return v + double_of(lo, hi);
+}
+// sum over the 64 lanes, the same value in every lane: neighbours, then quads, octets, 16-lane rows and halves
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = double_of(lo[0], hi[0]) + double_of(lo[1], hi[1]);
+    }
+    {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        v = double_of(lo[0], hi[0]) + double_of(lo[1], hi[1]);
+    }
+    return v;
+}
+__device__ __forceinline__ float rms_factor(double ss, int K, float eps) {
+    const float ms = (float)(ss / (double)K);
+    return 1.0f / sqrtf(ms + eps);
+}
+
+__device__ __forceinline__ void unpack8(uint4 u, float (&v)[8]) {
+    v[0] = bf16_lo(u.x); v[1] = bf16_hi(u.x);
+    v[2] = bf16_lo(u.y); v[3] = bf16_hi(u.y);
+    v[4] = bf16_lo(u.z); v[5] = bf16_hi(u.z);
+    v[6] = bf16_lo(u.w); v[7] = bf16_hi(u.w);
+}
+__device__ __forceinline__ double piece_of(const float* v) {
+    double p = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p = fma((double)v[i], (double)v[i], p);
+    return p;
+}
+
+// A workgroup of K / 8 threads (whole waves) per row, one piece per thread (K <= 8192): for few rows, where a
+// call is bound by its chain of latencies (launch, first loads, instruction fetch, reduction, division), not by bytes.
+__global__ __launch_bounds__(1024) void rmsnorm_quant_row_kernel(const uint16_t* __restrict__ x,
+                                                                 const uint16_t* __restrict__ gamma, float eps,
+                                                                 int K, uint8_t* __restrict__ q,
+                                                                 float* __restrict__ s) {
+    __shared__ double2 pieces[512];
+    const int t = threadIdx.x, l = t & 63;
+    const long m = blockIdx.x;
+    const int n_pieces = K >> 3;
+    const bool mine = t < n_pieces;                      // whole 16-lane rows: K is a multiple of 128
+    float v[8], gm[8];
+    uint4 gu = {0, 0, 0, 0};
+    if (mine) {
+        const uint4 xu = *reinterpret_cast<const uint4*>(x + m * K + t * 8);
+        gu = *reinterpret_cast<const uint4*>(gamma + t * 8);
+        unpack8(xu, v);
+        reinterpret_cast<double*>(pieces)[t] = piece_of(v);
+    }
+    __syncthreads();
+    double ss = 0.0;
+    for (int i = l; 2 * i < n_pieces; i += 64) {         // the 64 pairs of pieces of each 1024 columns
+        const double2 p = pieces[i];
+        ss += p.x;
+        ss += p.y;
+    }
+    const float r = rms_factor(wave_sum(ss), K, eps);
+    if (!mine) return;
+    unpack8(gu, gm);
+    float am = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const uint32_t n2 = bf16_pack2(v[i] * r, v[i + 1] * r);
+        const uint32_t h2 = bf16_pack2(gm[i] * bf16_lo(n2), gm[i + 1] * bf16_hi(n2));
+        v[i] = bf16_lo(h2);
+        v[i + 1] = bf16_hi(h2);
+        am = fmaxf(am, fmaxf(fabsf(v[i]), fabsf(v[i + 1])));
+    }
+    const GroupScale gs = make_scale(team16_max(am));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = div_by_scale(v[i], gs);
+    uint2 o;
+    o.x = e4m3_pack4(v[0], v[1], v[2], v[3]);
+    o.y = e4m3_pack4(v[4], v[5], v[6], v[7]);
+    *reinterpret_cast<uint2*>(q + m * K + t * 8) = o;
+    if ((t & 15) == 0) s[m * (K >> 7) + (t >> 4)] = gs.S;
+}
+
+// A team of kTeam threads per row, which stays in registers (a thread holds 16-element chunks, one per
+// 16 kTeam columns): kTeam = 64, a wave per row and four rows per workgroup without a barrier, for rows up
+// to 8192 columns; kTeam = 256 (the workgroup, one barrier) beyond.
 template <int kTeam, int MAXCH>
 __global__ __launch_bounds__(256) void rmsnorm_quant_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ gamma, float eps,
@@ -137,19 +236,17 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_kernel(const uint16_t* __re
     for (int c = 0; c < MAXCH; ++c) {
         const int k0 = (c * kTeam + lane) * 16;
         if (k0 < K) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) ss = fma((double)v[c][i], (double)v[c][i], ss);
+            ss += piece_of(v[c]);
+            ss += piece_of(v[c] + 8);
         }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) ss += __shfl_xor(ss, d, 64);
+    ss = wave_sum(ss);
     if (kTeam == 256) {
         if ((t & 63) == 0) part[t >> 6] = ss;
         __syncthreads();
         ss = (part[0] + part[1]) + (part[2] + part[3]);
     }
-    const float ms = (float)(ss / (double)K);
-    const float r = 1.0f / sqrtf(ms + eps);
+    const float r = rms_factor(ss, K, eps);
 #pragma unroll
     for (int c = 0; c < MAXCH; ++c) {
         const int k0 = (c * kTeam + lane) * 16;
@@ -259,6 +356,14 @@ hipError_t launch_rmsnorm_quant(const void* x, const void* gamma, float eps, lon
     const uint16_t* gp = static_cast<const uint16_t*>(gamma);
 #define JET_RMS(TEAM, N, GRID) \
     hipLaunchKernelGGL((rmsnorm_quant_kernel<TEAM, N>), dim3((unsigned)(GRID)), dim3(256), 0, st, xp, gp, eps, M, (int)K, q, s)
+    // Few rows: a wave per row would leave its CU with one wave that runs 64 elements and 8 KB of cold
+    // instructions one after the other.  4096 columns, captured back to back: 6.2 -> 2.8 us at 8 rows, 6.3 -> 3.2 at
+    // 256, 6.8 -> 5.8 at 1000; at 2048 rows the barrier costs more than it gives (9.7 against 8.7).
+    if (K <= 8192 && M <= 1024) {
+        const unsigned threads = (unsigned)((K / 8 + 63) / 64 * 64);
+        hipLaunchKernelGGL(rmsnorm_quant_row_kernel, dim3((unsigned)M), dim3(threads), 0, st, xp, gp, eps, (int)K, q, s);
+        return hipGetLastError();
+    }
     if (K <= 8192) {
         const int chunks = (int)((K + 1023) / 1024);
         const long grid = (M + 3) / 4;

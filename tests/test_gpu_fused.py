@@ -94,6 +94,21 @@ def test_rmsnorm_quant(jet, M, K, eps):
     _same("s_row", host(got["s_row"]), want["s_row"])
 
 
+@pytest.mark.parametrize("K", [128, 640, 1024, 1152, 5120, 8064, 8192])
+def test_rmsnorm_quant_row_bytes_do_not_depend_on_the_batch(jet, K):
+    """1 to 1024 rows run a workgroup per row, more a wave per row: both equal the oracle, and a row has the
+    same bytes in either (one order of the binary64 sum)."""
+    M = 1025
+    x = ji.activations(M, K, seed=1700 + K)
+    gamma = ji.norm_weight(K, seed=1701 + K)
+    gd = dev_bf16(gamma.reshape(1, K)).reshape(K)
+    want = orc.rmsnorm_quant(x, gamma, 1e-6)
+    for rows in (1, 3, 1024, 1025):
+        got = jet.rmsnorm_quant(dev_bf16(x[M - rows:]), gd, 1e-6)
+        _same(f"q_row, {rows} rows", host(got["q_row"]), want["q_row"][M - rows:])
+        _same(f"s_row, {rows} rows", host(got["s_row"]), want["s_row"][M - rows:])
+
+
 def test_rmsnorm_quant_many_rows_of_the_hidden_size(jet):
     """4096 rows of the 8B-class hidden size: every row has its own mean, so a wrong rounding of the
     mean, the root or the reciprocal would show in some row."""
