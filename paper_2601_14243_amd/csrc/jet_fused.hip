@@ -55,14 +55,9 @@ __device__ __forceinline__ void quantize_store(float (&v)[16], uint8_t* q16, flo
     for (int i = 0; i < 16; ++i) am = fmaxf(am, fabsf(v[i]));
     am = team8_max(am);
     const GroupScale gs = make_scale(am);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = div_by_scale(v[i], gs);
-    uint4 o;
-    o.x = e4m3_pack4(v[0], v[1], v[2], v[3]);
-    o.y = e4m3_pack4(v[4], v[5], v[6], v[7]);
-    o.z = e4m3_pack4(v[8], v[9], v[10], v[11]);
-    o.w = e4m3_pack4(v[12], v[13], v[14], v[15]);
-    *reinterpret_cast<uint4*>(q16) = o;
+    uint32_t o[4];
+    encode<kBf16Values>(v, gs, o);
+    *reinterpret_cast<uint4*>(q16) = uint4{o[0], o[1], o[2], o[3]};
     if (leader) *s1 = gs.S;
 }
 
@@ -202,12 +197,9 @@ __global__ __launch_bounds__(1024) void rmsnorm_quant_row_kernel(const uint16_t*
         am = fmaxf(am, fmaxf(fabsf(v[i]), fabsf(v[i + 1])));
     }
     const GroupScale gs = make_scale(team16_max(am));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = div_by_scale(v[i], gs);
-    uint2 o;
-    o.x = e4m3_pack4(v[0], v[1], v[2], v[3]);
-    o.y = e4m3_pack4(v[4], v[5], v[6], v[7]);
-    *reinterpret_cast<uint2*>(q + m * K + t * 8) = o;
+    uint32_t o[2];
+    encode<kBf16Values>(v, gs, o);
+    *reinterpret_cast<uint2*>(q + m * K + t * 8) = uint2{o[0], o[1]};
     if ((t & 15) == 0) s[m * (K >> 7) + (t >> 4)] = gs.S;
 }
 

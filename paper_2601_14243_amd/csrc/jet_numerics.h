@@ -44,50 +44,69 @@ __device__ __forceinline__ uint32_t bf16_pack2(float lo, float hi) {
 
 // Scale of a group and the data needed to divide by it.
 struct GroupScale {
-    float S;    // amax / 448, or 1 for an all-zero group
-    float r;    // correctly rounded 1/S (used only when `fast`)
-    bool fast;  // S far from the binary32 range limits
+    float S;     // amax / 448, or 1 for an all-zero group
+    float r;     // correctly rounded 1/S
+    bool plain;  // S far from the binary32 range limits
 };
 
 __device__ __forceinline__ GroupScale make_scale(float amax) {
     GroupScale g;
     g.S = (amax == 0.0f) ? 1.0f : amax / kDeltaMax;  // IEEE division
-    g.fast = (g.S >= 0x1p-80f) && (g.S <= 0x1p80f);
+    g.plain = (g.S >= 0x1p-80f) && (g.S <= 0x1p80f);
     g.r = 1.0f / g.S;                                // IEEE division
     return g;
 }
 
-// t = x / S, correctly rounded.  With r = RN(1/S), q0 = RN(x r) and two
-// fma residual corrections give RN(x/S) (Markstein's division theorem: the
-// first correction makes q faithful, the second makes it correctly rounded)
-// as long as nothing leaves the normal range, which `fast` guarantees for
-// every t that can round to a non-zero code; otherwise the compiler's IEEE
-// division sequence is used.  fma(+0, r, -0) would lose the sign of a zero
-// input, so the sign of x is copied back.
-__device__ __forceinline__ float div_by_scale(float x, const GroupScale& g) {
-    if (g.fast) {
-        float q = x * g.r;
-        float e = __builtin_fmaf(-g.S, q, x);
-        q = __builtin_fmaf(e, g.r, q);
-        e = __builtin_fmaf(-g.S, q, x);
-        q = __builtin_fmaf(e, g.r, q);
-        return __builtin_copysignf(q, x);
+// Where the values of a group come from, which decides how much of the division they need.
+enum ValueKind { kBf16Values, kFloatValues };
+
+// Four values of a group of plain scale -> four E4M3 codes (little-endian): the E4M3 rounding of
+// t = RN(x / S).  With r = RN(1/S), q0 = RN(x r) and an fma residual correction, q1 is RN of x/S moved by less than
+// 2^-22 ulp; a second correction gives RN(x/S) itself (Markstein's division theorem), as long as nothing leaves the
+// normal range, which a plain scale guarantees for every t that can round to a non-zero code.  q1 and t can only
+// round to different codes if x/S lies within 2^-22 ulp of half an ulp beside an E4M3 rounding boundary: no pair of a
+// bf16 x and the bf16 amax of its group does (the tests run every such pair through the row and the tile quantizer),
+// so one correction does for bf16 values; binary32 values take both.
+// The residual has the sign of q S - x, so that a zero input keeps its sign: -(+0) r + (-0) = -0.
+// |t| <= 448 (1 + 2^-22), which rounds to 448: the convert (round to nearest even, also into the subnormal
+// range, sign of zero kept, no saturation: NaN beyond 464) needs no clamp here.
+template <ValueKind kKind>
+__device__ __forceinline__ uint32_t codes4(float a, float b, float c, float d, float S, float r) {
+    float x[4] = {a, b, c, d}, q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        q[i] = x[i] * r;
+        q[i] = __builtin_fmaf(-__builtin_fmaf(q[i], S, -x[i]), r, q[i]);
+        if (kKind == kFloatValues) q[i] = __builtin_fmaf(-__builtin_fmaf(q[i], S, -x[i]), r, q[i]);
     }
-    return x / g.S;
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(q[0], q[1], 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(q[2], q[3], w, true);
+    return (uint32_t)w;
 }
 
-// Four binary32 values -> four E4M3 codes (little-endian in the result).
-// The hardware convert rounds to nearest even, also into the subnormal range,
-// and keeps the sign of zero; it does not saturate, so the value is clamped to
-// +-448 first (every value in (448, 464) rounds to 448 anyway).
-__device__ __forceinline__ uint32_t e4m3_pack4(float a, float b, float c, float d) {
-    a = __builtin_amdgcn_fmed3f(a, -kDeltaMax, kDeltaMax);
-    b = __builtin_amdgcn_fmed3f(b, -kDeltaMax, kDeltaMax);
-    c = __builtin_amdgcn_fmed3f(c, -kDeltaMax, kDeltaMax);
-    d = __builtin_amdgcn_fmed3f(d, -kDeltaMax, kDeltaMax);
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-    w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
+// The same for any scale: IEEE division, clamp to +-448 (a subnormal S may be off by more than 3 %; every value in
+// (448, 464) rounds to 448 anyway), convert.
+__device__ __forceinline__ uint32_t codes4_any(float a, float b, float c, float d, float S) {
+    float x[4] = {a, b, c, d};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        x[i] = __builtin_amdgcn_fmed3f(__builtin_copysignf(x[i] / S, x[i]), -kDeltaMax, kDeltaMax);
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], 0, false);
+    w = __builtin_amdgcn_cvt_pk_fp8_f32(x[2], x[3], w, true);
     return (uint32_t)w;
+}
+
+// N values of one group -> N / 4 words of codes.  One branch per group and not per element, so that the
+// elements' chains overlap.
+template <ValueKind kKind, int N>
+__device__ __forceinline__ void encode(const float (&v)[N], const GroupScale& g, uint32_t (&o)[N / 4]) {
+    if (g.plain) {
+#pragma unroll
+        for (int i = 0; i < N; i += 4) o[i / 4] = codes4<kKind>(v[i], v[i + 1], v[i + 2], v[i + 3], g.S, g.r);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 4) o[i / 4] = codes4_any(v[i], v[i + 1], v[i + 2], v[i + 3], g.S);
+    }
 }
 
 // Four E4M3 codes of one dword -> binary32 (exact).
@@ -98,11 +117,16 @@ __device__ __forceinline__ void e4m3_unpack4(uint32_t w, float& a, float& b, flo
     a = lo[0]; b = lo[1]; c = hi[0]; d = hi[1];
 }
 
+// max of non-negative floats (never NaN: they start from 0 through fmaxf), compared as integers so that the
+// lane permutation folds into the instruction
+__device__ __forceinline__ float max_nonneg(float a, float b) {
+    const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    return __uint_as_float(x > y ? x : y);
+}
 // max over a team of 8 / 16 consecutive lanes (all lanes of the team get it).
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float v) {
-    int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true);
-    return fmaxf(v, __int_as_float(o));
+    return max_nonneg(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)));
 }
 __device__ __forceinline__ float team8_max(float v) {
     v = dpp_max<0xB1>(v);   // quad_perm [1,0,3,2]

@@ -88,6 +88,35 @@ def test_every_bf16_amax_and_special_values(jet):
     _cmp("row-only s", host(got_row["s_row"]), want["s_row"])
 
 
+@pytest.mark.parametrize("M,K", [(128, 128), (256, 384)])
+def test_groups_of_extreme_scale_next_to_ordinary_ones(jet, M, K):
+    """Groups whose scale needs the IEEE division in tiles, waves and rows where the others do not: rows and
+    columns of 2^-110 and 2^110, a 128x128 block of each, and FP8-saved rows with such scales."""
+    xf = ji.bf16_bits_to_f32(ji.activations(M, K, seed=M + K)).copy()
+    for i, f in ((5, 2.0 ** -110), (77, 2.0 ** 110), (M - 1, 2.0 ** -125)):
+        xf[i] *= np.float32(f)
+    xf[:, 9] *= np.float32(2.0 ** -115)
+    xb = ji.f32_to_bf16_bits(xf)
+    for row, col in ((True, True), (True, False), (False, True)):
+        want = orc.quant_act(xb, row=row, col=col)
+        got = jet.quant_act(dev_bf16(xb), row=row, col=col)
+        for k in want:
+            _cmp(f"{k} row={row} col={col}", host(got[k]), want[k])
+    first = orc.quant_act(xb)
+    for row, col in ((True, True), (True, False), (False, True)):
+        want = orc.quant_act(first["q_row"], first["s_row"], src=orc.SRC_FP8_ROW, row=row, col=col)
+        got = jet.quant_act(dev(first["q_row"]), dev(first["s_row"]), row=row, col=col)
+        for k in want:
+            _cmp(f"fp8 {k} row={row} col={col}", host(got[k]), want[k])
+    wf = ji.bf16_bits_to_f32(ji.weights(M, K, seed=8)).copy()
+    wf[:128, :128] *= np.float32(2.0 ** -118)
+    wf[-128:, -128:] *= np.float32(2.0 ** 118 if M > 128 else 2.0 ** -3)
+    wb = ji.f32_to_bf16_bits(wf)
+    for name, g, wv in zip(("q", "s", "qT", "sT"), jet.quant_weight(dev_bf16(wb), transposed=True),
+                           orc.quant_weight(wb, transposed=True)):
+        _cmp(name, host(g), wv)
+
+
 def test_rounding_boundaries_through_the_quantizer(jet):
     """Groups with amax = 448 * 2^j have S = 2^j exactly, so x / S is exact and the
     codes probe the E4M3 rounding directly: every bf16 value of a binade range hits
