@@ -10,6 +10,7 @@
 // row bit-identical between decode-shaped and training-shaped calls (Sec. 4.1).
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "jet_internal.h"
 #include "jet_numerics.h"
@@ -73,7 +74,7 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 //
 // Per step the operand tiles of one group (BM + BN rows x 128 bytes) go global->LDS
 // directly as whole cache lines, swizzled so that every fragment ds_read_b128 is
-// conflict-free.  S LDS stages (two; four for the 128x128 and 128x64 tiles when there is at
+// conflict-free.  S LDS stages (two; three for the 256x128 tile; four for the 128x128 tile when there is at
 // most one workgroup per CU); step q lives in stage q % S and is copied S - 1 steps ahead.
 //
 // Pipeline of one step q, written for S = 2 (t counts the wave's MFMA tiles, row m = t / TN,
@@ -99,8 +100,7 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 //         cycles per ds_read_b128 (160 B/clk/CU) against 16.4 for a plain row-major tile
 //   scales: wave w's 256 B = [sa rows 32w..32w+31][sb of columns 32w..32w+31, clamped to the tile]
 // BM = 32 * waves, so every wave copies 4 A blocks and one scale line per step, and 4 B blocks
-// (BN = 32 * waves) or 2 (BN = 16 * waves, block scales only: the 128x64 tile for batches whose
-// 128x128 tiles would occupy at most half of the CUs).
+// (BN = 32 * waves) or 2 (BN = 16 * waves, block scales only: the 256x128 tile).
 // ------------------------------------------------------------------------
 template <int WI, int WJ, int TM, int TN, int S = 2>
 struct TileCfg {
@@ -456,35 +456,31 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 }
 
 // ------------------------------------------------------------------------
-// Skinny kernel for I <= 32 (decode): bound by streaming B (the weights) once.
+// Skinny kernel for I <= 16 (decode): bound by streaming B (the weights) once.
 // A workgroup of kSkWaves waves owns 16 output columns and the whole reduction.  The
-// groups of a pass (32 / RM groups) are dealt to the waves in runs of consecutive
+// groups of a pass (32 groups) are dealt to the waves in runs of consecutive
 // groups; every wave streams its own units (16 weight rows + the 16 or 32 activation
 // rows + scales of one group) through a private LDS ring with kSkDepth units in flight,
 // using the same whole-line LDS-DMA and swizzled fragment layout as the tile kernel --
 // no barrier is needed for the ring.  After every pass the p_g and s_g meet in LDS and
 // four waves per row tile run the ordered fma chain for their quarter of the outputs.
 // ------------------------------------------------------------------------
-constexpr int sk_unit_bytes(int rm) { return 2048 + rm * 2048 + 256; }    // weight fragment, RM activation fragments, scales
-constexpr int sk_group_bytes(int rm) { return rm * (4 * 64 * 4 + 64 * 4); } // per row tile: p[4][64] + s[64]
-constexpr int sk_pass(int rm) { return 32 / rm; }                          // groups chained per pass
-constexpr int sk_lds_bytes(int depth, int waves, int rm) {
-    return waves * depth * sk_unit_bytes(rm) + sk_pass(rm) * sk_group_bytes(rm);
-}
+constexpr int kSkUnit = 2048 + 2048 + 256;        // weight fragment, activation fragment, scales
+constexpr int kSkGroupBytes = 4 * 64 * 4 + 64 * 4;  // p[4][64] + s[64]
+constexpr int kSkPass = 32;                       // groups chained per pass
+constexpr int sk_lds_bytes(int depth, int waves) { return waves * depth * kSkUnit + kSkPass * kSkGroupBytes; }
 
 // kSkDepth = units in flight per wave: 3 or 6 when there is at most one workgroup per CU, 1 when
 // the strips outnumber the CUs (two workgroups then share a CU and cover each other's start-up,
 // chain passes and drain)
 // kSkWaves = waves splitting the groups of a strip (runs of consecutive groups): 8 unless the
 // reduction is very short
-// RM = 16-row tiles of the batch (1: I <= 16, 2: I <= 32); a unit then carries RM activation
-// fragments and gives RM MFMAs with the same weight fragment
 // ABLK = 8-row blocks of activations that hold a row of the batch ((I + 7) / 8): only these are
 // copied, and of the last one only the lines of existing rows -- every byte through a CU's
 // memory pipeline costs the same there whether it misses or hits, so at I = 1 the copy of 15
 // repeated rows would double the time of a strip.  The fragments of the other rows are read from
 // LDS that no copy wrote; their products land in output rows that are never stored.
-template <int kSkDepth, int kSkWaves, int RM, int ABLK = 2 * RM>
+template <int kSkDepth, int kSkWaves, int ABLK>
 __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_t* __restrict__ A,
                                                                      const float* __restrict__ sa,
                                                                      const uint8_t* __restrict__ B,
@@ -494,12 +490,12 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = t >> 6, l = t & 63, r = l & 15, c4 = l >> 4;
-    constexpr int kUnit = sk_unit_bytes(RM), kGroupBytes = sk_group_bytes(RM), kPass = sk_pass(RM);
+    constexpr int kUnit = kSkUnit, kGroupBytes = kSkGroupBytes, kPass = kSkPass;
     constexpr int kSkRingBytes = kSkDepth * kUnit;
     constexpr int kSkRun = kPass / kSkWaves;                 // consecutive groups per wave per pass
     constexpr int kCopies = 2 + ABLK + 1;                    // vector-memory operations per unit
-    static_assert(kSkRun >= 1 && RM <= 2 && 4 * RM <= kSkWaves && (kSkDepth - 1) * kCopies < 64, "");
-    static_assert(ABLK >= 1 && ABLK <= 2 * RM, "");
+    static_assert(kSkRun >= 1 && 4 <= kSkWaves && (kSkDepth - 1) * kCopies < 64, "");
+    static_assert(ABLK >= 1 && ABLK <= 2, "");
     const int G = R / kGroup;
     const int j0 = blockIdx.x * 16;
 
@@ -518,7 +514,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
         offX[b] = (uint32_t)min(row, I - 1) * (uint32_t)R + 16 * ((l & 7) ^ ((row >> 1) & 7));
     }
     const uint8_t* baseW = B + (size_t)j0 * R;
-    // scale line of a unit: lanes 0 .. 16 RM - 1 fetch sa of the batch rows (clamped), lanes 32-63 the block scale
+    // scale line of a unit: lanes 0 .. 15 fetch sa of the batch rows (clamped), lanes 32-63 the block scale
     const float* gs = (l < 32) ? sa + (size_t)min(l, I - 1) * G : sb + (size_t)(j0 >> 7) * G;
     const int swz = (r >> 1) & 7;
     const int frag_lo = (r >> 3) * 1024 + (r & 7) * 128 + 16 * (c4 ^ swz);
@@ -542,13 +538,12 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 #pragma unroll
         for (int b = 0; b < ABLK; ++b)
             if (rowX[b]) dma16(u + 2048 + b * 1024, A + (size_t)g * kGroup, offX[b]);
-        dma4(u + 2048 + RM * 2048, gs + g);
+        dma4(u + 4096, gs + g);
     };
 
     for (int i = 0; i < kSkDepth && i < n_units; ++i) issue(i);
 
-    // chain owner: wave w < 4 RM owns row tile w >> 2 and the columns j0 + 4 c4 + (w & 3)
-    const int cm = w >> 2, cq = w & 3;
+    // chain owner: wave w < 4 owns the columns j0 + 4 c4 + w
     float acc = 0.0f;
     int i = 0;
     for (int g0 = 0; g0 < G; g0 += kPass) {
@@ -568,325 +563,280 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
             asm volatile("" ::: "memory");
             const uint8_t* u = ring_p + (i % kSkDepth) * kUnit;
             const v8i wf = load_frag(u + frag_lo, u + frag_hi);
-            const float sbv = *reinterpret_cast<const float*>(u + 2048 + RM * 2048 + 128);
+            const float sbv = *reinterpret_cast<const float*>(u + 4096 + 128);
             float* dst = reinterpret_cast<float*>(pass_p + (seq(i) - g0) * kGroupBytes);
+            const v8i xf = load_frag(u + 2048 + frag_lo, u + 2048 + frag_hi);
+            const float s = *reinterpret_cast<const float*>(u + 4096 + 4 * r) * sbv;
+            const v4f p = group_product(wf, xf);
 #pragma unroll
-            for (int m = 0; m < RM; ++m) {
-                const v8i xf = load_frag(u + 2048 + m * 2048 + frag_lo, u + 2048 + m * 2048 + frag_hi);
-                const float s = *reinterpret_cast<const float*>(u + 2048 + RM * 2048 + 4 * (16 * m + r)) * sbv;
-                const v4f p = group_product(wf, xf);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) dst[m * 320 + e * 64 + l] = p[e];
-                dst[m * 320 + 256 + l] = s;
-            }
+            for (int e = 0; e < 4; ++e) dst[e * 64 + l] = p[e];
+            dst[256 + l] = s;
             asm volatile("" ::: "memory");
             if (i + kSkDepth < n_units) issue(i + kSkDepth);
         }
         __syncthreads();
-        if (w < 4 * RM) {                                // wave-uniform
-            const float* src = reinterpret_cast<const float*>(pass_p) + cm * 320;
+        if (w < 4) {                                     // wave-uniform
+            const float* src = reinterpret_cast<const float*>(pass_p);
             if (ng == kPass) {
                 // all LDS reads of the pass first, then the ordered chain: a loop of read, read, fma
                 // pays the LDS latency once per group (1.6 us per pass of 32 groups)
                 float pv[kPass], sv[kPass];
 #pragma unroll
                 for (int g = 0; g < kPass; ++g) {
-                    pv[g] = src[g * (kGroupBytes / 4) + cq * 64 + l];
+                    pv[g] = src[g * (kGroupBytes / 4) + w * 64 + l];
                     sv[g] = src[g * (kGroupBytes / 4) + 256 + l];
                 }
 #pragma unroll
                 for (int g = 0; g < kPass; ++g) acc = chain(pv[g], sv[g], acc);
             } else {
                 for (int g = 0; g < ng; ++g)
-                    acc = chain(src[g * (kGroupBytes / 4) + cq * 64 + l], src[g * (kGroupBytes / 4) + 256 + l], acc);
+                    acc = chain(src[g * (kGroupBytes / 4) + w * 64 + l], src[g * (kGroupBytes / 4) + 256 + l], acc);
             }
         }
         __syncthreads();
     }
-    const int row = 16 * cm + r;
-    if (w < 4 * RM && row < I) out[(size_t)row * J + j0 + 4 * c4 + cq] = (uint16_t)bf16_rne(acc);
+    if (w < 4 && r < I) out[(size_t)r * J + j0 + 4 * c4 + w] = (uint16_t)bf16_rne(acc);
 }
 
 // ------------------------------------------------------------------------
-// Strip kernel for decode batches, 16 < I <= 256 (block scales only).  The weights are
-// streamed once per row block of the batch, so the kernel lives on memory-level
-// parallelism, not on the matrix core.  A workgroup of 8 waves owns a (16 RM) x (16 CN)
-// output tile and walks the whole reduction two groups (a "pair") at a time.  Waves 0-3
-// (one per SIMD) compute; waves 4-7 only copy, so that no MFMA stream ever waits behind
-// a copy.  The weight rows and scale lines (from HBM) and the activation rows
-// (L2-resident) travel global->LDS through two separate rings.  The outstanding-copy
-// counter of a wave retires in issue order, so a wave that issued both streams could
-// never keep the weights further ahead than the activations: waves 4 and 5 copy only
-// weights and scales, waves 6 and 7 only activations.  One barrier per pair; the
-// fragments of pair p+2 are fetched from LDS into registers while pair p is computed, so
-// neither the LDS latency nor the barrier is paid per group.  Computing wave w owns
-// RM*CN/4 of the MFMA tiles and runs their ordered fma chains in registers: the same chain
-// as every other kernel, so rows are bit-identical.
-// Two configurations: 32-row blocks with rings shallow enough for two workgroups per CU
-// (they cover each other's start-up and drain), 64-row blocks with deep rings.
+// Panel kernel (block scales only): batches of 17 to 1024 rows, and larger ones against narrow matrices, whose
+// output makes one or two rounds of tiles on the CUs.  One workgroup per CU owns a BM x BN output tile and walks the
+// whole reduction, a step of one or two groups at a time; WR x WC waves compute, kCopy waves copy the operands and
+// one the scales.
+// What bounds it: a CU can have about 320 cache lines on their way and gets them back in order, so an
+// activation line (an L2 hit) waits behind the weight lines (HBM misses) in front of it.  A tile takes about
+// (BM + BN) * G * 2.4 ns, whatever its lines hit (measured from 48 to 240 lines per group), plus 3-4 us of launch, ring
+// fill and output.  So the tile is chosen by its lines (pick_tile), and a wide matrix gets wide tiles: the
+// activations of a group pass once per 112 columns and not once per 32.
+// Ring of S stages, per group [W: BN rows x 128][A: BM rows x 128] in the swizzled fragment layout of the tile
+// kernel; scales travel in chunks of 16 groups, [row][16] with the group xor (row >> 2) & 3 (conflict-free), two buffers.
+// Step p: the copying waves wait until step p+1 has landed; barrier; they refill the slot of step p with step p+S
+// while the computing waves fetch the fragments of step p+1 into registers and compute step p.  The copying loop is
+// straight-line (a compare chain for the wait and a branch per copy cost 0.3 us per step), and the fetch stays in front
+// of the MFMAs by scheduling barriers.  Every output element takes the chain of the other kernels.
+// From HBM, against the strip kernel of 64x32 and 32x32 tiles and the 128x128 tiles before it (us): 4096x14336 77 rows
+// 30.5 -> 22.8, 256 rows 59 -> 37; 28672x4096 32 rows 34 -> 29, 64 rows 47 -> 31; 6144x4096 128 rows 23 -> 13.6;
+// 5120x27648 64 rows 57 -> 50, 256 rows 152 -> 81; 55296x5120 64 rows 101 -> 67.
+// Measured and left out: workgroups on idle CUs that pull the weights into the L2 ahead (32-row tiles of 4096x14336
+// 22.4 -> 18.1 us, elsewhere within 10 % either way), a wave that touches the XCD's weight lines a chunk ahead (its
+// burst holds up the barrier: 30 % slower).
 // ------------------------------------------------------------------------
-template <int RM, int CN, int WDEPTH, int ADEPTH>
-struct StripCfg {
-    static constexpr int kWaves = 4;
-    static constexpr int BM = 16 * RM, BN = 16 * CN;
-    static constexpr int kWDepth = WDEPTH, kADepth = ADEPTH;    // ring depths in pairs
-    static constexpr int kWGroup = CN * 2048 + 512;             // weight fragments, then sa[64] and the sb line
-    static constexpr int kAGroup = RM * 2048;                   // activation fragments
-    static constexpr int kWStage = 2 * kWGroup, kAStage = 2 * kAGroup;
-    static constexpr int kSinkBytes = 256;                      // landing zone of the L2 warm-up loads
-    // 64-row blocks fetch the activation scales a chunk of 16 groups ahead, [row][16 groups], into
-    // three chunk buffers (the one being read, the next one, and the one being filled); 32-row
-    // blocks fetch one scale per row with every group (measured: the chunks gain 15 % on 64-row
-    // blocks with a long reduction and lose 10 % on 32-row blocks with a short one)
-    static constexpr bool kSaAhead = BM == 64;
-    static constexpr int kSaChunk = 16, kSaBufBytes = BM * kSaChunk * 4, kSaBufs = 3;
-    static constexpr int kSaOffset = kWDepth * kWStage + kADepth * kAStage + kSinkBytes;
-    static constexpr int kLdsBytes = kSaOffset + (kSaAhead ? kSaBufs * kSaBufBytes : 0);
-    static constexpr int kWOps = 2 * (CN + 1), kAOps = 2 * RM;  // copies per wave per pair
-    static constexpr int kTiles = RM * CN / kWaves;             // MFMA tiles per wave
-    static constexpr int kNM = (kTiles + CN - 1) / CN;          // distinct row tiles per wave
-    static constexpr int kNN = kTiles < CN ? kTiles : CN;       // distinct column tiles per wave
-    static constexpr int kFetchOps = 2 * (2 * (kNM + kNN) + kNM + 1);   // LDS reads of one pair
-    static_assert(RM % 2 == 0 && CN % 2 == 0 && RM * CN % kWaves == 0 && BM <= 64 && 128 % BN == 0, "");
-    static_assert(kNM * kNN == kTiles, "a wave's tiles form a kNM x kNN rectangle");
-    static_assert(kWDepth >= 4 && kADepth >= 4 && (kWDepth - 3) * kWOps < 64 && (kADepth - 3) * kAOps < 64, "");
-    // Iteration p fills the buffer of chunk (2 (p + kWDepth) + 1) / 16 + 1 while the reads are at group
-    // 2 p + 4 or later: the chunk that buffer held (three chunks back) must be behind every read.
-    static_assert(kSaChunk == 16 && BM / 4 <= kSaChunk && (!kSaAhead || 2 * kWDepth + 1 < kSaChunk + 6), "");
-    static_assert(kLdsBytes <= 160 * 1024, "");
+template <int TM_, int TN_, int WR_, int WC_, int S_, int GP_ = 1>
+struct PanelCfg {
+    static constexpr int TM = TM_, TN = TN_, WR = WR_, WC = WC_, S = S_, GP = GP_;
+    static constexpr int BM = 16 * TM * WR, BN = 16 * TN * WC;
+    static constexpr int kWBlocks = BN / 8, kABlocks = BM / 8;            // 1 KB copies of a group
+    static constexpr int kCopy = (kWBlocks % 4 == 0 && kABlocks % 4 == 0 && WR * WC <= 3) ? 4 : 2;
+    static constexpr int kCompute = WR * WC, kThreads = 64 * (kCompute + kCopy + 1);
+    static constexpr int kWPer = kWBlocks / kCopy, kAPer = kABlocks / kCopy, kPer = GP * (kWPer + kAPer);
+    static constexpr int kGroupBytes = (BM + BN) * 128, kStage = GP * kGroupBytes;
+    static constexpr int kChunk = 16, kSaBuf = BM * kChunk * 4, kSbBuf = 256;
+    static constexpr int kSaOff = S * kStage, kSbOff = kSaOff + 2 * kSaBuf, kSink = kSbOff + 2 * kSbBuf;
+    static constexpr int kLds = kSink + 256;
+    static_assert(kWBlocks % kCopy == 0 && kABlocks % kCopy == 0, "");
+    static_assert(S >= 3 && (S - 1) * kPer < 64 && BN <= 256 && kLds <= 160 * 1024 && kChunk % GP == 0, "");
 };
 
-template <int RM, int CN, int WDEPTH, int ADEPTH>
-__global__ __launch_bounds__(512) void gemm_strip_kernel(const uint8_t* __restrict__ A,
-                                                          const float* __restrict__ sa,
-                                                          const uint8_t* __restrict__ B,
-                                                          const float* __restrict__ sb,
-                                                          uint16_t* __restrict__ out, int I, int J, int R,
-                                                          int row_blocks) {
-    using C = StripCfg<RM, CN, WDEPTH, ADEPTH>;
+// wait until at most n steps' copies (kCnt each) of this wave are outstanding
+template <int kCnt, int kMax>
+__device__ __forceinline__ void wait_steps(int n) {
+    if (n >= kMax) {
+        JET_WAIT_VMCNT(kMax * kCnt);
+    } else if constexpr (kMax > 0) {
+        wait_steps<kCnt, kMax - 1>(n);
+    }
+}
+__device__ __forceinline__ void step_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <class C>
+__global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* __restrict__ A,
+                                                                  const float* __restrict__ sa,
+                                                                  const uint8_t* __restrict__ B,
+                                                                  const float* __restrict__ sb,
+                                                                  uint16_t* __restrict__ out, int I, int J, int ldo, int R,
+                                                                  int row_blocks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, r = l & 15, c4 = l >> 4;
-    const int G = R / kGroup, P = (G + 1) / 2;
+    const int G = R / kGroup, P = (G + C::GP - 1) / C::GP;
+    // row blocks that share a weight panel are neighbours on one XCD, so the panel leaves HBM once
+    const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int rb = id % row_blocks, panel = id / row_blocks;
+    const int i0 = rb * C::BM, j0 = panel * C::BN;
 
-    // workgroups that share a weight strip (different row blocks) sit next to each other on
-    // one XCD, so the strip leaves HBM once
-    const int strips = J / C::BN, b = blockIdx.x;
-    int rb, strip;
-    if (strips % 8 == 0) {
-        rb = (b >> 3) % row_blocks;
-        strip = ((b >> 3) / row_blocks) * 8 + (b & 7);
-    } else {
-        rb = b % row_blocks;
-        strip = b / row_blocks;
-    }
-    const int i0 = rb * C::BM, j0 = strip * C::BN;
-
-    // ---- copies: a wave copies kMine consecutive 1 KB blocks (8 rows) of each group of a
-    // pair; block b is half b & 1 of fragment b >> 1 ----
-    // waves 0-3 compute (one per SIMD); waves 4-7 only copy: 4, 5 the weights, 6, 7 the activations
-    const bool copier = w >= 4;
-    const bool w_stream = w < 6;
-    const int side = w & 1;
-    constexpr int kWMine = CN, kAMine = RM;
-    constexpr int kMineMax = RM > CN ? RM : CN;
-    const uint32_t lane_chunk = 16 * ((l & 7) ^ (l >> 4));
-    const uint8_t* baseW = static_cast<const uint8_t*>(uniform_ptr(B + (size_t)j0 * R));
-    const uint8_t* baseA = static_cast<const uint8_t*>(uniform_ptr(A + (size_t)i0 * R));
-    uint32_t off[kMineMax];
-#pragma unroll
-    for (int i = 0; i < kMineMax; ++i) {
-        if (w_stream) {
-            const int blk = side * kWMine + (i < kWMine ? i : 0);
-            off[i] = (uint32_t)(8 * blk + (l >> 3)) * (uint32_t)R + (lane_chunk ^ ((blk & 1) * 64));
-        } else {
-            const int blk = side * kAMine + (i < kAMine ? i : 0);
-            const int row = min(i0 + 8 * blk + (l >> 3), I - 1) - i0;   // rows past the end repeat the last one
-            off[i] = (uint32_t)row * (uint32_t)R + (lane_chunk ^ ((blk & 1) * 64));
-        }
-    }
-    // scales travel with the weights (the weight waves have far fewer copies to issue than the
-    // activation waves).  Wave 5 copies the block scale of every group.  Wave 4 copies the
-    // activation scales: one per row with every group, or (kSaAhead) a chunk of 16 groups ahead:
-    // with group g it fetches 4 rows x the 16 groups of the next chunk (4 cache lines per
-    // instruction instead of one per lane), so the chunk after g's is complete before its
-    // first group is.
-    const bool sa_wave = w == 4;
-    const float* sb_line = sb + (size_t)(j0 >> 7) * G;
-    const float* gs = sa_wave ? sa + (size_t)min(i0 + l, I - 1) * G : sb_line;   // one scale per lane and group
-    const int sa_grp = l & 15;
-    const int sa_off0 = (i0 + (l >> 4)) * G, sa_off_last = (I - 1) * G;          // chunk copies: this lane's row of quad 0
-    const uint32_t lds_w = __builtin_amdgcn_readfirstlane(lds0 + side * kWMine * 1024);
-    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lds0 + C::kWDepth * C::kWStage + side * kAMine * 1024);
-    const uint32_t lds_s = __builtin_amdgcn_readfirstlane(lds0 + CN * 2048 + side * 256);
-    const uint32_t lds_sa = __builtin_amdgcn_readfirstlane(lds0 + C::kSaOffset);
-    // rows 4 rq .. 4 rq + 3 of the tile (past the end: the last row), groups of chunk c (past the end: the last group)
-    auto sa_src = [&](int c, int rq) {
-        return sa + min(sa_off0 + rq * 4 * G, sa_off_last) + min(C::kSaChunk * c + sa_grp, G - 1);
-    };
-    auto sa_dst = [&](int c, int rq) { return lds_sa + (c % C::kSaBufs) * C::kSaBufBytes + rq * 256; };
-    // this wave's copies of pair p (groups past the end repeat the last one)
-    auto issue = [&](int p) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int g = min(2 * p + h, G - 1);
-            if (w_stream) {
-                const uint32_t st = (p % C::kWDepth) * C::kWStage + h * C::kWGroup;
-#pragma unroll
-                for (int i = 0; i < kWMine; ++i) dma16(lds_w + st + i * 1024, baseW + (size_t)g * kGroup, off[i]);
-                // (a branch between the two waves' copies: selecting source and destination per copy
-                // instead measured 10 % slower)
-                if (!C::kSaAhead || !sa_wave) {
-                    dma4(lds_s + st, gs + g);
-                } else {
-                    const int c = g / C::kSaChunk + 1, rq = (g % C::kSaChunk) % (C::BM / 4);
-                    dma4(sa_dst(c, rq), sa_src(c, rq));
-                }
-            } else {
-                const uint32_t st = (p % C::kADepth) * C::kAStage + h * C::kAGroup;
-#pragma unroll
-                for (int i = 0; i < kAMine; ++i) dma16(lds_a + st + i * 1024, baseA + (size_t)g * kGroup, off[i]);
-            }
-        }
-    };
-
-    // ---- this wave's MFMA tiles: rows m0 .. m0+kNM-1, columns n0 .. n0+kNN-1 (in tiles) ----
-    const int first = (w & 3) * C::kTiles, m0 = first / CN, n0 = first % CN;
-    const int swz = (r >> 1) & 7;
-    const int frag_lo = (r >> 3) * 1024 + (r & 7) * 128 + 16 * (c4 ^ swz);
-    const int frag_hi = (r >> 3) * 1024 + (r & 7) * 128 + 16 * ((4 + c4) ^ swz);
-    struct Operands {           // of one pair
-        v8i wf[2][C::kNN], xf[2][C::kNM];
-        float sa[2][C::kNM], sb[2];
-    };
-    auto fetch = [&](int p, Operands& o) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int g = min(2 * p + h, G - 1);
-            const uint8_t* ps = smem + C::kSaOffset + ((g / C::kSaChunk) % C::kSaBufs) * C::kSaBufBytes + (g % C::kSaChunk) * 4;
-            const uint8_t* pw = smem + (p % C::kWDepth) * C::kWStage + h * C::kWGroup;
-            const uint8_t* pa = smem + C::kWDepth * C::kWStage + (p % C::kADepth) * C::kAStage + h * C::kAGroup;
-#pragma unroll
-            for (int n = 0; n < C::kNN; ++n)
-                o.wf[h][n] = load_frag(pw + (n0 + n) * 2048 + frag_lo, pw + (n0 + n) * 2048 + frag_hi);
-#pragma unroll
-            for (int m = 0; m < C::kNM; ++m) {
-                o.xf[h][m] = load_frag(pa + (m0 + m) * 2048 + frag_lo, pa + (m0 + m) * 2048 + frag_hi);
-                o.sa[h][m] = C::kSaAhead
-                                 ? *reinterpret_cast<const float*>(ps + ((m0 + m) * 16 + r) * (C::kSaChunk * 4))
-                                 : *reinterpret_cast<const float*>(pw + CN * 2048 + ((m0 + m) * 16 + r) * 4);
-            }
-            o.sb[h] = *reinterpret_cast<const float*>(pw + CN * 2048 + 256);
-        }
-    };
-    v4f acc[C::kNM][C::kNN];
-#pragma unroll
-    for (int m = 0; m < C::kNM; ++m)
-#pragma unroll
-        for (int n = 0; n < C::kNN; ++n) acc[m][n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    auto compute = [&](int p, const Operands& o) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (2 * p + h >= G) break;               // odd G: the last pair has one group
-#pragma unroll
-            for (int m = 0; m < C::kNM; ++m) {
-                const float s = o.sa[h][m] * o.sb[h];
-#pragma unroll
-                for (int n = 0; n < C::kNN; ++n) {
-                    const v4f pg = group_product(o.wf[h][n], o.xf[h][m]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[m][n][e] = chain(pg[e], s, acc[m][n][e]);
-                }
-            }
-        }
-    };
-    // "of my copies only those of the last n pairs I issued may still be on their way", n = depth - less
-    auto wait_copies = [&](int less) {
-        if (w_stream) {
-            if (less == 3) JET_WAIT_VMCNT((C::kWDepth - 3) * C::kWOps);
-            else JET_WAIT_VMCNT((C::kWDepth - 2) * C::kWOps);
-        } else {
-            if (less == 3) JET_WAIT_VMCNT((C::kADepth - 3) * C::kAOps);
-            else JET_WAIT_VMCNT((C::kADepth - 2) * C::kAOps);
-        }
-    };
-
-    // ---- L2 warm-up of this row block's activations ----
-    // Every workgroup of an XCD walks the same activation rows group by group at about the
-    // same time, so without help each group's copy would be a fresh miss to HBM.  The
-    // workgroups of an XCD touch one dword of every cache line once, up front, sharing the
-    // lines between them; the ring copies then hit in the L2.
+    // ---- L2 warm-up: the workgroups of an XCD touch one dword of every line of their activations once ----
     {
-        const int per_xcd = (gridDim.x + 7) >> 3, me = b >> 3;
-        const int rows = min(C::BM, I - i0);
-        const long lines = (long)rows * G;
-        const uint32_t sink = __builtin_amdgcn_readfirstlane(lds0 + C::kWDepth * C::kWStage + C::kADepth * C::kAStage);
-        for (long x = (long)me * 512 + t; x < lines; x += (long)per_xcd * 512) {
-            const long row = x / G, g = x - row * G;
-            dma4(sink, reinterpret_cast<const float*>(baseA + (size_t)row * R + (size_t)g * kGroup));
+        const int per_xcd = ((int)gridDim.x + 7) >> 3, me = blockIdx.x >> 3;
+        const int lines = min(C::BM, I - i0) * G;
+        const uint32_t sink = __builtin_amdgcn_readfirstlane(lds0 + C::kSink);
+        for (int x = me * C::kThreads + t; x < lines; x += per_xcd * C::kThreads) {
+            const int row = x / G, g = x - row * G;
+            dma4(sink, reinterpret_cast<const float*>(A + (size_t)(i0 + row) * R + (size_t)g * kGroup));
         }
     }
 
-    // ---- prologue: fill both rings, fetch pairs 0 and 1 ----
-    // iteration p of the main loop issues pair p + depth; the prologue issues pairs 0 .. depth-1
-    // in the same relative order, so the steady-state counts hold from the start
-    if (C::kSaAhead && !copier) {
-        // chunk 0 of the activation scales: the computing waves have nothing else to do yet
-        for (int rq = w; rq < C::BM / 4; rq += C::kWaves) dma4(sa_dst(0, rq), sa_src(0, rq));
+    if (w >= C::kCompute + C::kCopy) {
+        // ---------------- scale wave: chunks of 16 groups, two buffers ----------------
+        auto copy_chunk = [&](int c) {
+            const uint32_t sa_dst = lds0 + C::kSaOff + (c & 1) * C::kSaBuf;
+            for (int rq = 0; rq < C::BM / 4; ++rq) {     // rows 4 rq .. 4 rq + 3
+                const int row = min(i0 + 4 * rq + (l >> 4), I - 1), g = min(C::kChunk * c + ((l & 15) ^ (rq & 3)), G - 1);
+                dma4(sa_dst + rq * 256, sa + (size_t)row * G + g);
+            }
+            const int blk = min((j0 >> 7) + (l >> 4), (J >> 7) - 1), g = min(C::kChunk * c + (l & 15), G - 1);
+            dma4(lds0 + C::kSbOff + (c & 1) * C::kSbBuf, sb + (size_t)blk * G + g);
+        };
+        constexpr int kSteps = C::kChunk / C::GP;        // steps of a chunk
+        copy_chunk(0);
         JET_WAIT_VMCNT(0);
+        step_barrier();
+        for (int p = 0, k = 0, c = 0; p < P; ++p) {
+            if (k == kSteps - 1) JET_WAIT_VMCNT(0);      // chunk c + 1: its first fetch follows this barrier
+            step_barrier();
+            if (k == 0 && (c + 1) * C::kChunk < G) copy_chunk(c + 1);   // nobody reads chunk c - 1 any more
+            if (++k == kSteps) { k = 0; ++c; }
+        }
+        JET_WAIT_VMCNT(0);
+        return;
     }
-    for (int v = 0; v < C::kWDepth; ++v)
-        if (copier && (w_stream || v < C::kADepth)) issue(v);
-    if (copier) wait_copies(2);                      // pairs 0 and 1 landed: depth-2 later pairs outstanding
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    // iteration p (one barrier): pairs <= p+2 have landed; the slots of pair p are free (its
-    // fragments are in registers).  The two kinds of wave run the same number of barriers.
-    // (Refilling the slots of pair p+1 as well -- one more pair in flight -- needs every LDS read of
-    // an iteration to return before the next barrier; measured: a few percent faster when the weights
-    // come from HBM, 10-25 % slower when they are cache-resident.)
-    if (copier) {
-        for (int p = 0; p < P; ++p) {
-            wait_copies(3);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            issue(p + (w_stream ? C::kWDepth : C::kADepth));
+    if (w >= C::kCompute) {
+        // ---------------- copying waves: blocks cw, cw + kCopy, ... of every group ----------------
+        const int cw = w - C::kCompute;
+        const uint8_t* baseW = static_cast<const uint8_t*>(uniform_ptr(B + (size_t)j0 * R));
+        const uint8_t* baseA = static_cast<const uint8_t*>(uniform_ptr(A + (size_t)i0 * R));
+        const uint32_t lane_chunk = (16 * ((l & 7) ^ (l >> 4))) ^ ((cw & 1) * 64);
+        uint32_t offW[C::kWPer], offA[C::kAPer];         // rows and columns past the end repeat the last one (never stored)
+#pragma unroll
+        for (int i = 0; i < C::kWPer; ++i)
+            offW[i] = (uint32_t)(min(j0 + 8 * (cw + C::kCopy * i) + (l >> 3), J - 1) - j0) * (uint32_t)R + lane_chunk;
+#pragma unroll
+        for (int i = 0; i < C::kAPer; ++i)
+            offA[i] = (uint32_t)(min(i0 + 8 * (cw + C::kCopy * i) + (l >> 3), I - 1) - i0) * (uint32_t)R + lane_chunk;
+        const uint32_t lds_c = __builtin_amdgcn_readfirstlane(lds0 + cw * 1024);
+        uint32_t st = lds_c;
+        auto issue = [&](int q) {
+#pragma unroll
+            for (int h = 0; h < C::GP; ++h) {
+                const size_t kb = (size_t)min(C::GP * q + h, G - 1) * kGroup;   // past the end: the last group again
+#pragma unroll
+                for (int i = 0; i < C::kWPer; ++i) dma16(st + h * C::kGroupBytes + i * (C::kCopy * 1024), baseW + kb, offW[i]);
+#pragma unroll
+                for (int i = 0; i < C::kAPer; ++i)
+                    dma16(st + h * C::kGroupBytes + C::BN * 128 + i * (C::kCopy * 1024), baseA + kb, offA[i]);
+            }
+            st = (st == lds_c + (C::S - 1) * C::kStage) ? lds_c : st + C::kStage;
+        };
+        for (int q = 0; q < C::S && q < P; ++q) issue(q);
+        wait_steps<C::kPer, C::S - 1>(min(P, C::S) - 1); // step 0
+        step_barrier();
+        int p = 0;
+        for (; p + C::S < P; ++p) {
+            JET_WAIT_VMCNT((C::S - 2) * C::kPer);        // step p + 1; younger: p + 2 .. p + S - 1
+            step_barrier();
+            issue(p + C::S);
+        }
+        for (; p < P; ++p) {
+            wait_steps<C::kPer, C::S - 1>(max(P - p - 2, 0));
+            step_barrier();
         }
         JET_WAIT_VMCNT(0);   // nothing may be in flight towards the LDS when it is released
         return;
     }
-    Operands op0, op1, op2;
-    fetch(0, op0);
-    fetch(min(1, P - 1), op1);
-    auto iteration = [&](int p, const Operands& cur, Operands& nxt2) {
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        fetch(min(p + 2, P - 1), nxt2);
-        compute(p, cur);
-        // my reads of pair p+1's slots are done before the next barrier lets them be overwritten
-        // (LDS reads return in order: at most the reads of pair p+2 stay outstanding)
-        __builtin_amdgcn_s_waitcnt(0xc07f | ((C::kFetchOps < 15 ? C::kFetchOps : 15) << 8));
+
+    // ---------------- computing waves ----------------
+    const int wr = w / C::WC, wc = w % C::WC;
+    const int swz = (r >> 1) & 7;
+    const int frag_lo = (r >> 3) * 1024 + (r & 7) * 128 + 16 * (c4 ^ swz);
+    const int frag_hi = (r >> 3) * 1024 + (r & 7) * 128 + 16 * ((4 + c4) ^ swz);
+    const uint8_t* const pw0 = smem + wc * C::TN * 2048;
+    const uint8_t* const pa0 = smem + C::BN * 128 + wr * C::TM * 2048;
+    const uint8_t* const ps0 = smem + C::kSaOff + (wr * C::TM * 16 + r) * 64;
+    const int sa_xor = ((r >> 2) & 3) * 4;
+    int sb_off[C::TN];                                   // block of a column tile in the chunk of block scales
+#pragma unroll
+    for (int n = 0; n < C::TN; ++n) sb_off[n] = (((j0 + 16 * (wc * C::TN + n)) >> 7) - (j0 >> 7)) * 64;
+    struct Operands {
+        v8i wf[C::GP][C::TN], xf[C::GP][C::TM];
+        float sa[C::GP][C::TM], sb[C::GP][C::TN];
+    };
+    auto fetch = [&](int p, int stage, Operands& o) {
+        const int buf = (C::GP * p / C::kChunk) & 1;
+#pragma unroll
+        for (int h = 0; h < C::GP; ++h) {
+            const int k4 = ((C::GP * p + h) % C::kChunk) * 4;
+            const uint8_t* pw = pw0 + stage + h * C::kGroupBytes;
+            const uint8_t* pa = pa0 + stage + h * C::kGroupBytes;
+            const uint8_t* ps = ps0 + buf * C::kSaBuf + (k4 ^ sa_xor);
+            const uint8_t* pb = smem + C::kSbOff + buf * C::kSbBuf + k4;
+#pragma unroll
+            for (int m = 0; m < C::TM; ++m) {
+                o.xf[h][m] = load_frag(pa + m * 2048 + frag_lo, pa + m * 2048 + frag_hi);
+                o.sa[h][m] = *reinterpret_cast<const float*>(ps + m * 1024);
+            }
+#pragma unroll
+            for (int n = 0; n < C::TN; ++n) {
+                o.wf[h][n] = load_frag(pw + n * 2048 + frag_lo, pw + n * 2048 + frag_hi);
+                o.sb[h][n] = *reinterpret_cast<const float*>(pb + sb_off[n]);
+            }
+        }
+    };
+    v4f acc[C::TM][C::TN];
+#pragma unroll
+    for (int m = 0; m < C::TM; ++m)
+#pragma unroll
+        for (int n = 0; n < C::TN; ++n) acc[m][n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int kTiles = C::TM * C::TN;
+    auto compute = [&](const Operands& o, auto groups) {
+        constexpr int kAll = kTiles * decltype(groups)::value, kLag = kAll < 2 ? kAll : 2;
+        v4f pr[3];
+#pragma unroll
+        for (int u = 0; u < kAll + kLag; ++u) {
+            if (u < kAll) pr[u % 3] = group_product(o.wf[u / kTiles][u % C::TN], o.xf[u / kTiles][u % kTiles / C::TN]);
+            if (u >= kLag) {
+                const int v = u - kLag, h = v / kTiles, m = v % kTiles / C::TN, n = v % C::TN;
+                const float s = o.sa[h][m] * o.sb[h][n];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[m][n][e] = chain(pr[v % 3][e], s, acc[m][n][e]);
+            }
+        }
+    };
+    JET_WAIT_VMCNT(0);                                   // own warm-up loads
+    step_barrier();                                      // step 0 has landed
+    Operands even, odd;
+    fetch(0, 0, even);
+    int stage = 0;
+    auto iteration = [&](int p, const Operands& cur, Operands& nxt) {
+        // this step's fragments are in registers: its slot may be overwritten
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0)
+        step_barrier();
+        stage = (stage == (C::S - 1) * C::kStage) ? 0 : stage + C::kStage;
+        fetch(p + 1, stage, nxt);                        // (after the last step: whatever is there, not used)
+        __builtin_amdgcn_sched_barrier(0);
+        if (C::GP == 1 || C::GP * (p + 1) <= G) compute(cur, std::integral_constant<int, C::GP>{});
+        else compute(cur, std::integral_constant<int, C::GP == 1 ? 1 : C::GP - 1>{});     // GP = 2, odd G: the last step has one group
     };
     int p = 0;
-    for (; p + 2 < P; p += 3) {
-        iteration(p, op0, op2);
-        iteration(p + 1, op1, op0);
-        iteration(p + 2, op2, op1);
+    for (; p + 1 < P; p += 2) {
+        iteration(p, even, odd);
+        iteration(p + 1, odd, even);
     }
-    if (p < P) iteration(p, op0, op2);
-    if (p + 1 < P) iteration(p + 1, op1, op0);
-    JET_WAIT_VMCNT(0);   // nothing may be in flight towards the LDS when it is released
+    if (p < P) iteration(p, even, odd);
 
 #pragma unroll
-    for (int m = 0; m < C::kNM; ++m) {
-        const int i = i0 + (m0 + m) * 16 + r;
+    for (int m = 0; m < C::TM; ++m) {
+        const int i = i0 + (wr * C::TM + m) * 16 + r;
 #pragma unroll
-        for (int n = 0; n < C::kNN; ++n) {
-            const int j = j0 + (n0 + n) * 16 + 4 * c4;
+        for (int n = 0; n < C::TN; ++n) {
+            const int j = j0 + (wc * C::TN + n) * 16 + 4 * c4;
             uint2 o;
             o.x = bf16_pack2(acc[m][n][0], acc[m][n][1]);
             o.y = bf16_pack2(acc[m][n][2], acc[m][n][3]);
-            if (i < I) *reinterpret_cast<uint2*>(out + (size_t)i * J + j) = o;
+            if (i < I && j < J) *reinterpret_cast<uint2*>(out + (size_t)i * ldo + j) = o;
         }
     }
 }
@@ -899,19 +849,15 @@ static hipError_t allow_lds(K kernel, int bytes) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// big tile: 256x256, 8 waves of 128x64;  small tile: 128x128, 4 waves of 64x64
+// big tile: 256x256, 8 waves of 128x64;  wide tile: 256x128, 8 waves of 64x64, three stages;  small tile: 128x128, 4 waves of 64x64
 #define JET_BIG 2, 4, 8, 4
+#define JET_WIDE 4, 2, 4, 4, 3
 #define JET_SMALL 2, 2, 4, 4
 #define JET_SMALL_DEEP 2, 2, 4, 4, 4   /* four stages, one workgroup per CU: copies three steps ahead */
-#define JET_HALF 4, 1, 2, 4, 4         /* 128x64 tile, 4 waves of 32x64, four stages (six measured the same) */
-#define JET_STRIP_SMALL 2, 2, 4, 4   /* 32-row blocks, two workgroups per CU */
-#define JET_STRIP_WIDE 4, 2, 7, 5    /* 64-row blocks */
-using StripSmall = StripCfg<JET_STRIP_SMALL>;
-using StripWide = StripCfg<JET_STRIP_WIDE>;
 using BigCfg = TileCfg<JET_BIG>;
+using WideCfg = TileCfg<JET_WIDE>;
 using SmallCfg = TileCfg<JET_SMALL>;
 using SmallDeepCfg = TileCfg<JET_SMALL_DEEP>;
-using HalfCfg = TileCfg<JET_HALF>;
 
 // compute units of the current device (256 on MI355X), asked once per process
 static int compute_units() {
@@ -925,21 +871,85 @@ static int compute_units() {
     return n;
 }
 
+template <class C>
+static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
+                               long J, long R, long ldo, hipStream_t st) {
+    const int rbs = (int)((I + C::BM - 1) / C::BM);
+    const long panels = (J + C::BN - 1) / C::BN;
+    hipLaunchKernelGGL((gemm_panel_kernel<C>), dim3((unsigned)(rbs * panels)), dim3(C::kThreads), C::kLds, st, A, sa, B,
+                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs);
+    return hipGetLastError();
+}
+
+// the panel tiles: X(TM, TN, WR, WC, stages, groups per step), 16 TM WR rows x 16 TN WC columns
+#define JET_PANELS(X)                                                                                       \
+    X(1, 1, 2, 1, 10, 2) X(1, 1, 2, 2, 8, 2) X(2, 1, 1, 3, 6, 2) X(2, 1, 1, 4, 6, 2) X(2, 1, 1, 7, 7, 1)    \
+    X(1, 2, 3, 1, 7, 2) X(1, 2, 3, 2, 5, 2) X(1, 7, 3, 1, 7, 1) X(2, 2, 2, 2, 4, 2) X(1, 7, 4, 1, 6, 1)     \
+    X(1, 4, 5, 1, 7, 1) X(1, 7, 5, 1, 5, 1) X(2, 4, 3, 1, 6, 1) X(2, 7, 3, 1, 5, 1) X(2, 4, 4, 1, 5, 1)     \
+    X(2, 7, 4, 1, 4, 1)
+
+struct TileChoice {
+    int bm, bn;
+    hipError_t (*panel)(const uint8_t*, const float*, const uint8_t*, const float*, uint16_t*, long, long, long, long,
+                        hipStream_t);      // nullptr: a tile of the tile kernel
+};
+#define JET_PANEL_ROW(TM, TN, WR, WC, S, GP) {16 * TM * WR, 16 * TN * WC, launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>},
+static const TileChoice kTileChoices[] = {JET_PANELS(JET_PANEL_ROW){128, 128, nullptr}, {256, 128, nullptr}, {256, 256, nullptr}};
+
+// The tile of a block-scaled product, by its shape alone: rounds of tiles on the CUs x the time of a tile, which grows
+// with its lines per group L = BM + BN as L (L + 550) (measured per group, from HBM, 1 to 4096 rows, 11 matrices:
+// 48 lines 0.12 us, 128 lines 0.30, 240 lines 0.62, 384 lines 1.2, 512 lines 1.83).  Over those 140 shapes the choice is
+// within 0.7 % of the best tile on average.
+static const TileChoice& pick_tile(long I, long J, long& rounds) {
+    const long cus = compute_units();
+    const TileChoice* best = nullptr;
+    long best_cost = 0;
+    for (const TileChoice& c : kTileChoices) {
+        if (c.bm >= I + 32 && !(c.bm > 128 && I > 100)) continue;         // mostly padding
+        if (c.bn == 256 && J % 256) continue;                             // the tile kernel has no ragged columns
+        const long n = ((I + c.bm - 1) / c.bm) * ((J + c.bn - 1) / c.bn), r = (n + cus - 1) / cus, L = c.bm + c.bn;
+        const long cost = r * L * (L + 550);
+        if (!best || cost < best_cost) { best = &c; best_cost = cost; rounds = r; }
+    }
+    return *best;
+}
+
+template <int SB_MODE, int... Cfg>
+static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
+                               long J, long R, long ldo, hipStream_t st) {
+    using C = TileCfg<Cfg...>;
+    const long ti = (I + C::BM - 1) / C::BM, tj = J / C::BN;
+    const long wgs = std::min<long>(ti * tj, (long)compute_units() * C::kOccupancy);
+    hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, Cfg...>), dim3((unsigned)wgs), dim3(C::kThreads), C::kLdsBytes, st, A,
+                       sa, B, sb, o, (int)I, (int)ldo, (int)R, (int)ti, (int)tj);
+    return hipGetLastError();
+}
+
 // out has row pitch ldo (>= J): the launches below also run on row or column ranges of a larger problem
 template <int SB_MODE>
 static hipError_t launch_tile(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb,
                               uint16_t* o, long I, long J, long R, long ldo, hipStream_t st) {
-    // shape-only choice: the big tile when it divides J and fills the 256 CUs.  The grid
-    // is persistent: at most one resident set of workgroups, each walking its tile list.
     const int cus = compute_units();
     const long G = R / kGroup;
+    if (SB_MODE == kSbBlock) {
+        // up to 1024 rows, and beyond where one round of tiles does (more rounds: the persistent kernel below, which
+        // has no gap between them and splits the last one)
+        long rounds = 0;
+        const TileChoice& c = pick_tile(I, J, rounds);
+        if (I <= 1024 || rounds == 1) {
+            if (c.panel) return c.panel(A, sa, B, sb, o, I, J, R, ldo, st);
+            if (c.bn == 256) return launch_tiles<kSbBlock, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
+            if (c.bm == 256) return launch_tiles<kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
+        }
+    }
+    // shape-only choice: the big tile when it divides J and fills the 256 CUs.  The grid
+    // is persistent: at most one resident set of workgroups, each walking its tile list.
     const long big_tiles = ((I + 255) / 256) * (J / 256);
     if (J % 256 == 0 && big_tiles >= 224) {
         const int ti = (int)((I + 255) / 256), tj = (int)(J / 256);
         // A last round that fills at most half of the CUs (896 tiles = 3.5 rounds for the 14336-wide
         // WGrads) would cost a whole round: split those tiles off as whole tile rows or tile columns
-        // and run them as 128x128 tiles, two workgroups per CU.  An output element takes the same
-        // chain in either kernel.
+        // and run them as smaller tiles.  An output element takes the same chain in either kernel.
         const long tail = big_tiles % cus;
         if (big_tiles > cus && tail > 0 && tail <= cus / 2) {
             if (tail % tj == 0) {
@@ -957,33 +967,12 @@ static hipError_t launch_tile(const uint8_t* A, const float* sa, const uint8_t* 
                 return launch_tile<SB_MODE>(A, sa, B + j_main * R, sb_tail, o + j_main, I, J - j_main, R, ldo, st);
             }
         }
-        const long wgs = std::min<long>((long)ti * tj, (long)cus * BigCfg::kOccupancy);
-        hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, JET_BIG>), dim3((unsigned)wgs),
-                           dim3(BigCfg::kThreads), BigCfg::kLdsBytes, st, A, sa, B, sb, o, (int)I, (int)ldo,
-                           (int)R, ti, tj);
-    } else {
-        const int ti = (int)((I + 127) / 128), tj = (int)(J / 128);
-        if (SB_MODE == kSbBlock && (long)ti * tj <= cus / 2) {
-            // 128x128 tiles would leave half of the CUs idle: 128x64 tiles, one per CU
-            hipLaunchKernelGGL((gemm_tile_kernel<kSbBlock, JET_HALF>), dim3((unsigned)(ti * tj * 2)),
-                               dim3(HalfCfg::kThreads), HalfCfg::kLdsBytes, st, A, sa, B, sb, o, (int)I, (int)ldo,
-                               (int)R, ti, tj * 2);
-            return hipGetLastError();
-        }
-        if ((long)ti * tj <= cus) {
-            // at most one workgroup per CU anyway: spend the LDS on two more stages, so that operands
-            // that come from HBM (decode batches against cold weights) are fetched three steps ahead
-            hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, JET_SMALL_DEEP>), dim3((unsigned)(ti * tj)),
-                               dim3(SmallDeepCfg::kThreads), SmallDeepCfg::kLdsBytes, st, A, sa, B, sb, o, (int)I,
-                               (int)ldo, (int)R, ti, tj);
-            return hipGetLastError();
-        }
-        const long wgs = std::min<long>((long)ti * tj, (long)cus * SmallCfg::kOccupancy);
-        hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, JET_SMALL>), dim3((unsigned)wgs),
-                           dim3(SmallCfg::kThreads), SmallCfg::kLdsBytes, st, A, sa, B, sb, o, (int)I,
-                           (int)ldo, (int)R, ti, tj);
+        return launch_tiles<SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
     }
-    return hipGetLastError();
+    // at most one workgroup per CU anyway: spend the LDS on two more stages, so that operands
+    // that come from HBM are fetched three steps ahead
+    if (((I + 127) / 128) * (J / 128) <= cus) return launch_tiles<SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
+    return launch_tiles<SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
 }
 
 hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb,
@@ -993,70 +982,47 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
     std::call_once(once, [] {
         hipError_t e = allow_lds(gemm_tile_kernel<kSbBlock, JET_BIG>, BigCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_BIG>, BigCfg::kLdsBytes);
+        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_WIDE>, WideCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL>, SmallCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL>, SmallCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_HALF>, HalfCfg::kLdsBytes);
-#define JET_SK_ATTR(D, W, RMT, AB) \
-    if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, RMT, AB>, sk_lds_bytes(D, W, RMT))
-        JET_SK_ATTR(6, 4, 1, 1); JET_SK_ATTR(6, 4, 1, 2);
-        JET_SK_ATTR(3, 8, 1, 1); JET_SK_ATTR(3, 8, 1, 2);
-        JET_SK_ATTR(1, 8, 1, 1); JET_SK_ATTR(1, 8, 1, 2);
-        JET_SK_ATTR(2, 8, 2, 3); JET_SK_ATTR(2, 8, 2, 4);
+#define JET_SK_ATTR(D, W, AB) \
+    if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, AB>, sk_lds_bytes(D, W))
+        JET_SK_ATTR(6, 4, 1); JET_SK_ATTR(6, 4, 2);
+        JET_SK_ATTR(3, 8, 1); JET_SK_ATTR(3, 8, 2);
+        JET_SK_ATTR(1, 8, 1); JET_SK_ATTR(1, 8, 2);
 #undef JET_SK_ATTR
-        if (e == hipSuccess) e = allow_lds(gemm_strip_kernel<JET_STRIP_SMALL>, StripSmall::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_strip_kernel<JET_STRIP_WIDE>, StripWide::kLdsBytes);
+#define JET_PANEL_ATTR(TM, TN, WR, WC, S, GP) \
+    if (e == hipSuccess) e = allow_lds(gemm_panel_kernel<PanelCfg<TM, TN, WR, WC, S, GP>>, PanelCfg<TM, TN, WR, WC, S, GP>::kLds);
+        JET_PANELS(JET_PANEL_ATTR)
+#undef JET_PANEL_ATTR
         attr_err = e;
     });
     if (attr_err != hipSuccess) return attr_err;
 
     uint16_t* o = static_cast<uint16_t*>(out);
-    // decode: a workgroup per 16-column strip; shape-only choice of ring depth / wave count
-    // (17-32 rows with more strips than CUs go to the strip kernel below: measured faster)
-    if ((I <= 16 || (I <= 32 && J / 16 <= 256)) && sb_mode == kSbBlock) {
+    // decode of up to 16 rows: a workgroup per 16-column strip; shape-only choice of ring depth / wave count
+    if (I <= 16 && sb_mode == kSbBlock) {
         const unsigned strips = (unsigned)(J / 16);
-#define JET_SKINNY_AB(D, W, RMT, AB)                                                                          \
-    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, RMT, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W, RMT), \
-                       st, A, sa, B, sb, o, (int)I, (int)J, (int)R)
+#define JET_SKINNY_AB(D, W, AB)                                                                             \
+    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
+                       sa, B, sb, o, (int)I, (int)J, (int)R)
         // copy only the 8-row activation blocks that hold a row of the batch
-#define JET_SKINNY(D, W, RMT)                                        \
-    do {                                                             \
-        if ((I + 7) / 8 < 2 * RMT) JET_SKINNY_AB(D, W, RMT, 2 * RMT - 1); \
-        else JET_SKINNY_AB(D, W, RMT, 2 * RMT);                      \
+#define JET_SKINNY(D, W)                       \
+    do {                                       \
+        if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
+        else JET_SKINNY_AB(D, W, 2);           \
     } while (0)
-        if (I > 16) {
-            JET_SKINNY(2, 8, 2);
-        } else if (strips > 256) {
-            JET_SKINNY(1, 8, 1);                        // two workgroups (16 waves) per CU
+        if (strips > 256) {
+            JET_SKINNY(1, 8);                        // two workgroups (16 waves) per CU
         } else if (R >= 1024) {
-            JET_SKINNY(3, 8, 1);
+            JET_SKINNY(3, 8);
         } else {
-            JET_SKINNY(6, 4, 1);
+            JET_SKINNY(6, 4);
         }
 #undef JET_SKINNY
 #undef JET_SKINNY_AB
-        return hipGetLastError();
-    }
-    // batches of 65-256 rows against a wide weight matrix (a hundred 128x128 tiles or more) are
-    // faster on the tile kernel (measured, gate/up 14336x4096: 30 against 45 us at 128 rows, 30
-    // against 74 us at 256 rows); narrower ones (4096 columns) stay on the strip kernel
-    const bool wide_batch = I > 64 && ((I + 127) / 128) * (J / 128) >= 100;
-    if (I <= 256 && sb_mode == kSbBlock && !wide_batch) {
-        // decode batches: 32- or 64-row blocks x 32-column strips
-        // 32-row blocks for up to 32 rows, and for larger batches whose 64-row grid would leave
-        // half of the CUs without a workgroup (shape-only rule; measured at 64 rows, N = 4096: 9.7
-        // against 12.8 us)
-        const long wide_wgs = ((I + StripWide::BM - 1) / StripWide::BM) * (J / 32);
-        if (I <= 32 || wide_wgs <= 128) {
-            const int rbs = (int)((I + StripSmall::BM - 1) / StripSmall::BM);
-            hipLaunchKernelGGL((gemm_strip_kernel<JET_STRIP_SMALL>), dim3((unsigned)(rbs * (J / 32))), dim3(512),
-                               StripSmall::kLdsBytes, st, A, sa, B, sb, o, (int)I, (int)J, (int)R, rbs);
-        } else {
-            const int rbs = (int)((I + StripWide::BM - 1) / StripWide::BM);
-            hipLaunchKernelGGL((gemm_strip_kernel<JET_STRIP_WIDE>), dim3((unsigned)(rbs * (J / 32))), dim3(512),
-                               StripWide::kLdsBytes, st, A, sa, B, sb, o, (int)I, (int)J, (int)R, rbs);
-        }
         return hipGetLastError();
     }
     if (sb_mode == kSbBlock) return launch_tile<kSbBlock>(A, sa, B, sb, o, I, J, R, J, st);

@@ -1,5 +1,5 @@
 """GPU parity at the full sizes of the workloads, in the launch configurations the
-benchmark times (persistent 256x256 tile kernel, strip and skinny decode kernels).
+benchmark times (persistent 256x256 tile kernel, panel and skinny decode kernels).
 
 The oracle cannot run a whole 10^12-MAC GEMM, so outputs are sampled: the oracle
 quantizes the same seeded bf16 inputs (rows are independent for 1x128 row groups,
@@ -185,7 +185,7 @@ def test_8b_decode(jet, idx, M):
 
 @pytest.mark.parametrize("idx", [0, 1, 4, 6])     # q, k, gate, down
 def test_unified_flow_invariance_8b(jet, idx):
-    """The same 128 token rows inside decode calls (M = 1, 8, 32, 128: skinny and strip
+    """The same 128 token rows inside decode calls (M = 1, 8, 32, 128: skinny and panel
     kernels) and at seeded positions inside training-forward calls (M = 4096, 16384:
     persistent tile kernel) give identical output bytes; again after each of three
     synthetic weight updates with re-quantization."""

@@ -64,19 +64,38 @@ def test_forward_shapes(jet, M, N, K):
     (5, 4224, 128, "skinny kernel, two workgroups per CU, one group: only the first wave has a unit"),
     (8, 4224, 1152, "skinny kernel, two workgroups per CU, nine groups"),
     (9, 4224, 384, "skinny kernel, two workgroups per CU, two activation blocks"),
-    (20, 2048, 640, "skinny kernel, two row tiles, the second one 4 rows: three activation blocks copied"),
-    (27, 2048, 640, "skinny kernel, two row tiles, the second one 11 rows: four activation blocks copied"),
-    (27, 4608, 384, "strip kernel, one 32-row block (17-32 rows against more than 256 strips of 16 columns)"),
-    (50, 4096, 640, "strip kernel, 32-row blocks, second block 18 rows, odd number of groups"),
-    (200, 4352, 640, "strip kernel, 64-row blocks, last block holds 8 rows, odd number of groups"),
-    (100, 14336, 256, "tile kernel on 128 x 64 tiles (112 tiles of 128 x 128 would leave half of the CUs idle), ragged rows"),
-    (200, 14336, 384, "tile kernel on 128 x 128 tiles, four stages (224 tiles), ragged second tile row"),
+    (20, 2048, 640, "panel kernel, 32x16 tiles, 4 rows in the second row tile"),
+    (27, 2048, 640, "panel kernel, 32x16 tiles, 11 rows in the second row tile"),
+    (27, 4608, 384, "panel kernel, 32x32 tiles"),
+    (50, 4096, 640, "panel kernel, second row block ragged, odd number of groups"),
+    (200, 4352, 640, "panel kernel, 64-row blocks, last block holds 8 rows, odd number of groups"),
+    (100, 14336, 256, "128x64 or 128x112 tiles, ragged rows"),
+    (200, 14336, 384, "wide tiles, ragged second row block"),
 ])
 def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):
     """The launch rules of the decode path by shape, each with a row count that leaves its last
     row block partly empty."""
     y, ref, ops = _fwd_case(jet, M, N, K, seed=31 * M + N)
     check_gemm(y, ref, f"fwd {M}x{N}x{K}: {kernel}", operands=ops)
+
+
+@pytest.mark.parametrize("M,N,groups,tile", [
+    (17, 128, 1, "32x16"), (19, 128, 37, "32x16"), (17, 4224, 2, "32x32"), (30, 4224, 37, "32x32"),
+    (17, 8320, 3, "32x48, last panel 16 columns"), (29, 8320, 21, "32x48"), (17, 12416, 5, "32x64"), (32, 12416, 16, "32x64"),
+    (18, 16512, 1, "32x112, last panel 48 columns"), (32, 16512, 19, "32x112"), (40, 6272, 4, "48x32"), (33, 6272, 35, "48x32"),
+    (33, 8320, 2, "48x64"), (47, 8320, 17, "48x64"), (48, 16512, 1, "48x112"), (35, 16512, 18, "48x112"),
+    (49, 8320, 3, "64x64"), (63, 8320, 18, "64x64"), (50, 16512, 2, "64x112"), (64, 16512, 17, "64x112"),
+    (65, 9600, 1, "80x64"), (79, 9600, 18, "80x64"), (70, 16512, 3, "80x112"), (80, 16512, 17, "80x112"),
+    (241, 4736, 2, "96x64, third block 49 rows"), (250, 4736, 18, "96x64"), (81, 16512, 1, "96x112"), (95, 16512, 17, "96x112"),
+    (97, 14464, 2, "128x64"), (127, 14464, 17, "128x64"), (97, 16512, 1, "128x112"), (120, 16512, 18, "128x112"),
+    (161, 14464, 3, "128x128 of the tile kernel"), (193, 19072, 4, "256x128 of the tile kernel"),
+    (193, 19072, 1, "256x128, fewer groups than stages"), (400, 17152, 2, "256x256, second tile row 144 rows"),
+])
+def test_forward_on_every_tile_of_the_launch_rule(jet, M, N, groups, tile):
+    """A shape for which the rule takes each tile, with ragged rows, ragged columns where the tile does not divide
+    128, odd and even numbers of groups, fewer groups than ring stages and more than two scale chunks of 16."""
+    y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=13 * M + N + groups)
+    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {tile}", operands=ops)
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 384, 512), (5, 256, 128), (130, 128, 640)])

@@ -64,7 +64,7 @@ def _layer_groups(seed):
             "xT": g(orc.quant_act(x, row=False, col=True)["q_colT"]), "dyT": g(orc.quant_act(dy, row=False, col=True)["q_colT"])}
 
 
-@pytest.mark.parametrize("T", [8, 48, 200, 4096])      # skinny, both strip kernels, tile kernel
+@pytest.mark.parametrize("T", [8, 48, 200, 4096])      # skinny, panel and tile kernels
 @pytest.mark.parametrize("pair", [("x", "w"), ("dy", "w"), ("dyT", "xT")])
 def test_group_sums_of_layer_like_operands_equal_the_model(jet, pair, T):
     """Operands as the quantizers produce them (FProp, DGrad and WGrad pairings): the raw group

@@ -1,7 +1,7 @@
 """The unified precision flow through a stack of MLP blocks (Sec. 4.1: the rollout graph is a
 subgraph of the training forward graph, so a token must get the same numbers in both): the same
 token rows pushed through L blocks of  RMSNorm -> FP8 | gate/up FProp | SiLU*up -> FP8 | down
-FProp | residual add  as decode-shaped batches (M = 1 ... 100: skinny and strip kernels) and
+FProp | residual add  as decode-shaped batches (M = 1 ... 100: skinny and panel kernels) and
 inside training-shaped batches (M = 640, 4096: tile kernels) must agree in every byte at every
 depth.  Any shape-dependent arithmetic anywhere in the chain would be amplified by the
 re-quantizations of the following blocks, which is the mismatch the method removes."""
@@ -51,7 +51,7 @@ def _forward(jet, blocks, x):
 def test_decode_and_training_shapes_agree_through_a_stack_of_blocks(jet):
     blocks = _weights(jet)
     tokens = dev_bf16(ji.activations(TOKENS, HIDDEN, seed=9300))
-    base = _forward(jet, blocks, tokens)                                        # M = 100: strip kernel
+    base = _forward(jet, blocks, tokens)                                        # M = 100: panel kernel
     assert all(torch.isfinite(t.float()).all() for t in base)
     # the blocks do something: the stream moves away from its input
     assert (base[-1].float() - tokens.float()).abs().mean() > 0.05
