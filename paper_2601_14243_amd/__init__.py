@@ -1,7 +1,8 @@
 """MI355X-native block-scaled FP8 linear layer (Jet-RL's unified precision flow).
 
 The product is ``libjet.so`` (hand-written HIP for gfx950 behind the C ABI of
-``include/jet.h``); this package is a thin ctypes binding with the same names.
+``include/jet.h``); this package is a thin binding with the same names (ctypes, and a native
+extension for the tensor helpers).
 PyTorch supplies device memory and streams only.
 """
 from .binding import (JET_SRC_BF16, JET_SRC_FP8_ROW, JetError, fp8_linear_dgrad, fp8_linear_fwd,

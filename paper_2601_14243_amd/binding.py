@@ -1,11 +1,13 @@
-"""ctypes binding of libjet.so: argument marshalling only.
+"""Binding of libjet.so: argument marshalling only.
 
-``jet_*`` functions mirror include/jet.h one to one (raw pointers, sizes, a
+``jet_*`` functions mirror include/jet.h one to one through ctypes (raw pointers, sizes, a
 stream handle; they return the status code).  The un-prefixed helpers take
 torch CUDA tensors, allocate the outputs with torch, pass ``data_ptr()`` and the
-current stream, and raise ``JetError`` on a non-zero status.  No arithmetic of
-the method happens in Python, and there is no fallback: if libjet.so is missing
-the import of the library fails loudly.
+current stream, and raise ``JetError`` on a non-zero status.  Calls of the plain form (exact tensors of
+the right type and shape) are answered by the extension ``_jet_host`` (csrc/jet_host.cpp), which does the
+same in one native call; what it does not take (None) goes through the Python code here, which also words
+the errors.  No arithmetic of the method happens in Python, and there is no fallback: if
+libjet.so or the extension is missing the first call fails loudly.
 """
 from __future__ import annotations
 
@@ -21,7 +23,10 @@ JET_SRC_BF16 = 0
 JET_SRC_FP8_ROW = 1
 GROUP = 128
 
+_HOST_PATH = os.path.join(_HERE, "_jet_host.so")
+
 _lib = None
+_host = None
 
 
 class JetError(RuntimeError):
@@ -59,6 +64,19 @@ def lib() -> ctypes.CDLL:
         L.jet_version.restype = i32
         _lib = L
     return _lib
+
+
+def _native():
+    """Load the native marshalling (built in-tree beside libjet.so)."""
+    global _host
+    if _host is None:
+        lib()
+        if not os.path.exists(_HOST_PATH):
+            raise FileNotFoundError(f"{_HOST_PATH} is missing: build it with `python -m paper_2601_14243_amd.build`")
+        from . import _jet_host
+        _jet_host.init(JetError, torch.OutOfMemoryError)
+        _host = _jet_host
+    return _host
 
 
 # ---------------------------------------------------------------- raw calls
@@ -122,6 +140,9 @@ def quant_act(x: torch.Tensor, x_scales: torch.Tensor | None = None, row: bool =
               col: bool = False, out: dict | None = None) -> dict:
     """1x128 quantization of a bf16 [M,K] tensor, or of an FP8-saved one (uint8 codes
     plus x_scales).  Returns dict(q_row, s_row, q_colT, s_colT) with the requested pairs."""
+    r = (_host or _native()).quant_act(x, x_scales, row, col, out)
+    if r is not None:
+        return r
     src = JET_SRC_BF16 if x_scales is None else JET_SRC_FP8_ROW
     _need(x, torch.bfloat16 if src == JET_SRC_BF16 else torch.uint8, "x")
     M, K = x.shape
@@ -152,6 +173,9 @@ def _row_pair(M, K, dev, out):
 
 def rmsnorm_quant(x: torch.Tensor, gamma: torch.Tensor, eps: float, out: dict | None = None) -> dict:
     """RMSNorm of bf16 [M,K] with bf16 weight [K], written as 1x128 FP8: dict(q_row, s_row)."""
+    r = (_host or _native()).rmsnorm_quant(x, gamma, eps, out)
+    if r is not None:
+        return r
     _need(x, torch.bfloat16, "x")
     M, K = x.shape
     if not gamma.is_cuda or not gamma.is_contiguous() or gamma.dtype != torch.bfloat16 or gamma.shape != (K,):
@@ -166,6 +190,9 @@ def rmsnorm_quant(x: torch.Tensor, gamma: torch.Tensor, eps: float, out: dict | 
 def silu_mul_quant(gate: torch.Tensor, up: torch.Tensor, out: dict | None = None) -> dict:
     """SiLU(gate) * up of two bf16 [M,K] tensors (contiguous, or the two halves of one
     contiguous [M,2K] tensor), written as 1x128 FP8: dict(q_row, s_row)."""
+    r = (_host or _native()).silu_mul_quant(gate, up, out)
+    if r is not None:
+        return r
     for t, name in ((gate, "gate"), (up, "up")):
         if not t.is_cuda or t.dtype != torch.bfloat16 or t.dim() != 2 or t.stride(1) != 1:
             raise TypeError(f"{name}: need a 2-D CUDA bf16 tensor with unit column stride")
@@ -182,6 +209,9 @@ def silu_mul_quant(gate: torch.Tensor, up: torch.Tensor, out: dict | None = None
 def silu_mul_bwd(gate: torch.Tensor, up: torch.Tensor, dh: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
     """Backward of h = SiLU(gate) * up: returns dgu bf16 [M, 2K] = [dgate | dup] (one contiguous
     tensor, the layout the fused gate/up projection's backward consumes)."""
+    r = (_host or _native()).silu_mul_bwd(gate, up, dh, out)
+    if r is not None:
+        return r
     for t, name in ((gate, "gate"), (up, "up")):
         if not t.is_cuda or t.dtype != torch.bfloat16 or t.dim() != 2 or t.stride(1) != 1:
             raise TypeError(f"{name}: need a 2-D CUDA bf16 tensor with unit column stride")
@@ -204,6 +234,9 @@ def silu_mul_bwd(gate: torch.Tensor, up: torch.Tensor, dh: torch.Tensor, out: to
 
 def quant_weight(w: torch.Tensor, transposed: bool = False, out: tuple | None = None):
     """128x128 quantization of bf16 [N,K].  Returns (q, s) or (q, s, qT, sT)."""
+    r = (_host or _native()).quant_weight(w, transposed, out)
+    if r is not None:
+        return r
     _need(w, torch.bfloat16, "w")
     N, K = w.shape
     dev = w.device
@@ -250,6 +283,9 @@ def _gemm_out(out, shape, a, b, name: str) -> torch.Tensor:
 
 def fp8_linear_fwd(qx, sx, qw, sw, out: torch.Tensor | None = None) -> torch.Tensor:
     """y bf16 [M,N] = X W^T."""
+    r = (_host or _native()).gemm(0, qx, sx, qw, sw, out)
+    if r is not None:
+        return r
     _need_operand(qx, sx, 1, "qx")
     _need_operand(qw, sw, GROUP, "qw")
     M, K = qx.shape
@@ -263,6 +299,9 @@ def fp8_linear_fwd(qx, sx, qw, sw, out: torch.Tensor | None = None) -> torch.Ten
 
 def fp8_linear_dgrad(qdy, sdy, qwT, swT, out: torch.Tensor | None = None) -> torch.Tensor:
     """dx bf16 [M,K] = dY W."""
+    r = (_host or _native()).gemm(1, qdy, sdy, qwT, swT, out)
+    if r is not None:
+        return r
     _need_operand(qdy, sdy, 1, "qdy")
     _need_operand(qwT, swT, GROUP, "qwT")
     M, N = qdy.shape
@@ -276,6 +315,9 @@ def fp8_linear_dgrad(qdy, sdy, qwT, swT, out: torch.Tensor | None = None) -> tor
 
 def fp8_linear_wgrad(qdyT, sdyT, qxT, sxT, out: torch.Tensor | None = None) -> torch.Tensor:
     """dw bf16 [N,K] = dY^T X."""
+    r = (_host or _native()).gemm(2, qdyT, sdyT, qxT, sxT, out)
+    if r is not None:
+        return r
     _need_operand(qdyT, sdyT, 1, "qdyT")
     _need_operand(qxT, sxT, 1, "qxT")
     N, M = qdyT.shape

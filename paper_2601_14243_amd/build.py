@@ -3,11 +3,13 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libjet.so")
 PROBE_LIB = os.path.join(HERE, "libjet_probe.so")     # measurement aid of bench.py, not part of the product ABI
+HOST_LIB = os.path.join(HERE, "_jet_host.so")         # native marshalling of the tensor helpers (host code only)
 SOURCES = ["jet_api.hip", "jet_quant.hip", "jet_fused.hip", "jet_gemm.hip"]
 PROBE_SOURCES = ["jet_probe.hip"]
 HEADERS = ["jet_internal.h", "jet_numerics.h", os.path.join("..", "..", "include", "jet.h")]
@@ -30,11 +32,33 @@ def _compile(lib: str, sources, force: bool) -> None:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
 
 
+def _compile_host(force: bool) -> None:
+    """The Python extension behind binding.py's tensor helpers: g++ against torch's headers, linked to libjet.so beside it."""
+    src = os.path.join(CSRC, "jet_host.cpp")
+    if not force and os.path.exists(HOST_LIB):
+        if os.path.getmtime(HOST_LIB) >= max(os.path.getmtime(p) for p in (src, os.path.join(CSRC, HEADERS[2]))):
+            return
+    import torch
+    from torch.utils import cpp_extension
+    rocm = cpp_extension.ROCM_HOME or "/opt/rocm"
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-variable",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{p}" for p in cpp_extension.include_paths()], f"-isystem{os.path.join(rocm, 'include')}",
+           f"-isystem{sysconfig.get_paths()['include']}", "-o", HOST_LIB, src,
+           f"-L{torch_lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-L{HERE}", "-l:libjet.so",
+           "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+
+
 def build(force: bool = True) -> str:
-    """Compile every HIP source: libjet.so (the product) and libjet_probe.so (the benchmark's
-    matrix-core rate probe).  Returns the path of libjet.so."""
+    """Compile every source: libjet.so (the product), its Python extension and libjet_probe.so (the
+    benchmark's matrix-core rate probe).  Returns the path of libjet.so."""
     _compile(LIB, SOURCES, force)
     _compile(PROBE_LIB, PROBE_SOURCES, force)
+    _compile_host(force)
     return LIB
 
 

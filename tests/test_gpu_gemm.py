@@ -68,8 +68,8 @@ def test_forward_shapes(jet, M, N, K):
     (27, 2048, 640, "panel kernel, 32x16 tiles, 11 rows in the second row tile"),
     (27, 4608, 384, "panel kernel, 32x32 tiles"),
     (50, 4096, 640, "panel kernel, second row block ragged, odd number of groups"),
-    (200, 4352, 640, "panel kernel, 64-row blocks, last block holds 8 rows, odd number of groups"),
-    (100, 14336, 256, "128x64 or 128x112 tiles, ragged rows"),
+    (200, 4352, 640, "panel kernel, 80x64 tiles, last block holds 40 rows, odd number of groups"),
+    (100, 14336, 256, "64x112 tiles, ragged second row block"),
     (200, 14336, 384, "wide tiles, ragged second row block"),
 ])
 def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):

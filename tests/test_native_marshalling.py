@@ -1,0 +1,116 @@
+"""The native marshalling of the tensor helpers (csrc/jet_host.cpp) against the Python path it stands in for: what it
+does not take it declines (None), what it takes has the same results, types and errors."""
+import pytest
+import torch
+
+from paper_2601_14243_amd import binding as b
+
+u8, f32, bf = torch.uint8, torch.float32, torch.bfloat16
+
+
+def test_declines_everything_but_the_plain_form():
+    h = b._native()
+    x, s = torch.zeros((4, 256), dtype=bf), torch.ones((4, 2))
+    q, w = torch.zeros((4, 256), dtype=u8), torch.zeros((128, 256), dtype=u8)
+    assert h.quant_act(x, None, True, False, None) is None                      # CPU tensors
+    assert h.quant_act("x", None, True, False, None) is None                    # no tensor at all
+    assert h.rmsnorm_quant(x, x[0], 1e-6, None) is None
+    assert h.silu_mul_quant(x, x, None) is None
+    assert h.silu_mul_bwd(x, x, x, None) is None
+    assert h.quant_weight(x, True, None) is None
+    for kind in (0, 1, 2):
+        assert h.gemm(kind, q, s, w, s, None) is None
+    with pytest.raises(TypeError):
+        h.gemm(0, q, s)
+    with pytest.raises(TypeError):
+        b.quant_act(x)                                                          # the Python path words the error
+    with pytest.raises(TypeError):
+        b.quant_weight(x)
+
+
+class _Declines:
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _flat(r):
+    if isinstance(r, dict):
+        return [r[k] for k in sorted(r)]
+    return list(r) if isinstance(r, tuple) else [r]
+
+
+@pytest.mark.gpu
+def test_same_results_as_the_python_path(monkeypatch):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(bf)
+    M, N, K = 128, 256, 384
+    x, dy, w, gamma, both, dh = rnd(M, K), rnd(M, N), torch.nn.Parameter(rnd(N, K)), rnd(K), rnd(M, 2 * K), rnd(M, K)
+    wq = b.quant_weight(w, transposed=True)
+    qx, qd = b.quant_act(x, row=True, col=True), b.quant_act(dy, row=True, col=True)
+
+    def calls():
+        e = lambda t: torch.empty_like(t)
+        o = {k: e(v) for k, v in qx.items()}
+        yield lambda: b.quant_act(x)
+        yield lambda: b.quant_act(x, row=False, col=True)
+        yield lambda: b.quant_act(x, row=True, col=True, out=o)
+        yield lambda: b.quant_act(qx["q_row"], qx["s_row"], row=False, col=True)
+        yield lambda: b.quant_act(x, col=True, out={"q_row": e(qx["q_row"]), "s_row": e(qx["s_row"])})   # half given: the rest is added
+        yield lambda: b.rmsnorm_quant(x, gamma, 1e-6)
+        yield lambda: b.rmsnorm_quant(x, gamma, 1, out={"q_row": e(qx["q_row"]), "s_row": e(qx["s_row"])})  # an int eps
+        yield lambda: b.silu_mul_quant(both[:, :K], both[:, K:])
+        yield lambda: b.silu_mul_bwd(both[:, :K], both[:, K:], dh)
+        yield lambda: b.silu_mul_bwd(both[:, :K], both[:, K:], dh, out=torch.empty((M, 2 * K), dtype=bf, device="cuda"))
+        yield lambda: b.quant_weight(w)
+        yield lambda: b.quant_weight(w, transposed=True)
+        yield lambda: b.quant_weight(w, transposed=True, out=tuple(e(t) for t in wq))
+        yield lambda: b.quant_weight(w, out=[e(t) for t in wq])
+        yield lambda: b.fp8_linear_fwd(qx["q_row"], qx["s_row"], wq[0], wq[1])
+        yield lambda: b.fp8_linear_fwd(qx["q_row"], qx["s_row"], wq[0], wq[1], out=torch.empty((M, N), dtype=bf, device="cuda"))
+        yield lambda: b.fp8_linear_dgrad(qd["q_row"], qd["s_row"], wq[2], wq[3])
+        yield lambda: b.fp8_linear_wgrad(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"])
+
+    for i, call in enumerate(calls()):
+        monkeypatch.undo()
+        r1 = [t.clone() for t in _flat(call())]
+        monkeypatch.setattr(b, "_host", _Declines())
+        r2 = _flat(call())
+        assert len(r1) == len(r2), i
+        for p, q in zip(r1, r2):
+            assert p.dtype == q.dtype and p.shape == q.shape and p.stride() == q.stride() and p.device == q.device, i
+            assert torch.equal(p.view(u8), q.view(u8)), i
+            assert not p.requires_grad and not q.requires_grad
+    monkeypatch.undo()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_same_errors_as_the_python_path(monkeypatch, native):
+    if not native:
+        monkeypatch.setattr(b, "_host", _Declines())
+    z = lambda *s, dt=bf: torch.zeros(s, dtype=dt, device="cuda")
+    with pytest.raises(b.JetError) as e:
+        b.quant_act(z(4, 200))                              # K % 128: the C ABI's status
+    assert e.value.status == 2 and "jet_quant_act" in str(e.value)
+    with pytest.raises(b.JetError) as e:
+        b.rmsnorm_quant(z(4, 128), z(128), -1.0)
+    assert e.value.status == 4
+    with pytest.raises(b.JetError):
+        b.quant_act(z(100, 128), row=False, col=True)       # M % 128 in column mode
+    with pytest.raises(TypeError):
+        b.quant_act(z(4, 128, dt=f32))
+    with pytest.raises(TypeError):
+        b.rmsnorm_quant(z(4, 128), z(256)[::2], 1e-6)
+    with pytest.raises(TypeError):
+        b.silu_mul_quant(z(4, 128), z(4, 256))
+    with pytest.raises(ValueError):
+        b.silu_mul_bwd(z(4, 128), z(4, 128), z(8, 128))
+    q, s, w, ws = z(4, 256, dt=u8), z(4, 2, dt=f32), z(128, 256, dt=u8), z(1, 2, dt=f32)
+    with pytest.raises(ValueError):
+        b.fp8_linear_fwd(q, s, w, z(1, 3, dt=f32))
+    with pytest.raises(ValueError):
+        b.fp8_linear_fwd(q, s, z(128, 128, dt=u8), z(1, 1, dt=f32))
+    with pytest.raises(ValueError):
+        b.fp8_linear_fwd(q, s, w, ws, out=z(4, 256))
+    with pytest.raises(TypeError):
+        b.fp8_linear_fwd(q[:, ::2], s, w, ws)
