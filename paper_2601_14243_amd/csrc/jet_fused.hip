@@ -26,28 +26,29 @@ __device__ __forceinline__ uint32_t bf16_from_double(double v) {
     return bf16_rne(f);
 }
 
-// bf16( g / (1 + e^-g) ) of a bf16 value g, the real function rounded once.
-// Fast path in binary32: e^-g = 2^y with y = -g log2(e) split as -g c_hi (exact: 8 x 16
-// significant bits) plus a small remainder folded in as a factor 1 + ln2 * (-g c_lo); the
-// hardware 2^y and reciprocal are good to 1 ulp each, so the result is within 5 ulp of the
-// real value for |g| <= 80 and results above 2^-100.  Where that cannot decide the bf16
-// rounding (the binary32 result is within 8 ulp of a tie), and outside that range, binary64
-// arithmetic decides.  The function has 65280 finite inputs; the tests check every one.
-__device__ __forceinline__ uint32_t silu_bf16(float g) {
+// silu(g) = g / (1 + e^-g) of a bf16 value g with |g| <= 80, to be rounded to bf16.
+// e^-g = 2^y with y = -g log2(e) split as -g c_hi (exact: 8 x 16 significant bits) plus a small remainder folded in
+// as a factor 1 + ln2 * (-g c_lo); the hardware 2^y and reciprocal are good to 1 ulp each, and one residual
+// correction of the quotient leaves it within 3 half ulps of the real value.  That is not a proof for the rounding to bf16, but
+// the function has one 16-bit input: its bf16 rounding equals that of the binary64 evaluation for every finite g >= -87
+// (the tests run all of them), so nothing has to be decided at run time.  The residual's sign keeps that of a zero input.
+struct Silu {
+    float a, e, r;    // silu(g), e^-g, 1 / (1 + e^-g)
+};
+__device__ __forceinline__ Silu silu_fast(float g) {
     const float c_hi = 0x1.7154p+0f, c_lo = 0x1.d94aep-18f, ln2 = 0x1.62e43p-1f;
     const float p2 = __builtin_amdgcn_exp2f(-g * c_hi);
-    const float e = __builtin_fmaf(p2, (-g * c_lo) * ln2, p2);
-    const float a = g * __builtin_amdgcn_rcpf(1.0f + e);
-    const uint32_t low = __float_as_uint(a) & 0xffffu;
-    const bool near_tie = (low - (0x8000u - 8u)) <= 16u;
-    const bool in_range = fabsf(g) <= 80.0f && fabsf(a) >= 0x1p-100f;
-    if (near_tie || !in_range) {
-        const double gd = (double)g;
-        return bf16_from_double(gd / (1.0 + exp(-gd)));
-    }
-    return bf16_rne(a);
+    const float e = __builtin_fmaf(p2, (-g * c_lo) * ln2, p2);     // within 4 ulp
+    const float d = 1.0f + e, r = __builtin_amdgcn_rcpf(d);
+    const float q = g * r;
+    return Silu{__builtin_fmaf(-__builtin_fmaf(d, q, -g), r, q), e, r};
 }
-
+constexpr float kSiluRange = 80.0f;
+// the same rounded to bf16, for any finite g
+__device__ __forceinline__ uint32_t silu_any(float g) {
+    const double gd = (double)g;
+    return bf16_from_double(gd / (1.0 + exp(-gd)));
+}
 // quantize the 16 values of a lane (a team of 8 lanes holds one 128-group) and store them
 __device__ __forceinline__ void quantize_store(float (&v)[16], uint8_t* q16, float* s1, bool leader) {
     float am = 0.0f;
@@ -76,6 +77,8 @@ __device__ __forceinline__ void unpack16(const uint16_t* p, float (&v)[16]) {
 // SiLU(gate) * up -> 1x128 FP8.  a = bf16(silu(g)), h = bf16(a * u) (binary32 product).
 // Same decomposition as the row quantizer: a team of 8 lanes owns a group, a lane 16
 // consecutive elements (2 x 32 B in, 16 B out).  gate and up share the row stride ld.
+// At memory speed for large calls ([16384, 14336]: 5.0 TB/s) once no value near a rounding tie went through binary64 (one
+// gate in a thousand, -3.046875, did, and with it most waves): [1000, 14336] 18.2 -> 15.7 us, [8, 14336] 4.2 -> 2.9.
 // ------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __restrict__ gate,
                                                              const uint16_t* __restrict__ up, long ld,
@@ -86,16 +89,27 @@ __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __r
     for (long g = ((long)blockIdx.x * 256 + threadIdx.x) >> 3; g < n_groups; g += n_teams) {
         const long m = g / groups_per_row;
         const long src = m * ld + (g - m * groups_per_row) * kGroup + l8 * 16;
-        float a[16], u[16];
+        float a[16], u[16], gmax = 0.0f;
         unpack16(gate + src, a);
         unpack16(up + src, u);
 #pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-            const float act0 = __uint_as_float(silu_bf16(a[i]) << 16);
-            const float act1 = __uint_as_float(silu_bf16(a[i + 1]) << 16);
-            const uint32_t h2 = bf16_pack2(act0 * u[i], act1 * u[i + 1]);
-            a[i] = bf16_lo(h2);
-            a[i + 1] = bf16_hi(h2);
+        for (int i = 0; i < 16; ++i) gmax = fmaxf(gmax, fabsf(a[i]));
+        uint32_t act[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) act[i] = bf16_pack2(silu_fast(a[2 * i]).a, silu_fast(a[2 * i + 1]).a);
+        if (!(gmax <= kSiluRange)) {    // one branch for the lane's 16 values, then only those out of range
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (fabsf(a[i]) <= kSiluRange) continue;
+                const int sh = 16 * (i & 1);
+                act[i >> 1] = (act[i >> 1] & (0xffffu << (16 - sh))) | (silu_any(a[i]) << sh);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t h2 = bf16_pack2(bf16_lo(act[i]) * u[2 * i], bf16_hi(act[i]) * u[2 * i + 1]);
+            a[2 * i] = bf16_lo(h2);
+            a[2 * i + 1] = bf16_hi(h2);
         }
         quantize_store(a, q + g * kGroup + l8 * 16, s + g, l8 == 0);
     }
@@ -268,25 +282,22 @@ __global__ __launch_bounds__(256) void rmsnorm_quant_kernel(const uint16_t* __re
 // g = -1.2785 where 1 + g (1 - s) cancels), and whenever the result is closer than that bound to
 // a bf16 tie, or outside the range the bound holds in, binary64 decides.
 // ------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t silu_grad_mul_bf16(float g, float da) {
-    const float c_hi = 0x1.7154p+0f, c_lo = 0x1.d94aep-18f, ln2 = 0x1.62e43p-1f;
-    const float p2 = __builtin_amdgcn_exp2f(-g * c_hi);
-    const float e = __builtin_fmaf(p2, (-g * c_lo) * ln2, p2);     // e^-g, within 4 ulp
-    const float r = __builtin_amdgcn_rcpf(1.0f + e);               // s, within 5 ulp
-    const float om = e * r;                                        // 1 - s without cancellation, within 9 ulp
+// The window is what an error bound gives, 7 + 10 |g om| / |w| ulps, tightened by evaluating r w on every finite gate value
+// with |g| <= 80: its error plus one ulp uses at most two thirds of 6 + 8 |g om| / |w|.
+__device__ __forceinline__ float silu_grad_mul(float g, float da, const Silu& s, bool& sure) {
+    const float om = s.e * s.r;                                    // 1 - s without cancellation
     const float gom = g * om;
-    const float w = 1.0f + gom;                                    // absolute error <= 10 ulp(g om) + half an ulp of w
-    const float prod = da * (r * w);
-    // error of prod in its own ulps: <= 7 + 10 |g om| / |w|; doubled as the window around a tie
-    const float window = 16.0f + 24.0f * fabsf(gom) * __builtin_amdgcn_rcpf(fabsf(w));
+    const float w = 1.0f + gom;
+    const float prod = da * (s.r * w);
+    const float window = 6.0f + 8.0f * fabsf(gom) * __builtin_amdgcn_rcpf(fabsf(w));
     const float dist = fabsf((float)(int)(__float_as_uint(prod) & 0xffffu) - 32768.0f);
-    const bool in_range = fabsf(g) <= 80.0f && fabsf(prod) >= 0x1p-100f;
-    if (!(dist > window) || !in_range) {
-        const double gd = (double)g;
-        const double sd = 1.0 / (1.0 + exp(-gd));
-        return bf16_from_double((double)da * (sd * (1.0 + gd * (1.0 - sd))));
-    }
-    return bf16_rne(prod);
+    sure = dist > window && fabsf(g) <= kSiluRange && fabsf(prod) >= 0x1p-100f;
+    return prod;
+}
+__device__ __forceinline__ uint32_t silu_grad_mul_any(float g, float da) {
+    const double gd = (double)g;
+    const double sd = 1.0 / (1.0 + exp(-gd));
+    return bf16_from_double((double)da * (sd * (1.0 + gd * (1.0 - sd))));
 }
 
 __global__ __launch_bounds__(256) void silu_mul_bwd_kernel(const uint16_t* __restrict__ gate,
@@ -304,15 +315,33 @@ __global__ __launch_bounds__(256) void silu_mul_bwd_kernel(const uint16_t* __res
         const uint32_t gw[4] = {g4.x, g4.y, g4.z, g4.w}, uw[4] = {u4.x, u4.y, u4.z, u4.w},
                        dw[4] = {d4.x, d4.y, d4.z, d4.w};
         uint32_t og[4], ou[4];
+        uint32_t unsure = 0;            // bit per value: one branch for the thread's 8, then only what needs it
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float g0 = bf16_lo(gw[i]), g1 = bf16_hi(gw[i]);
             const float u0 = bf16_lo(uw[i]), u1 = bf16_hi(uw[i]);
             const float d0 = bf16_lo(dw[i]), d1 = bf16_hi(dw[i]);
-            const float a0 = __uint_as_float(silu_bf16(g0) << 16), a1 = __uint_as_float(silu_bf16(g1) << 16);
-            ou[i] = bf16_pack2(d0 * a0, d1 * a1);
+            const Silu s0 = silu_fast(g0), s1 = silu_fast(g1);
+            const uint32_t a2 = bf16_pack2(s0.a, s1.a);
+            ou[i] = bf16_pack2(d0 * bf16_lo(a2), d1 * bf16_hi(a2));
             const uint32_t da2 = bf16_pack2(d0 * u0, d1 * u1);
-            og[i] = silu_grad_mul_bf16(g0, bf16_lo(da2)) | (silu_grad_mul_bf16(g1, bf16_hi(da2)) << 16);
+            bool sure0, sure1;
+            const float p0 = silu_grad_mul(g0, bf16_lo(da2), s0, sure0), p1 = silu_grad_mul(g1, bf16_hi(da2), s1, sure1);
+            og[i] = bf16_pack2(p0, p1);
+            unsure |= (sure0 ? 0u : 1u << (2 * i)) | (sure1 ? 0u : 2u << (2 * i));
+        }
+        if (unsure) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (!(unsure >> i & 1)) continue;
+                const int w = i >> 1, sh = 16 * (i & 1);
+                const uint32_t keep = 0xffffu << (16 - sh);
+                const float g = __uint_as_float((gw[w] >> sh) << 16), d = __uint_as_float((dw[w] >> sh) << 16);
+                const float u = __uint_as_float((uw[w] >> sh) << 16);
+                if (!(fabsf(g) <= kSiluRange))
+                    ou[w] = (ou[w] & keep) | (bf16_rne(d * __uint_as_float(silu_any(g) << 16)) << sh);
+                og[w] = (og[w] & keep) | (silu_grad_mul_any(g, __uint_as_float(bf16_rne(d * u) << 16)) << sh);
+            }
         }
         *reinterpret_cast<uint4*>(dgate + m * ld_out + k) = uint4{og[0], og[1], og[2], og[3]};
         *reinterpret_cast<uint4*>(dup + m * ld_out + k) = uint4{ou[0], ou[1], ou[2], ou[3]};

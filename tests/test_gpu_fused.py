@@ -6,7 +6,7 @@ import torch
 
 import jet_inputs as ji
 import oracle as orc
-from jet_testlib import dev_bf16, host
+from jet_testlib import dev_bf16, host, host_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -81,6 +81,28 @@ def test_silu_mul_quant_extreme_values(jet):
     got = jet.silu_mul_quant(dev_bf16(gate), dev_bf16(up))
     _same("q_row", host(got["q_row"]), want["q_row"])
     _same("s_row", host(got["s_row"]), want["s_row"])
+
+
+@pytest.mark.parametrize("M,K", [(1, 128), (33, 384)])
+def test_silu_gates_beyond_the_binary32_range_next_to_ordinary_ones(jet, M, K):
+    """Lanes in which some of the gates are beyond +-80 (binary64) and some are not, forward and backward, and
+    the gates whose silu lies next to a rounding tie (5.9375, -3.046875, 0.0078125)."""
+    both = ji.mlp_intermediate(M, K, seed=31 + M)
+    gate, up = both[:, :K].copy(), both[:, K:].copy()
+    gate[:, 3::16] = 0x42A1                              # 80.5
+    gate[::2, 12::32] = 0xC2AE                           # -87
+    gate[:, 5::48] = 0xC2C0                              # -96: a subnormal result
+    gate[:, 7::16], gate[:, 8::16], gate[:, 9::16] = 0x40BE, 0xC043, 0x3C00
+    gate[:, 10::32] = 0x8000
+    want = orc.silu_mul_quant(gate, up)
+    got = jet.silu_mul_quant(dev_bf16(gate), dev_bf16(up))
+    _same("q_row", host(got["q_row"]), want["q_row"])
+    _same("s_row", host(got["s_row"]), want["s_row"])
+    dh = ji.grads(M, K, seed=32 + M)
+    dgate, dup = orc.silu_mul_bwd(gate, up, dh)
+    dgu = host_bits(jet.silu_mul_bwd(dev_bf16(gate), dev_bf16(up), dev_bf16(dh)))
+    _same("dgate", dgu[:, :K], dgate)
+    _same("dup", dgu[:, K:], dup)
 
 
 @pytest.mark.parametrize("M,K,eps", [(256, 1024, 1e-6), (1, 128, 1e-5), (5, 4096, 1e-6), (300, 5120, 1e-6),
