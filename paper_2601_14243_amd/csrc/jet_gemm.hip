@@ -601,7 +601,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 // ------------------------------------------------------------------------
 // Panel kernel (block scales only): batches of 17 to 1024 rows, and larger ones against narrow matrices, whose
 // output makes one or two rounds of tiles on the CUs.  One workgroup per CU owns a BM x BN output tile and walks the
-// whole reduction, a step of one or two groups at a time; WR x WC waves compute, kCopy waves copy the operands and
+// whole reduction, a step of one, two or four groups at a time; WR x WC waves compute, kCopy waves copy the operands and
 // one the scales.
 // What bounds it: a CU can have about 320 cache lines on their way and gets them back in order, so an
 // activation line (an L2 hit) waits behind the weight lines (HBM misses) in front of it.  A tile takes about
@@ -610,13 +610,17 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 // activations of a group pass once per 112 columns and not once per 32.
 // Ring of S stages, per group [W: BN rows x 128][A: BM rows x 128] in the swizzled fragment layout of the tile
 // kernel; scales travel in chunks of 16 groups, [row][16] with the group xor (row >> 2) & 3 (conflict-free), two buffers.
-// Step p: the copying waves wait until step p+1 has landed; barrier; they refill the slot of step p with step p+S
-// while the computing waves fetch the fragments of step p+1 into registers and compute step p.  The copying loop is
+// The computing waves fetch the fragments of the next group into registers while they compute one; before the last group
+// of step p, when all of the step is in registers, the barrier: the copying waves have waited until step p+1 has
+// landed and now refill the slot of step p with step p+S.  As many groups per step as the LDS takes with three stages:
+// the copies of a row then fetch 256 or 512 bytes at a time (all CUs walk the same 128-byte column of rows 4 KB apart), and
+// there are fewer barriers: 2-8 % over a step of one or two groups.  The copying loop is
 // straight-line (a compare chain for the wait and a branch per copy cost 0.3 us per step), and the fetch stays in front
 // of the MFMAs by scheduling barriers.  Every output element takes the chain of the other kernels.
 // From HBM, against the strip kernel of 64x32 and 32x32 tiles and the 128x128 tiles before it (us): 4096x14336 77 rows
-// 30.5 -> 22.8, 256 rows 59 -> 37; 28672x4096 32 rows 34 -> 29, 64 rows 47 -> 31; 6144x4096 128 rows 23 -> 13.6;
-// 5120x27648 64 rows 57 -> 50, 256 rows 152 -> 81; 55296x5120 64 rows 101 -> 67.
+// 30.5 -> 22.7, 128 rows 30.5 -> 27.1, 256 rows 59 -> 37; 28672x4096 32 rows 34 -> 29, 64 rows 47 -> 31; 6144x4096 128 rows
+// 23 -> 13.9; 5120x27648 64 rows 57 -> 46, 256 rows 152 -> 79; 55296x5120 64 rows 101 -> 65.  The copying side alone takes 90 % of
+// that, the computing side alone 55-85 %; the weights without the activations 16.7 of 29 us (4096x14336, 128 rows).
 // Measured and left out: workgroups on idle CUs that pull the weights into the L2 ahead (32-row tiles of 4096x14336
 // 22.4 -> 18.1 us, elsewhere within 10 % either way), a wave that touches the XCD's weight lines a chunk ahead (its
 // burst holds up the barrier: 30 % slower).
@@ -720,15 +724,19 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
         const uint32_t lds_c = __builtin_amdgcn_readfirstlane(lds0 + cw * 1024);
         uint32_t st = lds_c;
         auto issue = [&](int q) {
+            size_t kb[C::GP];                            // past the end: the last group again
 #pragma unroll
-            for (int h = 0; h < C::GP; ++h) {
-                const size_t kb = (size_t)min(C::GP * q + h, G - 1) * kGroup;   // past the end: the last group again
+            for (int h = 0; h < C::GP; ++h) kb[h] = (size_t)min(C::GP * q + h, G - 1) * kGroup;
+            // the groups of a row next to each other
 #pragma unroll
-                for (int i = 0; i < C::kWPer; ++i) dma16(st + h * C::kGroupBytes + i * (C::kCopy * 1024), baseW + kb, offW[i]);
+            for (int i = 0; i < C::kWPer; ++i)
 #pragma unroll
-                for (int i = 0; i < C::kAPer; ++i)
-                    dma16(st + h * C::kGroupBytes + C::BN * 128 + i * (C::kCopy * 1024), baseA + kb, offA[i]);
-            }
+                for (int h = 0; h < C::GP; ++h) dma16(st + h * C::kGroupBytes + i * (C::kCopy * 1024), baseW + kb[h], offW[i]);
+#pragma unroll
+            for (int i = 0; i < C::kAPer; ++i)
+#pragma unroll
+                for (int h = 0; h < C::GP; ++h)
+                    dma16(st + h * C::kGroupBytes + C::BN * 128 + i * (C::kCopy * 1024), baseA + kb[h], offA[i]);
             st = (st == lds_c + (C::S - 1) * C::kStage) ? lds_c : st + C::kStage;
         };
         for (int q = 0; q < C::S && q < P; ++q) issue(q);
@@ -761,28 +769,24 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
 #pragma unroll
     for (int n = 0; n < C::TN; ++n) sb_off[n] = (((j0 + 16 * (wc * C::TN + n)) >> 7) - (j0 >> 7)) * 64;
     struct Operands {
-        v8i wf[C::GP][C::TN], xf[C::GP][C::TM];
-        float sa[C::GP][C::TM], sb[C::GP][C::TN];
+        v8i wf[C::TN], xf[C::TM];
+        float sa[C::TM], sb[C::TN];
     };
-    auto fetch = [&](int p, int stage, Operands& o) {
-        const int buf = (C::GP * p / C::kChunk) & 1;
+    auto fetch = [&](int g, int base, Operands& o) {     // group g, at LDS offset base
+        const int buf = (g / C::kChunk) & 1, k4 = (g % C::kChunk) * 4;
+        const uint8_t* pw = pw0 + base;
+        const uint8_t* pa = pa0 + base;
+        const uint8_t* ps = ps0 + buf * C::kSaBuf + (k4 ^ sa_xor);
+        const uint8_t* pb = smem + C::kSbOff + buf * C::kSbBuf + k4;
 #pragma unroll
-        for (int h = 0; h < C::GP; ++h) {
-            const int k4 = ((C::GP * p + h) % C::kChunk) * 4;
-            const uint8_t* pw = pw0 + stage + h * C::kGroupBytes;
-            const uint8_t* pa = pa0 + stage + h * C::kGroupBytes;
-            const uint8_t* ps = ps0 + buf * C::kSaBuf + (k4 ^ sa_xor);
-            const uint8_t* pb = smem + C::kSbOff + buf * C::kSbBuf + k4;
+        for (int m = 0; m < C::TM; ++m) {
+            o.xf[m] = load_frag(pa + m * 2048 + frag_lo, pa + m * 2048 + frag_hi);
+            o.sa[m] = *reinterpret_cast<const float*>(ps + m * 1024);
+        }
 #pragma unroll
-            for (int m = 0; m < C::TM; ++m) {
-                o.xf[h][m] = load_frag(pa + m * 2048 + frag_lo, pa + m * 2048 + frag_hi);
-                o.sa[h][m] = *reinterpret_cast<const float*>(ps + m * 1024);
-            }
-#pragma unroll
-            for (int n = 0; n < C::TN; ++n) {
-                o.wf[h][n] = load_frag(pw + n * 2048 + frag_lo, pw + n * 2048 + frag_hi);
-                o.sb[h][n] = *reinterpret_cast<const float*>(pb + sb_off[n]);
-            }
+        for (int n = 0; n < C::TN; ++n) {
+            o.wf[n] = load_frag(pw + n * 2048 + frag_lo, pw + n * 2048 + frag_hi);
+            o.sb[n] = *reinterpret_cast<const float*>(pb + sb_off[n]);
         }
     };
     v4f acc[C::TM][C::TN];
@@ -790,16 +794,15 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
     for (int m = 0; m < C::TM; ++m)
 #pragma unroll
         for (int n = 0; n < C::TN; ++n) acc[m][n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr int kTiles = C::TM * C::TN;
-    auto compute = [&](const Operands& o, auto groups) {
-        constexpr int kAll = kTiles * decltype(groups)::value, kLag = kAll < 2 ? kAll : 2;
+    auto compute = [&](const Operands& o) {
+        constexpr int kTiles = C::TM * C::TN, kLag = kTiles < 2 ? kTiles : 2;
         v4f pr[3];
 #pragma unroll
-        for (int u = 0; u < kAll + kLag; ++u) {
-            if (u < kAll) pr[u % 3] = group_product(o.wf[u / kTiles][u % C::TN], o.xf[u / kTiles][u % kTiles / C::TN]);
+        for (int u = 0; u < kTiles + kLag; ++u) {
+            if (u < kTiles) pr[u % 3] = group_product(o.wf[u % C::TN], o.xf[u / C::TN]);
             if (u >= kLag) {
-                const int v = u - kLag, h = v / kTiles, m = v % kTiles / C::TN, n = v % C::TN;
-                const float s = o.sa[h][m] * o.sb[h][n];
+                const int v = u - kLag, m = v / C::TN, n = v % C::TN;
+                const float s = o.sa[m] * o.sb[n];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[m][n][e] = chain(pr[v % 3][e], s, acc[m][n][e]);
             }
@@ -810,22 +813,37 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
     Operands even, odd;
     fetch(0, 0, even);
     int stage = 0;
-    auto iteration = [&](int p, const Operands& cur, Operands& nxt) {
-        // this step's fragments are in registers: its slot may be overwritten
-        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0)
-        step_barrier();
-        stage = (stage == (C::S - 1) * C::kStage) ? 0 : stage + C::kStage;
-        fetch(p + 1, stage, nxt);                        // (after the last step: whatever is there, not used)
+    // one group: `cur` holds its fragments, the next group's go to `nxt`.  Before the last group of a step the barrier:
+    // the step's fragments are all in registers, so its slot may be overwritten, and the next step has landed.
+    auto group = [&](int g, int h, const Operands& cur, Operands& nxt) {
         __builtin_amdgcn_sched_barrier(0);
-        if (C::GP == 1 || C::GP * (p + 1) <= G) compute(cur, std::integral_constant<int, C::GP>{});
-        else compute(cur, std::integral_constant<int, C::GP == 1 ? 1 : C::GP - 1>{});     // GP = 2, odd G: the last step has one group
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0)
+        if (h == C::GP - 1) {
+            step_barrier();
+            stage = (stage == (C::S - 1) * C::kStage) ? 0 : stage + C::kStage;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(g + 1, stage + (h == C::GP - 1 ? 0 : (h + 1) * C::kGroupBytes), nxt);   // (after the last: whatever is there, not used)
+        __builtin_amdgcn_sched_barrier(0);
+        if (g < G) compute(cur);                         // a last step may hold fewer groups
     };
+    static_assert(C::GP == 1 || C::GP % 2 == 0, "the two operand buffers alternate");
     int p = 0;
-    for (; p + 1 < P; p += 2) {
-        iteration(p, even, odd);
-        iteration(p + 1, odd, even);
+    if constexpr (C::GP == 1) {
+        for (; p + 1 < P; p += 2) {
+            group(p, 0, even, odd);
+            group(p + 1, 0, odd, even);
+        }
+        if (p < P) group(p, 0, even, odd);
+    } else {
+        for (; p < P; ++p) {
+#pragma unroll
+            for (int h = 0; h < C::GP; h += 2) {
+                group(C::GP * p + h, h, even, odd);
+                group(C::GP * p + h + 1, h + 1, odd, even);
+            }
+        }
     }
-    if (p < P) iteration(p, even, odd);
 
 #pragma unroll
     for (int m = 0; m < C::TM; ++m) {
@@ -883,10 +901,10 @@ static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t*
 
 // the panel tiles: X(TM, TN, WR, WC, stages, groups per step), 16 TM WR rows x 16 TN WC columns
 #define JET_PANELS(X)                                                                                       \
-    X(1, 1, 2, 1, 10, 2) X(1, 1, 2, 2, 8, 2) X(2, 1, 1, 3, 6, 2) X(2, 1, 1, 4, 6, 2) X(2, 1, 1, 7, 7, 1)    \
-    X(1, 2, 3, 1, 7, 2) X(1, 2, 3, 2, 5, 2) X(1, 7, 3, 1, 7, 1) X(2, 2, 2, 2, 4, 2) X(1, 7, 4, 1, 6, 1)     \
-    X(1, 4, 5, 1, 7, 1) X(1, 7, 5, 1, 5, 1) X(2, 4, 3, 1, 6, 1) X(2, 7, 3, 1, 5, 1) X(2, 4, 4, 1, 5, 1)     \
-    X(2, 7, 4, 1, 4, 1)
+    X(1, 1, 2, 1, 6, 4) X(1, 1, 2, 2, 4, 4) X(2, 1, 1, 3, 3, 4) X(1, 2, 4, 1, 3, 4) X(2, 1, 1, 4, 3, 4)     \
+    X(2, 1, 1, 7, 4, 2) X(1, 2, 3, 1, 3, 4) X(1, 2, 3, 2, 5, 2) X(1, 7, 3, 1, 3, 2) X(2, 2, 2, 2, 4, 2)     \
+    X(1, 7, 4, 1, 3, 2) X(1, 4, 5, 1, 4, 2) X(1, 7, 5, 1, 3, 2) X(2, 4, 3, 1, 3, 2) X(2, 7, 3, 1, 5, 1)     \
+    X(2, 4, 4, 1, 5, 1) X(2, 7, 4, 1, 4, 1)
 
 struct TileChoice {
     int bm, bn;

@@ -83,7 +83,7 @@ def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):
     (17, 128, 1, "32x16"), (19, 128, 37, "32x16"), (17, 4224, 2, "32x32"), (30, 4224, 37, "32x32"),
     (17, 8320, 3, "32x48, last panel 16 columns"), (29, 8320, 21, "32x48"), (17, 12416, 5, "32x64"), (32, 12416, 16, "32x64"),
     (18, 16512, 1, "32x112, last panel 48 columns"), (32, 16512, 19, "32x112"), (40, 6272, 4, "48x32"), (33, 6272, 35, "48x32"),
-    (33, 8320, 2, "48x64"), (47, 8320, 17, "48x64"), (48, 16512, 1, "48x112"), (35, 16512, 18, "48x112"),
+    (50, 6272, 2, "64x32"), (63, 6272, 37, "64x32"), (33, 8320, 2, "48x64"), (47, 8320, 17, "48x64"), (48, 16512, 1, "48x112"), (35, 16512, 18, "48x112"),
     (49, 8320, 3, "64x64"), (63, 8320, 18, "64x64"), (50, 16512, 2, "64x112"), (64, 16512, 17, "64x112"),
     (65, 9600, 1, "80x64"), (79, 9600, 18, "80x64"), (70, 16512, 3, "80x112"), (80, 16512, 17, "80x112"),
     (241, 4736, 2, "96x64, third block 49 rows"), (250, 4736, 18, "96x64"), (81, 16512, 1, "96x112"), (95, 16512, 17, "96x112"),
