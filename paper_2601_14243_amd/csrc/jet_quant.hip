@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const void* __restrict__
 // divisions, 25 instructions) is therefore formed once per group and not by each of the threads that hold it.
 // Before that, with a branch per element and conflicts on the maxima in LDS, the kernel was bound by its
 // instructions.  [16384, 4096]: row + column 59 -> 49.5 us, column from FP8 30 -> 25; [128, 4096]: 8.9 -> 5.0 and
-// 5.5 -> 4.3; a weight with its transposed copy [4096, 4096] 18.4 -> 17, [128, 4096] 5.2 -> 3.5 (captured, back to back).
+// 5.5 -> 4.3; a weight with its transposed copy [128, 4096] 5.2 -> 3.5, 14 matrices of two 8B layers 399 -> 377.
 // ------------------------------------------------------------------------
 
 // broadcast of lane N of every 16-lane row
