@@ -470,11 +470,10 @@ constexpr int kSkGroupBytes = 4 * 64 * 4 + 64 * 4;  // p[4][64] + s[64]
 constexpr int kSkPass = 32;                       // groups chained per pass
 constexpr int sk_lds_bytes(int depth, int waves) { return waves * depth * kSkUnit + kSkPass * kSkGroupBytes; }
 
-// kSkDepth = units in flight per wave: 3 or 6 when there is at most one workgroup per CU, 1 when
+// kSkDepth = units in flight per wave: 3 when there is at most one workgroup per CU, 1 when
 // the strips outnumber the CUs (two workgroups then share a CU and cover each other's start-up,
 // chain passes and drain)
-// kSkWaves = waves splitting the groups of a strip (runs of consecutive groups): 8 unless the
-// reduction is very short
+// kSkWaves = waves splitting the groups of a strip (runs of consecutive groups)
 // ABLK = 8-row blocks of activations that hold a row of the batch ((I + 7) / 8): only these are
 // copied, and of the last one only the lines of existing rows -- every byte through a CU's
 // memory pipeline costs the same there whether it misses or hits, so at I = 1 the copy of 15
@@ -599,7 +598,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 }
 
 // ------------------------------------------------------------------------
-// Panel kernel (block scales only): batches of 17 to 1024 rows, and larger ones against narrow matrices, whose
+// Panel kernel (block scales only): batches of up to 1024 rows, and larger ones against narrow matrices, whose
 // output makes one or two rounds of tiles on the CUs.  One workgroup per CU owns a BM x BN output tile and walks the
 // whole reduction, a step of one, two or four groups at a time; WR x WC waves compute, kCopy waves copy the operands and
 // one the scales.
@@ -932,6 +931,17 @@ static const TileChoice& pick_tile(long I, long J, long& rounds) {
     return *best;
 }
 
+// Up to 16 rows: the strips of the skinny kernel stream the weights fastest while their passes of 32 groups and the
+// CUs' shares of strips are nearly full (28672x4096, 1 row: 26.7 us against 28.7 on panels; 4096x4096 6.1 against 7.1); in a
+// partial pass or round waves and CUs wait (55296x5120, 8 and 16 rows: 70 and 78 us, panels 54 and 55; 5120x27648, 1 row:
+// 36.7, panels 32).  The part that is full must be 0.7, and 0.9 from 9 rows on, where a strip copies both activation
+// blocks (14336x4096, 16 rows: full to 0.875, 17.2 us, panels 14.6).
+static bool strips_keep_busy(long I, long J, long G) {
+    const long cus = compute_units(), strips = J / 16;
+    const long slots = strips <= cus ? strips : (strips + cus - 1) / cus * cus, groups = (G + kSkPass - 1) / kSkPass * kSkPass;
+    return 10 * G * strips >= (I <= 8 ? 7 : 9) * groups * slots;
+}
+
 template <int SB_MODE, int... Cfg>
 static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
                                long J, long R, long ldo, hipStream_t st) {
@@ -1007,7 +1017,6 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
 #define JET_SK_ATTR(D, W, AB) \
     if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, AB>, sk_lds_bytes(D, W))
-        JET_SK_ATTR(6, 4, 1); JET_SK_ATTR(6, 4, 2);
         JET_SK_ATTR(3, 8, 1); JET_SK_ATTR(3, 8, 2);
         JET_SK_ATTR(1, 8, 1); JET_SK_ATTR(1, 8, 2);
 #undef JET_SK_ATTR
@@ -1020,8 +1029,8 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
     if (attr_err != hipSuccess) return attr_err;
 
     uint16_t* o = static_cast<uint16_t*>(out);
-    // decode of up to 16 rows: a workgroup per 16-column strip; shape-only choice of ring depth / wave count
-    if (I <= 16 && sb_mode == kSbBlock) {
+    // decode of up to 16 rows: a workgroup per 16-column strip; shape-only choice of ring depth
+    if (I <= 16 && sb_mode == kSbBlock && strips_keep_busy(I, J, R / kGroup)) {
         const unsigned strips = (unsigned)(J / 16);
 #define JET_SKINNY_AB(D, W, AB)                                                                             \
     hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
@@ -1032,13 +1041,8 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
         if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
         else JET_SKINNY_AB(D, W, 2);           \
     } while (0)
-        if (strips > 256) {
-            JET_SKINNY(1, 8);                        // two workgroups (16 waves) per CU
-        } else if (R >= 1024) {
-            JET_SKINNY(3, 8);
-        } else {
-            JET_SKINNY(6, 4);
-        }
+        if (strips > 256) JET_SKINNY(1, 8);              // two workgroups (16 waves) per CU
+        else JET_SKINNY(3, 8);
 #undef JET_SKINNY
 #undef JET_SKINNY_AB
         return hipGetLastError();

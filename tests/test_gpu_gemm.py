@@ -60,10 +60,10 @@ def test_forward_shapes(jet, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,kernel", [
-    (1, 4224, 384, "skinny kernel, two workgroups per CU (more than 256 strips), three groups"),
-    (5, 4224, 128, "skinny kernel, two workgroups per CU, one group: only the first wave has a unit"),
-    (8, 4224, 1152, "skinny kernel, two workgroups per CU, nine groups"),
-    (9, 4224, 384, "skinny kernel, two workgroups per CU, two activation blocks"),
+    (1, 4224, 384, "1 row on 32x32 panels, three groups"),
+    (5, 4224, 128, "5 rows on 32x32 panels, one group"),
+    (8, 4224, 1152, "8 rows on 32x32 panels, nine groups"),
+    (9, 4224, 384, "9 rows on 32x32 panels"),
     (20, 2048, 640, "panel kernel, 32x16 tiles, 4 rows in the second row tile"),
     (27, 2048, 640, "panel kernel, 32x16 tiles, 11 rows in the second row tile"),
     (27, 4608, 384, "panel kernel, 32x32 tiles"),
@@ -96,6 +96,18 @@ def test_forward_on_every_tile_of_the_launch_rule(jet, M, N, groups, tile):
     128, odd and even numbers of groups, fewer groups than ring stages and more than two scale chunks of 16."""
     y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=13 * M + N + groups)
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {tile}", operands=ops)
+
+
+@pytest.mark.parametrize("M,N,groups,kernel", [
+    (1, 8192, 32, "strips, two workgroups per CU"), (8, 8192, 29, "strips, last run of a pass one group"),
+    (9, 8192, 32, "strips, two activation blocks"), (16, 8192, 30, "strips, two activation blocks, partial pass"),
+    (3, 4096, 24, "strips, one workgroup per CU"), (7, 384, 64, "strips, two passes"), (12, 1024, 61, "strips, two passes, the second partial"),
+    (1, 8192, 22, "panel: a pass of 32 groups is two thirds full"), (16, 8192, 28, "panel: 0.875 full"), (1, 5120, 32, "panel: 320 strips on 256 CUs"),
+    (5, 5120, 40, "panel"), (16, 128, 1, "panel"),
+])
+def test_forward_of_a_few_rows_on_both_sides_of_the_strip_rule(jet, M, N, groups, kernel):
+    y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=17 * M + N + groups)
+    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {kernel}", operands=ops)
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 384, 512), (5, 256, 128), (130, 128, 640)])
