@@ -136,6 +136,34 @@ def _need(t: torch.Tensor, dtype, name: str):
         raise TypeError(f"{name}: need a contiguous 2-D CUDA tensor of {dtype}")
 
 
+def _need_rows(t, dtype, rows: int, cols: int, like: torch.Tensor, name: str):
+    """A quantizer's output (or the scales of its input) in the caller's tensor: the kernels go through
+    [rows, cols] densely from data_ptr(), so it lies on the operand's device, is contiguous, has the element size and
+    at least that many elements, and, unless it is flat, rows of `cols`.  More rows (a buffer of a larger batch) are fine.
+    Codes may be in any one-byte type.  None is left to the C ABI."""
+    if t is None:
+        return
+    fits = t.element_size() == 1 if dtype == torch.uint8 else t.dtype == dtype
+    if not t.is_cuda or not t.is_contiguous() or not fits:
+        raise TypeError(f"{name}: need a contiguous CUDA tensor of {dtype}")
+    cols = max(cols, 1)
+    if t.numel() < rows * cols or (t.dim() != 1 and (t.dim() == 0 or t.shape[-1] != cols)):
+        raise ValueError(f"{name}: shape {tuple(t.shape)}, need {(rows, cols)}")
+    if t.device != like.device:
+        raise ValueError(f"{name}: on {t.device}, the operand on {like.device}")
+
+
+def _need_row_pair(o: dict, M: int, K: int, like: torch.Tensor):
+    _need_rows(o.get("q_row"), torch.uint8, M, K, like, "q_row")
+    _need_rows(o.get("s_row"), torch.float32, M, K // GROUP, like, "s_row")
+
+
+def _same_device(like: torch.Tensor, **others: torch.Tensor):
+    for name, t in others.items():
+        if t.device != like.device:
+            raise ValueError(f"{name}: on {t.device}, the other operand on {like.device}")
+
+
 def quant_act(x: torch.Tensor, x_scales: torch.Tensor | None = None, row: bool = True,
               col: bool = False, out: dict | None = None) -> dict:
     """1x128 quantization of a bf16 [M,K] tensor, or of an FP8-saved one (uint8 codes
@@ -147,6 +175,8 @@ def quant_act(x: torch.Tensor, x_scales: torch.Tensor | None = None, row: bool =
     _need(x, torch.bfloat16 if src == JET_SRC_BF16 else torch.uint8, "x")
     M, K = x.shape
     dev = x.device
+    if src == JET_SRC_FP8_ROW:
+        _need_rows(x_scales, torch.float32, M, K // GROUP, x, "x_scales")
     o = {} if out is None else out
     if row and "q_row" not in o:
         o["q_row"] = torch.empty((M, K), dtype=torch.uint8, device=dev)
@@ -154,6 +184,11 @@ def quant_act(x: torch.Tensor, x_scales: torch.Tensor | None = None, row: bool =
     if col and "q_colT" not in o:
         o["q_colT"] = torch.empty((K, M), dtype=torch.uint8, device=dev)
         o["s_colT"] = torch.empty((K, max(M // GROUP, 1)), dtype=torch.float32, device=dev)
+    if row:
+        _need_row_pair(o, M, K, x)
+    if col:
+        _need_rows(o.get("q_colT"), torch.uint8, K, M, x, "q_colT")
+        _need_rows(o.get("s_colT"), torch.float32, K, M // GROUP, x, "s_colT")
     st = jet_quant_act(_ptr(x), _ptr(x_scales), src, M, K,
                        _ptr(o.get("q_row")) if row else None, _ptr(o.get("s_row")) if row else None,
                        _ptr(o.get("q_colT")) if col else None, _ptr(o.get("s_colT")) if col else None,
@@ -163,11 +198,12 @@ def quant_act(x: torch.Tensor, x_scales: torch.Tensor | None = None, row: bool =
     return o
 
 
-def _row_pair(M, K, dev, out):
+def _row_pair(M, K, like, out):
     o = {} if out is None else out
     if "q_row" not in o:
-        o["q_row"] = torch.empty((M, K), dtype=torch.uint8, device=dev)
-        o["s_row"] = torch.empty((M, max(K // GROUP, 1)), dtype=torch.float32, device=dev)
+        o["q_row"] = torch.empty((M, K), dtype=torch.uint8, device=like.device)
+        o["s_row"] = torch.empty((M, max(K // GROUP, 1)), dtype=torch.float32, device=like.device)
+    _need_row_pair(o, M, K, like)
     return o
 
 
@@ -180,7 +216,8 @@ def rmsnorm_quant(x: torch.Tensor, gamma: torch.Tensor, eps: float, out: dict | 
     M, K = x.shape
     if not gamma.is_cuda or not gamma.is_contiguous() or gamma.dtype != torch.bfloat16 or gamma.shape != (K,):
         raise TypeError("gamma: need a contiguous CUDA bf16 tensor of K elements")
-    o = _row_pair(M, K, x.device, out)
+    _same_device(x, gamma=gamma)
+    o = _row_pair(M, K, x, out)
     st = jet_rmsnorm_quant(_ptr(x), _ptr(gamma), eps, M, K, _ptr(o["q_row"]), _ptr(o["s_row"]), _stream())
     if st:
         raise JetError(st, "jet_rmsnorm_quant")
@@ -198,8 +235,9 @@ def silu_mul_quant(gate: torch.Tensor, up: torch.Tensor, out: dict | None = None
             raise TypeError(f"{name}: need a 2-D CUDA bf16 tensor with unit column stride")
     if gate.shape != up.shape or gate.stride(0) != up.stride(0):
         raise TypeError("gate and up need one shape and one row stride")
+    _same_device(gate, up=up)
     M, K = gate.shape
-    o = _row_pair(M, K, gate.device, out)
+    o = _row_pair(M, K, gate, out)
     st = jet_silu_mul_quant(_ptr(gate), _ptr(up), gate.stride(0), M, K, _ptr(o["q_row"]), _ptr(o["s_row"]), _stream())
     if st:
         raise JetError(st, "jet_silu_mul_quant")
@@ -225,6 +263,7 @@ def silu_mul_bwd(gate: torch.Tensor, up: torch.Tensor, dh: torch.Tensor, out: to
     _need(dgu, torch.bfloat16, "out")
     if tuple(dgu.shape) != (M, 2 * K):
         raise ValueError("out: need [M, 2K]")
+    _same_device(gate, up=up, dh=dh, out=dgu)
     st = jet_silu_mul_bwd(_ptr(gate), _ptr(up), gate.stride(0), _ptr(dh), M, K, _ptr(dgu),
                           dgu.data_ptr() + 2 * K, 2 * K, _stream())
     if st:
@@ -247,6 +286,10 @@ def quant_weight(w: torch.Tensor, transposed: bool = False, out: tuple | None = 
         sT = torch.empty((max(K // GROUP, 1), max(N // GROUP, 1)), dtype=torch.float32, device=dev) if transposed else None
     else:
         q, s, qT, sT = (tuple(out) + (None, None))[:4]
+        _need_rows(q, torch.uint8, N, K, w, "q")
+        _need_rows(s, torch.float32, N // GROUP, K // GROUP, w, "s")
+        _need_rows(qT, torch.uint8, K, N, w, "qT")
+        _need_rows(sT, torch.float32, K // GROUP, N // GROUP, w, "sT")
     st = jet_quant_weight(_ptr(w), N, K, _ptr(q), _ptr(s), _ptr(qT), _ptr(sT), _stream())
     if st:
         raise JetError(st, "jet_quant_weight")

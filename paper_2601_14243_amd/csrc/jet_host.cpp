@@ -2,9 +2,9 @@
 // one Python call each.  A small layer is bound by what the host does per launch: through ctypes and a dozen tensor
 // attributes quant_act took 11.1 us, a GEMM call 11.6, quant_weight with its copy 14.8; here 5.3, 4.3 and 6.9.
 //
-// Every function returns None when a call is not of the plain form (exact torch tensors on the GPU of the expected
-// dtype, layout and shapes; `out` absent or complete): binding.py then takes its Python path, which words the
-// error or handles the unusual form.  Only calls that that path would accept are answered here, with the same results.
+// Every function returns None when a call is not of the plain form (exact torch tensors on one GPU, of the expected
+// dtype, layout and shapes, outputs included; `out` absent or complete): binding.py then takes its Python path, which words
+// the error or handles the unusual form.  Only calls that that path would accept are answered here, with the same results.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -34,6 +34,15 @@ const at::Tensor* plain(PyObject* obj, at::ScalarType dtype) {
 const at::Tensor* plain2d(PyObject* obj, at::ScalarType dtype) {
     const at::Tensor* t = plain(obj, dtype);
     return (t && t->dim() == 2 && t->is_contiguous()) ? t : nullptr;
+}
+// t may hold [rows, cols] densely from its start (binding.py's _need_rows): on like's device, contiguous, of the element
+// size, with room, and with rows of `cols` unless it is flat
+enum Kind { kCodes, kScales };
+bool holds(const at::Tensor& t, Kind kind, int64_t rows, int64_t cols, const at::Tensor& like) {
+    cols = std::max<int64_t>(cols, 1);
+    return t.is_cuda() && t.device() == like.device() && t.is_contiguous() &&
+           (kind == kCodes ? t.element_size() == 1 : t.scalar_type() == at::kFloat) && t.numel() >= rows * cols &&
+           (t.dim() == 1 || (t.dim() > 1 && t.size(-1) == cols));
 }
 bool modes_active() { return at::impl::torch_function_mode_enabled(); }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
@@ -83,13 +92,13 @@ bool set_item(PyObject* d, const char* key, const at::Tensor& t) {
 struct Pair {
     at::Tensor q, s;
 };
-// false: not of the plain form
-bool take_pair(PyObject* out, const char* qk, const char* sk, Pair& p) {
+// codes [rows, cols] with scales [rows, cols / 128]; false: not of the plain form
+bool take_pair(PyObject* out, const char* qk, const char* sk, int64_t rows, int64_t cols, const at::Tensor& like, Pair& p) {
     PyObject *q = PyDict_GetItemString(out, qk), *s = PyDict_GetItemString(out, sk);
     if (!q || !s || !THPVariable_CheckExact(q) || !THPVariable_CheckExact(s)) return false;
     p.q = THPVariable_Unpack(q);
     p.s = THPVariable_Unpack(s);
-    return true;
+    return holds(p.q, kCodes, rows, cols, like) && holds(p.s, kScales, rows, cols / kGroup, like);
 }
 PyObject* dict_of(const Pair* row, const Pair* col) {
     PyObject* d = PyDict_New();
@@ -121,17 +130,19 @@ PyObject* quant_act(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (row < 0 || col < 0) return nullptr;
         PyObject* out = a[4];
         const at::Tensor* x = plain2d(a[0], fp8 ? at::kByte : at::kBFloat16);
-        if (!x || (fp8 && !THPVariable_CheckExact(a[1])) || (out != Py_None && !PyDict_CheckExact(out)) || modes_active())
-            Py_RETURN_NONE;
+        const at::Tensor* xs_t = fp8 ? plain(a[1], at::kFloat) : nullptr;
+        if (!x || (fp8 && !xs_t) || (out != Py_None && !PyDict_CheckExact(out)) || modes_active()) Py_RETURN_NONE;
         const int64_t M = x->size(0), K = x->size(1);
+        if (fp8 && !holds(*xs_t, kScales, M, K / kGroup, *x)) Py_RETURN_NONE;
         Pair r, c;
         if (out != Py_None) {
-            if ((row && !take_pair(out, "q_row", "s_row", r)) || (col && !take_pair(out, "q_colT", "s_colT", c))) Py_RETURN_NONE;
+            if ((row && !take_pair(out, "q_row", "s_row", M, K, *x, r)) || (col && !take_pair(out, "q_colT", "s_colT", K, M, *x, c)))
+                Py_RETURN_NONE;
         } else {
             if (row) r = {make(M, K, at::kByte, *x), make(M, std::max<int64_t>(K / kGroup, 1), at::kFloat, *x)};
             if (col) c = {make(K, M, at::kByte, *x), make(K, std::max<int64_t>(M / kGroup, 1), at::kFloat, *x)};
         }
-        const float* xs = fp8 ? in<float>(THPVariable_Unpack(a[1])) : nullptr;
+        const float* xs = fp8 ? in<float>(*xs_t) : nullptr;
         uint8_t *qr = row ? outp(r.q) : nullptr, *qc = col ? outp(c.q) : nullptr;
         float *sr = row ? outp<float>(r.s) : nullptr, *sc = col ? outp<float>(c.s) : nullptr;
         const void* xp = in(*x);
@@ -150,7 +161,7 @@ bool row_pair(PyObject* out, int64_t M, int64_t K, const at::Tensor& like, Pair&
         r = {make(M, K, at::kByte, like), make(M, std::max<int64_t>(K / kGroup, 1), at::kFloat, like)};
         return true;
     }
-    return PyDict_CheckExact(out) && take_pair(out, "q_row", "s_row", r);
+    return PyDict_CheckExact(out) && take_pair(out, "q_row", "s_row", M, K, like, r);
 }
 
 // rmsnorm_quant(x, gamma, eps, out | None)
@@ -160,7 +171,7 @@ PyObject* rmsnorm_quant(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor *x = plain2d(a[0], at::kBFloat16), *g = plain(a[1], at::kBFloat16);
         if (!x || !g || !PyFloat_CheckExact(a[2]) || modes_active()) Py_RETURN_NONE;
         const int64_t M = x->size(0), K = x->size(1);
-        if (g->dim() != 1 || g->size(0) != K || !g->is_contiguous()) Py_RETURN_NONE;
+        if (g->dim() != 1 || g->size(0) != K || !g->is_contiguous() || g->device() != x->device()) Py_RETURN_NONE;
         Pair r;
         if (!row_pair(a[3], M, K, *x, r)) Py_RETURN_NONE;
         const float eps = (float)PyFloat_AS_DOUBLE(a[2]);
@@ -176,12 +187,12 @@ PyObject* rmsnorm_quant(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// gate and up: GPU bf16 [M, K] of unit column stride and one row stride
+// gate and up: bf16 [M, K] on one GPU, of unit column stride and one row stride
 bool gate_up(PyObject* const* a, const at::Tensor*& g, const at::Tensor*& u) {
     g = plain(a[0], at::kBFloat16);
     u = plain(a[1], at::kBFloat16);
     return g && u && g->dim() == 2 && u->dim() == 2 && g->stride(1) == 1 && u->stride(1) == 1 &&
-           g->sizes() == u->sizes() && g->stride(0) == u->stride(0);
+           g->sizes() == u->sizes() && g->stride(0) == u->stride(0) && g->device() == u->device();
 }
 
 // silu_mul_quant(gate, up, out | None)
@@ -210,14 +221,14 @@ PyObject* silu_mul_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!args(n, 4)) return nullptr;
     return guarded([&]() -> PyObject* {
         const at::Tensor *g, *u, *dh = plain2d(a[2], at::kBFloat16);
-        if (!gate_up(a, g, u) || !dh || dh->sizes() != g->sizes() || modes_active()) Py_RETURN_NONE;
+        if (!gate_up(a, g, u) || !dh || dh->sizes() != g->sizes() || dh->device() != g->device() || modes_active()) Py_RETURN_NONE;
         const int64_t M = g->size(0), K = g->size(1), ld = g->stride(0);
         at::Tensor o;
         if (a[3] == Py_None) {
             o = make(M, 2 * K, at::kBFloat16, *g);
         } else {
             const at::Tensor* t = plain2d(a[3], at::kBFloat16);
-            if (!t || t->size(0) != M || t->size(1) != 2 * K) Py_RETURN_NONE;
+            if (!t || t->size(0) != M || t->size(1) != 2 * K || t->device() != g->device()) Py_RETURN_NONE;
             o = *t;
         }
         const void *gp = in(*g), *up = in(*u), *dp = in(*dh);
@@ -263,6 +274,9 @@ PyObject* quant_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
                 if (!THPVariable_CheckExact(o[i])) Py_RETURN_NONE;
                 t[i] = THPVariable_Unpack(o[i]);
             }
+            if (!holds(t[0], kCodes, N, K, *w) || !holds(t[1], kScales, N / kGroup, K / kGroup, *w) ||
+                (have == 4 && !(holds(t[2], kCodes, K, N, *w) && holds(t[3], kScales, K / kGroup, N / kGroup, *w))))
+                Py_RETURN_NONE;
         }
         const void* wp = in(*w);
         uint8_t *q = outp(t[0]), *qT = have == 4 ? outp(t[2]) : nullptr;

@@ -114,3 +114,108 @@ def test_same_errors_as_the_python_path(monkeypatch, native):
         b.fp8_linear_fwd(q, s, w, ws, out=z(4, 256))
     with pytest.raises(TypeError):
         b.fp8_linear_fwd(q[:, ::2], s, w, ws)
+
+
+class _OnGpu(torch.Tensor):
+    """A CPU tensor that passes for a GPU one, for checks that come before any launch."""
+    is_cuda = property(lambda self: True)
+
+
+def _bad_buffers(make, other):
+    """(name of the call, call) pairs whose output or scales the kernels would run out of or misread.  make(*shape,
+    dtype=) makes a tensor on the operand's device, other(*shape, dtype=) one somewhere else."""
+    M, K = 128, 384
+    x, gamma, both = make(M, K, dtype=bf), make(K, dtype=bf), make(M, 2 * K, dtype=bf)
+    q, s = make(M, K, dtype=u8), make(M, K // 128, dtype=f32)
+    qT, sT = make(K, M, dtype=u8), make(K, 1, dtype=f32)
+    wq = [make(M, K, dtype=u8), make(1, 3, dtype=f32), make(K, M, dtype=u8), make(3, 1, dtype=f32)]
+    pairs = [(q, make(M, 2, dtype=f32)), (make(M - 1, K, dtype=u8), s), (make(K, M, dtype=u8), s), (other(M, K, dtype=u8), s),
+             (q, other(M, 3, dtype=f32)), (make(M, K, dtype=bf), s), (q, make(M, 3, dtype=torch.float64)), (q, make(M, 3, dtype=bf)),
+             (make(M, 2 * K, dtype=u8)[:, :K], s), (make(M, 2 * K, dtype=u8)[:, ::2], s), (q, make(M, 6, dtype=f32)[:, ::2]),
+             (q, make(M * 3 - 1, dtype=f32))]
+    for i, (a, b_) in enumerate(pairs):
+        o = {"q_row": a, "s_row": b_}
+        yield f"quant_act {i}", lambda o=o: b.quant_act(x, out=o)
+        yield f"quant_act both {i}", lambda o=o: b.quant_act(x, col=True, out={**o, "q_colT": qT, "s_colT": sT})
+        yield f"rmsnorm_quant {i}", lambda o=o: b.rmsnorm_quant(x, gamma, 1e-6, out=o)
+        yield f"silu_mul_quant {i}", lambda o=o: b.silu_mul_quant(both[:, :K], both[:, K:], out=o)
+    for i, (a, b_) in enumerate([(make(M, K, dtype=u8), sT), (qT, make(K - 1, 1, dtype=f32)), (other(K, M, dtype=u8), sT),
+                                 (make(K, 2 * M, dtype=u8), sT), (qT, make(K, 1, dtype=torch.float16))]):
+        yield f"quant_act col {i}", lambda o={"q_colT": a, "s_colT": b_}: b.quant_act(x, row=False, col=True, out=o)
+    for i, xs in enumerate([other(M, 3, dtype=f32), make(M, 2, dtype=f32), make(M - 1, 3, dtype=f32), make(M, 3, dtype=torch.float64),
+                            make(M, 3, dtype=torch.float16), make(M, 6, dtype=f32)[:, ::2], make(M, 6, dtype=f32)]):
+        yield f"x_scales {i}", lambda xs=xs: b.quant_act(q, xs)
+        yield f"x_scales col {i}", lambda xs=xs: b.quant_act(q, xs, row=False, col=True, out={"q_colT": qT, "s_colT": sT})
+    for i, bad in enumerate([make(M - 1, K, dtype=u8), make(1, 2, dtype=f32), make(M, K, dtype=u8), make(2, 1, dtype=f32)]):
+        o = list(wq)
+        o[i] = bad
+        yield f"quant_weight {i}", lambda o=o: b.quant_weight(x, transposed=True, out=tuple(o))
+        yield f"quant_weight list {i}", lambda o=o: b.quant_weight(x, transposed=True, out=o)
+        o = list(wq)
+        o[i] = other(*wq[i].shape, dtype=wq[i].dtype)
+        yield f"quant_weight elsewhere {i}", lambda o=o: b.quant_weight(x, transposed=True, out=tuple(o))
+    yield "quant_weight without copy", lambda: b.quant_weight(x, out=(wq[0], make(1, 2, dtype=f32)))
+
+
+def _no_call(name):
+    def f(*a):
+        raise AssertionError(f"{name} was called with pointers that do not hold the result")
+    return f
+
+
+RAW = ("jet_quant_act", "jet_quant_weight", "jet_rmsnorm_quant", "jet_silu_mul_quant", "jet_silu_mul_bwd")
+
+
+def test_buffers_that_do_not_hold_the_result_are_refused_before_the_call(monkeypatch):
+    """Outputs and scales reach the kernels as raw pointers: too small, of another type, strided, of another row length
+    or not on the GPU, they raise in the Python path and the C call is not made."""
+    monkeypatch.setattr(b, "_stream", lambda: None)
+    for name in RAW:
+        monkeypatch.setattr(b, name, _no_call(name))
+    make = lambda *sh, dtype: torch.zeros(sh, dtype=dtype).as_subclass(_OnGpu)
+    other = lambda *sh, dtype: torch.zeros(sh, dtype=dtype)
+    for name, call in _bad_buffers(make, other):
+        with pytest.raises((TypeError, ValueError)):
+            call()
+            pytest.fail(name)
+
+
+def test_buffers_with_room_are_taken(monkeypatch):
+    """Flat workspaces, buffers of a larger batch and one-byte types other than uint8 hold the result as well."""
+    seen = []
+    monkeypatch.setattr(b, "_stream", lambda: None)
+    for name in RAW:
+        monkeypatch.setattr(b, name, lambda *a, name=name: seen.append(name) or 0)
+    make = lambda *sh, dtype: torch.zeros(sh, dtype=dtype).as_subclass(_OnGpu)
+    _good_buffers(make)
+    assert seen == ["jet_quant_act"] * 5 + ["jet_rmsnorm_quant", "jet_quant_weight"]
+
+
+def _good_buffers(make):
+    M, K = 128, 384
+    x, gamma, q, s = make(M, K, dtype=bf), make(K, dtype=bf), make(M, K, dtype=u8), make(M, 3, dtype=f32)
+    b.quant_act(x, out={"q_row": make(M * K, dtype=u8), "s_row": make(M * 3 + 5, dtype=f32)})
+    b.quant_act(x, out={"q_row": make(2 * M, K, dtype=u8), "s_row": make(2 * M, 3, dtype=f32)})
+    b.quant_act(x, out={"q_row": make(2, M // 2, K, dtype=torch.int8), "s_row": s})
+    b.quant_act(x, row=False, col=True, out={"q_colT": make(K, M, dtype=u8), "s_colT": make(K, 1, dtype=f32)})
+    b.quant_act(q, make(M + 1, 3, dtype=f32), row=True, out={"q_row": make(M, K, dtype=u8), "s_row": make(M, 3, dtype=f32)})
+    b.rmsnorm_quant(x, gamma, 1e-6, out={"q_row": q, "s_row": s})
+    b.quant_weight(x, out=(q, make(3, dtype=f32)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_buffers_on_the_gpu(monkeypatch, native):
+    """The same calls on GPU tensors: the native path declines them and the Python path raises, both on the host before
+    any launch; what has room runs."""
+    if not native:
+        monkeypatch.setattr(b, "_host", _Declines())
+    make = lambda *sh, dtype: torch.zeros(sh, dtype=dtype, device="cuda")
+    other = lambda *sh, dtype: torch.zeros(sh, dtype=dtype)
+    _good_buffers(make)
+    for name in RAW:
+        monkeypatch.setattr(b, name, _no_call(name))
+    for name, call in _bad_buffers(make, other):
+        with pytest.raises((TypeError, ValueError)):
+            call()
+            pytest.fail(name)
