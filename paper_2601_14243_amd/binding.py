@@ -6,13 +6,16 @@ torch CUDA tensors, allocate the outputs with torch, pass ``data_ptr()`` and the
 current stream, and raise ``JetError`` on a non-zero status.  Calls of the plain form (exact tensors of
 the right type and shape) are answered by the extension ``_jet_host`` (csrc/jet_host.cpp), which does the
 same in one native call; what it does not take (None) goes through the Python code here, which also words
-the errors.  No arithmetic of the method happens in Python, and there is no fallback: if
-libjet.so or the extension is missing the first call fails loudly.
+the errors and takes every call, with a warning, where the extension is missing or was built for another Python or
+torch.  No arithmetic of the method happens in Python, and libjet.so has no fallback: if it is missing the first
+call fails loudly.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 import torch
 
@@ -66,16 +69,31 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _PythonMarshalling:
+    """Stands in for the extension where it cannot be loaded: takes no call, so that the Python code does."""
+
+    @staticmethod
+    def _declined(*args):
+        return None
+
+    quant_act = rmsnorm_quant = silu_mul_quant = silu_mul_bwd = quant_weight = gemm = _declined
+
+
 def _native():
     """Load the native marshalling (built in-tree beside libjet.so)."""
     global _host
     if _host is None:
         lib()
-        if not os.path.exists(_HOST_PATH):
-            raise FileNotFoundError(f"{_HOST_PATH} is missing: build it with `python -m paper_2601_14243_amd.build`")
-        from . import _jet_host
-        _jet_host.init(JetError, torch.OutOfMemoryError)
-        _host = _jet_host
+        try:
+            if not os.path.exists(_HOST_PATH):
+                raise ImportError(f"{_HOST_PATH} is missing")
+            host = importlib.import_module("._jet_host", __package__)
+            host.init(JetError, getattr(torch, "OutOfMemoryError", torch.cuda.OutOfMemoryError))
+        except ImportError as e:
+            warnings.warn(f"native marshalling not available ({e}); build it with `python -m paper_2601_14243_amd.build`.  "
+                          "The kernels are the same, a call takes some 5 us more on the host.", RuntimeWarning, stacklevel=3)
+            host = _PythonMarshalling
+        _host = host
     return _host
 
 

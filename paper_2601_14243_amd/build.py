@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -54,11 +55,16 @@ def _compile_host(force: bool) -> None:
 
 
 def build(force: bool = True) -> str:
-    """Compile every source: libjet.so (the product), its Python extension and libjet_probe.so (the
-    benchmark's matrix-core rate probe).  Returns the path of libjet.so."""
+    """Compile every source: libjet.so (the product), libjet_probe.so (the benchmark's matrix-core rate probe) and the
+    Python extension, without which the helpers work too.  Returns the path of libjet.so."""
     _compile(LIB, SOURCES, force)
     _compile(PROBE_LIB, PROBE_SOURCES, force)
-    _compile_host(force)
+    try:
+        _compile_host(force)
+    except (RuntimeError, OSError) as e:     # no g++, no headers, another torch: the library works without it
+        if os.path.exists(HOST_LIB):
+            os.remove(HOST_LIB)              # not one that is older than its source
+        warnings.warn(f"the native marshalling was not built, binding.py stands in for it: {e}", RuntimeWarning)
     return LIB
 
 

@@ -1,11 +1,18 @@
 """The native marshalling of the tensor helpers (csrc/jet_host.cpp) against the Python path it stands in for: what it
 does not take it declines (None), what it takes has the same results, types and errors."""
+import warnings
+
 import pytest
 import torch
 
 from paper_2601_14243_amd import binding as b
 
 u8, f32, bf = torch.uint8, torch.float32, torch.bfloat16
+
+
+class _OnGpu(torch.Tensor):
+    """A CPU tensor that passes for a GPU one, for checks that come before any launch."""
+    is_cuda = property(lambda self: True)
 
 
 def test_declines_everything_but_the_plain_form():
@@ -26,6 +33,46 @@ def test_declines_everything_but_the_plain_form():
         b.quant_act(x)                                                          # the Python path words the error
     with pytest.raises(TypeError):
         b.quant_weight(x)
+
+
+@pytest.mark.parametrize("broken", ["missing", "of another Python or torch"])
+def test_the_helpers_work_without_the_extension(monkeypatch, broken):
+    """libjet.so alone is enough: the Python path takes every call, after one warning."""
+    monkeypatch.setattr(b, "_host", None)
+    if broken == "missing":
+        monkeypatch.setattr(b, "_HOST_PATH", b._HOST_PATH + ".none")
+    else:
+        def undefined(*a):
+            raise ImportError("undefined symbol: THPVariableClass")
+        monkeypatch.setattr(b.importlib, "import_module", undefined)
+    calls = []
+    monkeypatch.setattr(b, "_stream", lambda: None)
+    monkeypatch.setattr(b, "jet_quant_act", lambda *a: calls.append(a) or 0)
+    x = torch.zeros((4, 256), dtype=bf).as_subclass(_OnGpu)
+    out = {"q_row": torch.zeros((4, 256), dtype=u8).as_subclass(_OnGpu), "s_row": torch.ones((4, 2)).as_subclass(_OnGpu)}
+    with pytest.warns(RuntimeWarning, match="native marshalling"):
+        assert b.quant_act(x, out=out) is out
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        b.quant_act(x, out=out)
+    assert len(calls) == 2
+    h = b._native()
+    assert all(getattr(h, name)() is None for name in ("quant_act", "rmsnorm_quant", "silu_mul_quant", "silu_mul_bwd", "quant_weight", "gemm"))
+
+
+def test_a_failed_build_of_the_extension_leaves_the_library(monkeypatch, tmp_path):
+    from paper_2601_14243_amd import build as jb
+
+    def no_compiler(force):
+        raise FileNotFoundError("g++")
+    stale = tmp_path / "_jet_host.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(jb, "HOST_LIB", str(stale))
+    monkeypatch.setattr(jb, "_compile", lambda *a: None)
+    monkeypatch.setattr(jb, "_compile_host", no_compiler)
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert jb.build() == jb.LIB
+    assert not stale.exists()
 
 
 class _Declines:
@@ -114,11 +161,6 @@ def test_same_errors_as_the_python_path(monkeypatch, native):
         b.fp8_linear_fwd(q, s, w, ws, out=z(4, 256))
     with pytest.raises(TypeError):
         b.fp8_linear_fwd(q[:, ::2], s, w, ws)
-
-
-class _OnGpu(torch.Tensor):
-    """A CPU tensor that passes for a GPU one, for checks that come before any launch."""
-    is_cuda = property(lambda self: True)
 
 
 def _bad_buffers(make, other):
