@@ -54,6 +54,22 @@ def test_silu_mul_bwd_every_gate_value(jet):
     _same_or_zero("dgate", got[:, :K], want_g)
 
 
+def test_silu_mul_bwd_every_gate_value_with_every_significand(jet):
+    """dgate = bf16(da silu'(g)) of every gate value whose product is formed in binary32 (|g| <= 80) with all 128
+    significands of da: scaling by a power of two and the sign change nothing, so no rounding tie is left out."""
+    bits = np.arange(0, 0x42A1, dtype=np.uint32)
+    bits = np.concatenate([bits, bits | 0x8000])
+    bits = np.concatenate([bits, np.zeros(-len(bits) % 128, np.uint32)]).astype(np.uint16)
+    K, M = len(bits), 128
+    gate = np.tile(bits, (M, 1))
+    dh = np.tile((0x3F80 + np.arange(M, dtype=np.uint16))[:, None], (1, K))
+    up = np.full((M, K), 0x3F80, np.uint16)
+    want_g, want_u = orc.silu_mul_bwd(gate, up, dh)
+    got = host_bits(jet.silu_mul_bwd(dev_bf16(gate), dev_bf16(up), dev_bf16(dh)))
+    _same("dup", got[:, K:], want_u)
+    _same("dgate", got[:, :K], want_g)
+
+
 @pytest.mark.parametrize("M,K,fused", [(256, 1024, True), (1, 128, False), (77, 384, True), (513, 3584, True)])
 def test_silu_mul_bwd_shapes_and_strides(jet, M, K, fused):
     both = ji.mlp_intermediate(M, K, seed=1200 + M + K)
