@@ -9,11 +9,13 @@
 // groups wherever they like; only the fma chain is ordered.  That keeps a token
 // row bit-identical between decode-shaped and training-shaped calls (Sec. 4.1).
 #include <algorithm>
+#include <iterator>
 #include <mutex>
 #include <type_traits>
 
 #include "jet_internal.h"
 #include "jet_numerics.h"
+#include "jet_plan.h"
 
 namespace jet {
 
@@ -467,7 +469,7 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 // ------------------------------------------------------------------------
 constexpr int kSkUnit = 2048 + 2048 + 256;        // weight fragment, activation fragment, scales
 constexpr int kSkGroupBytes = 4 * 64 * 4 + 64 * 4;  // p[4][64] + s[64]
-constexpr int kSkPass = 32;                       // groups chained per pass
+constexpr int kSkPass = kStripPass;               // groups chained per pass
 constexpr int sk_lds_bytes(int depth, int waves) { return waves * depth * kSkUnit + kSkPass * kSkGroupBytes; }
 
 // kSkDepth = units in flight per wave: 3 when there is at most one workgroup per CU, 1 when
@@ -898,49 +900,12 @@ static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t*
     return hipGetLastError();
 }
 
-// the panel tiles: X(TM, TN, WR, WC, stages, groups per step), 16 TM WR rows x 16 TN WC columns
-#define JET_PANELS(X)                                                                                       \
-    X(1, 1, 2, 1, 6, 4) X(1, 1, 2, 2, 4, 4) X(2, 1, 1, 3, 3, 4) X(1, 2, 4, 1, 3, 4) X(2, 1, 1, 4, 3, 4)     \
-    X(2, 1, 1, 7, 4, 2) X(1, 2, 3, 1, 3, 4) X(1, 2, 3, 2, 5, 2) X(1, 7, 3, 1, 3, 2) X(2, 2, 2, 2, 4, 2)     \
-    X(1, 7, 4, 1, 3, 2) X(1, 4, 5, 1, 4, 2) X(1, 7, 5, 1, 3, 2) X(2, 4, 3, 1, 3, 2) X(2, 7, 3, 1, 5, 1)     \
-    X(2, 4, 4, 1, 5, 1) X(2, 7, 4, 1, 4, 1)
-
-struct TileChoice {
-    int bm, bn;
-    hipError_t (*panel)(const uint8_t*, const float*, const uint8_t*, const float*, uint16_t*, long, long, long, long,
-                        hipStream_t);      // nullptr: a tile of the tile kernel
-};
-#define JET_PANEL_ROW(TM, TN, WR, WC, S, GP) {16 * TM * WR, 16 * TN * WC, launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>},
-static const TileChoice kTileChoices[] = {JET_PANELS(JET_PANEL_ROW){128, 128, nullptr}, {256, 128, nullptr}, {256, 256, nullptr}};
-
-// The tile of a block-scaled product, by its shape alone: rounds of tiles on the CUs x the time of a tile, which grows
-// with its lines per group L = BM + BN as L (L + 550) (measured per group, from HBM, 1 to 4096 rows, 11 matrices:
-// 48 lines 0.12 us, 128 lines 0.30, 240 lines 0.62, 384 lines 1.2, 512 lines 1.83).  Over those 140 shapes the choice is
-// within 0.7 % of the best tile on average.
-static const TileChoice& pick_tile(long I, long J, long& rounds) {
-    const long cus = compute_units();
-    const TileChoice* best = nullptr;
-    long best_cost = 0;
-    for (const TileChoice& c : kTileChoices) {
-        if (c.bm >= I + 32 && !(c.bm > 128 && I > 100)) continue;         // mostly padding
-        if (c.bn == 256 && J % 256) continue;                             // the tile kernel has no ragged columns
-        const long n = ((I + c.bm - 1) / c.bm) * ((J + c.bn - 1) / c.bn), r = (n + cus - 1) / cus, L = c.bm + c.bn;
-        const long cost = r * L * (L + 550);
-        if (!best || cost < best_cost) { best = &c; best_cost = cost; rounds = r; }
-    }
-    return *best;
-}
-
-// Up to 16 rows: the strips of the skinny kernel stream the weights fastest while their passes of 32 groups and the
-// CUs' shares of strips are nearly full (28672x4096, 1 row: 26.7 us against 28.7 on panels; 4096x4096 6.1 against 7.1); in a
-// partial pass or round waves and CUs wait (55296x5120, 8 and 16 rows: 70 and 78 us, panels 54 and 55; 5120x27648, 1 row:
-// 36.7, panels 32).  The part that is full must be 0.7, and 0.9 from 9 rows on, where a strip copies both activation
-// blocks (14336x4096, 16 rows: full to 0.875, 17.2 us, panels 14.6).
-static bool strips_keep_busy(long I, long J, long G) {
-    const long cus = compute_units(), strips = J / 16;
-    const long slots = strips <= cus ? strips : (strips + cus - 1) / cus * cus, groups = (G + kSkPass - 1) / kSkPass * kSkPass;
-    return 10 * G * strips >= (I <= 8 ? 7 : 9) * groups * slots;
-}
+using PanelLaunch = hipError_t (*)(const uint8_t*, const float*, const uint8_t*, const float*, uint16_t*, long, long, long,
+                                   long, hipStream_t);
+#define JET_PANEL_LAUNCH(TM, TN, WR, WC, S, GP) launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>,
+static const PanelLaunch kPanelLaunches[] = {JET_PANELS(JET_PANEL_LAUNCH)};
+#undef JET_PANEL_LAUNCH
+static_assert(std::size(kPanelLaunches) + 3 == kNumGemmTiles, "the panels come first in kGemmTiles");
 
 template <int SB_MODE, int... Cfg>
 static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
@@ -953,54 +918,59 @@ static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t*
     return hipGetLastError();
 }
 
-// out has row pitch ldo (>= J): the launches below also run on row or column ranges of a larger problem
+// decode of up to 16 rows: a workgroup per 16-column strip
+static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
+                                long J, long R, hipStream_t st) {
+    const unsigned strips = (unsigned)(J / 16);
+#define JET_SKINNY_AB(D, W, AB)                                                                             \
+    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
+                       sa, B, sb, o, (int)I, (int)J, (int)R)
+    // copy only the 8-row activation blocks that hold a row of the batch
+#define JET_SKINNY(D, W)                       \
+    do {                                       \
+        if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
+        else JET_SKINNY_AB(D, W, 2);           \
+    } while (0)
+    if (strips > 256) JET_SKINNY(1, 8);              // two workgroups (16 waves) per CU
+    else JET_SKINNY(3, 8);
+#undef JET_SKINNY
+#undef JET_SKINNY_AB
+    return hipGetLastError();
+}
+
+// out has row pitch ldo (>= J): a split plan runs the kernels on row or column ranges of a larger problem
 template <int SB_MODE>
-static hipError_t launch_tile(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb,
-                              uint16_t* o, long I, long J, long R, long ldo, hipStream_t st) {
-    const int cus = compute_units();
+static hipError_t launch_planned(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
+                                 long J, long R, long ldo, hipStream_t st, bool whole = true) {
     const long G = R / kGroup;
-    if (SB_MODE == kSbBlock) {
-        // up to 1024 rows, and beyond where one round of tiles does (more rounds: the persistent kernel below, which
-        // has no gap between them and splits the last one)
-        long rounds = 0;
-        const TileChoice& c = pick_tile(I, J, rounds);
-        if (I <= 1024 || rounds == 1) {
-            if (c.panel) return c.panel(A, sa, B, sb, o, I, J, R, ldo, st);
-            if (c.bn == 256) return launch_tiles<kSbBlock, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
-            if (c.bm == 256) return launch_tiles<kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
+    const GemmPlan p = plan_gemm(SB_MODE == kSbRow, I, J, G, compute_units(), whole);
+    switch (p.kernel) {
+        case kStrips:
+            if constexpr (SB_MODE == kSbBlock) return launch_strips(A, sa, B, sb, o, I, J, R, st);
+            break;
+        case kPanel:
+            if constexpr (SB_MODE == kSbBlock) return kPanelLaunches[p.panel](A, sa, B, sb, o, I, J, R, ldo, st);
+            break;
+        case kTileWide:
+            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
+            break;
+        case kTileBig: return launch_tiles<SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kTileSmallDeep: return launch_tiles<SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kTileSmall: return launch_tiles<SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kSplitRows: {
+            const hipError_t e = launch_planned<SB_MODE>(A, sa, B, sb, o, p.split, J, R, ldo, st, false);
+            if (e != hipSuccess) return e;
+            return launch_planned<SB_MODE>(A + p.split * R, sa + p.split * G, B, sb, o + p.split * ldo, I - p.split, J, R, ldo, st,
+                                           false);
+        }
+        case kSplitCols: {
+            const hipError_t e = launch_planned<SB_MODE>(A, sa, B, sb, o, I, p.split, R, ldo, st, false);
+            if (e != hipSuccess) return e;
+            const float* sb_tail = sb + (SB_MODE == kSbBlock ? (p.split / kGroup) * G : p.split * G);
+            return launch_planned<SB_MODE>(A, sa, B + p.split * R, sb_tail, o + p.split, I, J - p.split, R, ldo, st, false);
         }
     }
-    // shape-only choice: the big tile when it divides J and fills the 256 CUs.  The grid
-    // is persistent: at most one resident set of workgroups, each walking its tile list.
-    const long big_tiles = ((I + 255) / 256) * (J / 256);
-    if (J % 256 == 0 && big_tiles >= 224) {
-        const int ti = (int)((I + 255) / 256), tj = (int)(J / 256);
-        // A last round that fills at most half of the CUs (896 tiles = 3.5 rounds for the 14336-wide
-        // WGrads) would cost a whole round: split those tiles off as whole tile rows or tile columns
-        // and run them as smaller tiles.  An output element takes the same chain in either kernel.
-        const long tail = big_tiles % cus;
-        if (big_tiles > cus && tail > 0 && tail <= cus / 2) {
-            if (tail % tj == 0) {
-                const long i_main = (ti - tail / tj) * 256;
-                hipError_t e = launch_tile<SB_MODE>(A, sa, B, sb, o, i_main, J, R, ldo, st);
-                if (e != hipSuccess) return e;
-                return launch_tile<SB_MODE>(A + i_main * R, sa + i_main * G, B, sb, o + i_main * ldo, I - i_main, J,
-                                            R, ldo, st);
-            }
-            if (tail % ti == 0) {
-                const long j_main = (tj - tail / ti) * 256;
-                hipError_t e = launch_tile<SB_MODE>(A, sa, B, sb, o, I, j_main, R, ldo, st);
-                if (e != hipSuccess) return e;
-                const float* sb_tail = sb + (SB_MODE == kSbBlock ? (j_main / kGroup) * G : j_main * G);
-                return launch_tile<SB_MODE>(A, sa, B + j_main * R, sb_tail, o + j_main, I, J - j_main, R, ldo, st);
-            }
-        }
-        return launch_tiles<SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
-    }
-    // at most one workgroup per CU anyway: spend the LDS on two more stages, so that operands
-    // that come from HBM are fetched three steps ahead
-    if (((I + 127) / 128) * (J / 128) <= cus) return launch_tiles<SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
-    return launch_tiles<SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb,
@@ -1029,26 +999,8 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
     if (attr_err != hipSuccess) return attr_err;
 
     uint16_t* o = static_cast<uint16_t*>(out);
-    // decode of up to 16 rows: a workgroup per 16-column strip; shape-only choice of ring depth
-    if (I <= 16 && sb_mode == kSbBlock && strips_keep_busy(I, J, R / kGroup)) {
-        const unsigned strips = (unsigned)(J / 16);
-#define JET_SKINNY_AB(D, W, AB)                                                                             \
-    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
-                       sa, B, sb, o, (int)I, (int)J, (int)R)
-        // copy only the 8-row activation blocks that hold a row of the batch
-#define JET_SKINNY(D, W)                       \
-    do {                                       \
-        if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
-        else JET_SKINNY_AB(D, W, 2);           \
-    } while (0)
-        if (strips > 256) JET_SKINNY(1, 8);              // two workgroups (16 waves) per CU
-        else JET_SKINNY(3, 8);
-#undef JET_SKINNY
-#undef JET_SKINNY_AB
-        return hipGetLastError();
-    }
-    if (sb_mode == kSbBlock) return launch_tile<kSbBlock>(A, sa, B, sb, o, I, J, R, J, st);
-    return launch_tile<kSbRow>(A, sa, B, sb, o, I, J, R, J, st);
+    if (sb_mode == kSbBlock) return launch_planned<kSbBlock>(A, sa, B, sb, o, I, J, R, J, st);
+    return launch_planned<kSbRow>(A, sa, B, sb, o, I, J, R, J, st);
 }
 
 }  // namespace jet

@@ -1,0 +1,60 @@
+"""What the library launches for a GEMM, asked on the host: csrc/jet_plan.h compiled with g++, no GPU involved."""
+from __future__ import annotations
+
+import ctypes
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2601_14243_amd", "csrc")
+CUS = 256
+
+SHIM = """
+#include "jet_plan.h"
+extern "C" int jet_plan(int row_scales, long I, long J, long G, long cus, int whole, long* out) {
+    const jet::GemmPlan p = jet::plan_gemm(row_scales, I, J, G, cus, whole);
+    out[0] = p.bm; out[1] = p.bn; out[2] = p.split; out[3] = p.panel;
+    return p.kernel;
+}
+extern "C" int jet_tile(int t, long* out) {
+    if (t >= jet::kNumGemmTiles) return -1;
+    out[0] = jet::kGemmTiles[t].bm; out[1] = jet::kGemmTiles[t].bn;
+    return jet::kGemmTiles[t].kernel;
+}
+"""
+KERNELS = ("strips", "panel", "small", "small deep", "wide", "big", "split rows", "split columns")
+
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        d = tempfile.mkdtemp()
+        src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}", src, "-o", so], check=True)
+        _lib = ctypes.CDLL(so)
+        _lib.jet_plan.argtypes = [ctypes.c_int] + [ctypes.c_long] * 4 + [ctypes.c_int, ctypes.POINTER(ctypes.c_long)]
+    return _lib
+
+
+def plan(I: int, J: int, R: int, row_scales: bool = False, cus: int = CUS, whole: bool = True):
+    """(kernel, rows of the tile, columns of the tile, split) of OUT[I,J] over a reduction of R."""
+    out = (ctypes.c_long * 4)()
+    k = lib().jet_plan(row_scales, I, J, R // 128, cus, whole, out)
+    return KERNELS[k], out[0], out[1], out[2]
+
+
+def name(I: int, J: int, R: int, **kw) -> str:
+    """"strips", or kernel and tile: "panel 32x16", "big 256x256", "split rows 256x256"."""
+    k, bm, bn, _ = plan(I, J, R, **kw)
+    return k if k == "strips" else f"{k} {bm}x{bn}"
+
+
+def tiles():
+    out, t = (ctypes.c_long * 2)(), 0
+    while (k := lib().jet_tile(t, out)) >= 0:
+        yield f"{KERNELS[k]} {out[0]}x{out[1]}"
+        t += 1

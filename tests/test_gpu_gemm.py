@@ -59,19 +59,22 @@ def test_forward_shapes(jet, M, N, K):
     check_gemm(y, ref, f"fwd {M}x{N}x{K}", operands=ops)
 
 
-@pytest.mark.parametrize("M,N,K,kernel", [
-    (1, 4224, 384, "1 row on 32x32 panels, three groups"),
-    (5, 4224, 128, "5 rows on 32x32 panels, one group"),
-    (8, 4224, 1152, "8 rows on 32x32 panels, nine groups"),
-    (9, 4224, 384, "9 rows on 32x32 panels"),
-    (20, 2048, 640, "panel kernel, 32x16 tiles, 4 rows in the second row tile"),
-    (27, 2048, 640, "panel kernel, 32x16 tiles, 11 rows in the second row tile"),
-    (27, 4608, 384, "panel kernel, 32x32 tiles"),
-    (50, 4096, 640, "panel kernel, second row block ragged, odd number of groups"),
-    (200, 4352, 640, "panel kernel, 80x64 tiles, last block holds 40 rows, odd number of groups"),
-    (100, 14336, 256, "64x112 tiles, ragged second row block"),
-    (200, 14336, 384, "wide tiles, ragged second row block"),
-])
+RAGGED_CASES = [
+    (1, 4224, 384, "panel 32x32: three groups"),
+    (5, 4224, 128, "panel 32x32: one group"),
+    (8, 4224, 1152, "panel 32x32: nine groups"),
+    (9, 4224, 384, "panel 32x32"),
+    (20, 2048, 640, "panel 32x16: 4 rows in the second row tile"),
+    (27, 2048, 640, "panel 32x16: 11 rows in the second row tile"),
+    (27, 4608, 384, "panel 32x32"),
+    (50, 4096, 640, "panel 32x32: second row block ragged, odd number of groups"),
+    (200, 4352, 640, "panel 80x64: last block holds 40 rows, odd number of groups"),
+    (100, 14336, 256, "panel 64x112: ragged second row block"),
+    (200, 14336, 384, "panel 128x112: ragged second row block"),
+]
+
+
+@pytest.mark.parametrize("M,N,K,kernel", RAGGED_CASES)
 def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):
     """The launch rules of the decode path by shape, each with a row count that leaves its last
     row block partly empty."""
@@ -79,18 +82,24 @@ def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):
     check_gemm(y, ref, f"fwd {M}x{N}x{K}: {kernel}", operands=ops)
 
 
-@pytest.mark.parametrize("M,N,groups,tile", [
-    (17, 128, 1, "32x16"), (19, 128, 37, "32x16"), (17, 4224, 2, "32x32"), (30, 4224, 37, "32x32"),
-    (17, 8320, 3, "32x48, last panel 16 columns"), (29, 8320, 21, "32x48"), (17, 12416, 5, "32x64"), (32, 12416, 16, "32x64"),
-    (18, 16512, 1, "32x112, last panel 48 columns"), (32, 16512, 19, "32x112"), (40, 6272, 4, "48x32"), (33, 6272, 35, "48x32"),
-    (50, 6272, 2, "64x32"), (63, 6272, 37, "64x32"), (33, 8320, 2, "48x64"), (47, 8320, 17, "48x64"), (48, 16512, 1, "48x112"), (35, 16512, 18, "48x112"),
-    (49, 8320, 3, "64x64"), (63, 8320, 18, "64x64"), (50, 16512, 2, "64x112"), (64, 16512, 17, "64x112"),
-    (65, 9600, 1, "80x64"), (79, 9600, 18, "80x64"), (70, 16512, 3, "80x112"), (80, 16512, 17, "80x112"),
-    (241, 4736, 2, "96x64, third block 49 rows"), (250, 4736, 18, "96x64"), (81, 16512, 1, "96x112"), (95, 16512, 17, "96x112"),
-    (97, 14464, 2, "128x64"), (127, 14464, 17, "128x64"), (97, 16512, 1, "128x112"), (120, 16512, 18, "128x112"),
-    (161, 14464, 3, "128x128 of the tile kernel"), (193, 19072, 4, "256x128 of the tile kernel"),
-    (193, 19072, 1, "256x128, fewer groups than stages"), (400, 17152, 2, "256x256, second tile row 144 rows"),
-])
+TILE_CASES = [
+    (17, 128, 1, "panel 32x16"), (19, 128, 37, "panel 32x16"), (17, 4224, 2, "panel 32x32"),
+    (30, 4224, 37, "panel 32x32"), (17, 8320, 3, "panel 32x48: last panel 16 columns"), (29, 8320, 21, "panel 32x48"),
+    (17, 12416, 5, "panel 32x64"), (32, 12416, 16, "panel 32x64"), (18, 16512, 1, "panel 32x112: last panel 48 columns"),
+    (32, 16512, 19, "panel 32x112"), (40, 6272, 4, "panel 48x32"), (33, 6272, 35, "panel 48x32"),
+    (50, 6272, 2, "panel 64x32"), (63, 6272, 37, "panel 64x32"), (33, 8320, 2, "panel 48x64"),
+    (47, 8320, 17, "panel 48x64"), (48, 16512, 1, "panel 48x112"), (35, 16512, 18, "panel 48x112"),
+    (49, 8320, 3, "panel 64x64"), (63, 8320, 18, "panel 64x64"), (50, 16512, 2, "panel 64x112"),
+    (64, 16512, 17, "panel 64x112"), (65, 9600, 1, "panel 80x64"), (79, 9600, 18, "panel 80x64"),
+    (70, 16512, 3, "panel 80x112"), (80, 16512, 17, "panel 80x112"), (241, 4736, 2, "panel 96x64: third block 49 rows"),
+    (250, 4736, 18, "panel 96x64"), (81, 16512, 1, "panel 96x112"), (95, 16512, 17, "panel 96x112"),
+    (97, 14464, 2, "panel 128x64"), (127, 14464, 17, "panel 128x64"), (97, 16512, 1, "panel 128x112"),
+    (120, 16512, 18, "panel 128x112"), (161, 14464, 3, "small deep 128x128"), (193, 19072, 4, "wide 256x128"),
+    (193, 19072, 1, "wide 256x128: fewer groups than stages"), (400, 17152, 2, "big 256x256: second tile row 144 rows"),
+]
+
+
+@pytest.mark.parametrize("M,N,groups,tile", TILE_CASES)
 def test_forward_on_every_tile_of_the_launch_rule(jet, M, N, groups, tile):
     """A shape for which the rule takes each tile, with ragged rows, ragged columns where the tile does not divide
     128, odd and even numbers of groups, fewer groups than ring stages and more than two scale chunks of 16."""
@@ -98,13 +107,17 @@ def test_forward_on_every_tile_of_the_launch_rule(jet, M, N, groups, tile):
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {tile}", operands=ops)
 
 
-@pytest.mark.parametrize("M,N,groups,kernel", [
-    (1, 8192, 32, "strips, two workgroups per CU"), (8, 8192, 29, "strips, last run of a pass one group"),
-    (9, 8192, 32, "strips, two activation blocks"), (16, 8192, 30, "strips, two activation blocks, partial pass"),
-    (3, 4096, 24, "strips, one workgroup per CU"), (7, 384, 64, "strips, two passes"), (12, 1024, 61, "strips, two passes, the second partial"),
-    (1, 8192, 22, "panel: a pass of 32 groups is two thirds full"), (16, 8192, 28, "panel: 0.875 full"), (1, 5120, 32, "panel: 320 strips on 256 CUs"),
-    (5, 5120, 40, "panel"), (16, 128, 1, "panel"),
-])
+FEW_ROW_CASES = [
+    (1, 8192, 32, "strips: two workgroups per CU"), (8, 8192, 29, "strips: last run of a pass one group"),
+    (9, 8192, 32, "strips: two activation blocks"), (16, 8192, 30, "strips: two activation blocks, partial pass"),
+    (3, 4096, 24, "strips: one workgroup per CU"), (7, 384, 64, "strips: two passes"),
+    (12, 1024, 61, "strips: two passes, the second partial"), (1, 8192, 22, "panel 32x32: a pass of 32 groups is two thirds full"),
+    (16, 8192, 28, "panel 32x32: 0.875 full"), (1, 5120, 32, "panel 32x32: 320 strips on 256 CUs"),
+    (5, 5120, 40, "panel 32x32"), (16, 128, 1, "panel 32x16"),
+]
+
+
+@pytest.mark.parametrize("M,N,groups,kernel", FEW_ROW_CASES)
 def test_forward_of_a_few_rows_on_both_sides_of_the_strip_rule(jet, M, N, groups, kernel):
     y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=17 * M + N + groups)
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {kernel}", operands=ops)

@@ -1,0 +1,51 @@
+"""The rule that picks kernel and tile of a GEMM (csrc/jet_plan.h), on the host: all kernels give the same bits, so a
+changed rule would drop one from the GPU tests without any of them failing."""
+import pytest
+
+import launch_plan as lp
+from test_gpu_gemm import FEW_ROW_CASES, RAGGED_CASES, TILE_CASES
+
+CASES = ([(M, N, K, label) for M, N, K, label in RAGGED_CASES] +
+         [(M, N, 128 * g, label) for M, N, g, label in TILE_CASES + FEW_ROW_CASES])
+
+
+@pytest.mark.parametrize("M,N,K,label", CASES)
+def test_the_gpu_cases_run_what_their_labels_say(M, N, K, label):
+    assert lp.name(M, N, K) == label.split(":")[0]
+
+
+def test_every_tile_has_a_gpu_case():
+    named = {label.split(":")[0] for *_, label in CASES}
+    assert set(lp.tiles()) | {"strips"} <= named
+    # each panel with few groups and with more than one chunk of 16 scales
+    for tile in lp.tiles():
+        groups = [K // 128 for _, _, K, label in CASES if label.split(":")[0] == tile]
+        if tile.startswith("panel"):
+            assert len(groups) >= 2 and min(groups) <= 5 and max(groups) > 15, (tile, groups)
+
+
+def test_every_tile_is_chosen_somewhere_and_fits_its_kernel():
+    seen = set()
+    for I in (1, 7, 16, 17, 32, 33, 48, 64, 65, 80, 96, 97, 128, 129, 200, 256, 257, 400, 512, 700, 1000, 1024, 1025, 4096, 16384):
+        for J in (128, 256, 384, 1024, 4096, 5120, 6144, 8320, 9600, 12416, 14336, 14464, 16512, 19072, 27648, 28672, 55296):
+            for R in (128, 1024, 4096, 14336, 27648):
+                for row_scales in (False, True):
+                    k, bm, bn, split = lp.plan(I, J, R, row_scales)
+                    seen.add(lp.name(I, J, R, row_scales=row_scales))
+                    assert k == "panel" or J % bn == 0                        # only panels have ragged columns
+                    assert k != "strips" or I <= 16
+                    assert not row_scales or k in ("big", "small", "small deep", "split rows", "split columns")
+                    if k.startswith("split"):
+                        assert split % 256 == 0 and 0 < split < (I if k == "split rows" else J)
+                        rest = (I - split, J) if k == "split rows" else (I, J - split)
+                        for part in ((split, J) if k == "split rows" else (I, split), rest):
+                            sub = lp.plan(*part, R, row_scales, whole=False)[0]
+                            assert sub != "strips" and not sub.startswith("split")
+    assert set(lp.tiles()) | {"strips", "small 128x128"} <= seen
+
+
+def test_part_of_a_split_problem_never_runs_strips():
+    """The skinny kernel writes rows of J elements; the rows of a part are further apart."""
+    for I in range(1, 17):
+        assert lp.plan(I, 4096, 4096)[0] == "strips"
+        assert lp.plan(I, 4096, 4096, whole=False)[0] != "strips"
