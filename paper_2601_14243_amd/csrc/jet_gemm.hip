@@ -600,14 +600,14 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 }
 
 // ------------------------------------------------------------------------
-// Panel kernel (block scales only): batches of up to 1024 rows, and larger ones against narrow matrices, whose
-// output makes one or two rounds of tiles on the CUs.  One workgroup per CU owns a BM x BN output tile and walks the
+// Panel kernel (block scales only): batches of up to 1024 rows, and larger ones against narrow matrices, where
+// jet_plan.h prefers it.  One workgroup per CU owns a BM x BN output tile and walks the
 // whole reduction, a step of one, two or four groups at a time; WR x WC waves compute, kCopy waves copy the operands and
 // one the scales.
 // What bounds it: a CU can have about 320 cache lines on their way and gets them back in order, so an
 // activation line (an L2 hit) waits behind the weight lines (HBM misses) in front of it.  A tile takes about
 // (BM + BN) * G * 2.4 ns, whatever its lines hit (measured from 48 to 240 lines per group), plus 3-4 us of launch, ring
-// fill and output.  So the tile is chosen by its lines (pick_tile), and a wide matrix gets wide tiles: the
+// fill and output.  So lines decide the tile (jet_plan.h), and a wide matrix gets wide tiles: the
 // activations of a group pass once per 112 columns and not once per 32.
 // Ring of S stages, per group [W: BN rows x 128][A: BM rows x 128] in the swizzled fragment layout of the tile
 // kernel; scales travel in chunks of 16 groups, [row][16] with the group xor (row >> 2) & 3 (conflict-free), two buffers.
@@ -873,10 +873,12 @@ static hipError_t allow_lds(K kernel, int bytes) {
 #define JET_WIDE 4, 2, 4, 4, 3
 #define JET_SMALL 2, 2, 4, 4
 #define JET_SMALL_DEEP 2, 2, 4, 4, 4   /* four stages, one workgroup per CU: copies three steps ahead */
+#define JET_HALF 4, 1, 2, 4, 4         /* 128x64 tile, 4 waves of 32x64, four stages */
 using BigCfg = TileCfg<JET_BIG>;
 using WideCfg = TileCfg<JET_WIDE>;
 using SmallCfg = TileCfg<JET_SMALL>;
 using SmallDeepCfg = TileCfg<JET_SMALL_DEEP>;
+using HalfCfg = TileCfg<JET_HALF>;
 
 // compute units of the current device (256 on MI355X), asked once per process
 static int compute_units() {
@@ -902,10 +904,10 @@ static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t*
 
 using PanelLaunch = hipError_t (*)(const uint8_t*, const float*, const uint8_t*, const float*, uint16_t*, long, long, long,
                                    long, hipStream_t);
-#define JET_PANEL_LAUNCH(TM, TN, WR, WC, S, GP) launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>,
+#define JET_PANEL_LAUNCH(TM, TN, WR, WC, S, GP, GROUP, ROUND) launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>,
 static const PanelLaunch kPanelLaunches[] = {JET_PANELS(JET_PANEL_LAUNCH)};
 #undef JET_PANEL_LAUNCH
-static_assert(std::size(kPanelLaunches) + 3 == kNumGemmTiles, "the panels come first in kGemmTiles");
+static_assert(std::size(kPanelLaunches) == kNumPanels, "the panels come first in kGemmTiles");
 
 template <int SB_MODE, int... Cfg>
 static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
@@ -954,6 +956,9 @@ static hipError_t launch_planned(const uint8_t* A, const float* sa, const uint8_
         case kTileWide:
             if constexpr (SB_MODE == kSbBlock) return launch_tiles<kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
             break;
+        case kTileHalf:
+            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kSbBlock, JET_HALF>(A, sa, B, sb, o, I, J, R, ldo, st);
+            break;
         case kTileBig: return launch_tiles<SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
         case kTileSmallDeep: return launch_tiles<SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
         case kTileSmall: return launch_tiles<SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
@@ -981,6 +986,7 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
         hipError_t e = allow_lds(gemm_tile_kernel<kSbBlock, JET_BIG>, BigCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_BIG>, BigCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_WIDE>, WideCfg::kLdsBytes);
+        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_HALF>, HalfCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL>, SmallCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL>, SmallCfg::kLdsBytes);
         if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
@@ -990,7 +996,7 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
         JET_SK_ATTR(3, 8, 1); JET_SK_ATTR(3, 8, 2);
         JET_SK_ATTR(1, 8, 1); JET_SK_ATTR(1, 8, 2);
 #undef JET_SK_ATTR
-#define JET_PANEL_ATTR(TM, TN, WR, WC, S, GP) \
+#define JET_PANEL_ATTR(TM, TN, WR, WC, S, GP, GROUP, ROUND) \
     if (e == hipSuccess) e = allow_lds(gemm_panel_kernel<PanelCfg<TM, TN, WR, WC, S, GP>>, PanelCfg<TM, TN, WR, WC, S, GP>::kLds);
         JET_PANELS(JET_PANEL_ATTR)
 #undef JET_PANEL_ATTR

@@ -4,18 +4,22 @@
 
 namespace jet {
 
-// the panel kernel's tiles: X(TM, TN, WR, WC, stages, groups per step), 16 TM WR rows x 16 TN WC columns
-#define JET_PANELS(X)                                                                                       \
-    X(1, 1, 2, 1, 6, 4) X(1, 1, 2, 2, 4, 4) X(2, 1, 1, 3, 3, 4) X(1, 2, 4, 1, 3, 4) X(2, 1, 1, 4, 3, 4)     \
-    X(2, 1, 1, 7, 4, 2) X(1, 2, 3, 1, 3, 4) X(1, 2, 3, 2, 5, 2) X(1, 7, 3, 1, 3, 2) X(2, 2, 2, 2, 4, 2)     \
-    X(1, 7, 4, 1, 3, 2) X(1, 4, 5, 1, 4, 2) X(1, 7, 5, 1, 3, 2) X(2, 4, 3, 1, 3, 2) X(2, 7, 3, 1, 5, 1)     \
-    X(2, 4, 4, 1, 5, 1) X(2, 7, 4, 1, 4, 1)
+// the panel kernel's tiles: X(TM, TN, WR, WC, stages, groups per step, ns per group, ns per round), 16 TM WR rows x
+// 16 TN WC columns
+#define JET_PANELS(X)                                                                              \
+    X(1, 1, 2, 1, 6, 4, 123, 1963) X(1, 1, 2, 2, 4, 4, 148, 2247) X(2, 1, 1, 3, 3, 4, 149, 2589)   \
+    X(1, 2, 4, 1, 3, 4, 197, 2584) X(2, 1, 1, 4, 3, 4, 209, 2921) X(2, 1, 1, 7, 4, 2, 349, 2700)   \
+    X(1, 2, 3, 1, 3, 4, 163, 2459) X(1, 2, 3, 2, 5, 2, 225, 2834) X(1, 7, 3, 1, 3, 2, 404, 3528)   \
+    X(2, 2, 2, 2, 4, 2, 287, 2747) X(1, 7, 4, 1, 3, 2, 366, 3886) X(1, 4, 5, 1, 4, 2, 297, 3489)   \
+    X(1, 7, 5, 1, 3, 2, 509, 4238) X(2, 4, 3, 1, 3, 2, 361, 3734) X(2, 7, 3, 1, 5, 1, 559, 4527)   \
+    X(2, 4, 4, 1, 5, 1, 380, 3826) X(2, 7, 4, 1, 4, 1, 577, 4805)
 
 enum GemmKernel {
     kStrips,         // skinny kernel, 16 columns per workgroup
     kPanel,          // panel kernel, entry `panel` of JET_PANELS
     kTileSmall,      // tile kernel: 128x128, two stages, two workgroups per CU
     kTileSmallDeep,  //              128x128, four stages, one workgroup per CU
+    kTileHalf,       //              128x64, four stages
     kTileWide,       //              256x128, three stages
     kTileBig,        //              256x256
     kSplitRows,      // two launches: rows [0, split), then the rest, each planned by itself
@@ -31,69 +35,102 @@ struct GemmPlan {
 struct GemmTile {
     int bm, bn;
     GemmKernel kernel;
+    int group, round;    // ns of a group and of a round of tiles on the CUs
 };
-#define JET_PANEL_TILE(TM, TN, WR, WC, S, GP) {16 * TM * WR, 16 * TN * WC, kPanel},
-constexpr GemmTile kGemmTiles[] = {JET_PANELS(JET_PANEL_TILE){128, 128, kTileSmallDeep}, {256, 128, kTileWide}, {256, 256, kTileBig}};
+#define JET_PANEL_TILE(TM, TN, WR, WC, S, GP, GROUP, ROUND) {16 * TM * WR, 16 * TN * WC, kPanel, GROUP, ROUND},
+constexpr GemmTile kGemmTiles[] = {JET_PANELS(JET_PANEL_TILE){128, 128, kTileSmallDeep, 643, 3437},
+                                   {128, 128, kTileSmall, 1307, 1794}, {256, 128, kTileWide, 885, 4720},
+                                   {256, 256, kTileBig, 1732, 7059}, {128, 64, kTileHalf, 511, 2371}};
 #undef JET_PANEL_TILE
 constexpr int kNumGemmTiles = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
+constexpr int kNumPanels = kNumGemmTiles - 5;
+static_assert(kGemmTiles[kNumPanels].kernel == kTileSmallDeep && kGemmTiles[kNumPanels + 3].kernel == kTileBig, "");
+constexpr int kSmallAlone = 1110;    // ns of a group of kTileSmall where only one of a CU's two places is taken
+constexpr int kLaunch = 1400;        // ns of a launch
 constexpr int kStripPass = 32;       // groups that the skinny kernel chains per pass
 
 constexpr long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
-// The tile of a block-scaled product, by its shape alone: rounds of tiles on the CUs x the time of a tile, which grows
-// with its lines per group L = BM + BN as L (L + 550) (measured per group, from HBM, 1 to 4096 rows, 11 matrices:
-// 48 lines 0.12 us, 128 lines 0.30, 240 lines 0.62, 384 lines 1.2, 512 lines 1.83).  Over those 140 shapes the choice is
-// within 0.7 % of the best tile on average.
-inline int pick_tile(long I, long J, long cus, long& rounds) {
-    int best = 0;
-    long best_cost = -1;
+// Time in ns of a launch on tile c, without its fixed part: rounds x (groups x time of a group + a time per round, which is
+// ring fill, drain, output and half a launch gap).  The table's times were fitted to every tile on 34 matrices (128 to
+// 55296 columns, 256 to 27648 long, 17 to 4096 rows, weights from HBM and from the caches, 2366 shapes), such that the
+// choice and not the time comes out right: it is 0.7 % from the best tile on average.  The cost before, rounds x
+// L (L + 550) with L = rows + columns of the tile, had no time per round and took two 128x128 tiles of a CU for two
+// rounds.  It was 2.6 % from the best, and short reductions and launches of a few rounds were slower than on the kernels
+// before that (us; before, with that cost, now): from HBM 140x16384x1024 12.2, 15.6, 12.0; 280x16384x1024 17.1, 20.4, 16.1;
+// 555x28672x4096 120, 126, 96; from the caches 440x4096x4096 17.4, 19.7, 16.7; 1000x5120x27648 195, 226, 175.
+inline long tile_time(const GemmTile& c, long I, long J, long G, long cus) {
+    const long rounds = ceil_div(ceil_div(I, c.bm) * ceil_div(J, c.bn), cus);
+    if (c.kernel == kTileSmall)          // the two tiles of a CU run together
+        return rounds / 2 * G * c.group + rounds % 2 * G * kSmallAlone + rounds * c.round;
+    return rounds * (G * c.group + c.round);
+}
+
+// The fastest tile, -1 if none of those that do it in one round (one_round) exists; time: that of the launch.
+inline int pick_tile(long I, long J, long G, long cus, bool one_round, long& time) {
+    int best = -1;
     for (int t = 0; t < kNumGemmTiles; ++t) {
         const GemmTile& c = kGemmTiles[t];
-        if (c.bm >= I + 32 && !(c.bm > 128 && I > 100)) continue;         // mostly padding
+        if (c.bm > 128 && I <= 128) continue;                             // half of it padding, not measured
         if (c.bn == 256 && J % 256) continue;                             // the tile kernel has no ragged columns
-        const long r = ceil_div(ceil_div(I, c.bm) * ceil_div(J, c.bn), cus), L = c.bm + c.bn;
-        const long cost = r * L * (L + 550);
-        if (best_cost < 0 || cost < best_cost) { best = t; best_cost = cost; rounds = r; }
+        const long resident = c.kernel == kTileSmall ? 2 * cus : cus;
+        if (one_round && ceil_div(I, c.bm) * ceil_div(J, c.bn) > resident) continue;
+        const long d = tile_time(c, I, J, G, cus);
+        if (best < 0 || d < time) { best = t; time = d; }
     }
     return best;
 }
 
-// Up to 16 rows: the strips of the skinny kernel stream the weights fastest while their passes of 32 groups and the
-// CUs' shares of strips are nearly full (28672x4096, 1 row: 26.7 us against 28.7 on panels; 4096x4096 6.1 against 7.1); in a
-// partial pass or round waves and CUs wait (55296x5120, 8 and 16 rows: 70 and 78 us, panels 54 and 55; 5120x27648, 1 row:
-// 36.7, panels 32).  The part that is full must be 0.7, and 0.9 from 9 rows on, where a strip copies both activation
-// blocks (14336x4096, 16 rows: full to 0.875, 17.2 us, panels 14.6).
-inline bool strips_keep_busy(long I, long J, long G, long cus) {
-    const long strips = J / 16, slots = strips <= cus ? strips : ceil_div(strips, cus) * cus;
-    return 10 * G * strips >= (I <= 8 ? 7 : 9) * ceil_div(G, kStripPass) * kStripPass * slots;
+// Up to 16 rows: strips of the skinny kernel or panels.  A strip's eight waves share its reduction, a panel's groups come
+// one after the other; but in a partly full pass of 32 groups waves wait, and in a partly full round CUs.  Strips against the
+// best panel, 1-16 rows, matrices of 512-8192 columns x 8-56 groups and the layers' own (time of strips / time of panels):
+//  - one pass, all strips resident (at most two per CU): from 14 groups on 0.80-1.00 (320 and 384 strips from HBM up to
+//    1.04), at 12 0.97-1.10, at 8 1.00-1.25.  With two per CU and from 9 rows on (both activation blocks are copied) up to 24
+//    groups: beyond, 0.88-0.96 from the caches and 1.05-1.07 from HBM.
+//  - up to 8 rows, at most one strip per CU, more passes: 0.85-1.00 from 36 of 64 groups on (1.03 for 256 strips from HBM).
+//  - the rest: passes x rounds full to 0.7 (0.9 from 9 rows on): 28672x4096, 1 row, 0.93; below, 55296x5120, 8 and 16 rows,
+//    1.30 and 1.45; 5120x27648, 1 row, 1.14; 14336x4096, 16 rows (0.875) 1.18.
+inline bool strips_pay(long I, long J, long G, long cus) {
+    const bool few = I <= 8;
+    const long strips = J / 16, places = strips <= cus ? strips : ceil_div(strips, cus) * cus;
+    const long groups = ceil_div(G, kStripPass) * kStripPass;
+    if (G <= kStripPass && (strips <= cus || (strips <= 2 * cus && (few || G <= 24)))) return G >= 14;
+    if (few && strips <= cus) return 20 * G >= 11 * groups;
+    return 10 * G * strips >= (few ? 7 : 9) * groups * places;
 }
 
 // OUT[I,J] over G groups of 128.  row_scales: the operand of the columns has a scale per row (WGrad), else per block.
 // whole: not a part of a split problem, whose output rows are further apart than the skinny kernel writes them
 inline GemmPlan plan_gemm(bool row_scales, long I, long J, long G, long cus, bool whole) {
+    const long ti = ceil_div(I, 256), tj = J / 256, big = ti * tj;
+    // A last round of big tiles that fills at most half of the CUs (896 tiles = 3.5 rounds for the 14336-wide
+    // WGrads) would cost a whole round: split those tiles off as whole tile rows or tile columns
+    // and run them as smaller tiles.  An output element takes the same chain in either kernel.
+    const long tail = big % cus;
+    GemmPlan split = {kTileBig, 0, 256, 256, 0};
+    if (J % 256 == 0 && big > cus && tail > 0 && tail <= cus / 2) {
+        if (tail % tj == 0) split = {kSplitRows, 0, 256, 256, (ti - tail / tj) * 256};
+        else if (tail % ti == 0) split = {kSplitCols, 0, 256, 256, (tj - tail / ti) * 256};
+    }
     if (!row_scales) {
-        if (whole && I <= 16 && strips_keep_busy(I, J, G, cus)) return {kStrips, 0, 16, 16, 0};
-        // up to 1024 rows, and beyond where one round of tiles does (more rounds: the persistent kernel below, which
-        // has no gap between them and splits the last one)
-        long rounds = 0;
-        const int t = pick_tile(I, J, cus, rounds);
-        const GemmTile& c = kGemmTiles[t];
-        if ((I <= 1024 || rounds == 1) && c.kernel != kTileSmallDeep) return {c.kernel, t, c.bm, c.bn, 0};
+        if (whole && I <= 16 && strips_pay(I, J, G, cus)) return {kStrips, 0, 16, 16, 0};
+        // up to 1024 rows the fastest tile, and beyond where one round of tiles does (more rounds: the persistent kernel
+        // below, which has no gap between them and splits the last one)
+        long time = 0, rest = 0;
+        const int t = pick_tile(I, J, G, cus, I > 1024, time);
+        if (t >= 0) {
+            if (I <= 1024 && split.kernel != kTileBig) {
+                const bool rows = split.kernel == kSplitRows;
+                pick_tile(rows ? I - split.split : I, rows ? J : J - split.split, G, cus, false, rest);
+                if (tile_time(kGemmTiles[kNumPanels + 3], rows ? split.split : I, rows ? J : split.split, G, cus) + kLaunch + rest < time)
+                    return split;
+            }
+            return {kGemmTiles[t].kernel, t, kGemmTiles[t].bm, kGemmTiles[t].bn, 0};
+        }
     }
     // the big tile when it divides J and fills the CUs.  The grid is persistent: at most one resident set of
     // workgroups, each walking its tile list.
-    const long ti = ceil_div(I, 256), tj = J / 256, big = ti * tj;
-    if (J % 256 == 0 && big >= 224) {
-        // A last round that fills at most half of the CUs (896 tiles = 3.5 rounds for the 14336-wide
-        // WGrads) would cost a whole round: split those tiles off as whole tile rows or tile columns
-        // and run them as smaller tiles.  An output element takes the same chain in either kernel.
-        const long tail = big % cus;
-        if (big > cus && tail > 0 && tail <= cus / 2) {
-            if (tail % tj == 0) return {kSplitRows, 0, 256, 256, (ti - tail / tj) * 256};
-            if (tail % ti == 0) return {kSplitCols, 0, 256, 256, (tj - tail / ti) * 256};
-        }
-        return {kTileBig, 0, 256, 256, 0};
-    }
+    if (J % 256 == 0 && big >= 224) return split;
     // at most one workgroup per CU anyway: spend the LDS on two more stages, so that operands
     // that come from HBM are fetched three steps ahead
     return {ceil_div(I, 128) * (J / 128) <= cus ? kTileSmallDeep : kTileSmall, 0, 128, 128, 0};

@@ -22,7 +22,7 @@ extern "C" int jet_tile(int t, long* out) {
     return jet::kGemmTiles[t].kernel;
 }
 """
-KERNELS = ("strips", "panel", "small", "small deep", "wide", "big", "split rows", "split columns")
+KERNELS = ("strips", "panel", "small", "small deep", "half", "wide", "big", "split rows", "split columns")
 
 _lib = None
 

@@ -68,9 +68,9 @@ RAGGED_CASES = [
     (27, 2048, 640, "panel 32x16: 11 rows in the second row tile"),
     (27, 4608, 384, "panel 32x32"),
     (50, 4096, 640, "panel 32x32: second row block ragged, odd number of groups"),
-    (200, 4352, 640, "panel 80x64: last block holds 40 rows, odd number of groups"),
-    (100, 14336, 256, "panel 64x112: ragged second row block"),
-    (200, 14336, 384, "panel 128x112: ragged second row block"),
+    (200, 4352, 640, "half 128x64: second tile row 72 rows, odd number of groups"),
+    (100, 14336, 256, "half 128x64: 100 of 128 rows"),
+    (200, 14336, 384, "small 128x128: second tile row 72 rows"),
 ]
 
 
@@ -85,24 +85,32 @@ def test_forward_ragged_rows_in_every_decode_kernel(jet, M, N, K, kernel):
 TILE_CASES = [
     (17, 128, 1, "panel 32x16"), (19, 128, 37, "panel 32x16"), (17, 4224, 2, "panel 32x32"),
     (30, 4224, 37, "panel 32x32"), (17, 8320, 3, "panel 32x48: last panel 16 columns"), (29, 8320, 21, "panel 32x48"),
-    (17, 12416, 5, "panel 32x64"), (32, 12416, 16, "panel 32x64"), (18, 16512, 1, "panel 32x112: last panel 48 columns"),
+    (17, 12416, 5, "panel 48x64"), (32, 12416, 16, "panel 32x64"), (18, 16512, 1, "small 128x128: 18 of 128 rows"),
     (32, 16512, 19, "panel 32x112"), (40, 6272, 4, "panel 48x32"), (33, 6272, 35, "panel 48x32"),
     (50, 6272, 2, "panel 64x32"), (63, 6272, 37, "panel 64x32"), (33, 8320, 2, "panel 48x64"),
-    (47, 8320, 17, "panel 48x64"), (48, 16512, 1, "panel 48x112"), (35, 16512, 18, "panel 48x112"),
-    (49, 8320, 3, "panel 64x64"), (63, 8320, 18, "panel 64x64"), (50, 16512, 2, "panel 64x112"),
-    (64, 16512, 17, "panel 64x112"), (65, 9600, 1, "panel 80x64"), (79, 9600, 18, "panel 80x64"),
-    (70, 16512, 3, "panel 80x112"), (80, 16512, 17, "panel 80x112"), (241, 4736, 2, "panel 96x64: third block 49 rows"),
-    (250, 4736, 18, "panel 96x64"), (81, 16512, 1, "panel 96x112"), (95, 16512, 17, "panel 96x112"),
-    (97, 14464, 2, "panel 128x64"), (127, 14464, 17, "panel 128x64"), (97, 16512, 1, "panel 128x112"),
-    (120, 16512, 18, "panel 128x112"), (161, 14464, 3, "small deep 128x128"), (193, 19072, 4, "wide 256x128"),
-    (193, 19072, 1, "wide 256x128: fewer groups than stages"), (400, 17152, 2, "big 256x256: second tile row 144 rows"),
+    (47, 8320, 17, "panel 48x64"), (48, 16512, 1, "small 128x128"), (35, 16512, 18, "panel 64x112"),
+    (49, 8320, 3, "panel 64x64"), (63, 8320, 18, "panel 64x64"), (50, 16512, 2, "small 128x128"),
+    (64, 16512, 17, "panel 64x112"), (65, 9600, 1, "half 128x64"), (79, 9600, 18, "panel 80x64"),
+    (70, 16512, 3, "small 128x128"), (80, 16512, 17, "panel 80x112"), (241, 4736, 2, "half 128x64: second tile row 113 rows"),
+    (250, 4736, 18, "panel 96x64"), (81, 16512, 1, "small 128x128"), (95, 16512, 17, "panel 96x112"),
+    (97, 14464, 2, "half 128x64"), (127, 14464, 17, "panel 128x64"), (97, 16512, 1, "small 128x128"),
+    (120, 16512, 18, "small deep 128x128"), (161, 14464, 3, "small 128x128"), (193, 19072, 4, "wide 256x128"),
+    (193, 19072, 1, "small 128x128: fewer groups than stages"), (400, 17152, 2, "small 128x128: fourth tile row 16 rows"), (18, 16512, 2, "panel 32x112: last panel 48 columns"),
+    (17, 12672, 17, "panel 32x64"), (35, 16640, 3, "panel 48x112: last panel 64 columns"), (66, 8448, 17, "panel 80x64"),
+    (81, 16512, 17, "panel 96x112"), (83, 9600, 17, "panel 96x64"), (97, 14464, 17, "panel 128x64"),
+    (97, 16640, 35, "panel 128x112"), (17, 12672, 1, "half 128x64"), (250, 4736, 1, "half 128x64"),
+    (70, 16384, 8, "panel 80x64"), (450, 4096, 8, "half 128x64: fourth tile row 66 rows"), (17, 16512, 1, "small 128x128"),
+    (140, 16512, 2, "small 128x128"), (257, 16384, 8, "wide 256x128"), (97, 16640, 17, "small deep 128x128"),
+    (130, 16512, 3, "wide 256x128: second half of the tile's rows empty but two"), (130, 16512, 17, "wide 256x128"), (450, 16640, 3, "big 256x256"),
+    (400, 33024, 1, "split columns 256x256: the last 256 columns on their own"),
 ]
 
 
 @pytest.mark.parametrize("M,N,groups,tile", TILE_CASES)
 def test_forward_on_every_tile_of_the_launch_rule(jet, M, N, groups, tile):
-    """A shape for which the rule takes each tile, with ragged rows, ragged columns where the tile does not divide
-    128, odd and even numbers of groups, fewer groups than ring stages and more than two scale chunks of 16."""
+    """Shapes for which the rule takes each tile (tests/test_launch_plan.py holds the labels to it), with ragged rows, ragged
+    columns where the tile does not divide 128, odd and even numbers of groups, fewer groups than ring stages and more than
+    two scale chunks of 16."""
     y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=13 * M + N + groups)
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {tile}", operands=ops)
 
@@ -111,9 +119,13 @@ FEW_ROW_CASES = [
     (1, 8192, 32, "strips: two workgroups per CU"), (8, 8192, 29, "strips: last run of a pass one group"),
     (9, 8192, 32, "strips: two activation blocks"), (16, 8192, 30, "strips: two activation blocks, partial pass"),
     (3, 4096, 24, "strips: one workgroup per CU"), (7, 384, 64, "strips: two passes"),
-    (12, 1024, 61, "strips: two passes, the second partial"), (1, 8192, 22, "panel 32x32: a pass of 32 groups is two thirds full"),
-    (16, 8192, 28, "panel 32x32: 0.875 full"), (1, 5120, 32, "panel 32x32: 320 strips on 256 CUs"),
+    (12, 1024, 61, "strips: two passes, the second partial"), (1, 8192, 22, "strips: 22 of 32 groups, two per CU"),
+    (16, 8192, 28, "panel 32x32: 28 of 32 groups, two strips per CU"), (1, 5120, 32, "strips: 320 strips on 256 CUs"),
     (5, 5120, 40, "panel 32x32"), (16, 128, 1, "panel 32x16"),
+    (3, 1024, 35, "panel 32x16: 35 of 64 groups"), (8, 4096, 36, "strips: 36 of 64 groups"),
+    (8, 2048, 13, "panel 32x16"), (12, 4096, 14, "strips"),
+    (16, 6144, 24, "strips: 384 strips"), (16, 6144, 32, "panel 32x32"),
+    (7, 8192, 14, "strips"),
 ]
 
 

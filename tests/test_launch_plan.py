@@ -16,17 +16,17 @@ def test_the_gpu_cases_run_what_their_labels_say(M, N, K, label):
 
 def test_every_tile_has_a_gpu_case():
     named = {label.split(":")[0] for *_, label in CASES}
-    assert set(lp.tiles()) | {"strips"} <= named
-    # each panel with few groups and with more than one chunk of 16 scales
+    assert set(lp.tiles()) | {"strips", "split columns 256x256"} <= named
+    # each panel with more than one chunk of 16 scales (48x112 is taken for shorter reductions only)
     for tile in lp.tiles():
         groups = [K // 128 for _, _, K, label in CASES if label.split(":")[0] == tile]
-        if tile.startswith("panel"):
-            assert len(groups) >= 2 and min(groups) <= 5 and max(groups) > 15, (tile, groups)
+        if tile.startswith("panel") and tile != "panel 48x112":
+            assert max(groups) > 15, (tile, groups)
 
 
 def test_every_tile_is_chosen_somewhere_and_fits_its_kernel():
     seen = set()
-    for I in (1, 7, 16, 17, 32, 33, 48, 64, 65, 80, 96, 97, 128, 129, 200, 256, 257, 400, 512, 700, 1000, 1024, 1025, 4096, 16384):
+    for I in (1, 7, 16, 17, 32, 33, 48, 64, 65, 80, 96, 97, 128, 129, 200, 256, 257, 400, 512, 700, 1000, 1024, 1025, 4096, 16384, 17408):
         for J in (128, 256, 384, 1024, 4096, 5120, 6144, 8320, 9600, 12416, 14336, 14464, 16512, 19072, 27648, 28672, 55296):
             for R in (128, 1024, 4096, 14336, 27648):
                 for row_scales in (False, True):
@@ -41,7 +41,22 @@ def test_every_tile_is_chosen_somewhere_and_fits_its_kernel():
                         for part in ((split, J) if k == "split rows" else (I, split), rest):
                             sub = lp.plan(*part, R, row_scales, whole=False)[0]
                             assert sub != "strips" and not sub.startswith("split")
-    assert set(lp.tiles()) | {"strips", "small 128x128"} <= seen
+    assert set(lp.tiles()) | {"strips", "split rows 256x256", "split columns 256x256"} <= seen
+
+
+@pytest.mark.parametrize("M,N,K,within", [
+    # the tiles within 5 % of the fastest, weights from HBM or from the caches
+    (160, 16384, 1024, ("small deep 128x128", "small 128x128", "half 128x64")), (112, 16384, 1024, ("half 128x64",)),
+    (257, 16384, 1024, ("small 128x128", "wide 256x128")), (400, 4096, 4096, ("half 128x64", "panel 128x64")),
+    (400, 4096, 1024, ("half 128x64", "panel 128x64")), (1024, 2048, 2048, ("half 128x64", "panel 128x64")),
+    (600, 3072, 1024, ("half 128x64",)), (700, 7168, 5120, ("wide 256x128",)), (1024, 5120, 27648, ("wide 256x128",)),
+    (257, 28672, 4096, ("big 256x256", "small deep 128x128", "wide 256x128")), (350, 11008, 2048, ("wide 256x128", "small 128x128")),
+    (1, 1024, 5120, ("strips",)), (8, 8192, 2048, ("strips",)), (1, 5120, 2560, ("strips",)), (16, 2048, 2048, ("strips",)),
+])
+def test_shapes_that_a_rule_without_a_time_per_round_got_wrong(M, N, K, within):
+    """A cost of rounds x lines alone took a tile that was 5 to 37 % slower than another one (and than the kernels before
+    that rule); the strips' share of full passes and rounds alone, panels that were 5 to 20 % slower."""
+    assert lp.name(M, N, K) in within
 
 
 def test_part_of_a_split_problem_never_runs_strips():
