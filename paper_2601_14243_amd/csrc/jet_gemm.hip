@@ -624,7 +624,8 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 // that, the computing side alone 55-85 %; the weights without the activations 16.7 of 29 us (4096x14336, 128 rows).
 // Measured and left out: workgroups on idle CUs that pull the weights into the L2 ahead (32-row tiles of 4096x14336
 // 22.4 -> 18.1 us, elsewhere within 10 % either way), a wave that touches the XCD's weight lines a chunk ahead (its
-// burst holds up the barrier: 30 % slower).
+// burst holds up the barrier: 30 % slower), the workgroups of an XCD touching its activation lines once at the start (dealt
+// among those that share a row block, 2-5 % slower than without, 139 shapes of one to five row blocks; the first copies wait).
 // ------------------------------------------------------------------------
 template <int TM_, int TN_, int WR_, int WC_, int S_, int GP_ = 1>
 struct PanelCfg {
@@ -636,8 +637,8 @@ struct PanelCfg {
     static constexpr int kWPer = kWBlocks / kCopy, kAPer = kABlocks / kCopy, kPer = GP * (kWPer + kAPer);
     static constexpr int kGroupBytes = (BM + BN) * 128, kStage = GP * kGroupBytes;
     static constexpr int kChunk = 16, kSaBuf = BM * kChunk * 4, kSbBuf = 256;
-    static constexpr int kSaOff = S * kStage, kSbOff = kSaOff + 2 * kSaBuf, kSink = kSbOff + 2 * kSbBuf;
-    static constexpr int kLds = kSink + 256;
+    static constexpr int kSaOff = S * kStage, kSbOff = kSaOff + 2 * kSaBuf;
+    static constexpr int kLds = kSbOff + 2 * kSbBuf;
     static_assert(kWBlocks % kCopy == 0 && kABlocks % kCopy == 0, "");
     static_assert(S >= 3 && (S - 1) * kPer < 64 && BN <= 256 && kLds <= 160 * 1024 && kChunk % GP == 0, "");
 };
@@ -673,17 +674,6 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
     const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
     const int rb = id % row_blocks, panel = id / row_blocks;
     const int i0 = rb * C::BM, j0 = panel * C::BN;
-
-    // ---- L2 warm-up: the workgroups of an XCD touch one dword of every line of their activations once ----
-    {
-        const int per_xcd = ((int)gridDim.x + 7) >> 3, me = blockIdx.x >> 3;
-        const int lines = min(C::BM, I - i0) * G;
-        const uint32_t sink = __builtin_amdgcn_readfirstlane(lds0 + C::kSink);
-        for (int x = me * C::kThreads + t; x < lines; x += per_xcd * C::kThreads) {
-            const int row = x / G, g = x - row * G;
-            dma4(sink, reinterpret_cast<const float*>(A + (size_t)(i0 + row) * R + (size_t)g * kGroup));
-        }
-    }
 
     if (w >= C::kCompute + C::kCopy) {
         // ---------------- scale wave: chunks of 16 groups, two buffers ----------------
@@ -809,7 +799,6 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
             }
         }
     };
-    JET_WAIT_VMCNT(0);                                   // own warm-up loads
     step_barrier();                                      // step 0 has landed
     Operands even, odd;
     fetch(0, 0, even);
