@@ -23,6 +23,10 @@ from jet_testlib import check_gemm, check_model, dev, host_bits
 pytestmark = pytest.mark.gpu
 
 ONE = 0x38          # E4M3 code of 1.0
+# rows, groups, and the kernel that 1024 columns then run on (tests/test_launch_plan.py holds these to the rule): the skinny,
+# the panel and the tile kernel
+KERNEL_CASES = [(8, 16, "strips"), (8, 2, "panel 32x16"), (48, 2, "panel 32x16"), (200, 2, "panel 32x32"), (4096, 2, "small 128x128"),
+                (4096, 16, "small deep 128x128"), (8192, 16, "wide 256x128")]
 FIN = np.array([c for c in range(256) if c not in (0x7F, 0xFF)], np.uint8)
 
 
@@ -40,19 +44,19 @@ def _code(v):
     return c
 
 
-def residual_bits(jet, A, Bv):
+def residual_bits(jet, A, Bv, groups=2):
     """A u8 [T,128], Bv u8 [N,128] (N a multiple of 128): bf16 bits of p_gpu - p_model for the
-    pairs (A[t], Bv[t % N]), and the model's p."""
+    pairs (A[t], Bv[t % N]), and the model's p.  Groups beyond the second are zeros, which add nothing."""
     T, N = A.shape[0], Bv.shape[0]
     cols = np.arange(T) % N
     p = mm.group_product(A, Bv[cols])
-    qx = np.zeros((T, 256), np.uint8)
+    qx = np.zeros((T, 128 * groups), np.uint8)
     qx[:, :128], qx[:, 128] = A, ONE
-    qw = np.zeros((N, 256), np.uint8)
+    qw = np.zeros((N, 128 * groups), np.uint8)
     qw[:, :128], qw[:, 128] = Bv, ONE
-    sx = np.ones((T, 2), np.float32)
+    sx = np.ones((T, groups), np.float32)
     sx[:, 1] = -p
-    sw = np.ones((N // 128, 2), np.float32)
+    sw = np.ones((N // 128, groups), np.float32)
     y = host_bits(jet.fp8_linear_fwd(dev(qx), dev(sx), dev(qw), dev(sw)))
     return y[np.arange(T), cols], p
 
@@ -64,16 +68,16 @@ def _layer_groups(seed):
             "xT": g(orc.quant_act(x, row=False, col=True)["q_colT"]), "dyT": g(orc.quant_act(dy, row=False, col=True)["q_colT"])}
 
 
-@pytest.mark.parametrize("T", [8, 48, 200, 4096])      # skinny, panel and tile kernels
+@pytest.mark.parametrize("T,groups,kernel", KERNEL_CASES)
 @pytest.mark.parametrize("pair", [("x", "w"), ("dy", "w"), ("dyT", "xT")])
-def test_group_sums_of_layer_like_operands_equal_the_model(jet, pair, T):
+def test_group_sums_of_layer_like_operands_equal_the_model(jet, pair, T, groups, kernel):
     """Operands as the quantizers produce them (FProp, DGrad and WGrad pairings): the raw group
     sum of the hardware equals the model in every bit, in every kernel."""
     G = _layer_groups(900)
     rng = np.random.default_rng(T)
     A = G[pair[0]][rng.integers(0, len(G[pair[0]]), T)]
     Bv = G[pair[1]][rng.integers(0, len(G[pair[1]]), 1024)]
-    res, p = residual_bits(jet, A, Bv)
+    res, p = residual_bits(jet, A, Bv, groups)
     assert np.count_nonzero(p) > 0.99 * T
     assert not np.any(res & 0x7FFF), f"{np.count_nonzero(res & 0x7FFF)} of {T} group sums differ from the model"
 

@@ -4,6 +4,7 @@ import pytest
 
 import launch_plan as lp
 from test_gpu_gemm import FEW_ROW_CASES, RAGGED_CASES, TILE_CASES
+from test_gpu_mfma import KERNEL_CASES
 
 CASES = ([(M, N, K, label) for M, N, K, label in RAGGED_CASES] +
          [(M, N, 128 * g, label) for M, N, g, label in TILE_CASES + FEW_ROW_CASES])
@@ -12,6 +13,11 @@ CASES = ([(M, N, K, label) for M, N, K, label in RAGGED_CASES] +
 @pytest.mark.parametrize("M,N,K,label", CASES)
 def test_the_gpu_cases_run_what_their_labels_say(M, N, K, label):
     assert lp.name(M, N, K) == label.split(":")[0]
+
+
+@pytest.mark.parametrize("T,groups,kernel", KERNEL_CASES)
+def test_the_group_sum_cases_run_on_the_kernels_they_name(T, groups, kernel):
+    assert lp.name(T, 1024, 128 * groups) == kernel
 
 
 def test_every_tile_has_a_gpu_case():
