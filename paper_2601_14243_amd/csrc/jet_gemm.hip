@@ -495,7 +495,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
     constexpr int kSkRingBytes = kSkDepth * kUnit;
     constexpr int kSkRun = kPass / kSkWaves;                 // consecutive groups per wave per pass
     constexpr int kCopies = 2 + ABLK + 1;                    // vector-memory operations per unit
-    static_assert(kSkRun >= 1 && 4 <= kSkWaves && (kSkDepth - 1) * kCopies < 64, "");
+    static_assert(kSkRun >= 1 && 4 <= kSkWaves && kSkDepth <= 3, "the waits below are for at most two younger units");
     static_assert(ABLK >= 1 && ABLK <= 2, "");
     const int G = R / kGroup;
     const int j0 = blockIdx.x * 16;
@@ -556,10 +556,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
             switch (younger) {
                 case 0: JET_WAIT_VMCNT(0); break;
                 case 1: JET_WAIT_VMCNT(kCopies); break;
-                case 2: JET_WAIT_VMCNT(2 * kCopies); break;
-                case 3: JET_WAIT_VMCNT(3 * kCopies); break;
-                case 4: JET_WAIT_VMCNT(4 * kCopies); break;
-                default: JET_WAIT_VMCNT(5 * kCopies); break;
+                default: JET_WAIT_VMCNT(2 * kCopies); break;
             }
             asm volatile("" ::: "memory");
             const uint8_t* u = ring_p + (i % kSkDepth) * kUnit;
@@ -922,7 +919,7 @@ static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t
         if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
         else JET_SKINNY_AB(D, W, 2);           \
     } while (0)
-    if (strips > 256) JET_SKINNY(1, 8);              // two workgroups (16 waves) per CU
+    if (strips > (unsigned)compute_units()) JET_SKINNY(1, 8);    // two workgroups (16 waves) per CU
     else JET_SKINNY(3, 8);
 #undef JET_SKINNY
 #undef JET_SKINNY_AB
