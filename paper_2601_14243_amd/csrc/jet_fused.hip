@@ -78,7 +78,8 @@ __device__ __forceinline__ void unpack16(const uint16_t* p, float (&v)[16]) {
 // Same decomposition as the row quantizer: a team of 8 lanes owns a group, a lane 16
 // consecutive elements (2 x 32 B in, 16 B out).  gate and up share the row stride ld.
 // At memory speed for large calls ([16384, 14336]: 5.0 TB/s) once no value near a rounding tie went through binary64 (one
-// gate in a thousand, -3.046875, did, and with it most waves): [1000, 14336] 18.2 -> 15.7 us, [8, 14336] 4.2 -> 2.9.
+// gate in a thousand, -3.046875, did, and with it most waves): captured back to back, [1000, 14336] 16.6 -> 14.4 us,
+// [8, 14336] 4.1 -> 2.9.
 // ------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __restrict__ gate,
                                                              const uint16_t* __restrict__ up, long ld,

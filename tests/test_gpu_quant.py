@@ -261,8 +261,9 @@ def test_every_pair_of_bf16_value_and_group_maximum(jet):
     All 5.3e8 pairs (|x| <= amax) of finite bf16 magnitudes, every second one negative: each group
     holds one amax and 127 consecutive smaller magnitudes.  The row kernel sees the groups as rows;
     the tile kernel (dual mode) sees them as columns, and mixtures of them as rows.  Codes and scales
-    must equal the oracle's in every byte -- the divider (reciprocal, two corrections, IEEE fallback)
-    and the hardware convert are exercised on every operand pair the bf16 path can produce."""
+    must equal the oracle's in every byte -- the divider of bf16 values (reciprocal, one correction, IEEE
+    fallback) and the hardware convert are exercised on every operand pair the bf16 path can produce;
+    the two corrections of binary32 values run in the FP8-source tests."""
     per = G - 1
     amax_bits = np.arange(1, 0x7F80, dtype=np.int64)
     n_groups = (amax_bits + per - 1) // per
