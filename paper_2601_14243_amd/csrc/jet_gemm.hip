@@ -616,8 +616,8 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 // straight-line (a compare chain for the wait and a branch per copy cost 0.3 us per step), and the fetch stays in front
 // of the MFMAs by scheduling barriers.  Every output element takes the chain of the other kernels.
 // From HBM, against the strip kernel of 64x32 and 32x32 tiles and the 128x128 tiles before it (us): 4096x14336 77 rows
-// 30.5 -> 22.7, 128 rows 30.5 -> 27.1, 256 rows 59 -> 37; 28672x4096 32 rows 34 -> 29, 64 rows 47 -> 31; 6144x4096 128 rows
-// 23 -> 13.9; 5120x27648 64 rows 57 -> 46, 256 rows 152 -> 79; 55296x5120 64 rows 101 -> 65.  The copying side alone takes 90 % of
+// 27.8 -> 20.9, 128 rows 29.5 -> 24.8, 256 rows 54.9 -> 35.8; 28672x4096 32 rows 32.3 -> 27.3, 64 rows 45.6 -> 29.2; 6144x4096
+// 128 rows 22.2 -> 13.4; 5120x27648 64 rows 55.7 -> 44.0, 256 rows 146 -> 76; 55296x5120 64 rows 100 -> 58.  The copying side alone takes 90 % of
 // that, the computing side alone 55-85 %; the weights without the activations 16.7 of 29 us (4096x14336, 128 rows).
 // Measured and left out: workgroups on idle CUs that pull the weights into the L2 ahead (32-row tiles of 4096x14336
 // 22.4 -> 18.1 us, elsewhere within 10 % either way), a wave that touches the XCD's weight lines a chunk ahead (its

@@ -30,12 +30,12 @@ _lib = None
 def lib():
     global _lib
     if _lib is None:
-        d = tempfile.mkdtemp()
-        src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
-        with open(src, "w") as f:
-            f.write(SHIM)
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}", src, "-o", so], check=True)
-        _lib = ctypes.CDLL(so)
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
+            with open(src, "w") as f:
+                f.write(SHIM)
+            subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", f"-I{CSRC}", src, "-o", so], check=True)
+            _lib = ctypes.CDLL(so)
         _lib.jet_plan.argtypes = [ctypes.c_int] + [ctypes.c_long] * 4 + [ctypes.c_int, ctypes.POINTER(ctypes.c_long)]
     return _lib
 
