@@ -88,8 +88,8 @@ inline int pick_tile(long I, long J, long G, long cus, bool one_round, long& tim
 //    1.04), at 12 0.97-1.10, at 8 1.00-1.25.  With two per CU and from 9 rows on (both activation blocks are copied) up to 24
 //    groups: beyond, 0.88-0.96 from the caches and 1.05-1.07 from HBM.
 //  - up to 8 rows, at most one strip per CU, more passes: 0.85-1.00 from 36 of 64 groups on (1.03 for 256 strips from HBM).
-//  - the rest: passes x rounds full to 0.7 (0.9 from 9 rows on): 28672x4096, 1 row, 0.93; below, 55296x5120, 8 and 16 rows,
-//    1.30 and 1.45; 5120x27648, 1 row, 1.14; 14336x4096, 16 rows (0.875) 1.18.
+//  - the rest, from HBM: passes x rounds full to 0.7 (0.9 from 9 rows on): 28672x4096, 1 and 8 rows, 0.97 and 1.01 (16 rows
+//    1.11); below, 55296x5120, 8 and 16 rows, 1.30 and 1.46; 5120x27648, 1 row, 1.16; 14336x4096, 16 rows (0.875) 1.16.
 inline bool strips_pay(long I, long J, long G, long cus) {
     const bool few = I <= 8;
     const long strips = J / 16, places = strips <= cus ? strips : ceil_div(strips, cus) * cus;
