@@ -31,13 +31,21 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
 }
+// kNt: a line that is not needed again (streams_past_the_caches, jet_plan.h)
+template <bool kNt = false>
 __device__ __forceinline__ void dma16(uint32_t lds, const void* base, uint32_t voff) {
     lds = __builtin_amdgcn_readfirstlane(lds);
     base = uniform_ptr(base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds), "v"(voff), "s"(base)
-                 : "memory");
+    if constexpr (kNt)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds), "v"(voff), "s"(base)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds), "v"(voff), "s"(base)
+                     : "memory");
 }
 // same, LDS address = lds_base + IMM formed directly in M0 (one scalar instruction)
 template <int IMM>
@@ -487,7 +495,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
                                                                      const uint8_t* __restrict__ B,
                                                                      const float* __restrict__ sb,
                                                                      uint16_t* __restrict__ out, int I, int J,
-                                                                     int R) {
+                                                                     int R, bool nt) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = t >> 6, l = t & 63, r = l & 15, c4 = l >> 4;
@@ -533,8 +541,13 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
     auto issue = [&](int i) {
         const int g = seq(i);
         const uint32_t u = ring + (i % kSkDepth) * kUnit;
-        dma16(u, baseW + (size_t)g * kGroup, offW[0]);
-        dma16(u + 1024, baseW + (size_t)g * kGroup, offW[1]);
+        if (nt) {
+            dma16<true>(u, baseW + (size_t)g * kGroup, offW[0]);
+            dma16<true>(u + 1024, baseW + (size_t)g * kGroup, offW[1]);
+        } else {
+            dma16(u, baseW + (size_t)g * kGroup, offW[0]);
+            dma16(u + 1024, baseW + (size_t)g * kGroup, offW[1]);
+        }
         // (block b < ABLK always holds row 8 b < I, so every wave issues the same number of copies)
 #pragma unroll
         for (int b = 0; b < ABLK; ++b)
@@ -662,7 +675,7 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
                                                                   const uint8_t* __restrict__ B,
                                                                   const float* __restrict__ sb,
                                                                   uint16_t* __restrict__ out, int I, int J, int ldo, int R,
-                                                                  int row_blocks) {
+                                                                  int row_blocks, bool nt) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, r = l & 15, c4 = l >> 4;
@@ -711,35 +724,41 @@ __global__ __launch_bounds__(C::kThreads) void gemm_panel_kernel(const uint8_t* 
             offA[i] = (uint32_t)(min(i0 + 8 * (cw + C::kCopy * i) + (l >> 3), I - 1) - i0) * (uint32_t)R + lane_chunk;
         const uint32_t lds_c = __builtin_amdgcn_readfirstlane(lds0 + cw * 1024);
         uint32_t st = lds_c;
-        auto issue = [&](int q) {
-            size_t kb[C::GP];                            // past the end: the last group again
+        auto copy_steps = [&](auto nt_tag) {             // straight-line for either policy of the weights
+            constexpr bool kNt = decltype(nt_tag)::value;
+            auto issue = [&](int q) {
+                size_t kb[C::GP];                        // past the end: the last group again
 #pragma unroll
-            for (int h = 0; h < C::GP; ++h) kb[h] = (size_t)min(C::GP * q + h, G - 1) * kGroup;
-            // the groups of a row next to each other
+                for (int h = 0; h < C::GP; ++h) kb[h] = (size_t)min(C::GP * q + h, G - 1) * kGroup;
+                // the groups of a row next to each other
 #pragma unroll
-            for (int i = 0; i < C::kWPer; ++i)
+                for (int i = 0; i < C::kWPer; ++i)
 #pragma unroll
-                for (int h = 0; h < C::GP; ++h) dma16(st + h * C::kGroupBytes + i * (C::kCopy * 1024), baseW + kb[h], offW[i]);
+                    for (int h = 0; h < C::GP; ++h)
+                        dma16<kNt>(st + h * C::kGroupBytes + i * (C::kCopy * 1024), baseW + kb[h], offW[i]);
 #pragma unroll
-            for (int i = 0; i < C::kAPer; ++i)
+                for (int i = 0; i < C::kAPer; ++i)
 #pragma unroll
-                for (int h = 0; h < C::GP; ++h)
-                    dma16(st + h * C::kGroupBytes + C::BN * 128 + i * (C::kCopy * 1024), baseA + kb[h], offA[i]);
-            st = (st == lds_c + (C::S - 1) * C::kStage) ? lds_c : st + C::kStage;
+                    for (int h = 0; h < C::GP; ++h)
+                        dma16(st + h * C::kGroupBytes + C::BN * 128 + i * (C::kCopy * 1024), baseA + kb[h], offA[i]);
+                st = (st == lds_c + (C::S - 1) * C::kStage) ? lds_c : st + C::kStage;
+            };
+            for (int q = 0; q < C::S && q < P; ++q) issue(q);
+            wait_steps<C::kPer, C::S - 1>(min(P, C::S) - 1); // step 0
+            step_barrier();
+            int p = 0;
+            for (; p + C::S < P; ++p) {
+                JET_WAIT_VMCNT((C::S - 2) * C::kPer);        // step p + 1; younger: p + 2 .. p + S - 1
+                step_barrier();
+                issue(p + C::S);
+            }
+            for (; p < P; ++p) {
+                wait_steps<C::kPer, C::S - 1>(max(P - p - 2, 0));
+                step_barrier();
+            }
         };
-        for (int q = 0; q < C::S && q < P; ++q) issue(q);
-        wait_steps<C::kPer, C::S - 1>(min(P, C::S) - 1); // step 0
-        step_barrier();
-        int p = 0;
-        for (; p + C::S < P; ++p) {
-            JET_WAIT_VMCNT((C::S - 2) * C::kPer);        // step p + 1; younger: p + 2 .. p + S - 1
-            step_barrier();
-            issue(p + C::S);
-        }
-        for (; p < P; ++p) {
-            wait_steps<C::kPer, C::S - 1>(max(P - p - 2, 0));
-            step_barrier();
-        }
+        if (nt) copy_steps(std::true_type{});
+        else copy_steps(std::false_type{});
         JET_WAIT_VMCNT(0);   // nothing may be in flight towards the LDS when it is released
         return;
     }
@@ -884,7 +903,7 @@ static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t*
     const int rbs = (int)((I + C::BM - 1) / C::BM);
     const long panels = (J + C::BN - 1) / C::BN;
     hipLaunchKernelGGL((gemm_panel_kernel<C>), dim3((unsigned)(rbs * panels)), dim3(C::kThreads), C::kLds, st, A, sa, B,
-                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs);
+                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs, streams_past_the_caches(J, R));
     return hipGetLastError();
 }
 
@@ -910,9 +929,10 @@ static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t*
 static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
                                 long J, long R, hipStream_t st) {
     const unsigned strips = (unsigned)(J / 16);
+    const bool nt = streams_past_the_caches(J, R);
 #define JET_SKINNY_AB(D, W, AB)                                                                             \
     hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
-                       sa, B, sb, o, (int)I, (int)J, (int)R)
+                       sa, B, sb, o, (int)I, (int)J, (int)R, nt)
     // copy only the 8-row activation blocks that hold a row of the batch
 #define JET_SKINNY(D, W)                       \
     do {                                       \

@@ -14,6 +14,14 @@ namespace jet {
     X(1, 7, 5, 1, 3, 2, 509, 4238) X(2, 4, 3, 1, 3, 2, 361, 3734) X(2, 7, 3, 1, 5, 1, 559, 4527)   \
     X(2, 4, 4, 1, 5, 1, 380, 3826) X(2, 7, 4, 1, 4, 1, 577, 4805)
 
+// Decode kernels (strips, panels): whether the weights are read as lines that are not needed again (`nt`), which leaves the
+// 256 MB memory-side cache to the activations and lets more of the stream through: LDS copies from HBM on all CUs 5.5 -> 6.05
+// TB/s, on a quarter of them 2.75 -> 2.94.  From 16 MB on, where a model has several times the cache in such
+// matrices: a pass over four captured 8B-class layers, 1 row 258 -> 244 us, 32 rows 359 -> 339, 128 rows 394 -> 373.  Below, the
+// same within 0.5 % either way (1024x4096 to 4096x3072, 1 to 128 rows).  A matrix that would stay in the memory-side cache between
+// calls loses by it (one 28672x4096 matrix over and over, 32 rows: 20 -> 24 us); the activations always do and stay without.
+constexpr bool streams_past_the_caches(long J, long R) { return J * R >= (1L << 24); }
+
 enum GemmKernel {
     kStrips,         // skinny kernel, 16 columns per workgroup
     kPanel,          // panel kernel, entry `panel` of JET_PANELS

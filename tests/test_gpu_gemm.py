@@ -135,6 +135,15 @@ def test_forward_of_a_few_rows_on_both_sides_of_the_strip_rule(jet, M, N, groups
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {kernel}", operands=ops)
 
 
+@pytest.mark.parametrize("M,N,groups", [(1, 4096, 32), (11, 8192, 16), (8, 4224, 32), (19, 4224, 32), (35, 16512, 9),
+                                        (130, 4352, 31)])
+def test_forward_with_weights_read_past_the_caches(jet, M, N, groups):
+    """Strips and panels of matrices just above 16 MB, where the copies of the weights change their cache policy."""
+    assert 1 << 24 <= N * groups * 128 < 1.2 * (1 << 24)
+    y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=19 * M + N + groups)
+    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups, past the caches", operands=ops)
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 384, 512), (5, 256, 128), (130, 128, 640)])
 def test_dgrad(jet, M, N, K):
     dy, w = ji.grads(M, N, seed=M + 1), ji.weights(N, K, seed=M + 2)
