@@ -101,27 +101,38 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 // latency of the next step's first fragments hides under the last row of this step,
 // and every copy has about one whole step to land.
 //
-// LDS stage layout: [A tile BM*128][B tile BN*128][scales: 256 bytes per wave]
+// LDS: S stages [A tile BM*128][B tile BN*128], then two chunks of scales
 //   tile: 1 KB block per 8 rows, copied by one instruction that moves 8 whole 128-byte
 //         lines (8 consecutive lanes = one line); fragment f (rows 16f..16f+15) = blocks 2f,
 //         2f+1.  Row q (0..7) of a block keeps its eight 16-byte chunks at
 //         q*128 + 16*(c ^ swz), swz = (row>>1)&7, so the 16 lanes of an MFMA fragment read
 //         (rows 0..15, same chunk) hit 16 different 16-byte bank groups: measured 6.4
 //         cycles per ds_read_b128 (160 B/clk/CU) against 16.4 for a plain row-major tile
-//   scales: wave w's 256 B = [sa rows 32w..32w+31][sb of columns 32w..32w+31, clamped to the tile]
-// BM = 32 * waves, so every wave copies 4 A blocks and one scale line per step, and 4 B blocks
-// (BN = 32 * waves) or 2 (BN = 16 * waves, block scales only: the 256x128 tile).
+//   scales: a chunk holds four consecutive steps of the stream, copied at the top of every fourth step for the
+//         next four.  256 bytes per 16 rows as blocks of [4 rows][4 steps][4 rows]: a copy's lanes read four neighbouring scales of
+//         a row together, a row's scale of one step and the scales of four neighbouring columns are conflict-free reads.
+//         Copied a step at a time, every scale was a request of its own, as many as a third (block scales) or half (WGrad) of the
+//         operand lines': us, before -> in chunks: from HBM 1000x4096x14336 82 -> 74, 1024x5120x27648 247 -> 196,
+//         1024x5120x5120 53 -> 44, 256x55296x5120 100 -> 93; 16384x28672x4096 1738 -> 1685, 16384x4096x14336 838 -> 785;
+//         WGrad 28672x4096 over 16384 tokens 1990 -> 1922, 1024x4096 96 -> 92.  Eight steps long calls in one round lose 2 %
+//         (257x16384x1024 15.0 -> 15.3: the first chunk's addresses).  Measured and left out: one piece of a chunk per step (its
+//         address in the MFMA stream: 3-5 % slower where one wave runs per SIMD), all operand copies of a step behind its barrier
+//         (2-5 % slower on one round of tiles), waits that count the scale copies exactly (7 % slower with four stages).
+// BM = 32 * waves, so every wave copies 4 A blocks per step, and 4 B blocks (BN = 32 * waves) or 2 (BN = 16 * waves,
+// block scales only: the 256x128 and the 128x64 tile).
 // ------------------------------------------------------------------------
-template <int WI, int WJ, int TM, int TN, int S = 2>
+template <int SB_MODE, int WI, int WJ, int TM, int TN, int S = 2>
 struct TileCfg {
     static constexpr int kWaves = WI * WJ;
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int BM = WI * TM * 16, BN = WJ * TN * 16;
     static constexpr int kABytes = BM * 128, kBBytes = BN * 128;
     static constexpr int kBCopies = BN / (8 * kWaves);     // 1 KB blocks of the B tile per wave and step
-    static constexpr int kStageBytes = kABytes + kBBytes + kWaves * 256;   // + one 256-byte scale line per wave
+    static constexpr int kStageBytes = kABytes + kBBytes;
     static constexpr int kStages = S;                    // LDS stages: copies run kStages - 1 steps ahead
-    static constexpr int kLdsBytes = kStages * kStageBytes;
+    static constexpr int kScaleBytes = BM * 16 + (SB_MODE == kSbBlock ? 256 : BN * 16);   // one chunk of four steps
+    static constexpr int kScaleOff = kStages * kStageBytes;
+    static constexpr int kLdsBytes = kScaleOff + 2 * kScaleBytes;
     static constexpr int kOccupancy =                    // workgroups per CU: by waves and by LDS
         (512 / kThreads) < (160 * 1024 / kLdsBytes) ? (512 / kThreads) : (160 * 1024 / kLdsBytes);
     static_assert(S >= 2 && kLdsBytes <= 160 * 1024, "stages");
@@ -154,7 +165,7 @@ __global__ __launch_bounds__(64 * WI * WJ, 512 / (64 * WI * WJ))
 void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ sa,
                       const uint8_t* __restrict__ B, const float* __restrict__ sb,
                       uint16_t* __restrict__ out, int I, int ldo, int R, int tiles_i, int tiles_j) {
-    using C = TileCfg<WI, WJ, TM, TN, S>;
+    using C = TileCfg<SB_MODE, WI, WJ, TM, TN, S>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = t >> 6, l = t & 63, r = l & 15, c4 = l >> 4;
@@ -175,15 +186,10 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         j0 = (within / rows_in_band) * C::BN;
     };
 
-    // ---- copy cursor: the step whose operand tiles are being copied ----
-    // copy schedule of this wave: A blocks 4w..4w+3, B blocks 4w..4w+3, one scale line.
-    // Block c holds tile rows 32w + 8c .. + 7; lane l copies 16 bytes of row 32w + 8c + (l>>3):
-    // chunk (l&7) ^ swizzle(row), swizzle = (row>>1)&7 = (l>>4) | ((c&1)<<2).
-    struct Cursor {
-        const uint8_t *pa, *pb;         // operand tiles of the step: tile origin + 128 g (wave-uniform)
-        const float* gs;                // this lane's scale of the step
-        int k, g, rows;                 // tile in the list, group, valid A rows of the tile
-    };
+    // ---- operand copies: the cursor stands on the step whose tiles are being copied ----
+    // Wave w copies the A rows 32w .. 32w+31 and as many or half as many B rows.  Block c holds tile rows
+    // 32w + 8c .. + 7; lane l copies 16 bytes of row 32w + 8c + (l>>3): chunk (l&7) ^ swizzle(row),
+    // swizzle = (row>>1)&7 = (l>>4) | ((c&1)<<2).
     const uint32_t lane_row = 32 * w + (l >> 3);
     const uint32_t lane_chunk = 16 * ((l & 7) ^ (l >> 4));
     constexpr int kBC = C::kBCopies;
@@ -192,66 +198,112 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 #pragma unroll
     for (int i = 0; i < kBC; ++i)
         offB[i] = (8 * kBC * w + (l >> 3) + 8 * i) * (uint32_t)R + (lane_chunk ^ ((i & 1) * 64));
-    auto cursor_at_tile = [&](int k) {
-        int i0, j0;
-        tile_origin(k, i0, j0);
-        Cursor c;
-        c.pa = static_cast<const uint8_t*>(uniform_ptr(A + (size_t)i0 * R));
-        c.pb = static_cast<const uint8_t*>(uniform_ptr(B + (size_t)j0 * R));
-        c.k = k;
-        c.g = 0;
-        c.rows = I - i0;
-        if (l < 32) {
-            c.gs = sa + (size_t)min(i0 + 32 * w + l, I - 1) * G;
-        } else if (SB_MODE == kSbBlock) {
-            c.gs = sb + (size_t)((j0 + min(32 * w + (l - 32), C::BN - 1)) >> 7) * G;
-        } else {
-            c.gs = sb + (size_t)(j0 + 32 * w + (l - 32)) * G;
-        }
-        return c;
+    const uint8_t *pa, *pb;             // operand tiles of the cursor's step: tile origin + 128 g (wave-uniform)
+    int ck, cg, crows;                  // its tile in the list, group, valid A rows of the tile
+    auto cursor_at_tile = [&](int k, int i0, int j0) {
+        pa = static_cast<const uint8_t*>(uniform_ptr(A + (size_t)i0 * R));
+        pb = static_cast<const uint8_t*>(uniform_ptr(B + (size_t)j0 * R));
+        ck = k;
+        cg = 0;
+        crows = I - i0;
     };
-    // the step after c; past the end of the list the cursor stays on the last step (its
-    // tiles are then copied again into a stage nobody reads: harmless, and branch-free)
-    auto cursor_after = [&](const Cursor& c) {
-        Cursor n = c;
-        if (c.g + 1 < G) {
-            n.g = c.g + 1;
-            n.pa = c.pa + kGroup;
-            n.pb = c.pb + kGroup;
-            n.gs = c.gs + 1;
-        } else if (c.k + 1 < mine.count) {
-            n = cursor_at_tile(c.k + 1);
+    // past the end of the list the cursor stays on the last step (its tiles are then copied again into a stage
+    // nobody reads: harmless, and branch-free)
+    auto cursor_next = [&]() {
+        if (cg + 1 < G) {
+            ++cg;
+            pa += kGroup;
+            pb += kGroup;
+        } else if (ck + 1 < mine.count) {
+            int i0, j0;
+            tile_origin(ck + 1, i0, j0);
+            cursor_at_tile(ck + 1, i0, j0);
         }
-        return n;
     };
     const uint32_t ldsw = __builtin_amdgcn_readfirstlane(lds0 + 4 * w * 1024);
     const uint32_t ldsb = __builtin_amdgcn_readfirstlane(lds0 + C::kABytes + kBC * w * 1024);
-    const uint32_t ldss = __builtin_amdgcn_readfirstlane(lds0 + C::kABytes + C::kBBytes + w * 256);
-    constexpr int kCopies = 4 + kBC + 1;
-    // copy i of step c into the stage at LDS offset st: 4 A blocks, kBC B blocks, the scale line
-    auto copy_one = [&](const Cursor& c, int i, uint32_t st) {
+    constexpr int kCopies = 4 + kBC;
+    // copy i of the cursor's step into the stage at LDS offset st: 4 A blocks, kBC B blocks
+    auto copy_one = [&](const uint8_t* pa, const uint8_t* pb, int crows, int i, uint32_t st) {
         const uint32_t base = ldsw + st;
         if (i < 4) {
             // rows past the end of A repeat the last valid one (their outputs are never stored)
-            const uint32_t row = min(lane_row + 8 * i, (uint32_t)(c.rows - 1));
+            const uint32_t row = min(lane_row + 8 * i, (uint32_t)(crows - 1));
             const uint32_t off = __umul24(row, (uint32_t)R) + (lane_chunk ^ ((i & 1) * 64));
             switch (i) {
-                case 0: dma16_at<0>(base, c.pa, off); break;
-                case 1: dma16_at<1024>(base, c.pa, off); break;
-                case 2: dma16_at<2048>(base, c.pa, off); break;
-                default: dma16_at<3072>(base, c.pa, off); break;
-            }
-        } else if (i < 4 + kBC) {
-            const uint32_t bbase = ldsb + st;
-            switch (i - 4) {
-                case 0: dma16_at<0>(bbase, c.pb, offB[0]); break;
-                case 1: dma16_at<1024>(bbase, c.pb, offB[1]); break;
-                case 2: dma16_at<2048>(bbase, c.pb, offB[kBC > 2 ? 2 : 0]); break;
-                default: dma16_at<3072>(bbase, c.pb, offB[kBC > 2 ? 3 : 0]); break;
+                case 0: dma16_at<0>(base, pa, off); break;
+                case 1: dma16_at<1024>(base, pa, off); break;
+                case 2: dma16_at<2048>(base, pa, off); break;
+                default: dma16_at<3072>(base, pa, off); break;
             }
         } else {
-            dma4(ldss + st, c.gs);
+            const uint32_t bbase = ldsb + st;
+            switch (i - 4) {
+                case 0: dma16_at<0>(bbase, pb, offB[0]); break;
+                case 1: dma16_at<1024>(bbase, pb, offB[1]); break;
+                case 2: dma16_at<2048>(bbase, pb, offB[kBC > 2 ? 2 : 0]); break;
+                default: dma16_at<3072>(bbase, pb, offB[kBC > 2 ? 3 : 0]); break;
+            }
         }
+    };
+
+    // ---- scale copies: chunks of four consecutive steps of the stream ----
+    // Wave w copies the scales of the A rows 32w .. 32w+31, and of as many columns or (every wave the same ones to the same
+    // place) the tile's block scales.  Lane l serves step (l >> 2) & 3 of the chunk, which may belong to another tile
+    // than its neighbours' steps, of row 4 (l >> 4) + (l & 3) of each 16.
+    constexpr int kScaleCopies = SB_MODE == kSbBlock ? 3 : 4;
+    const int lstep = (l >> 2) & 3, lrow = 4 * (l >> 4) + (l & 3);
+    const float* gs[kScaleCopies];
+    int sk, chunk_g;                    // tile and group of the chunk's first step
+    auto scales_in_tile = [&](int i0, int j0) {          // all four steps in the tile at i0, j0
+        const float* a0 = static_cast<const float*>(uniform_ptr(sa + (size_t)i0 * G + chunk_g));
+        const float* b0 = static_cast<const float*>(uniform_ptr(sb + (size_t)(SB_MODE == kSbBlock ? j0 >> 7 : j0) * G + chunk_g));
+        const int row = 32 * w + lrow, last = I - 1 - i0;
+        gs[0] = a0 + (__umul24(min(row, last), G) + lstep);
+        gs[1] = a0 + (__umul24(min(row + 16, last), G) + lstep);
+        if (SB_MODE == kSbBlock) {
+            gs[2] = b0 + (__umul24(min(lrow, (C::BN + 127) / 128 - 1), G) + lstep);
+        } else {
+            gs[2] = b0 + (__umul24(row, G) + lstep);
+            gs[kScaleCopies - 1] = b0 + (__umul24(row + 16, G) + lstep);
+        }
+    };
+    auto scales_across_tiles = [&]() {                   // this lane's step may belong to a later tile than the chunk's first
+        const int dk = (chunk_g + lstep) / G, g = chunk_g + lstep - dk * G, row = 32 * w + lrow;
+        int i0, j0;
+        tile_origin(min(sk + dk, mine.count - 1), i0, j0);   // past the end of the list: steps nobody computes
+        gs[0] = sa + (size_t)min(i0 + row, I - 1) * G + g;
+        gs[1] = sa + (size_t)min(i0 + row + 16, I - 1) * G + g;
+        if (SB_MODE == kSbBlock) {
+            gs[2] = sb + (size_t)((j0 >> 7) + min(lrow, (C::BN + 127) / 128 - 1)) * G + g;
+        } else {
+            gs[2] = sb + (size_t)(j0 + row) * G + g;
+            gs[kScaleCopies - 1] = sb + (size_t)(j0 + row + 16) * G + g;
+        }
+    };
+    auto scales_next = [&]() {
+        chunk_g += 4;
+        if (chunk_g + 4 <= G) {         // both chunks inside one tile
+#pragma unroll
+            for (int i = 0; i < kScaleCopies; ++i) gs[i] += 4;
+            return;
+        }
+        while (chunk_g >= G) { chunk_g -= G; ++sk; }
+        if (chunk_g + 4 <= G) {
+            int i0, j0;
+            tile_origin(min(sk, mine.count - 1), i0, j0);
+            scales_in_tile(i0, j0);
+        } else {
+            scales_across_tiles();
+        }
+    };
+    const uint32_t ldss = __builtin_amdgcn_readfirstlane(lds0 + C::kScaleOff + 32 * w * 16);
+    const uint32_t ldst = __builtin_amdgcn_readfirstlane(lds0 + C::kScaleOff + C::BM * 16 + (SB_MODE == kSbBlock ? 0 : 32 * w * 16));
+    auto copy_scales = [&](uint32_t buf) {
+        dma4(ldss + buf, gs[0]);
+        dma4(ldss + buf + 256, gs[1]);
+        dma4(ldst + buf, gs[2]);
+        if (SB_MODE != kSbBlock) dma4(ldst + buf + 256, gs[kScaleCopies - 1]);
     };
 
     // ---- fragment addressing ----
@@ -269,32 +321,24 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         return load_frag(p + frag_lo, p + frag_hi);
     };
     // scales of a step as the lane needs them: sa of its row in each of the TM row tiles and
-    // the scale(s) of its columns
+    // the scale(s) of its columns; off: chunk buffer of the step + 16 * (step & 3)
     // (the per-column scales of WGrad are fetched at the top of the step instead: the
     // first fma needs them two MFMAs later, and there are no registers to hold them early)
     struct RawScales {
         float a[TM];
         float b_block;
     };
-    auto load_scales = [&](int slot, RawScales& s) {
-        const uint8_t* sc = smem + slot * C::kStageBytes + C::kABytes + C::kBBytes;
+    const uint8_t* const sc_rows = smem + C::kScaleOff + wi * TM * 256 + (r >> 2) * 64 + (r & 3) * 4;
+    const uint8_t* const sc_cols = smem + C::kScaleOff + C::BM * 16 + wj * TN * 256 + c4 * 64;
+    const uint8_t* const sc_block = smem + C::kScaleOff + C::BM * 16 + ((wj * TN * 16) >> 7) * 4;   // one 128-wide block
+    auto load_scales = [&](int off, RawScales& s) {
 #pragma unroll
-        for (int m = 0; m < TM; ++m) {
-            const int ii = (wi * TM + m) * 16 + r;
-            s.a[m] = *reinterpret_cast<const float*>(sc + (ii >> 5) * 256 + (ii & 31) * 4);
-        }
-        if (SB_MODE == kSbBlock) {
-            const int jj = wj * TN * 16;   // the wave's columns share one 128-wide block
-            s.b_block = *reinterpret_cast<const float*>(sc + (jj >> 5) * 256 + 128 + (jj & 31) * 4);
-        }
+        for (int m = 0; m < TM; ++m) s.a[m] = *reinterpret_cast<const float*>(sc_rows + off + m * 256);
+        if (SB_MODE == kSbBlock) s.b_block = *reinterpret_cast<const float*>(sc_block + off);
     };
-    auto load_col_scales = [&](int slot, v4f (&s)[TN]) {
-        const uint8_t* sc = smem + slot * C::kStageBytes + C::kABytes + C::kBBytes;
+    auto load_col_scales = [&](int off, v4f (&s)[TN]) {
 #pragma unroll
-        for (int n = 0; n < TN; ++n) {
-            const int jj = (wj * TN + n) * 16 + 4 * c4;
-            s[n] = *reinterpret_cast<const v4f*>(sc + (jj >> 5) * 256 + 128 + (jj & 31) * 4);
-        }
+        for (int n = 0; n < TN; ++n) s[n] = *reinterpret_cast<const v4f*>(sc_cols + off + n * 256);
     };
 
     constexpr int kTiles = TM * TN, kLag = 2;
@@ -304,20 +348,31 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     constexpr bool kFmaFirst = (SB_MODE != kSbBlock);
     constexpr int kRing = kFmaFirst ? 2 : 3;
     constexpr int kSync = (TM - 1) * TN;                 // first tile of the last row
-    constexpr int kLate = kTiles + kLag - 1 - kSync;     // copies issued after the barrier of a step
+    constexpr int kLate = kTiles + kLag - 1 - kSync;     // operand copies issued behind the barrier, the rest at the top of the next step
     static_assert(kLate >= 1 && kLate <= kCopies && kCopies - kLate <= kSync, "copy slots");
 
-    // ---- prologue: step 0 into stage 0, first copies of step 1, fragments of step 0 ----
-    // steps 0 .. S-2 whole, the first copies of step S-1; then wait for step 0 only
-    Cursor cur = cursor_at_tile(0);
+    // Vector-memory operations of a wave in step j, in their order: at the top of every fourth step the scales of chunk
+    // j / 4 + 1, the rest of the operand copies of step j + S - 1, behind the barrier the first kLate operand copies of step
+    // j + S, behind a tile's last step its stores.  The scales of chunk c (steps 4c .. 4c + 3) are first read behind
+    // the barrier of step 4c - 1, which waits for the operands of step 4c, whose last copies are issued in step
+    // 4c + 1 - S >= 4c - 3, behind the scales.  Their buffer held chunk c - 2, last read in step 4c - 5.
+    constexpr int kYounger = (S - 2) * kCopies;      // at the barrier of step q, behind the copies of step q + 1 (at least)
+    // ---- prologue: chunk 0, operands of steps 0 .. S - 1 (of the last the first kLate) ----
+    int first_i0, first_j0;
+    tile_origin(0, first_i0, first_j0);
+    cursor_at_tile(0, first_i0, first_j0);
 #pragma unroll
-    for (int s = 0; s + 1 < S; ++s) {
+    for (int s = 0; s < S; ++s) {
+        if (s) cursor_next();
 #pragma unroll
-        for (int i = 0; i < kCopies; ++i) copy_one(cur, i, (uint32_t)(s * C::kStageBytes));
-        cur = cursor_after(cur);
+        for (int i = 0; i < (s + 1 < S ? kCopies : kLate); ++i) copy_one(pa, pb, crows, i, (uint32_t)(s * C::kStageBytes));
+        if (s == 0) {
+            sk = chunk_g = 0;
+            if (G >= 4) scales_in_tile(first_i0, first_j0);
+            else scales_across_tiles();
+            copy_scales(0);
+        }
     }
-#pragma unroll
-    for (int i = 0; i < kLate; ++i) copy_one(cur, i, (uint32_t)((S - 1) * C::kStageBytes));
     JET_WAIT_VMCNT((S - 2) * kCopies + kLate);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -340,13 +395,23 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // `cur` is the cursor of step q+S-1 at the top of step q (its first copies are already issued)
+    int sc_off = 0;                     // where the scales of step q are, from the first buffer
     for (int q = 0, k = 0, g = 0; q < n_steps; ++q) {
         const int slot = ((S & (S - 1)) == 0) ? (q & (S - 1)) : (q % S);
-        const int nslot = (slot + 1 == S) ? 0 : slot + 1, oslot = (slot == 0) ? S - 1 : slot - 1;   // steps q+1, q+S-1
-        const Cursor after = cursor_after(cur);     // step q+S (all control flow of a step is here)
+        const int nslot = (slot + 1 == S) ? 0 : slot + 1;
+        const int oslot = (slot == 0) ? S - 1 : slot - 1;   // of step q+S-1
         const uint32_t st_this = __builtin_amdgcn_readfirstlane(slot * C::kStageBytes);
         const uint32_t st_other = __builtin_amdgcn_readfirstlane(oslot * C::kStageBytes);
+        // all control flow of a step is here
+        if ((q & 3) == 0 && q + 4 < n_steps) {
+            scales_next();
+            copy_scales((q & 4) ? 0 : C::kScaleBytes);
+        }
+        const uint8_t *pa0 = pa, *pb0 = pb;         // the rest of step q + S - 1 is copied first
+        const int crows0 = crows;
+        cursor_next();                              // step q + S
+        int sc_next = sc_off + 16;
+        if ((q & 3) == 3) sc_next = (q & 4) ? 0 : C::kScaleBytes;
 
         // ---- one straight-line block from here to the end of the tile loop ----
         // scales of this step: s = sa * sb, one binary32 product per (row, column scale)
@@ -354,7 +419,7 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         v4f sbj[TN];
 #pragma unroll
         for (int m = 0; m < TM; ++m) sai[m] = sai_n[m];
-        if (SB_MODE != kSbBlock) load_col_scales(slot, sbj);
+        if (SB_MODE != kSbBlock) load_col_scales(sc_off, sbj);
 
         v4f pr[kRing];
 #pragma unroll
@@ -385,12 +450,11 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
             if (t == kSync) {
                 // every read of stage `slot` has returned (the MFMA above needed the last one);
                 // of this wave's copies only those of steps q+2 .. q+S-1 may still be on their way
-                JET_WAIT_VMCNT((S - 2) * kCopies);
+                JET_WAIT_VMCNT(kYounger);
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                cur = after;                          // step q+S goes into stage `slot`
                 xf[TM & 1] = row_frag(nslot, 0);      // TM even: the buffer the last row does not use
-                load_scales(nslot, next);
+                load_scales(sc_next, next);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (t == kTiles - 1) {
@@ -404,13 +468,14 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (t > kSync) {
-                copy_one(cur, t - kSync - 1, st_this);   // copies 0 .. kLate-1 of step q+S
+                copy_one(pa, pb, crows, t - kSync - 1, st_this);          // step q+S goes into stage `slot`
                 __builtin_amdgcn_sched_barrier(0);
             } else if (t < kCopies - kLate) {
-                copy_one(cur, kLate + t, st_other);   // remaining copies of step q+S-1
+                copy_one(pa0, pb0, crows0, kLate + t, st_other);          // remaining copies of step q+S-1
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        sc_off = sc_next;
         if (++g < G) continue;
         g = 0;
 
@@ -879,11 +944,6 @@ static hipError_t allow_lds(K kernel, int bytes) {
 #define JET_SMALL 2, 2, 4, 4
 #define JET_SMALL_DEEP 2, 2, 4, 4, 4   /* four stages, one workgroup per CU: copies three steps ahead */
 #define JET_HALF 4, 1, 2, 4, 4         /* 128x64 tile, 4 waves of 32x64, four stages */
-using BigCfg = TileCfg<JET_BIG>;
-using WideCfg = TileCfg<JET_WIDE>;
-using SmallCfg = TileCfg<JET_SMALL>;
-using SmallDeepCfg = TileCfg<JET_SMALL_DEEP>;
-using HalfCfg = TileCfg<JET_HALF>;
 
 // compute units of the current device (256 on MI355X), asked once per process
 static int compute_units() {
@@ -917,7 +977,7 @@ static_assert(std::size(kPanelLaunches) == kNumPanels, "the panels come first in
 template <int SB_MODE, int... Cfg>
 static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
                                long J, long R, long ldo, hipStream_t st) {
-    using C = TileCfg<Cfg...>;
+    using C = TileCfg<SB_MODE, Cfg...>;
     const long ti = (I + C::BM - 1) / C::BM, tj = J / C::BN;
     const long wgs = std::min<long>(ti * tj, (long)compute_units() * C::kOccupancy);
     hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, Cfg...>), dim3((unsigned)wgs), dim3(C::kThreads), C::kLdsBytes, st, A,
@@ -989,14 +1049,20 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        hipError_t e = allow_lds(gemm_tile_kernel<kSbBlock, JET_BIG>, BigCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_BIG>, BigCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_WIDE>, WideCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_HALF>, HalfCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL>, SmallCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL>, SmallCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbBlock, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
-        if (e == hipSuccess) e = allow_lds(gemm_tile_kernel<kSbRow, JET_SMALL_DEEP>, SmallDeepCfg::kLdsBytes);
+        hipError_t e = hipSuccess;
+        auto allow_tiles = [&](auto kernel, int bytes) {
+            if (e == hipSuccess) e = allow_lds(kernel, bytes);
+        };
+#define JET_TILE_ATTR(MODE, ...) allow_tiles(gemm_tile_kernel<MODE, __VA_ARGS__>, TileCfg<MODE, __VA_ARGS__>::kLdsBytes)
+        JET_TILE_ATTR(kSbBlock, JET_BIG);
+        JET_TILE_ATTR(kSbRow, JET_BIG);
+        JET_TILE_ATTR(kSbBlock, JET_WIDE);
+        JET_TILE_ATTR(kSbBlock, JET_HALF);
+        JET_TILE_ATTR(kSbBlock, JET_SMALL);
+        JET_TILE_ATTR(kSbRow, JET_SMALL);
+        JET_TILE_ATTR(kSbBlock, JET_SMALL_DEEP);
+        JET_TILE_ATTR(kSbRow, JET_SMALL_DEEP);
+#undef JET_TILE_ATTR
 #define JET_SK_ATTR(D, W, AB) \
     if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, AB>, sk_lds_bytes(D, W))
         JET_SK_ATTR(3, 8, 1); JET_SK_ATTR(3, 8, 2);

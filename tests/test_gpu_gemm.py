@@ -6,7 +6,7 @@ import torch
 
 import jet_inputs as ji
 import oracle as orc
-from jet_testlib import check_gemm, dev, dev_bf16, host, host_bits
+from jet_testlib import check_gemm, check_model, dev, dev_bf16, host, host_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -235,6 +235,38 @@ def test_wgrad_with_the_last_round_split_off(jet, N, K):
     dw = jet.fp8_linear_wgrad(dev(qd["q_colT"]), dev(qd["s_colT"]), dev(qx["q_colT"]), dev(qx["s_colT"]))
     assert tuple(dw.shape) == (N, K)
     check_gemm(host_bits(dw), ref, f"wgrad split {M}x{N}x{K}",
+               operands=(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], True))
+
+
+@pytest.mark.parametrize("M,N,groups,what", [
+    (4400, 8192, 3, "256x256, chunks across tiles"),
+    (4400, 8192, 5, "256x256, chunks across tiles"), (16500, 1152, 7, "128x128, two workgroups per CU"),
+    (9000, 1024, 9, "256x256, one tile per workgroup"),
+])
+def test_scale_chunks_of_reductions_that_four_does_not_divide(jet, M, N, groups, what):
+    """The tile kernel copies the scales of four steps at a time, whatever tiles the steps belong to: workgroups with several
+    tiles, and reductions where a chunk ends inside the next tile."""
+    y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=23 * M + N + groups)
+    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {what}", operands=ops)
+
+
+def test_scale_chunks_of_a_tile_per_step(jet):
+    """One group: every step is another tile.  Against the matrix-core model, bit for bit, alone: one instruction deviates by
+    up to 2^-13 of sum|a b| (the worst seen, mfma_model), which is the two bf16 ulps that check_gemm allows at its
+    |acc| = 2^-6 sum|a b|, and 36 million elements of a single group reach it."""
+    M, N = 4400, 8192
+    y, _, ops = _fwd_case(jet, M, N, 128, seed=23 * M + N + 1)
+    check_model(y, ops, f"fwd {M}x{N}, one group")
+
+
+@pytest.mark.parametrize("M,N,K", [(384, 16384, 2304), (640, 2304, 8192), (896, 8192, 1152), (128, 8192, 2304)])
+def test_wgrad_scale_chunks_of_reductions_that_four_does_not_divide(jet, M, N, K):
+    dy, x = ji.grads(M, N, seed=95), ji.activations(M, K, seed=96)
+    qd = orc.quant_act(dy, row=False, col=True)
+    qx = orc.quant_act(x, row=False, col=True)
+    ref = orc.gemm(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], sb_mode=orc.SB_ROW)
+    dw = jet.fp8_linear_wgrad(dev(qd["q_colT"]), dev(qd["s_colT"]), dev(qx["q_colT"]), dev(qx["s_colT"]))
+    check_gemm(host_bits(dw), ref, f"wgrad {M}x{N}x{K}",
                operands=(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], True))
 
 
