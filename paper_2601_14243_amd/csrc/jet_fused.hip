@@ -62,9 +62,10 @@ __device__ __forceinline__ void quantize_store(float (&v)[16], uint8_t* q16, flo
     if (leader) *s1 = gs.S;
 }
 
+template <bool kNt = false>
 __device__ __forceinline__ void unpack16(const uint16_t* p, float (&v)[16]) {
     const uint4* p4 = reinterpret_cast<const uint4*>(p);
-    const uint4 u0 = p4[0], u1 = p4[1];
+    const uint4 u0 = kNt ? load16_nt(p4) : p4[0], u1 = kNt ? load16_nt(p4 + 1) : p4[1];
     const uint32_t w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -81,6 +82,7 @@ __device__ __forceinline__ void unpack16(const uint16_t* p, float (&v)[16]) {
 // gate in a thousand, -3.046875, did, and with it most waves): captured back to back, [1000, 14336] 16.6 -> 14.4 us,
 // [8, 14336] 4.1 -> 2.9.
 // ------------------------------------------------------------------------
+template <bool kNt>
 __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __restrict__ gate,
                                                              const uint16_t* __restrict__ up, long ld,
                                                              int groups_per_row, long n_groups,
@@ -91,8 +93,8 @@ __global__ __launch_bounds__(256) void silu_mul_quant_kernel(const uint16_t* __r
         const long m = g / groups_per_row;
         const long src = m * ld + (g - m * groups_per_row) * kGroup + l8 * 16;
         float a[16], u[16], gmax = 0.0f;
-        unpack16(gate + src, a);
-        unpack16(up + src, u);
+        unpack16<kNt>(gate + src, a);
+        unpack16<kNt>(up + src, u);
 #pragma unroll
         for (int i = 0; i < 16; ++i) gmax = fmaxf(gmax, fabsf(a[i]));
         uint32_t act[8];
@@ -356,7 +358,11 @@ hipError_t launch_silu_mul_quant(const void* gate, const void* up, long ld, long
                                  float* s, hipStream_t st) {
     const long n_groups = M * (K / kGroup);
     const long blocks = std::min<long>((n_groups + 31) / 32, 256L * 64);
-    hipLaunchKernelGGL(silu_mul_quant_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
+    // An input larger than the 256 MB memory-side cache is not in it any more when it is read, and reading it past that cache
+    // leaves the codes there for the down projection: [16384, 14336] 230 -> 221 us, with that GEMM 1067 -> 1041, [8192, 14336]
+    // 520 -> 510.  Smaller inputs, which the gate/up GEMM has just written, lose by it (1000 rows with the GEMM 92.7 -> 94.5).
+    const auto kernel = 4 * M * K > (256L << 20) ? silu_mul_quant_kernel<true> : silu_mul_quant_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st,
                        static_cast<const uint16_t*>(gate), static_cast<const uint16_t*>(up), ld,
                        (int)(K / kGroup), n_groups, q, s);
     return hipGetLastError();

@@ -40,6 +40,16 @@ __device__ __forceinline__ uint32_t bf16_pack2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// Loads of lines that are not needed again: they leave the 256 MB memory-side cache to what is.
+__device__ __forceinline__ uint4 load16_nt(const void* p) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(static_cast<const u32x4*>(p)));
+}
+__device__ __forceinline__ uint2 load8_nt(const void* p) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint2, __builtin_nontemporal_load(static_cast<const u32x2*>(p)));
+}
+
 // ------------------------------------------------------------- quantizer --
 
 // Scale of a group and the data needed to divide by it.

@@ -71,6 +71,11 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const void* __restrict__
 // Before that, with a branch per element and conflicts on the maxima in LDS, the kernel was bound by its
 // instructions.  [16384, 4096]: row + column 59 -> 49.5 us, column from FP8 30 -> 25; [128, 4096]: 8.9 -> 5.0 and
 // 5.5 -> 4.3; a weight with its transposed copy [128, 4096] 5.2 -> 3.5, 14 matrices of two 8B layers 399 -> 377.
+// The source is read past the memory-side cache (gradients, FP8-saved activations and master weights are not read
+// again soon), so that what is written stays in it: row + column [16384, 1024] 17.4 -> 15.0 us, column from FP8 [16384, 14336]
+// 132 -> 123, a weight [4096, 4096] 11.9 -> 10.6, with its transposed copy 15.0 -> 13.5.  Stores past it as well would
+// gain 3-8 % more here and cost the GEMM that reads the codes next as much or more (weight [14336, 4096] and the FProp of 32
+// rows behind it 51 -> 55 us); the row quantizer, whose source the operator before has just written, gains nothing.
 // ------------------------------------------------------------------------
 
 // broadcast of lane N of every 16-lane row
@@ -149,13 +154,13 @@ __global__ __launch_bounds__(256) void quant_tile_kernel(const void* __restrict_
     for (int p = 0; p < 8; ++p) {
         const long row = m0 + 8 * rr + p;
         if (SRC == JET_SRC_BF16) {
-            const uint4 u = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + row * K + k0 + 8 * cc);
+            const uint4 u = load16_nt(static_cast<const uint16_t*>(x) + row * K + k0 + 8 * cc);
             v[p][0] = bf16_lo(u.x); v[p][1] = bf16_hi(u.x);
             v[p][2] = bf16_lo(u.y); v[p][3] = bf16_hi(u.y);
             v[p][4] = bf16_lo(u.z); v[p][5] = bf16_hi(u.z);
             v[p][6] = bf16_lo(u.w); v[p][7] = bf16_hi(u.w);
         } else {
-            const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint8_t*>(x) + row * K + k0 + 8 * cc);
+            const uint2 u = load8_nt(static_cast<const uint8_t*>(x) + row * K + k0 + 8 * cc);
             const float sc = xs[row * GK + blockIdx.x];
             e4m3_unpack4(u.x, v[p][0], v[p][1], v[p][2], v[p][3]);
             e4m3_unpack4(u.y, v[p][4], v[p][5], v[p][6], v[p][7]);
