@@ -532,23 +532,35 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 
 // ------------------------------------------------------------------------
 // Skinny kernel for I <= 16 (decode): bound by streaming B (the weights) once.
-// A workgroup of kSkWaves waves owns 16 output columns and the whole reduction.  The
-// groups of a pass (32 groups) are dealt to the waves in runs of consecutive
-// groups; every wave streams its own units (16 weight rows + the 16 or 32 activation
-// rows + scales of one group) through a private LDS ring with kSkDepth units in flight,
+// A workgroup of kWaves waves owns 16 output columns and the whole reduction.  The
+// groups of a pass (32 groups) are dealt to the waves in runs of four consecutive
+// groups, those of a last, partial pass evenly; every wave streams its own units (16 weight rows + the rows of the batch's
+// 8-row blocks of one group) through a private LDS ring with kDepth units in flight, and the scales of a run at once,
 // using the same whole-line LDS-DMA and swizzled fragment layout as the tile kernel --
 // no barrier is needed for the ring.  After every pass the p_g and s_g meet in LDS and
-// four waves per row tile run the ordered fma chain for their quarter of the outputs.
+// four waves run the ordered fma chain for their quarter of the outputs.
+// A CU has about 320 lines in flight, and every 4-byte scale fetched on its own costs one: with the scales of four groups in one
+// copy, partial passes dealt evenly and (up to 8 rows, more than one round of strips) a second unit in flight per wave,
+// for which only the batch's rows of a group meet in the LDS, from HBM, us, before -> now: 28672x4096 1 row 25.1 -> 22.3, 8 rows
+// 25.9 -> 22.6; 14336x4096 1 row 14.5 -> 13.6; 4096x14336 1 row 14.7 -> 14.3; 6144x2048 1 row 6.4 -> 5.6; 4096x4096 16 rows
+// 7.1 -> 6.7; 1024x4096 1 row 5.4 -> 5.1.  With two units in flight where all strips are resident, 8 rows of 6144x4096 take 8.5
+// instead of 7.9.
 // ------------------------------------------------------------------------
-constexpr int kSkUnit = 2048 + 2048 + 256;        // weight fragment, activation fragment, scales
-constexpr int kSkGroupBytes = 4 * 64 * 4 + 64 * 4;  // p[4][64] + s[64]
 constexpr int kSkPass = kStripPass;               // groups chained per pass
-constexpr int sk_lds_bytes(int depth, int waves) { return waves * depth * kSkUnit + kSkPass * kSkGroupBytes; }
+template <int kDepth, int kWaves, int ABLK>
+struct SkinnyCfg {
+    // rows of the output that meet in the LDS: all 16, or with two units in flight and two workgroups per CU those of the block
+    static constexpr int kRows = kDepth == 2 ? 8 * ABLK : 16;
+    static constexpr int kUnit = 2048 + 1024 * ABLK;                 // weight fragment, activation fragment of a group
+    static constexpr int kScales = 256 * ABLK;                       // scales of a run of four groups: [row][4], then the block's
+    static constexpr int kRing = kDepth * kUnit + 2 * kScales;       // of a wave
+    static constexpr int kGroupBytes = 20 * kRows * 4;                // p[4][4][kRows], s[4][kRows]
+    static constexpr int kLds = kWaves * kRing + kSkPass * kGroupBytes;
+};
 
-// kSkDepth = units in flight per wave: 3 when there is at most one workgroup per CU, 1 when
-// the strips outnumber the CUs (two workgroups then share a CU and cover each other's start-up,
-// chain passes and drain)
-// kSkWaves = waves splitting the groups of a strip (runs of consecutive groups)
+// kSkDepth = units in flight per wave: 3 when there is at most one workgroup per CU, 1 or 2 when the strips outnumber the CUs (two
+// workgroups then share a CU and cover each other's start-up, chain passes and drain)
+// kSkWaves = waves splitting the groups of a strip
 // ABLK = 8-row blocks of activations that hold a row of the batch ((I + 7) / 8): only these are
 // copied, and of the last one only the lines of existing rows -- every byte through a CU's
 // memory pipeline costs the same there whether it misses or hits, so at I = 1 the copy of 15
@@ -561,14 +573,13 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
                                                                      const float* __restrict__ sb,
                                                                      uint16_t* __restrict__ out, int I, int J,
                                                                      int R, bool nt) {
+    using C = SkinnyCfg<kSkDepth, kSkWaves, ABLK>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
     const int t = threadIdx.x, w = t >> 6, l = t & 63, r = l & 15, c4 = l >> 4;
-    constexpr int kUnit = kSkUnit, kGroupBytes = kSkGroupBytes, kPass = kSkPass;
-    constexpr int kSkRingBytes = kSkDepth * kUnit;
-    constexpr int kSkRun = kPass / kSkWaves;                 // consecutive groups per wave per pass
-    constexpr int kCopies = 2 + ABLK + 1;                    // vector-memory operations per unit
-    static_assert(kSkRun >= 1 && 4 <= kSkWaves && kSkDepth <= 3, "the waits below are for at most two younger units");
+    constexpr int kUnit = C::kUnit, kPass = kSkPass, kRows = C::kRows, kRun = 4;
+    constexpr int kCopies = 2 + ABLK;                        // operand copies of a unit
+    static_assert(kRun * kSkWaves == kPass && kSkWaves >= 4 && kSkDepth <= 3, "the waits below are for at most two younger units");
     static_assert(ABLK >= 1 && ABLK <= 2, "");
     const int G = R / kGroup;
     const int j0 = blockIdx.x * 16;
@@ -588,20 +599,26 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
         offX[b] = (uint32_t)min(row, I - 1) * (uint32_t)R + 16 * ((l & 7) ^ ((row >> 1) & 7));
     }
     const uint8_t* baseW = B + (size_t)j0 * R;
-    // scale line of a unit: lanes 0 .. 15 fetch sa of the batch rows (clamped), lanes 32-63 the block scale
-    const float* gs = (l < 32) ? sa + (size_t)min(l, I - 1) * G : sb + (size_t)(j0 >> 7) * G;
+    // scales of a run: lanes 0 .. 31 fetch four groups of rows 0 .. 7 (clamped), the others of rows 8 .. 15 or of the block
+    const int srow = l >> 2;
+    const float* const gb = sb + (size_t)(j0 >> 7) * G;
+    const float* const gs = (l < 32 * ABLK) ? sa + (size_t)min(srow, I - 1) * G : gb;
     const int swz = (r >> 1) & 7;
     const int frag_lo = (r >> 3) * 1024 + (r & 7) * 128 + 16 * (c4 ^ swz);
     const int frag_hi = (r >> 3) * 1024 + (r & 7) * 128 + 16 * ((4 + c4) ^ swz);
 
-    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + w * kSkRingBytes);
-    uint8_t* const ring_p = smem + w * kSkRingBytes;
-    uint8_t* const pass_p = smem + kSkWaves * kSkRingBytes;
+    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds0 + w * C::kRing);
+    const uint32_t ring_s = __builtin_amdgcn_readfirstlane(ring + kSkDepth * kUnit);
+    uint8_t* const ring_p = smem + w * C::kRing;
+    uint8_t* const scale_p = ring_p + kSkDepth * kUnit;
+    uint8_t* const pass_p = smem + kSkWaves * C::kRing;
 
-    // unit i of this wave is group seq(i); the wave has n_units of them
-    auto seq = [&](int i) { return (i / kSkRun) * kPass + w * kSkRun + (i % kSkRun); };
-    const int full = G / kPass, tail = G - full * kPass;
-    const int n_units = full * kSkRun + max(0, min(kSkRun, tail - w * kSkRun));
+    // unit i of this wave is group seq(i); the wave has n_units of them.  The groups of a last, partial pass are dealt evenly.
+    const int full = G / kPass, tail = G - full * kPass, run_t = (tail + kSkWaves - 1) / kSkWaves;
+    auto seq = [&](int i) {
+        return i < kRun * full ? (i / kRun) * kPass + w * kRun + (i % kRun) : kPass * full + w * run_t + (i - kRun * full);
+    };
+    const int n_units = full * kRun + max(0, min(run_t, tail - w * run_t));
 
     auto issue = [&](int i) {
         const int g = seq(i);
@@ -617,7 +634,11 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 #pragma unroll
         for (int b = 0; b < ABLK; ++b)
             if (rowX[b]) dma16(u + 2048 + b * 1024, A + (size_t)g * kGroup, offX[b]);
-        dma4(u + 4096, gs + g);
+        if (i % kRun == 0) {                                 // the run's scales, into the buffer that the run before last had
+            const int gl = min(g + (l & 3), G - 1);
+            dma4(ring_s + ((i / kRun) & 1) * C::kScales, gs + gl);
+            if (ABLK == 2 && l < 4) dma4(ring_s + ((i / kRun) & 1) * C::kScales + 256, gb + gl);
+        }
     };
 
     for (int i = 0; i < kSkDepth && i < n_units; ++i) issue(i);
@@ -627,46 +648,55 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
     int i = 0;
     for (int g0 = 0; g0 < G; g0 += kPass) {
         const int ng = min(kPass, G - g0);
-        for (int j = 0; j < kSkRun; ++j, ++i) {
-            if (i >= n_units) break;                 // wave-uniform
-            // unit i has landed once at most the younger units' copies are outstanding
+        auto unit = [&](auto j_tag) {
+            constexpr int j = decltype(j_tag)::value;
+            if (i >= n_units) return;                // wave-uniform
+            // unit i has landed once at most the younger units' copies are outstanding, and the scales behind a run's first unit
             const int younger = min(n_units, i + kSkDepth) - i - 1;
             switch (younger) {
                 case 0: JET_WAIT_VMCNT(0); break;
-                case 1: JET_WAIT_VMCNT(kCopies); break;
-                default: JET_WAIT_VMCNT(2 * kCopies); break;
+                case 1: JET_WAIT_VMCNT(kCopies + (j + 1 >= kRun ? ABLK : 0)); break;
+                default: JET_WAIT_VMCNT(2 * kCopies + (j + 2 >= kRun ? ABLK : 0)); break;
             }
             asm volatile("" ::: "memory");
             const uint8_t* u = ring_p + (i % kSkDepth) * kUnit;
+            const uint8_t* us = scale_p + ((i / kRun) & 1) * C::kScales + 4 * j;
             const v8i wf = load_frag(u + frag_lo, u + frag_hi);
-            const float sbv = *reinterpret_cast<const float*>(u + 4096 + 128);
-            float* dst = reinterpret_cast<float*>(pass_p + (seq(i) - g0) * kGroupBytes);
+            const float sbv = *reinterpret_cast<const float*>(us + 128 * ABLK);
+            float* dst = reinterpret_cast<float*>(pass_p + (seq(i) - g0) * C::kGroupBytes);
             const v8i xf = load_frag(u + 2048 + frag_lo, u + 2048 + frag_hi);
-            const float s = *reinterpret_cast<const float*>(u + 4096 + 4 * r) * sbv;
+            const float s = *reinterpret_cast<const float*>(us + 16 * (r & (8 * ABLK - 1))) * sbv;
             const v4f p = group_product(wf, xf);
+            if (kRows == 16 || r < 8) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e * 64 + l] = p[e];
-            dst[256 + l] = s;
+                for (int e = 0; e < 4; ++e) dst[(4 * e + c4) * kRows + r] = p[e];
+                dst[(16 + c4) * kRows + r] = s;
+            }
             asm volatile("" ::: "memory");
             if (i + kSkDepth < n_units) issue(i + kSkDepth);
-        }
+            ++i;
+        };
+        unit(std::integral_constant<int, 0>{});
+        unit(std::integral_constant<int, 1>{});
+        unit(std::integral_constant<int, 2>{});
+        unit(std::integral_constant<int, 3>{});
         __syncthreads();
         if (w < 4) {                                     // wave-uniform
-            const float* src = reinterpret_cast<const float*>(pass_p);
+            const float* src_p = reinterpret_cast<const float*>(pass_p) + (4 * w + c4) * kRows + (r & (kRows - 1));
+            const float* src_s = reinterpret_cast<const float*>(pass_p) + (16 + c4) * kRows + (r & (kRows - 1));
             if (ng == kPass) {
                 // all LDS reads of the pass first, then the ordered chain: a loop of read, read, fma
                 // pays the LDS latency once per group (1.6 us per pass of 32 groups)
                 float pv[kPass], sv[kPass];
 #pragma unroll
                 for (int g = 0; g < kPass; ++g) {
-                    pv[g] = src[g * (kGroupBytes / 4) + w * 64 + l];
-                    sv[g] = src[g * (kGroupBytes / 4) + 256 + l];
+                    pv[g] = src_p[g * (C::kGroupBytes / 4)];
+                    sv[g] = src_s[g * (C::kGroupBytes / 4)];
                 }
 #pragma unroll
                 for (int g = 0; g < kPass; ++g) acc = chain(pv[g], sv[g], acc);
             } else {
-                for (int g = 0; g < ng; ++g)
-                    acc = chain(src[g * (kGroupBytes / 4) + w * 64 + l], src[g * (kGroupBytes / 4) + 256 + l], acc);
+                for (int g = 0; g < ng; ++g) acc = chain(src_p[g * (C::kGroupBytes / 4)], src_s[g * (C::kGroupBytes / 4)], acc);
             }
         }
         __syncthreads();
@@ -991,7 +1021,7 @@ static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t
     const unsigned strips = (unsigned)(J / 16);
     const bool nt = streams_past_the_caches(J, R);
 #define JET_SKINNY_AB(D, W, AB)                                                                             \
-    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), sk_lds_bytes(D, W), st, A, \
+    hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), (SkinnyCfg<D, W, AB>::kLds), st, A, \
                        sa, B, sb, o, (int)I, (int)J, (int)R, nt)
     // copy only the 8-row activation blocks that hold a row of the batch
 #define JET_SKINNY(D, W)                       \
@@ -999,7 +1029,9 @@ static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t
         if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
         else JET_SKINNY_AB(D, W, 2);           \
     } while (0)
-    if (strips > (unsigned)compute_units()) JET_SKINNY(1, 8);    // two workgroups (16 waves) per CU
+    const unsigned cus = (unsigned)compute_units();
+    if (strips > 2 * cus && I <= 8) JET_SKINNY_AB(2, 8, 1);     // more than one round of two workgroups (16 waves) per CU
+    else if (strips > cus) JET_SKINNY(1, 8);                    // two per CU
     else JET_SKINNY(3, 8);
 #undef JET_SKINNY
 #undef JET_SKINNY_AB
@@ -1064,9 +1096,9 @@ hipError_t launch_gemm(const uint8_t* A, const float* sa, const uint8_t* B, cons
         JET_TILE_ATTR(kSbRow, JET_SMALL_DEEP);
 #undef JET_TILE_ATTR
 #define JET_SK_ATTR(D, W, AB) \
-    if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, AB>, sk_lds_bytes(D, W))
+    if (e == hipSuccess) e = allow_lds(gemm_skinny_kernel<D, W, AB>, SkinnyCfg<D, W, AB>::kLds)
         JET_SK_ATTR(3, 8, 1); JET_SK_ATTR(3, 8, 2);
-        JET_SK_ATTR(1, 8, 1); JET_SK_ATTR(1, 8, 2);
+        JET_SK_ATTR(1, 8, 1); JET_SK_ATTR(1, 8, 2); JET_SK_ATTR(2, 8, 1);
 #undef JET_SK_ATTR
 #define JET_PANEL_ATTR(TM, TN, WR, WC, S, GP, GROUP, ROUND) \
     if (e == hipSuccess) e = allow_lds(gemm_panel_kernel<PanelCfg<TM, TN, WR, WC, S, GP>>, PanelCfg<TM, TN, WR, WC, S, GP>::kLds);
