@@ -20,7 +20,10 @@ namespace jet {
 // matrices: a pass over four captured 8B-class layers, 1 row 258 -> 244 us, 32 rows 359 -> 339, 128 rows 394 -> 373.  Below, the
 // same within 0.5 % either way (1024x4096 to 4096x3072, 1 to 128 rows).  A matrix that would stay in the memory-side cache between
 // calls loses by it (one 28672x4096 matrix over and over, 32 rows: 20 -> 24 us); the activations always do and stay without.
-constexpr bool streams_past_the_caches(long J, long R) { return J * R >= (1L << 24); }
+// Only where each weight is read once: the second of two workgroups that share a panel finds nothing in the L2 if it is
+// not close behind the first, as beside a partly filled row block (32-row tiles of 3584x26496, 37 rows 31.7 -> 40.0 us, 64
+// rows the same within 1 %).  One row block, 1 to 128 rows: 0 to 10 % faster on all of 120 shapes.
+constexpr bool streams_past_the_caches(long row_blocks, long J, long R) { return row_blocks == 1 && J * R >= (1L << 24); }
 
 enum GemmKernel {
     kStrips,         // skinny kernel, 16 columns per workgroup
