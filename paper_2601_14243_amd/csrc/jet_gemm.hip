@@ -993,7 +993,7 @@ static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t*
     const int rbs = (int)((I + C::BM - 1) / C::BM);
     const long panels = (J + C::BN - 1) / C::BN;
     hipLaunchKernelGGL((gemm_panel_kernel<C>), dim3((unsigned)(rbs * panels)), dim3(C::kThreads), C::kLds, st, A, sa, B,
-                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs, streams_past_the_caches(rbs, J, R));
+                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs, streams_past_the_caches(rbs == 1 || I % C::BM == 0, J, R));
     return hipGetLastError();
 }
 
@@ -1019,7 +1019,7 @@ static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t*
 static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
                                 long J, long R, hipStream_t st) {
     const unsigned strips = (unsigned)(J / 16);
-    const bool nt = streams_past_the_caches(1, J, R);
+    const bool nt = streams_past_the_caches(true, J, R);
 #define JET_SKINNY_AB(D, W, AB)                                                                             \
     hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), (SkinnyCfg<D, W, AB>::kLds), st, A, \
                        sa, B, sb, o, (int)I, (int)J, (int)R, nt)

@@ -20,10 +20,11 @@ namespace jet {
 // matrices: a pass over four captured 8B-class layers, 1 row 258 -> 244 us, 32 rows 359 -> 339, 128 rows 394 -> 373.  Below, the
 // same within 0.5 % either way (1024x4096 to 4096x3072, 1 to 128 rows).  A matrix that would stay in the memory-side cache between
 // calls loses by it (one 28672x4096 matrix over and over, 32 rows: 20 -> 24 us); the activations always do and stay without.
-// Only where each weight is read once: the second of two workgroups that share a panel finds nothing in the L2 if it is
-// not close behind the first, as beside a partly filled row block (32-row tiles of 3584x26496, 37 rows 31.7 -> 40.0 us, 64
-// rows the same within 1 %).  One row block, 1 to 128 rows: 0 to 10 % faster on all of 120 shapes.
-constexpr bool streams_past_the_caches(long row_blocks, long J, long R) { return row_blocks == 1 && J * R >= (1L << 24); }
+// Only where the workgroups that share a panel of weights read it together (or one alone does): beside a partly filled row block,
+// whose workgroup has fewer lines to wait for, the other one finds nothing in the L2 any more (32-row tiles of 3584x26496, 37 rows
+// 31.7 -> 40.0 us; 100x5120x14336 28.9 -> 36.4).  One row block, 1 to 128 rows: 0 to 10 % faster on all of 120 shapes; several
+// full ones: 0 to 4 % faster on 53 of 58 (worst 2.7 % slower, 256x7552x5120).
+constexpr bool streams_past_the_caches(bool in_step, long J, long R) { return in_step && J * R >= (1L << 24); }
 
 enum GemmKernel {
     kStrips,         // skinny kernel, 16 columns per workgroup
