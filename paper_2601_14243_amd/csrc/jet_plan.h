@@ -95,20 +95,24 @@ inline int pick_tile(long I, long J, long G, long cus, bool one_round, long& tim
 
 // Up to 16 rows: strips of the skinny kernel or panels.  A strip's eight waves share its reduction, a panel's groups come
 // one after the other; but in a partly full pass of 32 groups waves wait, and in a partly full round CUs.  Strips against the
-// best panel, 1-16 rows, matrices of 512-8192 columns x 8-56 groups and the layers' own (time of strips / time of panels):
-//  - one pass, all strips resident (at most two per CU): from 14 groups on 0.80-1.00 (320 and 384 strips from HBM up to
-//    1.04), at 12 0.97-1.10, at 8 1.00-1.25.  With two per CU and from 9 rows on (both activation blocks are copied) up to 24
-//    groups: beyond, 0.88-0.96 from the caches and 1.05-1.07 from HBM.
-//  - up to 8 rows, at most one strip per CU, more passes: 0.85-1.00 from 36 of 64 groups on (1.03 for 256 strips from HBM).
-//  - the rest, from HBM: passes x rounds full to 0.7 (0.9 from 9 rows on): 28672x4096, 1 and 8 rows, 0.97 and 1.01 (16 rows
-//    1.11); below, 55296x5120, 8 and 16 rows, 1.30 and 1.46; 5120x27648, 1 row, 1.16; 14336x4096, 16 rows (0.875) 1.16.
+// best panel, 1-16 rows, 11 widths of 1024-55296 columns x 8-216 groups (time of strips / time of panels, from HBM):
+//  - one pass, all strips resident (at most two per CU): from 14 groups on 0.77-1.05 (320 to 512 strips x 20 to 28 groups up to
+//    1.11; from 9 rows on only up to 24 groups); at 8 groups 0.95-1.00.
+//  - up to 8 rows, at most one strip per CU, more passes: 0.82-1.03 from 36 of 64 groups on.
+//  - more strips than CUs and more than two passes: 1.03-1.33.  More than two per CU and 9 rows or more (both activation blocks,
+//    one unit in flight per wave): 1.00-1.45.
+//  - the rest: passes x rounds full to 0.9: 28672x4096, 1 and 8 rows, 0.86 and 0.86, 8192x8192 0.99 and 1.03; below, 8 rows of 28672
+//    columns x 24, 28, 48 and 56 groups 1.11, 1.13, 1.05 and 1.06, 14336x4096 1.03, 8192x6144 1.09.  A line at 0.7, as it was while
+//    panels read their weights through the caches, left these (us, 8 rows) at 18.9 for 17.1 and 21.1 for 18.7 (28672x3072, x3584).
 inline bool strips_pay(long I, long J, long G, long cus) {
     const bool few = I <= 8;
     const long strips = J / 16, places = strips <= cus ? strips : ceil_div(strips, cus) * cus;
     const long groups = ceil_div(G, kStripPass) * kStripPass;
     if (G <= kStripPass && (strips <= cus || (strips <= 2 * cus && (few || G <= 24)))) return G >= 14;
     if (few && strips <= cus) return 20 * G >= 11 * groups;
-    return 10 * G * strips >= (few ? 7 : 9) * groups * places;
+    if (strips > cus && G > 2 * kStripPass) return false;
+    if (!few && strips > 2 * cus) return false;
+    return 10 * G * strips >= 9 * groups * places;
 }
 
 // OUT[I,J] over G groups of 128.  row_scales: the operand of the columns has a scale per row (WGrad), else per block.
