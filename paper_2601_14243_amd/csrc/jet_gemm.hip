@@ -182,8 +182,10 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         const int band = lid / (kBand * tiles_j);
         const int within = lid - band * (kBand * tiles_j);
         const int rows_in_band = min(kBand, tiles_i - band * kBand);
-        i0 = (band * kBand + within % rows_in_band) * C::BM;
-        j0 = (within / rows_in_band) * C::BN;
+        int col = within / kBand;                    // a whole band without a division: three origins per tile are
+        if (rows_in_band != kBand) col = within / rows_in_band;   // 1 % of a tile of 2 to 8 steps
+        i0 = (band * kBand + within - col * rows_in_band) * C::BM;
+        j0 = col * C::BN;
     };
 
     // ---- operand copies: the cursor stands on the step whose tiles are being copied ----
