@@ -991,25 +991,26 @@ static int compute_units() {
 
 template <class C>
 static hipError_t launch_panel(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
-                               long J, long R, long ldo, hipStream_t st) {
+                               long J, long R, long ldo, bool nt, hipStream_t st) {
     const int rbs = (int)((I + C::BM - 1) / C::BM);
     const long panels = (J + C::BN - 1) / C::BN;
     hipLaunchKernelGGL((gemm_panel_kernel<C>), dim3((unsigned)(rbs * panels)), dim3(C::kThreads), C::kLds, st, A, sa, B,
-                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs, streams_past_the_caches(rbs == 1 || I % C::BM == 0, J, R));
+                       sb, o, (int)I, (int)J, (int)ldo, (int)R, rbs, nt);
     return hipGetLastError();
 }
 
 using PanelLaunch = hipError_t (*)(const uint8_t*, const float*, const uint8_t*, const float*, uint16_t*, long, long, long,
-                                   long, hipStream_t);
+                                   long, bool, hipStream_t);
 #define JET_PANEL_LAUNCH(TM, TN, WR, WC, S, GP, GROUP, ROUND) launch_panel<PanelCfg<TM, TN, WR, WC, S, GP>>,
 static const PanelLaunch kPanelLaunches[] = {JET_PANELS(JET_PANEL_LAUNCH)};
 #undef JET_PANEL_LAUNCH
 static_assert(std::size(kPanelLaunches) == kNumPanels, "the panels come first in kGemmTiles");
 
-template <int SB_MODE, int... Cfg>
+template <GemmKernel KERNEL, int SB_MODE, int... Cfg>
 static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
                                long J, long R, long ldo, hipStream_t st) {
     using C = TileCfg<SB_MODE, Cfg...>;
+    static_assert(C::kOccupancy == resident_per_cu(KERNEL), "the plan's rounds");
     const long ti = (I + C::BM - 1) / C::BM, tj = J / C::BN;
     const long wgs = std::min<long>(ti * tj, (long)compute_units() * C::kOccupancy);
     hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, Cfg...>), dim3((unsigned)wgs), dim3(C::kThreads), C::kLdsBytes, st, A,
@@ -1019,9 +1020,8 @@ static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t*
 
 // decode of up to 16 rows: a workgroup per 16-column strip
 static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t* B, const float* sb, uint16_t* o, long I,
-                                long J, long R, hipStream_t st) {
+                                long J, long R, int depth, bool nt, hipStream_t st) {
     const unsigned strips = (unsigned)(J / 16);
-    const bool nt = streams_past_the_caches(true, J, R);
 #define JET_SKINNY_AB(D, W, AB)                                                                             \
     hipLaunchKernelGGL((gemm_skinny_kernel<D, W, AB>), dim3(strips), dim3(64 * W), (SkinnyCfg<D, W, AB>::kLds), st, A, \
                        sa, B, sb, o, (int)I, (int)J, (int)R, nt)
@@ -1031,10 +1031,10 @@ static hipError_t launch_strips(const uint8_t* A, const float* sa, const uint8_t
         if (I <= 8) JET_SKINNY_AB(D, W, 1);    \
         else JET_SKINNY_AB(D, W, 2);           \
     } while (0)
-    const unsigned cus = (unsigned)compute_units();
-    if (strips > 2 * cus && I <= 8) JET_SKINNY_AB(2, 8, 1);     // more than one round of two workgroups (16 waves) per CU
-    else if (strips > cus) JET_SKINNY(1, 8);                    // two per CU
-    else JET_SKINNY(3, 8);
+    if (depth == 3) JET_SKINNY(3, 8);                           // a workgroup per CU
+    else if (depth == 1) JET_SKINNY(1, 8);                      // two (16 waves) per CU
+    else if (I <= 8) JET_SKINNY_AB(2, 8, 1);                    // two, more than one round of them
+    else return hipErrorInvalidValue;
 #undef JET_SKINNY
 #undef JET_SKINNY_AB
     return hipGetLastError();
@@ -1048,20 +1048,20 @@ static hipError_t launch_planned(const uint8_t* A, const float* sa, const uint8_
     const GemmPlan p = plan_gemm(SB_MODE == kSbRow, I, J, G, compute_units(), whole);
     switch (p.kernel) {
         case kStrips:
-            if constexpr (SB_MODE == kSbBlock) return launch_strips(A, sa, B, sb, o, I, J, R, st);
+            if constexpr (SB_MODE == kSbBlock) return launch_strips(A, sa, B, sb, o, I, J, R, p.depth, p.nt, st);
             break;
         case kPanel:
-            if constexpr (SB_MODE == kSbBlock) return kPanelLaunches[p.panel](A, sa, B, sb, o, I, J, R, ldo, st);
+            if constexpr (SB_MODE == kSbBlock) return kPanelLaunches[p.panel](A, sa, B, sb, o, I, J, R, ldo, p.nt, st);
             break;
         case kTileWide:
-            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
+            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kTileWide, kSbBlock, JET_WIDE>(A, sa, B, sb, o, I, J, R, ldo, st);
             break;
         case kTileHalf:
-            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kSbBlock, JET_HALF>(A, sa, B, sb, o, I, J, R, ldo, st);
+            if constexpr (SB_MODE == kSbBlock) return launch_tiles<kTileHalf, kSbBlock, JET_HALF>(A, sa, B, sb, o, I, J, R, ldo, st);
             break;
-        case kTileBig: return launch_tiles<SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
-        case kTileSmallDeep: return launch_tiles<SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
-        case kTileSmall: return launch_tiles<SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kTileBig: return launch_tiles<kTileBig, SB_MODE, JET_BIG>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kTileSmallDeep: return launch_tiles<kTileSmallDeep, SB_MODE, JET_SMALL_DEEP>(A, sa, B, sb, o, I, J, R, ldo, st);
+        case kTileSmall: return launch_tiles<kTileSmall, SB_MODE, JET_SMALL>(A, sa, B, sb, o, I, J, R, ldo, st);
         case kSplitRows: {
             const hipError_t e = launch_planned<SB_MODE>(A, sa, B, sb, o, p.split, J, R, ldo, st, false);
             if (e != hipSuccess) return e;

@@ -42,7 +42,12 @@ struct GemmPlan {
     int panel;       // of kPanel
     int bm, bn;      // tile
     long split;      // of kSplit*
+    int depth = 0;   // of kStrips: units in flight per wave
+    bool nt = false; // of kStrips and kPanel: the weights are read past the caches
 };
+
+// workgroups of a tile or panel kernel that the CUs hold at a time
+constexpr int resident_per_cu(GemmKernel k) { return k == kTileSmall ? 2 : 1; }
 
 struct GemmTile {
     int bm, bn;
@@ -85,8 +90,7 @@ inline int pick_tile(long I, long J, long G, long cus, bool one_round, long& tim
         const GemmTile& c = kGemmTiles[t];
         if (c.bm > 128 && I <= 128) continue;                             // half of it padding, not measured
         if (c.bn == 256 && J % 256) continue;                             // the tile kernel has no ragged columns
-        const long resident = c.kernel == kTileSmall ? 2 * cus : cus;
-        if (one_round && ceil_div(I, c.bm) * ceil_div(J, c.bn) > resident) continue;
+        if (one_round && ceil_div(I, c.bm) * ceil_div(J, c.bn) > resident_per_cu(c.kernel) * cus) continue;
         const long d = tile_time(c, I, J, G, cus);
         if (best < 0 || d < time) { best = t; time = d; }
     }
@@ -115,6 +119,14 @@ inline bool strips_pay(long I, long J, long G, long cus) {
     return 10 * G * strips >= 9 * groups * places;
 }
 
+// Units in flight per wave of the skinny kernel: three up to a strip per CU, one where all strips are resident two per CU, two (up
+// to 8 rows, whose smaller passes leave room for them) beyond.  Times beside the kernel.
+inline int strip_depth(long I, long J, long cus) {
+    const long strips = J / 16;
+    if (strips <= cus) return 3;
+    return strips > 2 * cus && I <= 8 ? 2 : 1;
+}
+
 // OUT[I,J] over G groups of 128.  row_scales: the operand of the columns has a scale per row (WGrad), else per block.
 // whole: not a part of a split problem, whose output rows are further apart than the skinny kernel writes them
 inline GemmPlan plan_gemm(bool row_scales, long I, long J, long G, long cus, bool whole) {
@@ -129,7 +141,8 @@ inline GemmPlan plan_gemm(bool row_scales, long I, long J, long G, long cus, boo
         else if (tail % ti == 0) split = {kSplitCols, 0, 256, 256, (tj - tail / ti) * 256};
     }
     if (!row_scales) {
-        if (whole && I <= 16 && strips_pay(I, J, G, cus)) return {kStrips, 0, 16, 16, 0};
+        if (whole && I <= 16 && strips_pay(I, J, G, cus))
+            return {kStrips, 0, 16, 16, 0, strip_depth(I, J, cus), streams_past_the_caches(true, J, G * 128)};
         // up to 1024 rows the fastest tile, and beyond where one round of tiles does (more rounds: the persistent kernel
         // below, which has no gap between them and splits the last one)
         long time = 0, rest = 0;
@@ -141,7 +154,9 @@ inline GemmPlan plan_gemm(bool row_scales, long I, long J, long G, long cus, boo
                 if (tile_time(kGemmTiles[kNumPanels + 3], rows ? split.split : I, rows ? J : split.split, G, cus) + kLaunch + rest < time)
                     return split;
             }
-            return {kGemmTiles[t].kernel, t, kGemmTiles[t].bm, kGemmTiles[t].bn, 0};
+            const GemmTile& c = kGemmTiles[t];
+            const bool in_step = I <= c.bm || I % c.bm == 0;
+            return {c.kernel, t, c.bm, c.bn, 0, 0, c.kernel == kPanel && streams_past_the_caches(in_step, J, G * 128)};
         }
     }
     // the big tile when it divides J and fills the CUs.  The grid is persistent: at most one resident set of

@@ -14,6 +14,7 @@ SHIM = """
 extern "C" int jet_plan(int row_scales, long I, long J, long G, long cus, int whole, long* out) {
     const jet::GemmPlan p = jet::plan_gemm(row_scales, I, J, G, cus, whole);
     out[0] = p.bm; out[1] = p.bn; out[2] = p.split; out[3] = p.panel;
+    out[4] = p.depth; out[5] = p.nt;
     return p.kernel;
 }
 extern "C" int jet_tile(int t, long* out) {
@@ -40,11 +41,25 @@ def lib():
     return _lib
 
 
-def plan(I: int, J: int, R: int, row_scales: bool = False, cus: int = CUS, whole: bool = True):
-    """(kernel, rows of the tile, columns of the tile, split) of OUT[I,J] over a reduction of R."""
-    out = (ctypes.c_long * 4)()
-    k = lib().jet_plan(row_scales, I, J, R // 128, cus, whole, out)
-    return KERNELS[k], out[0], out[1], out[2]
+def _plan(I, J, R, row_scales=False, cus=CUS, whole=True):
+    out = (ctypes.c_long * 6)()
+    return KERNELS[lib().jet_plan(row_scales, I, J, R // 128, cus, whole, out)], list(out)
+
+
+def plan(I: int, J: int, R: int, row_scales: bool = False, **kw):
+    """(kernel, rows of the tile, columns of the tile, split) of OUT[I,J] over a reduction of R.  Keywords: cus, whole."""
+    k, out = _plan(I, J, R, row_scales, **kw)
+    return k, out[0], out[1], out[2]
+
+
+def strip_depth(I: int, J: int, R: int) -> int:
+    """Units in flight per wave, 0 where the launch runs no strips."""
+    return _plan(I, J, R)[1][4]
+
+
+def past_the_caches(I: int, J: int, R: int) -> bool:
+    """Whether the decode kernel reads its weights with the policy of lines that are not needed again."""
+    return bool(_plan(I, J, R)[1][5])
 
 
 def name(I: int, J: int, R: int, **kw) -> str:

@@ -135,26 +135,43 @@ def test_forward_of_a_few_rows_on_both_sides_of_the_strip_rule(jet, M, N, groups
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {kernel}", operands=ops)
 
 
-@pytest.mark.parametrize("M,N,groups", [
-    (1, 12288, 32), (8, 12288, 29), (5, 12288, 61),                             # two units in flight, packed rows
-    (2, 5120, 31), (8, 8192, 17), (13, 8192, 18), (16, 6144, 23),               # two workgroups per CU, partial passes
-    (1, 1024, 14), (4, 1024, 17), (16, 1024, 23), (9, 512, 25), (8, 384, 30),   # one per CU, every length of the waves' runs
-    (2, 512, 36), (7, 384, 45), (12, 256, 59), (3, 256, 73), (16, 128, 64),     # further passes
-])
-def test_strips_deal_runs_of_groups_to_their_waves(jet, M, N, groups):
+# rows, columns, groups, units in flight per wave
+STRIP_CASES = [
+    (1, 12288, 32, 2), (8, 12288, 29, 2), (5, 12288, 61, 2),                                    # two units in flight, packed rows
+    (2, 5120, 31, 1), (8, 8192, 17, 1), (13, 8192, 18, 1), (16, 6144, 23, 1),                   # two workgroups per CU, partial passes
+    (8, 8192, 61, 1), (16, 8192, 64, 1),                                                        # and a second pass
+    (1, 1024, 14, 3), (4, 1024, 17, 3), (16, 1024, 23, 3), (9, 512, 25, 3), (8, 384, 30, 3),    # one per CU, every length of the waves' runs
+    (2, 512, 36, 3), (7, 384, 45, 3), (12, 256, 59, 3), (3, 256, 73, 3), (16, 128, 64, 3),      # further passes
+]
+
+
+@pytest.mark.parametrize("M,N,groups,depth", STRIP_CASES)
+def test_strips_deal_runs_of_groups_to_their_waves(jet, M, N, groups, depth):
     """Against the matrix-core model, bit for bit: outputs of a few hundred elements are too few for check_gemm's share of
     99.5 % (five misses of 1024, at 0.2 to 0.5 % expected)."""
     y, _, ops = _fwd_case(jet, M, N, 128 * groups, seed=29 * M + N + groups)
-    check_model(y, ops, f"fwd {M}x{N}, {groups} groups, strips")
+    check_model(y, ops, f"fwd {M}x{N}, {groups} groups, strips with {depth} units in flight")
 
 
-@pytest.mark.parametrize("M,N,groups", [(1, 4096, 32), (11, 8192, 16), (8, 4224, 32), (19, 4224, 32), (35, 16512, 9),
-                                        (130, 4352, 31)])
-def test_forward_with_weights_read_past_the_caches(jet, M, N, groups):
-    """Strips and panels of matrices just above 16 MB, where the copies of the weights change their cache policy."""
-    assert 1 << 24 <= N * groups * 128 < 1.2 * (1 << 24)
+# rows, columns, groups, kernel, whether its weights are read past the caches
+CACHE_CASES = [
+    (1, 4096, 32, "strips", True), (11, 8192, 16, "strips", True), (8, 4224, 32, "strips", True),
+    (8, 8192, 16, "strips", True), (16, 8192, 15, "strips", False),
+    (19, 4224, 32, "panel 32x32", True), (35, 16512, 9, "panel 48x112", True),                  # one row block
+    (64, 4224, 32, "panel 32x48", True), (128, 4096, 32, "panel 64x32", True),                  # full ones
+    (192, 4224, 32, "panel 64x64", True), (240, 8320, 17, "panel 80x112", True),
+    (130, 4352, 31, "panel 48x64", False), (127, 4096, 32, "panel 64x32", False),               # the last one partly filled
+    (128, 4096, 30, "panel 64x32", False),                                                      # below 16 MB
+]
+
+
+@pytest.mark.parametrize("M,N,groups,kernel,past", CACHE_CASES)
+def test_forward_on_both_sides_of_the_cache_policy(jet, M, N, groups, kernel, past):
+    """Strips and panels of matrices around 16 MB, where the copies of the weights change their cache policy if no row block is
+    partly filled beside others."""
+    assert 0.9 * (1 << 24) <= N * groups * 128 < 1.2 * (1 << 24)
     y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=19 * M + N + groups)
-    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups, past the caches", operands=ops)
+    check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups, past the caches: {past}", operands=ops)
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 384, 512), (5, 256, 128), (130, 128, 640)])

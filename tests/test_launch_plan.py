@@ -3,7 +3,7 @@ changed rule would drop one from the GPU tests without any of them failing."""
 import pytest
 
 import launch_plan as lp
-from test_gpu_gemm import FEW_ROW_CASES, RAGGED_CASES, TILE_CASES
+from test_gpu_gemm import CACHE_CASES, FEW_ROW_CASES, RAGGED_CASES, STRIP_CASES, TILE_CASES
 from test_gpu_mfma import KERNEL_CASES
 
 CASES = ([(M, N, K, label) for M, N, K, label in RAGGED_CASES] +
@@ -18,6 +18,21 @@ def test_the_gpu_cases_run_what_their_labels_say(M, N, K, label):
 @pytest.mark.parametrize("T,groups,kernel", KERNEL_CASES)
 def test_the_group_sum_cases_run_on_the_kernels_they_name(T, groups, kernel):
     assert lp.name(T, 1024, 128 * groups) == kernel
+
+
+@pytest.mark.parametrize("M,N,groups,depth", STRIP_CASES)
+def test_the_strip_cases_run_strips_of_their_depth(M, N, groups, depth):
+    assert lp.name(M, N, 128 * groups) == "strips" and lp.strip_depth(M, N, 128 * groups) == depth
+
+
+def test_every_strip_kernel_has_a_case_of_one_pass_and_one_of_more():
+    seen = {(depth, -(-M // 8), groups > 32) for M, _, groups, depth in STRIP_CASES}
+    assert seen >= {(depth, blocks, more) for depth in (1, 3) for blocks in (1, 2) for more in (False, True)} | {(2, 1, False), (2, 1, True)}
+
+
+@pytest.mark.parametrize("M,N,groups,kernel,past", CACHE_CASES)
+def test_the_cache_policy_cases_run_the_policy_they_name(M, N, groups, kernel, past):
+    assert lp.name(M, N, 128 * groups) == kernel and lp.past_the_caches(M, N, 128 * groups) == past
 
 
 def test_every_tile_has_a_gpu_case():
