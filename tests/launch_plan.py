@@ -14,7 +14,7 @@ SHIM = """
 extern "C" int jet_plan(int row_scales, long I, long J, long G, long cus, int whole, long* out) {
     const jet::GemmPlan p = jet::plan_gemm(row_scales, I, J, G, cus, whole);
     out[0] = p.bm; out[1] = p.bn; out[2] = p.split; out[3] = p.panel;
-    out[4] = p.depth; out[5] = p.nt;
+    out[4] = p.depth; out[5] = p.nt; out[6] = jet::resident_per_cu(p.kernel);
     return p.kernel;
 }
 extern "C" int jet_tile(int t, long* out) {
@@ -42,7 +42,7 @@ def lib():
 
 
 def _plan(I, J, R, row_scales=False, cus=CUS, whole=True):
-    out = (ctypes.c_long * 6)()
+    out = (ctypes.c_long * 7)()
     return KERNELS[lib().jet_plan(row_scales, I, J, R // 128, cus, whole, out)], list(out)
 
 
@@ -60,6 +60,17 @@ def strip_depth(I: int, J: int, R: int) -> int:
 def past_the_caches(I: int, J: int, R: int) -> bool:
     """Whether the decode kernel reads its weights with the policy of lines that are not needed again."""
     return bool(_plan(I, J, R)[1][5])
+
+
+def launches(I: int, J: int, R: int, row_scales: bool = False, whole: bool = True):
+    """Launches of a GEMM on the tile kernel: (kernel and tile, tiles of the workgroup that has most)."""
+    k, (bm, bn, split, _, _, _, per_cu) = _plan(I, J, R, row_scales=row_scales, whole=whole)
+    if k.startswith("split"):
+        rows = k == "split rows"
+        parts = ((split, J), (I - split, J)) if rows else ((I, split), (I, J - split))
+        return [launch for i, j in parts for launch in launches(i, j, R, row_scales, whole=False)]
+    n_tiles = -(-I // bm) * -(-J // bn)
+    return [(f"{k} {bm}x{bn}", -(-n_tiles // min(n_tiles, CUS * per_cu)))]
 
 
 def name(I: int, J: int, R: int, **kw) -> str:

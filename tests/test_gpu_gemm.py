@@ -268,36 +268,80 @@ def test_wgrad_with_the_last_round_split_off(jet, N, K):
                operands=(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], True))
 
 
-@pytest.mark.parametrize("M,N,groups,what", [
-    (4400, 8192, 3, "256x256, chunks across tiles"),
-    (4400, 8192, 5, "256x256, chunks across tiles"), (16500, 1152, 7, "128x128, two workgroups per CU"),
-    (9000, 1024, 9, "256x256, one tile per workgroup"),
-])
+# rows, columns, groups, tile and most tiles of a workgroup (of the larger part of a split launch).  The tile kernel copies the
+# scales of four steps at a time, whatever tiles the steps belong to.  Tiles of four stages get one tile per workgroup.
+CHUNK_CASES = [
+    (4400, 8192, 3, "big 256x256: 2 tiles"), (4400, 8192, 5, "big 256x256: 2 tiles"),
+    (16500, 1152, 7, "small 128x128: 3 tiles"), (9000, 1024, 9, "big 256x256: 1 tiles"),
+]
+# the same, outputs too large for the oracle or of too few groups for its rule
+SAMPLED_CHUNK_CASES = [
+    (4400, 8192, 1, "big 256x256: 2 tiles"), (2000, 55296, 1, "big 256x256: 7 tiles"), (8000, 14336, 2, "big 256x256: 7 tiles"),
+    (6000, 14336, 3, "big 256x256: 6 tiles"), (2000, 55296, 7, "big 256x256: 7 tiles"),
+    (650, 28672, 3, "wide 256x128: 3 tiles"), (520, 28672, 5, "wide 256x128: 3 tiles"), (520, 28672, 9, "wide 256x128: 3 tiles"),
+    (806, 55296, 1, "small 128x128: 6 tiles"), (780, 55296, 2, "small 128x128: 6 tiles"), (780, 55296, 3, "small 128x128: 6 tiles"),
+    (260, 55296, 7, "small 128x128: 3 tiles"), (130, 9728, 5, "small deep 128x128: 1 tiles"), (572, 2304, 7, "half 128x64: 1 tiles"),
+]
+# tokens, rows and columns of the output
+WGRAD_CHUNK_CASES = [
+    (384, 16384, 2304, "big 256x256: 2 tiles"), (640, 2304, 8192, "big 256x256: 1 tiles"), (896, 8192, 1152, "small 128x128: 2 tiles"),
+    (128, 8192, 2304, "big 256x256: 1 tiles"),
+]
+SAMPLED_WGRAD_CHUNK_CASES = [
+    (128, 28672, 4096, "big 256x256: 7 tiles"), (256, 28672, 4096, "big 256x256: 7 tiles"), (384, 7552, 14336, "big 256x256: 7 tiles"),
+    (1152, 27648, 4096, "big 256x256: 7 tiles"), (128, 27648, 1152, "small 128x128: 4 tiles"), (384, 25600, 1152, "small 128x128: 4 tiles"),
+    (640, 25600, 1152, "small 128x128: 4 tiles"),
+]
+
+
+@pytest.mark.parametrize("M,N,groups,what", CHUNK_CASES)
 def test_scale_chunks_of_reductions_that_four_does_not_divide(jet, M, N, groups, what):
-    """The tile kernel copies the scales of four steps at a time, whatever tiles the steps belong to: workgroups with several
-    tiles, and reductions where a chunk ends inside the next tile."""
+    """Workgroups with several tiles, and reductions where a chunk ends inside the next tile."""
     y, ref, ops = _fwd_case(jet, M, N, 128 * groups, seed=23 * M + N + groups)
     check_gemm(y, ref, f"fwd {M}x{N}, {groups} groups: {what}", operands=ops)
 
 
-def test_scale_chunks_of_a_tile_per_step(jet):
-    """One group: every step is another tile.  Against the matrix-core model, bit for bit, alone: one instruction deviates by
-    up to 2^-13 of sum|a b| (the worst seen, mfma_model), which is the two bf16 ulps that check_gemm allows at its
-    |acc| = 2^-6 sum|a b|, and 36 million elements of a single group reach it."""
-    M, N = 4400, 8192
-    y, _, ops = _fwd_case(jet, M, N, 128, seed=23 * M + N + 1)
-    check_model(y, ops, f"fwd {M}x{N}, one group")
+def _one_row_per_block(M, seed):
+    """A row of every 128, the first and the last: every tile row."""
+    rng = np.random.default_rng(seed)
+    rows = [min(M - 1, 128 * b + int(rng.integers(128))) for b in range(-(-M // 128))]
+    return np.unique([0, M - 1] + rows)
 
 
-@pytest.mark.parametrize("M,N,K", [(384, 16384, 2304), (640, 2304, 8192), (896, 8192, 1152), (128, 8192, 2304)])
-def test_wgrad_scale_chunks_of_reductions_that_four_does_not_divide(jet, M, N, K):
+@pytest.mark.parametrize("M,N,groups,what", SAMPLED_CHUNK_CASES)
+def test_scale_chunks_across_tiles(jet, M, N, groups, what):
+    """Chunks that hold the steps of several tiles, and more than one chunk per workgroup.  Against the matrix-core model, bit
+    for bit, alone: one instruction deviates by up to 2^-13 of sum|a b| (the worst seen, mfma_model), which is the two bf16
+    ulps that check_gemm allows at its |acc| = 2^-6 sum|a b|, and millions of elements of a single group reach it."""
+    qa = orc.quant_act(ji.activations(M, 128 * groups, 23 * M + N + groups))
+    qw, sw = orc.quant_weight(ji.weights(N, 128 * groups, 23 * M + N + groups + 1))
+    y = jet.fp8_linear_fwd(dev(qa["q_row"]), dev(qa["s_row"]), dev(qw), dev(sw))
+    rows = _one_row_per_block(M, groups)
+    check_model(host_bits(y[torch.from_numpy(rows).to(y.device)]), (qa["q_row"][rows], qa["s_row"][rows], qw, sw, False),
+                f"fwd {M}x{N}, {groups} groups: {what}", max_rows=len(rows), max_products=1 << 18)
+
+
+@pytest.mark.parametrize("M,N,K,what", WGRAD_CHUNK_CASES)
+def test_wgrad_scale_chunks_of_reductions_that_four_does_not_divide(jet, M, N, K, what):
     dy, x = ji.grads(M, N, seed=95), ji.activations(M, K, seed=96)
     qd = orc.quant_act(dy, row=False, col=True)
     qx = orc.quant_act(x, row=False, col=True)
     ref = orc.gemm(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], sb_mode=orc.SB_ROW)
     dw = jet.fp8_linear_wgrad(dev(qd["q_colT"]), dev(qd["s_colT"]), dev(qx["q_colT"]), dev(qx["s_colT"]))
-    check_gemm(host_bits(dw), ref, f"wgrad {M}x{N}x{K}",
+    check_gemm(host_bits(dw), ref, f"wgrad {M}x{N}x{K}: {what}",
                operands=(qd["q_colT"], qd["s_colT"], qx["q_colT"], qx["s_colT"], True))
+
+
+@pytest.mark.parametrize("M,N,K,what", SAMPLED_WGRAD_CHUNK_CASES)
+def test_wgrad_scale_chunks_across_tiles(jet, M, N, K, what):
+    """As above: against the model, a row of every tile row."""
+    qd = orc.quant_act(ji.grads(M, N, seed=97), row=False, col=True)
+    qx = orc.quant_act(ji.activations(M, K, seed=98), row=False, col=True)
+    dw = jet.fp8_linear_wgrad(dev(qd["q_colT"]), dev(qd["s_colT"]), dev(qx["q_colT"]), dev(qx["s_colT"]))
+    rows = _one_row_per_block(N, M)
+    check_model(host_bits(dw[torch.from_numpy(rows).to(dw.device)]),
+                (qd["q_colT"][rows], qd["s_colT"][rows], qx["q_colT"], qx["s_colT"], True), f"wgrad {M}x{N}x{K}: {what}",
+                max_rows=len(rows), max_products=1 << 18)
 
 
 def test_full_backward_from_fp8_saved_activation(jet):

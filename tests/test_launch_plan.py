@@ -3,7 +3,8 @@ changed rule would drop one from the GPU tests without any of them failing."""
 import pytest
 
 import launch_plan as lp
-from test_gpu_gemm import CACHE_CASES, FEW_ROW_CASES, RAGGED_CASES, STRIP_CASES, TILE_CASES
+from test_gpu_gemm import (CACHE_CASES, CHUNK_CASES, FEW_ROW_CASES, RAGGED_CASES, SAMPLED_CHUNK_CASES, SAMPLED_WGRAD_CHUNK_CASES,
+                           STRIP_CASES, TILE_CASES, WGRAD_CHUNK_CASES)
 from test_gpu_mfma import KERNEL_CASES
 
 CASES = ([(M, N, K, label) for M, N, K, label in RAGGED_CASES] +
@@ -33,6 +34,27 @@ def test_every_strip_kernel_has_a_case_of_one_pass_and_one_of_more():
 @pytest.mark.parametrize("M,N,groups,kernel,past", CACHE_CASES)
 def test_the_cache_policy_cases_run_the_policy_they_name(M, N, groups, kernel, past):
     assert lp.name(M, N, 128 * groups) == kernel and lp.past_the_caches(M, N, 128 * groups) == past
+
+
+CHUNKS = ([(lp.launches(M, N, 128 * g), g, label) for M, N, g, label in CHUNK_CASES + SAMPLED_CHUNK_CASES],
+          [(lp.launches(N, K, M, row_scales=True), M // 128, label) for M, N, K, label in WGRAD_CHUNK_CASES + SAMPLED_WGRAD_CHUNK_CASES])
+
+
+@pytest.mark.parametrize("launches,groups,label", CHUNKS[0] + CHUNKS[1])
+def test_the_chunk_cases_run_what_their_labels_say(launches, groups, label):
+    kernel, tiles = launches[0]
+    assert f"{kernel}: {tiles} tiles" == label
+
+
+@pytest.mark.parametrize("cases,kernels", [(CHUNKS[0], ("big 256x256", "wide 256x128", "small 128x128")), (CHUNKS[1], ("big 256x256", "small 128x128"))])
+def test_the_chunk_cases_cross_tiles(cases, kernels):
+    """Every kernel that gets several tiles per workgroup: a chunk behind the first one that starts in a later tile and ends in
+    another, three chunks and more; and (256x128 is not chosen for so few groups) one or two groups, where four steps are
+    two tiles or more."""
+    for kernel in kernels:
+        of = [(launches[0][1], g) for launches, g, _ in cases if launches[0][0] == kernel]
+        assert any(g % 4 and tiles >= 3 and tiles * g > 8 for tiles, g in of), kernel
+        assert kernel == "wide 256x128" or any(g <= 2 and tiles >= 4 for tiles, g in of), kernel
 
 
 def test_every_tile_has_a_gpu_case():
