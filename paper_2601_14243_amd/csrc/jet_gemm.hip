@@ -114,8 +114,12 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 //         Copied a step at a time, every scale was a request of its own, as many as a third (block scales) or half (WGrad) of the
 //         operand lines': us, before -> in chunks: from HBM 1000x4096x14336 82 -> 74, 1024x5120x27648 247 -> 196,
 //         1024x5120x5120 53 -> 44, 256x55296x5120 100 -> 93; 16384x28672x4096 1738 -> 1685, 16384x4096x14336 838 -> 785;
-//         WGrad 28672x4096 over 16384 tokens 1990 -> 1922, 1024x4096 96 -> 92.  Eight steps long calls in one round lose 2 %
-//         (257x16384x1024 15.0 -> 15.3: the first chunk's addresses).  Measured and left out: one piece of a chunk per step (its
+//         WGrad 28672x4096 over 16384 tokens 1990 -> 1922, 1024x4096 96 -> 92.  A chunk's addresses take no division
+//         (tile origins by reciprocals from the host) and inside a workgroup's last tile a step on: with three divisions per lane
+//         and origin, reductions of 2 to 9 groups were 1.6 % slower than with the scales a step at a time (150 shapes from the
+//         caches; now 0.1 % faster; us, step at a time, with divisions, now: 257x4096x256 4.48, 4.60, 4.37; 9000x1024x256 11.5,
+//         12.0, 11.5; 257x8192x768 7.8, 8.1, 7.7; 600x8192x768 11.4, 11.8, 11.65), from HBM 0.5 % (now 0.4 % faster).
+//         Measured and left out: one piece of a chunk per step (its
 //         address in the MFMA stream: 3-5 % slower where one wave runs per SIMD), all operand copies of a step behind its barrier
 //         (2-5 % slower on one round of tiles), waits that count the scale copies exactly (7 % slower with four stages).
 // BM = 32 * waves, so every wave copies 4 A blocks per step, and 4 B blocks (BN = 32 * waves) or 2 (BN = 16 * waves,
@@ -164,7 +168,8 @@ template <int SB_MODE, int WI, int WJ, int TM, int TN, int S = 2>
 __global__ __launch_bounds__(64 * WI * WJ, 512 / (64 * WI * WJ))
 void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ sa,
                       const uint8_t* __restrict__ B, const float* __restrict__ sb,
-                      uint16_t* __restrict__ out, int I, int ldo, int R, int tiles_i, int tiles_j) {
+                      uint16_t* __restrict__ out, int I, int ldo, int R, int tiles_i, int tiles_j, uint32_t band_recip,
+                      uint32_t rest_recip) {
     using C = TileCfg<SB_MODE, WI, WJ, TM, TN, S>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
@@ -175,16 +180,14 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     if (mine.count == 0) return;                     // whole workgroup
     const int n_steps = mine.count * G;
 
-    // logical id -> tile origin: bands of 8 tile rows, walked column by column
+    // logical id -> tile origin: bands of 8 tile rows, the last one of the rest, walked column by column
     auto tile_origin = [&](int k, int& i0, int& j0) {
         constexpr int kBand = 8;
-        const int lid = mine.first + k * mine.stride;
-        const int band = lid / (kBand * tiles_j);
-        const int within = lid - band * (kBand * tiles_j);
-        const int rows_in_band = min(kBand, tiles_i - band * kBand);
-        int col = within / kBand;                    // a whole band without a division: three origins per tile are
-        if (rows_in_band != kBand) col = within / rows_in_band;   // 1 % of a tile of 2 to 8 steps
-        i0 = (band * kBand + within - col * rows_in_band) * C::BM;
+        const int lid = mine.first + k * mine.stride, per_band = kBand * tiles_j, rest = tiles_i % kBand;
+        const int band = quotient(lid, per_band, band_recip), within = lid - band * per_band;
+        const bool whole = band < tiles_i / kBand;
+        const int col = whole ? within / kBand : quotient(within, rest, rest_recip);
+        i0 = (band * kBand + within - col * (whole ? kBand : rest)) * C::BM;
         j0 = col * C::BN;
     };
 
@@ -257,21 +260,22 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     const int lstep = (l >> 2) & 3, lrow = 4 * (l >> 4) + (l & 3);
     const float* gs[kScaleCopies];
     int sk, chunk_g;                    // tile and group of the chunk's first step
-    auto scales_in_tile = [&](int i0, int j0) {          // all four steps in the tile at i0, j0
+    auto scales_in_tile = [&](int i0, int j0) {          // all steps of the chunk that somebody computes are in the tile at i0, j0
+        const int ls = min(lstep, G - 1 - chunk_g);
         const float* a0 = static_cast<const float*>(uniform_ptr(sa + (size_t)i0 * G + chunk_g));
         const float* b0 = static_cast<const float*>(uniform_ptr(sb + (size_t)(SB_MODE == kSbBlock ? j0 >> 7 : j0) * G + chunk_g));
         const int row = 32 * w + lrow, last = I - 1 - i0;
-        gs[0] = a0 + (__umul24(min(row, last), G) + lstep);
-        gs[1] = a0 + (__umul24(min(row + 16, last), G) + lstep);
+        gs[0] = a0 + (__umul24(min(row, last), G) + ls);
+        gs[1] = a0 + (__umul24(min(row + 16, last), G) + ls);
         if (SB_MODE == kSbBlock) {
-            gs[2] = b0 + (__umul24(min(lrow, (C::BN + 127) / 128 - 1), G) + lstep);
+            gs[2] = b0 + (__umul24(min(lrow, (C::BN + 127) / 128 - 1), G) + ls);
         } else {
-            gs[2] = b0 + (__umul24(row, G) + lstep);
-            gs[kScaleCopies - 1] = b0 + (__umul24(row + 16, G) + lstep);
+            gs[2] = b0 + (__umul24(row, G) + ls);
+            gs[kScaleCopies - 1] = b0 + (__umul24(row + 16, G) + ls);
         }
     };
     auto scales_across_tiles = [&]() {                   // this lane's step may belong to a later tile than the chunk's first
-        const int dk = (chunk_g + lstep) / G, g = chunk_g + lstep - dk * G, row = 32 * w + lrow;
+        const int st = chunk_g + lstep, dk = (st >= G) + (st >= 2 * G) + (st >= 3 * G), g = st - dk * G, row = 32 * w + lrow;
         int i0, j0;
         tile_origin(min(sk + dk, mine.count - 1), i0, j0);   // past the end of the list: steps nobody computes
         gs[0] = sa + (size_t)min(i0 + row, I - 1) * G + g;
@@ -285,13 +289,14 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     };
     auto scales_next = [&]() {
         chunk_g += 4;
-        if (chunk_g + 4 <= G) {         // both chunks inside one tile
+        if (chunk_g + 4 <= G || (chunk_g < G && sk + 1 == mine.count)) {   // the last chunk's steps and this one's are in one tile
+            const int d = min(4, G - chunk_g + 3 - lstep);                 // steps behind the tile's last one repeat it
 #pragma unroll
-            for (int i = 0; i < kScaleCopies; ++i) gs[i] += 4;
+            for (int i = 0; i < kScaleCopies; ++i) gs[i] += d;
             return;
         }
         while (chunk_g >= G) { chunk_g -= G; ++sk; }
-        if (chunk_g + 4 <= G) {
+        if (chunk_g + 4 <= G || sk + 1 >= mine.count) {
             int i0, j0;
             tile_origin(min(sk, mine.count - 1), i0, j0);
             scales_in_tile(i0, j0);
@@ -364,17 +369,20 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     tile_origin(0, first_i0, first_j0);
     cursor_at_tile(0, first_i0, first_j0);
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (s) cursor_next();
+    for (int i = 0; i < kCopies; ++i) copy_one(pa, pb, crows, i, 0);
+    sk = chunk_g = 0;
+    if (G >= 4 || mine.count == 1) scales_in_tile(first_i0, first_j0);
+    else scales_across_tiles();
+    copy_scales(0);
+#pragma unroll 1
+    for (int s = 1; s < S - 1; ++s) {
+        cursor_next();
 #pragma unroll
-        for (int i = 0; i < (s + 1 < S ? kCopies : kLate); ++i) copy_one(pa, pb, crows, i, (uint32_t)(s * C::kStageBytes));
-        if (s == 0) {
-            sk = chunk_g = 0;
-            if (G >= 4) scales_in_tile(first_i0, first_j0);
-            else scales_across_tiles();
-            copy_scales(0);
-        }
+        for (int i = 0; i < kCopies; ++i) copy_one(pa, pb, crows, i, (uint32_t)(s * C::kStageBytes));
     }
+    cursor_next();
+#pragma unroll
+    for (int i = 0; i < kLate; ++i) copy_one(pa, pb, crows, i, (uint32_t)((S - 1) * C::kStageBytes));
     JET_WAIT_VMCNT((S - 2) * kCopies + kLate);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -1014,7 +1022,8 @@ static hipError_t launch_tiles(const uint8_t* A, const float* sa, const uint8_t*
     const long ti = (I + C::BM - 1) / C::BM, tj = J / C::BN;
     const long wgs = std::min<long>(ti * tj, (long)compute_units() * C::kOccupancy);
     hipLaunchKernelGGL((gemm_tile_kernel<SB_MODE, Cfg...>), dim3((unsigned)wgs), dim3(C::kThreads), C::kLdsBytes, st, A,
-                       sa, B, sb, o, (int)I, (int)ldo, (int)R, (int)ti, (int)tj);
+                       sa, B, sb, o, (int)I, (int)ldo, (int)R, (int)ti, (int)tj, reciprocal((unsigned)(8 * tj)),
+                       reciprocal((unsigned)std::max<long>(ti % 8, 1)));
     return hipGetLastError();
 }
 

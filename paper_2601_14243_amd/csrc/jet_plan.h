@@ -68,6 +68,14 @@ constexpr int kStripPass = 32;       // groups that the skinny kernel chains per
 
 constexpr long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
+// n / d for 0 <= n < 2^31, d > 0, without a division, with m = reciprocal(d): 2^32 - d <= m d < 2^32, so n m / 2^32 is below n / d by
+// less than 1/2, and its whole part is the quotient or one less.
+constexpr unsigned reciprocal(unsigned d) { return 0xffffffffu / d; }
+constexpr int quotient(int n, int d, unsigned m) {
+    const int q = (int)(((unsigned long long)(unsigned)n * m) >> 32);
+    return n - q * d >= d ? q + 1 : q;
+}
+
 // Time in ns of a launch on tile c, without its fixed part: rounds x (groups x time of a group + a time per round, which is
 // ring fill, drain, output and half a launch gap).  The table's times were fitted to every tile on 34 matrices (128 to
 // 55296 columns, 256 to 27648 long, 17 to 4096 rows, weights from HBM and from the caches, 2366 shapes), such that the

@@ -17,6 +17,7 @@ extern "C" int jet_plan(int row_scales, long I, long J, long G, long cus, int wh
     out[4] = p.depth; out[5] = p.nt; out[6] = jet::resident_per_cu(p.kernel);
     return p.kernel;
 }
+extern "C" int jet_quotient(int n, int d) { return jet::quotient(n, d, jet::reciprocal(d)); }
 extern "C" int jet_tile(int t, long* out) {
     if (t >= jet::kNumGemmTiles) return -1;
     out[0] = jet::kGemmTiles[t].bm; out[1] = jet::kGemmTiles[t].bn;

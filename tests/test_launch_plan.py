@@ -107,3 +107,13 @@ def test_part_of_a_split_problem_never_runs_strips():
     for I in range(1, 17):
         assert lp.plan(I, 4096, 4096)[0] == "strips"
         assert lp.plan(I, 4096, 4096, whole=False)[0] != "strips"
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 8, 24, 127, 1736, 65535, 65536, 8388607, 1 << 27, (1 << 31) - 1])
+def test_quotients_without_a_division(d):
+    """Tile origins of the tile kernel: multiples of the divisor and their neighbours, and both ends of the range."""
+    top = (1 << 31) - 1
+    multiples = {k * d for k in (1, 2, 3, 5, 1000, top // d // 2, top // d - 1, top // d)}
+    for n in {0, 1, top - 1, top} | {m + e for m in multiples for e in (-1, 0, 1)}:
+        if 0 <= n <= top:
+            assert lp.lib().jet_quotient(n, d) == n // d, (n, d)
