@@ -280,7 +280,8 @@ SAMPLED_CHUNK_CASES = [
     (6000, 14336, 3, "big 256x256: 6 tiles"), (2000, 55296, 7, "big 256x256: 7 tiles"),
     (650, 28672, 3, "wide 256x128: 3 tiles"), (520, 28672, 5, "wide 256x128: 3 tiles"), (520, 28672, 9, "wide 256x128: 3 tiles"),
     (806, 55296, 1, "small 128x128: 6 tiles"), (780, 55296, 2, "small 128x128: 6 tiles"), (780, 55296, 3, "small 128x128: 6 tiles"),
-    (260, 55296, 7, "small 128x128: 3 tiles"), (130, 9728, 5, "small deep 128x128: 1 tiles"), (572, 2304, 7, "half 128x64: 1 tiles"),
+    (260, 55296, 7, "small 128x128: 3 tiles"), (257, 49280, 17, "small deep 128x128: 5 tiles"),
+    (130, 9728, 5, "small deep 128x128: 1 tiles"), (572, 2304, 7, "half 128x64: 1 tiles"),
 ]
 # tokens, rows and columns of the output
 WGRAD_CHUNK_CASES = [

@@ -46,15 +46,29 @@ def test_the_chunk_cases_run_what_their_labels_say(launches, groups, label):
     assert f"{kernel}: {tiles} tiles" == label
 
 
-@pytest.mark.parametrize("cases,kernels", [(CHUNKS[0], ("big 256x256", "wide 256x128", "small 128x128")), (CHUNKS[1], ("big 256x256", "small 128x128"))])
+SEVERAL_TILES = ({"big 256x256", "wide 256x128", "small 128x128", "small deep 128x128"}, {"big 256x256", "small 128x128"})
+
+
+@pytest.mark.parametrize("cases,kernels", zip(CHUNKS, SEVERAL_TILES), ids=("fprop", "wgrad"))
 def test_the_chunk_cases_cross_tiles(cases, kernels):
     """Every kernel that gets several tiles per workgroup: a chunk behind the first one that starts in a later tile and ends in
-    another, three chunks and more; and (256x128 is not chosen for so few groups) one or two groups, where four steps are
-    two tiles or more."""
+    another, three chunks and more; and (256x128 and 128x128 with four stages are not chosen for so few groups) one or two
+    groups, where four steps are two tiles or more."""
     for kernel in kernels:
         of = [(launches[0][1], g) for launches, g, _ in cases if launches[0][0] == kernel]
         assert any(g % 4 and tiles >= 3 and tiles * g > 8 for tiles, g in of), kernel
-        assert kernel == "wide 256x128" or any(g <= 2 and tiles >= 4 for tiles, g in of), kernel
+        assert kernel in ("wide 256x128", "small deep 128x128") or any(g <= 2 and tiles >= 4 for tiles, g in of), kernel
+
+
+@pytest.mark.parametrize("row_scales", (False, True))
+def test_which_kernels_get_several_tiles_per_workgroup(row_scales):
+    several = set()
+    for I in (17, 100, 129, 257, 300, 385, 520, 641, 771, 897, 1000, 1024, 1025, 1300, 2048, 4096, 16384):
+        for J in (*range(128, 8448, 384), *range(8448, 60000, 1408), 16384, 28672, 55296):
+            for G in (1, 2, 3, 7, 9, 17, 32, 40, 111, 216):
+                if lp.name(I, J, 128 * G, row_scales=row_scales).split()[0] not in ("panel", "strips"):
+                    several |= {k for k, tiles in lp.launches(I, J, 128 * G, row_scales) if tiles > 1}
+    assert several == SEVERAL_TILES[row_scales]
 
 
 def test_every_tile_has_a_gpu_case():
