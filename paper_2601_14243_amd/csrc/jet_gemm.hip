@@ -108,9 +108,11 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 //         q*128 + 16*(c ^ swz), swz = (row>>1)&7, so the 16 lanes of an MFMA fragment read
 //         (rows 0..15, same chunk) hit 16 different 16-byte bank groups: measured 6.4
 //         cycles per ds_read_b128 (160 B/clk/CU) against 16.4 for a plain row-major tile
-//   scales: a chunk holds four consecutive steps of the stream, copied at the top of every fourth step for the
-//         next four.  256 bytes per 16 rows as blocks of [4 rows][4 steps][4 rows]: a copy's lanes read four neighbouring scales of
-//         a row together, a row's scale of one step and the scales of four neighbouring columns are conflict-free reads.
+//   scales: a chunk holds four consecutive steps of the stream, copied at the top of every fourth step into one of two buffers for the
+//         next four.  256 bytes per 16 rows (jet_plan.h): a copy's lanes read four neighbouring scales of a row together, a step's
+//         scales of 16 rows and of four neighbouring columns are conflict-free reads.  With rows r and r + 8 in one bank the
+//         reads took 4.2 M cycles more per 16384x4096x4096 launch (SQ_LDS_BANK_CONFLICT; now 0, SQ_WAIT_INST_LDS 20.1 -> 12.0 M) and
+//         16384x28672x4096 1691 us instead of 1661, 16384x8192x4096 493 instead of 479.
 //         Copied a step at a time, every scale was a request of its own, as many as a third (block scales) or half (WGrad) of the
 //         operand lines': us, before -> in chunks: from HBM 1000x4096x14336 82 -> 74, 1024x5120x27648 247 -> 196,
 //         1024x5120x5120 53 -> 44, 256x55296x5120 100 -> 93; 16384x28672x4096 1738 -> 1685, 16384x4096x14336 838 -> 785;
@@ -254,10 +256,10 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 
     // ---- scale copies: chunks of four consecutive steps of the stream ----
     // Wave w copies the scales of the A rows 32w .. 32w+31, and of as many columns or (every wave the same ones to the same
-    // place) the tile's block scales.  Lane l serves step (l >> 2) & 3 of the chunk, which may belong to another tile
-    // than its neighbours' steps, of row 4 (l >> 4) + (l & 3) of each 16.
+    // place) the tile's block scales.  Lane l serves step chunk_step(l) of the chunk, which may belong to another
+    // tile than its neighbours' steps, of row chunk_row(l) of each 16.
     constexpr int kScaleCopies = SB_MODE == kSbBlock ? 3 : 4;
-    const int lstep = (l >> 2) & 3, lrow = 4 * (l >> 4) + (l & 3);
+    const int lstep = chunk_step(l), lrow = chunk_row(l);
     const float* gs[kScaleCopies];
     int sk, chunk_g;                    // tile and group of the chunk's first step
     auto scales_in_tile = [&](int i0, int j0) {          // all steps of the chunk that somebody computes are in the tile at i0, j0
@@ -335,17 +337,18 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         float a[TM];
         float b_block;
     };
-    const uint8_t* const sc_rows = smem + C::kScaleOff + wi * TM * 256 + (r >> 2) * 64 + (r & 3) * 4;
-    const uint8_t* const sc_cols = smem + C::kScaleOff + C::BM * 16 + wj * TN * 256 + c4 * 64;
+    const uint8_t* const sc_rows = smem + C::kScaleOff + wi * TM * 256 + chunk_place(r);
+    const uint8_t* const sc_cols = smem + C::kScaleOff + C::BM * 16 + wj * TN * 256 + chunk_place(4 * c4);
+    const int swap_row = chunk_swap(r), swap_col = chunk_swap(4 * c4);
     const uint8_t* const sc_block = smem + C::kScaleOff + C::BM * 16 + ((wj * TN * 16) >> 7) * 4;   // one 128-wide block
     auto load_scales = [&](int off, RawScales& s) {
 #pragma unroll
-        for (int m = 0; m < TM; ++m) s.a[m] = *reinterpret_cast<const float*>(sc_rows + off + m * 256);
+        for (int m = 0; m < TM; ++m) s.a[m] = *reinterpret_cast<const float*>(sc_rows + (off ^ swap_row) + m * 256);
         if (SB_MODE == kSbBlock) s.b_block = *reinterpret_cast<const float*>(sc_block + off);
     };
     auto load_col_scales = [&](int off, v4f (&s)[TN]) {
 #pragma unroll
-        for (int n = 0; n < TN; ++n) s[n] = *reinterpret_cast<const v4f*>(sc_cols + off + n * 256);
+        for (int n = 0; n < TN; ++n) s[n] = *reinterpret_cast<const v4f*>(sc_cols + (off ^ swap_col) + n * 256);
     };
 
     constexpr int kTiles = TM * TN, kLag = 2;

@@ -76,6 +76,15 @@ constexpr int quotient(int n, int d, unsigned m) {
     return n - q * d >= d ? q + 1 : q;
 }
 
+// Scales of a chunk in the LDS (tile kernel): 16 rows x 4 steps in 256 bytes, blocks of [4 rows][4 steps][4 rows].  Lane l of a copy,
+// which writes bytes 4 l .. 4 l + 3, brings step chunk_step(l) of row chunk_row(l); step s of row r is at chunk_place(r) +
+// (16 s ^ chunk_swap(r)).  The rows from 8 on have their steps swapped in pairs: the scales of 16 rows, or of 4 x 4
+// columns, then lie in 16 of the 32 banks, where rows r and r + 8 would share one.
+constexpr int chunk_row(int l) { return 4 * (l >> 4) + (l & 3); }
+constexpr int chunk_step(int l) { return ((l >> 2) & 3) ^ (l >> 5); }
+constexpr int chunk_place(int r) { return 64 * (r >> 2) + 4 * (r & 3); }
+constexpr int chunk_swap(int r) { return 16 * (r >> 3); }
+
 // Time in ns of a launch on tile c, without its fixed part: rounds x (groups x time of a group + a time per round, which is
 // ring fill, drain, output and half a launch gap).  The table's times were fitted to every tile on 34 matrices (128 to
 // 55296 columns, 256 to 27648 long, 17 to 4096 rows, weights from HBM and from the caches, 2366 shapes), such that the

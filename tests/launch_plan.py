@@ -18,6 +18,10 @@ extern "C" int jet_plan(int row_scales, long I, long J, long G, long cus, int wh
     return p.kernel;
 }
 extern "C" int jet_quotient(int n, int d) { return jet::quotient(n, d, jet::reciprocal(d)); }
+extern "C" void jet_chunk(int lane, int row, int step, int* out) {
+    out[0] = jet::chunk_row(lane); out[1] = jet::chunk_step(lane);
+    out[2] = jet::chunk_place(row) + ((16 * step) ^ jet::chunk_swap(row));
+}
 extern "C" int jet_tile(int t, long* out) {
     if (t >= jet::kNumGemmTiles) return -1;
     out[0] = jet::kGemmTiles[t].bm; out[1] = jet::kGemmTiles[t].bn;
@@ -78,6 +82,13 @@ def name(I: int, J: int, R: int, **kw) -> str:
     """"strips", or kernel and tile: "panel 32x16", "big 256x256", "split rows 256x256"."""
     k, bm, bn, _ = plan(I, J, R, **kw)
     return k if k == "strips" else f"{k} {bm}x{bn}"
+
+
+def chunk(lane: int = 0, row: int = 0, step: int = 0):
+    """(row, step) that a lane of a scale copy brings, and the byte of a row's step in the chunk."""
+    out = (ctypes.c_int * 3)()
+    lib().jet_chunk(lane, row, step, out)
+    return (out[0], out[1]), out[2]
 
 
 def tiles():

@@ -131,3 +131,19 @@ def test_quotients_without_a_division(d):
     for n in {0, 1, top - 1, top} | {m + e for m in multiples for e in (-1, 0, 1)}:
         if 0 <= n <= top:
             assert lp.lib().jet_quotient(n, d) == n // d, (n, d)
+
+
+def test_scales_are_read_where_a_copy_has_put_them():
+    placed = {lp.chunk(lane=lane)[0]: 4 * lane for lane in range(64)}
+    assert len(placed) == 64
+    for row in range(16):
+        for step in range(4):
+            assert lp.chunk(row=row, step=step)[1] == placed[row, step]
+            # four neighbouring columns are one 16-byte read
+            assert lp.chunk(row=row, step=step)[1] == lp.chunk(row=row & ~3, step=step)[1] + 4 * (row & 3)
+
+
+def test_scales_of_a_step_lie_in_different_banks():
+    """A 4-byte read takes 32 banks at a time; lanes of equal rows read the same word."""
+    for step in range(4):
+        assert len({lp.chunk(row=row, step=step)[1] // 4 % 32 for row in range(16)}) == 16
