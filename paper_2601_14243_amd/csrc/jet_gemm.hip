@@ -121,9 +121,14 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 //         and origin, reductions of 2 to 9 groups were 1.6 % slower than with the scales a step at a time (150 shapes from the
 //         caches; now 0.1 % faster; us, step at a time, with divisions, now: 257x4096x256 4.48, 4.60, 4.37; 9000x1024x256 11.5,
 //         12.0, 11.5; 257x8192x768 7.8, 8.1, 7.7; 600x8192x768 11.4, 11.8, 11.65), from HBM 0.5 % (now 0.4 % faster).
+//         What is slower than a step at a time, with the weights in the caches: the 256x128 tile (700x7168x5120 37.8 -> 39.0,
+//         1024x5120x27648 175 -> 179) and 128x128 tiles in several rounds (257x49280x2176 53.5 -> 55.6), and on a hot chip (it
+//         differs by box) long calls of 16 tile columns (16384x4096x4096 227 -> 231; on another box 223 -> 221).
 //         Measured and left out: one piece of a chunk per step (its
 //         address in the MFMA stream: 3-5 % slower where one wave runs per SIMD), all operand copies of a step behind its barrier
-//         (2-5 % slower on one round of tiles), waits that count the scale copies exactly (7 % slower with four stages).
+//         (2-5 % slower on one round of tiles), waits that count the scale copies exactly (7 % slower with four stages), the
+//         copies of a chunk inside the MFMA stream, before or behind the operands' (up to 4 % slower, one round 6-14 %), row scales
+//         as [16 rows][4 steps] (the same within 0.1 % on average).
 // BM = 32 * waves, so every wave copies 4 A blocks per step, and 4 B blocks (BN = 32 * waves) or 2 (BN = 16 * waves,
 // block scales only: the 256x128 and the 128x64 tile).
 // ------------------------------------------------------------------------
@@ -545,10 +550,10 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
 
 // ------------------------------------------------------------------------
 // Skinny kernel for I <= 16 (decode): bound by streaming B (the weights) once.
-// A workgroup of kWaves waves owns 16 output columns and the whole reduction.  The
+// A workgroup of kSkWaves waves owns 16 output columns and the whole reduction.  The
 // groups of a pass (32 groups) are dealt to the waves in runs of four consecutive
 // groups, those of a last, partial pass evenly; every wave streams its own units (16 weight rows + the rows of the batch's
-// 8-row blocks of one group) through a private LDS ring with kDepth units in flight, and the scales of a run at once,
+// 8-row blocks of one group) through a private LDS ring with kSkDepth units in flight, and the scales of a run at once,
 // using the same whole-line LDS-DMA and swizzled fragment layout as the tile kernel --
 // no barrier is needed for the ring.  After every pass the p_g and s_g meet in LDS and
 // four waves run the ordered fma chain for their quarter of the outputs.

@@ -19,11 +19,17 @@ namespace jet {
 // TB/s, on a quarter of them 2.75 -> 2.94.  From 16 MB on, where a model has several times the cache in such
 // matrices: a pass over four captured 8B-class layers, 1 row 258 -> 244 us, 32 rows 359 -> 339, 128 rows 394 -> 373.  Below, the
 // same within 0.5 % either way (1024x4096 to 4096x3072, 1 to 128 rows).  A matrix that would stay in the memory-side cache between
-// calls loses by it (one 28672x4096 matrix over and over, 32 rows: 20 -> 24 us); the activations always do and stay without.
+// calls loses by it, up to half as much again: one matrix over and over, us through the caches -> past them, 5120x27648 16 rows
+// 25.2 -> 30.6, 32 rows 26.4 -> 36.4, 64 rows 29.9 -> 43.3; 4096x14336 64 rows 15.5 -> 19.0; 28672x4096 32 rows 19.6 -> 22.9; but
+// 14336x4096 1 row 11.2 -> 10.6, and up to 32 MB -1 to +10 %.  Weights read right after they were quantized (18 calls):
+// 5120x27648 32 rows 48 -> 33, 4096x14336 32 rows 16.1 -> 13.5, at worst 28672x4096 32 rows 20.7 -> 23.8.  The activations always
+// stay in the caches and are read through them.
 // Only where the workgroups that share a panel of weights read it together (or one alone does): beside a partly filled row block,
 // whose workgroup has fewer lines to wait for, the other one finds nothing in the L2 any more (32-row tiles of 3584x26496, 37 rows
 // 31.7 -> 40.0 us; 100x5120x14336 28.9 -> 36.4).  One row block, 1 to 128 rows: 0 to 10 % faster on all of 120 shapes; several
-// full ones: 0 to 4 % faster on 53 of 58 (worst 2.7 % slower, 256x7552x5120).
+// full ones: 0 to 4 % faster on 53 of 58 (worst 2.7 % slower, 256x7552x5120).  By how much of the last of several blocks is filled
+// (114 shapes, 17 to 250 rows of seven matrices, past / through): below a quarter 0.98-1.37 (1.11 on average), below half
+// 0.95-1.25 (1.06), below three quarters 0.92-1.12 (0.99), from there on 0.91-1.00 (0.95).  The line could lie at three quarters.
 constexpr bool streams_past_the_caches(bool in_step, long J, long R) { return in_step && J * R >= (1L << 24); }
 
 enum GemmKernel {
@@ -88,7 +94,11 @@ constexpr int chunk_swap(int r) { return 16 * (r >> 3); }
 // Time in ns of a launch on tile c, without its fixed part: rounds x (groups x time of a group + a time per round, which is
 // ring fill, drain, output and half a launch gap).  The table's times were fitted to every tile on 34 matrices (128 to
 // 55296 columns, 256 to 27648 long, 17 to 4096 rows, weights from HBM and from the caches, 2366 shapes), such that the
-// choice and not the time comes out right: it is 0.7 % from the best tile on average.  The cost before, rounds x
+// choice and not the time comes out right: it was 0.7 % from the best tile on average.  They were fitted before the tile kernel's
+// scales travelled in chunks and the panels' weights past the caches.  With both (448 cases, 16 matrices of 1024 to 55296 columns,
+// 20 to 1000 rows): from HBM 0.7 % from the best on average, 10 of 224 above 5 %, worst 100x11008x2048 12 % and 140 rows of
+// 5120 columns x 5120 and 27648 9 and 10 % (48x64, not 64x64); from the caches 1.6 %, 23 above 5 %, worst 24 % where the
+// 128x112 panel reads a resident matrix past them (100x28672x4096 28.9 us, 128x128 tiles 23.3).  The cost before, rounds x
 // L (L + 550) with L = rows + columns of the tile, had no time per round and took two 128x128 tiles of a CU for two
 // rounds.  It was 2.6 % from the best, and short reductions and launches of a few rounds were slower than on the kernels
 // before that (us; before, with that cost, now): from HBM 140x16384x1024 12.2, 15.6, 12.0; 280x16384x1024 17.1, 20.4, 16.1;
@@ -118,7 +128,9 @@ inline int pick_tile(long I, long J, long G, long cus, bool one_round, long& tim
 // one after the other; but in a partly full pass of 32 groups waves wait, and in a partly full round CUs.  Strips against the
 // best panel, 1-16 rows, 11 widths of 1024-55296 columns x 8-216 groups (time of strips / time of panels, from HBM):
 //  - one pass, all strips resident (at most two per CU): from 14 groups on 0.77-1.05 (320 to 512 strips x 20 to 28 groups up to
-//    1.11; from 9 rows on only up to 24 groups); at 8 groups 0.95-1.00.
+//    1.11; from 9 rows on only up to 24 groups).  At 8 to 13 groups (240 cases, 512 to 8192 columns, against the panel of the
+//    rule) 0.84-1.01 for up to 256 strips, 0.85-1.06 beyond, the slow ones at 10 to 12 groups: the line at 14 was drawn on the
+//    strips before and lies too high by now.
 //  - up to 8 rows, at most one strip per CU, more passes: 0.82-1.03 from 36 of 64 groups on.
 //  - more strips than CUs and more than two passes: 1.03-1.33.  More than two per CU and 9 rows or more (both activation blocks,
 //    one unit in flight per wave): 1.00-1.45.
