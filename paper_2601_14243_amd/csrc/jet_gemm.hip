@@ -87,19 +87,31 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 // conflict-free.  S LDS stages (two; three for the 256x128 tile; four for the 128x128 tile when there is at
 // most one workgroup per CU); step q lives in stage q % S and is copied S - 1 steps ahead.
 //
-// Pipeline of one step q, written for S = 2 (t counts the wave's MFMA tiles, row m = t / TN,
-// column n = t % TN):
+// Pipeline of one step q, written for S = 2 (t counts the wave's MFMA tiles; `tail` = the last one to three rows of them, which
+// tile_schedule says):
 //   top      : the column fragments cf[0..TN), the first row fragment and the scales of
 //              step q are already in registers (fetched during step q-1)
-//   t < last row : MFMA stream; row fragment m+1 is fetched from stage q&1 while row m runs;
+//   in front of the tail : MFMA stream, row by row; row fragment m+1 is fetched from stage q&1 while row m runs;
 //              the scale fmas of tile t-2 run on the VALU under the MFMA of tile t
-//   t = first tile of the last row : every LDS read of stage q&1 has returned.  Wait for this
-//              wave's copies of step q+1, workgroup barrier.  Now stage (q+1)&1 is complete
-//              and stage q&1 is free: start fetching step q+1's fragments (cf[n] right after the
-//              last MFMA that uses the old cf[n]) and start copying step q+2 into stage q&1.
+//   t = first tile of the tail : every LDS read of stage q&1 has returned, the fragments of all tail rows are in registers.  Wait
+//              for this wave's copies of step q+1, workgroup barrier.  Now stage (q+1)&1 is complete
+//              and stage q&1 is free: start fetching step q+1's fragments and copying step q+2 into stage q&1.
+//   tail     : column by column, so that cf[n] is free for step q+1 after every third (second) MFMA
 // The only barrier of a step therefore sits in the middle of the MFMA stream, the LDS
-// latency of the next step's first fragments hides under the last row of this step,
+// latency of the next step's first fragments hides under the tail of this step,
 // and every copy has about one whole step to land.
+// With a tail of one row, all waves fetch TN + 1 fragments (80 KB on the 256x256 tile, 500 cycles of the LDS) under their last four
+// MFMAs, as many copies as fit go out at once, the A tile's first, and the matrix cores wait for both.  A tail of three rows
+// spreads the fetch over twelve MFMAs; the B copies (lines that eight workgroups of an XCD share) go first and the A copies behind
+// a gap, since a burst of all eight holds up the LDS reads: with the same tail and no gap 16384x4096x4096 takes as long as
+// before.  One row / the schedule now, us: 256x256 block scales 16384x28672x4096 1658 / 1518, 16384x4096x14336 803 / 764,
+// 16384x14336x4096 832 / 762, 16384x4096x4096 232 / 217, 1000x14336x4096 62.1 / 56.3, 6016x5120x27648 736 / 710; all A copies of a step
+// at its top (late = 4) is 1-2 % faster there on 4096-long reductions and 4 % slower on 14336-long ones from HBM.  256x256 WGrad
+// (256 registers: no room for a tail of three) 28672x4096 over 16384 tokens 1886 / 1789, 5120x5120 over 6016 183 / 172.  256x128
+// 1024x5120x27648 195 / 180, 700x7168x5120 42.6 / 40.0.  128x128 WGrad 1024x5120 over 16384 tokens 157 / 144, four stages 1024x4096
+// 94.5 / 91.  128x128 block scales, one wave per SIMD: waits for its copies and not for the LDS, so a longer tail, which shortens
+// their lead, is 1-3 % slower.  fma lag 3: a wave alone on its SIMD issues an MFMA every 34.5 cycles instead of 39 in a
+// register-only loop, two waves 3 % more of them; in the kernel nothing (one wave waits for its copies) or up to 2 % slower.
 //
 // LDS: S stages [A tile BM*128][B tile BN*128], then two chunks of scales
 //   tile: 1 KB block per 8 rows, copied by one instruction that moves 8 whole 128-byte
@@ -132,6 +144,22 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 // BM = 32 * waves, so every wave copies 4 A blocks per step, and 4 B blocks (BN = 32 * waves) or 2 (BN = 16 * waves,
 // block scales only: the 256x128 and the 128x64 tile).
 // ------------------------------------------------------------------------
+
+// How a step of the tile kernel is ordered.
+struct TileSchedule {
+    int tail_rows;   // rows of the wave's MFMA tiles behind the barrier, walked column by column
+    int late, gap;   // operand copies issued behind the barrier, one per MFMA, `gap` MFMAs between the B and the A copies
+};
+template <int SB_MODE, int TM, int S>
+constexpr TileSchedule tile_schedule() {
+    constexpr bool block = SB_MODE == kSbBlock;
+    if (TM == 8) return block ? TileSchedule{3, 6, 5} : TileSchedule{2, 4, 0};                // 256x256
+    if (TM == 2) return {1, 2, 0};                                                            // 128x64
+    if (S == 3) return {3, 4, 3};                                                             // 256x128
+    if (block) return {1, 4, 0};                                                              // 128x128
+    return S == 4 ? TileSchedule{3, 4, 0} : TileSchedule{3, 8, 2};
+}
+
 template <int SB_MODE, int WI, int WJ, int TM, int TN, int S = 2>
 struct TileCfg {
     static constexpr int kWaves = WI * WJ;
@@ -235,10 +263,11 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     const uint32_t ldsw = __builtin_amdgcn_readfirstlane(lds0 + 4 * w * 1024);
     const uint32_t ldsb = __builtin_amdgcn_readfirstlane(lds0 + C::kABytes + kBC * w * 1024);
     constexpr int kCopies = 4 + kBC;
-    // copy i of the cursor's step into the stage at LDS offset st: 4 A blocks, kBC B blocks
-    auto copy_one = [&](const uint8_t* pa, const uint8_t* pb, int crows, int i, uint32_t st) {
-        const uint32_t base = ldsw + st;
-        if (i < 4) {
+    // copy c of the cursor's step into the stage at LDS offset st: kBC B blocks, 4 A blocks
+    auto copy_one = [&](const uint8_t* pa, const uint8_t* pb, int crows, int c, uint32_t st) {
+        if (c >= kBC) {
+            const int i = c - kBC;
+            const uint32_t base = ldsw + st;
             // rows past the end of A repeat the last valid one (their outputs are never stored)
             const uint32_t row = min(lane_row + 8 * i, (uint32_t)(crows - 1));
             const uint32_t off = __umul24(row, (uint32_t)R) + (lane_chunk ^ ((i & 1) * 64));
@@ -250,7 +279,7 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
             }
         } else {
             const uint32_t bbase = ldsb + st;
-            switch (i - 4) {
+            switch (c) {
                 case 0: dma16_at<0>(bbase, pb, offB[0]); break;
                 case 1: dma16_at<1024>(bbase, pb, offB[1]); break;
                 case 2: dma16_at<2048>(bbase, pb, offB[kBC > 2 ? 2 : 0]); break;
@@ -356,15 +385,30 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         for (int n = 0; n < TN; ++n) s[n] = *reinterpret_cast<const v4f*>(sc_cols + (off ^ swap_col) + n * 256);
     };
 
+    constexpr TileSchedule kSchedule = tile_schedule<SB_MODE, TM, S>();
     constexpr int kTiles = TM * TN, kLag = 2;
     // The scale fmas of tile t-2 run next to the MFMA of tile t, far enough behind their own
     // MFMA that its result needs no wait.  FProp/DGrad: MFMA first, three result buffers.
     // WGrad (twice the VALU work, 16 more registers of column scales): fmas first, two buffers.
     constexpr bool kFmaFirst = (SB_MODE != kSbBlock);
     constexpr int kRing = kFmaFirst ? 2 : 3;
-    constexpr int kSync = (TM - 1) * TN;                 // first tile of the last row
-    constexpr int kLate = kTiles + kLag - 1 - kSync;     // operand copies issued behind the barrier, the rest at the top of the next step
+    // MFMA tile t: row by row in front of the barrier, column by column in the kTail rows behind it
+    constexpr int kTail = kSchedule.tail_rows, kHead = TM - kTail;
+    constexpr int kSync = kHead * TN;                    // the barrier stands behind the MFMA of this tile
+    auto tile_row = [](int t) { return t < kSync ? t / TN : kHead + (t - kSync) % kTail; };
+    auto tile_col = [](int t) { return t < kSync ? t % TN : (t - kSync) / kTail; };
+    // Buffer of a row's fragment: two take turns, and the rows behind the barrier beyond the first have one each.  That first row
+    // takes the buffer that the last row in front of the barrier does not have, and the next step's row 0, fetched behind the
+    // barrier, takes the other one: the last row in front of it has row 0's, so where their number is even, row 2 goes elsewhere.
+    static_assert(kHead % 2 == 1 || (kHead >= 6 && kTail >= 2), "row 2's buffer is free again when it is needed");
+    auto row_buf = [](int m) { return m > kHead ? m - kHead + 1 : kHead % 2 ? m & 1 : m < 3 ? m : (m - 3) & 1; };
+    constexpr int kLate = kSchedule.late;                // operand copies issued behind the barrier, the rest at the top of the next step
+    auto late_copy = [](int t) {                         // the one behind the MFMA of tile t, -1 if none
+        const int v = t - kSync - 1, c = v < kBC ? v : v - kSchedule.gap;
+        return v >= 0 && (v < kBC || c >= kBC) && c < kLate ? c : -1;
+    };
     static_assert(kLate >= 1 && kLate <= kCopies && kCopies - kLate <= kSync, "copy slots");
+    static_assert(kSync + kLate + (kLate > kBC ? kSchedule.gap : 0) < kTiles + kLag, "copy slots");
 
     // Vector-memory operations of a wave in step j, in their order: at the top of every fourth step the scales of chunk
     // j / 4 + 1, the rest of the operand copies of step j + S - 1, behind the barrier the first kLate operand copies of step
@@ -395,7 +439,7 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    v8i cf[TN], xf[2];
+    v8i cf[TN], xf[kTail + 1];
     RawScales next;
 #pragma unroll
     for (int n = 0; n < TN; ++n) cf[n] = col_frag(0, n);
@@ -444,7 +488,7 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
         for (int t = 0; t < kTiles + kLag; ++t) {
             auto scale_fmas = [&]() {
                 if (t < kLag) return;
-                const int u = t - kLag, m = u / TN, n = u % TN;
+                const int u = t - kLag, m = tile_row(u), n = tile_col(u);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float s = (SB_MODE == kSbBlock) ? sai[m] : sai[m] * sbj[n][e];
@@ -456,22 +500,29 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (t < kTiles) {
-                const int m = t / TN, n = t % TN;
-                pr[t % kRing] = group_product(cf[n], xf[m & 1]);
+                const int m = tile_row(t), n = tile_col(t);
+                pr[t % kRing] = group_product(cf[n], xf[row_buf(m)]);
                 // next row's fragment, fetched behind the MFMA: a fetch in front of it would be
                 // included in whatever LDS wait that MFMA's operands need
                 __builtin_amdgcn_sched_barrier(0);
-                if (n == 0 && m + 1 < TM) xf[(m + 1) & 1] = row_frag(slot, m + 1);
+                if (t < kSync && n == 0) xf[row_buf(m + 1)] = row_frag(slot, m + 1);
+                // those of the other rows behind the barrier, a row earlier where there is one
+                constexpr int kOthers = (kHead > 2 ? kHead - 2 : 0) * TN + 1;
+                if (t >= kOthers && t < kOthers + kTail - 1) {
+                    const int row = kHead + 1 + t - kOthers;
+                    xf[row_buf(row)] = row_frag(slot, row);
+                }
             }
             if (!kFmaFirst) scale_fmas();
             __builtin_amdgcn_sched_barrier(0);
             if (t == kSync) {
-                // every read of stage `slot` has returned (the MFMA above needed the last one);
+                // every read of stage `slot` has returned: the MFMA above needed the last one, or it is waited for;
                 // of this wave's copies only those of steps q+2 .. q+S-1 may still be on their way
+                if (kTail > 1) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
                 JET_WAIT_VMCNT(kYounger);
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                xf[TM & 1] = row_frag(nslot, 0);      // TM even: the buffer the last row does not use
+                xf[0] = row_frag(nslot, 0);
                 load_scales(sc_next, next);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -481,12 +532,12 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
                 for (int m = 0; m < TM; ++m) sai_n[m] = (SB_MODE == kSbBlock) ? next.a[m] * next.b_block : next.a[m];
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (t >= kSync && t < kTiles) {
-                cf[t - kSync] = col_frag(nslot, t - kSync);      // its last MFMA of this step is issued
+            if (t >= kSync && t < kTiles && tile_row(t) == TM - 1) {
+                cf[tile_col(t)] = col_frag(nslot, tile_col(t));      // its last MFMA of this step is issued
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (t > kSync) {
-                copy_one(pa, pb, crows, t - kSync - 1, st_this);          // step q+S goes into stage `slot`
+            if (late_copy(t) >= 0) {
+                copy_one(pa, pb, crows, late_copy(t), st_this);           // step q+S goes into stage `slot`
                 __builtin_amdgcn_sched_barrier(0);
             } else if (t < kCopies - kLate) {
                 copy_one(pa0, pb0, crows0, kLate + t, st_other);          // remaining copies of step q+S-1
