@@ -188,6 +188,16 @@ JET_API jet_status jet_silu_mul_bwd(const void* gate, const void* up, int64_t ld
                                     int64_t M, int64_t K, void* dgate, void* dup, int64_t ld_out,
                                     void* stream);
 
+/*
+ * The same, with the row and column quantization of dgu = [dgate | dup] formed in the same pass: dgu bf16 [M,2K] and
+ * (q_row, s_row) u8 [M,2K], f32 [M,2K/128], (q_colT, s_colT) u8 [2K,M], f32 [2K,M/128] are
+ * bit-identical to jet_silu_mul_bwd followed by jet_quant_act with both pairs.  M, K multiples of 128.
+ */
+JET_API jet_status jet_silu_mul_bwd_quant(const void* gate, const void* up, int64_t ld,
+                                const void* dh, int64_t M, int64_t K, void* dgu,
+                                uint8_t* q_row, float* s_row, uint8_t* q_colT, float* s_colT,
+                                void* stream);
+
 /* Text for a status code (static storage). */
 JET_API const char* jet_status_str(jet_status st);
 

@@ -10,7 +10,7 @@ from .binding import (JET_SRC_BF16, JET_SRC_FP8_ROW, JetError, fp8_linear_dgrad,
                       jet_fp8_linear_wgrad, jet_quant_act, jet_quant_weight, jet_status_str,
                       jet_version, lib, quant_act, quant_weight,
                       jet_rmsnorm_quant, jet_silu_mul_quant, rmsnorm_quant, silu_mul_quant,
-                      jet_silu_mul_bwd, silu_mul_bwd)
+                      jet_silu_mul_bwd, silu_mul_bwd, jet_silu_mul_bwd_quant, silu_mul_bwd_quant)
 
 __all__ = [
     "JET_SRC_BF16", "JET_SRC_FP8_ROW", "JetError", "lib", "jet_version", "jet_status_str",
@@ -18,4 +18,5 @@ __all__ = [
     "jet_fp8_linear_wgrad", "quant_act", "quant_weight", "fp8_linear_fwd", "fp8_linear_dgrad",
     "fp8_linear_wgrad", "jet_rmsnorm_quant",
     "jet_silu_mul_quant", "rmsnorm_quant", "silu_mul_quant", "jet_silu_mul_bwd", "silu_mul_bwd",
+    "jet_silu_mul_bwd_quant", "silu_mul_bwd_quant",
 ]

@@ -60,6 +60,8 @@ def lib() -> ctypes.CDLL:
         L.jet_rmsnorm_quant.argtypes = [vp, vp, ctypes.c_float, i64, i64, vp, vp, vp]
         L.jet_silu_mul_quant.restype = i32
         L.jet_silu_mul_quant.argtypes = [vp, vp, i64, i64, i64, vp, vp, vp]
+        L.jet_silu_mul_bwd_quant.restype = i32
+        L.jet_silu_mul_bwd_quant.argtypes = [vp, vp, i64, vp, i64, i64, vp, vp, vp, vp, vp, vp]
         L.jet_silu_mul_bwd.restype = i32
         L.jet_silu_mul_bwd.argtypes = [vp, vp, i64, vp, i64, i64, vp, vp, i64, vp]
         L.jet_status_str.restype = ctypes.c_char_p
@@ -133,6 +135,10 @@ def jet_rmsnorm_quant(x, gamma, eps, M, K, q_row, s_row, stream) -> int:
 
 def jet_silu_mul_quant(gate, up, ld, M, K, q_row, s_row, stream) -> int:
     return int(lib().jet_silu_mul_quant(gate, up, ld, M, K, q_row, s_row, stream))
+
+
+def jet_silu_mul_bwd_quant(gate, up, ld, dh, M, K, dgu, q_row, s_row, q_colT, s_colT, stream) -> int:
+    return int(lib().jet_silu_mul_bwd_quant(gate, up, ld, dh, M, K, dgu, q_row, s_row, q_colT, s_colT, stream))
 
 
 def jet_silu_mul_bwd(gate, up, ld, dh, M, K, dgate, dup, ld_out, stream) -> int:
@@ -287,6 +293,29 @@ def silu_mul_bwd(gate: torch.Tensor, up: torch.Tensor, dh: torch.Tensor, out: to
     if st:
         raise JetError(st, "jet_silu_mul_bwd")
     return dgu
+
+
+def silu_mul_bwd_quant(gate: torch.Tensor, up: torch.Tensor, dh: torch.Tensor) -> tuple:
+    """silu_mul_bwd and quant_act(dgu, row=True, col=True) in one pass: (dgu, dict(q_row, s_row, q_colT, s_colT))."""
+    for t, name in ((gate, "gate"), (up, "up")):
+        if not t.is_cuda or t.dtype != torch.bfloat16 or t.dim() != 2 or t.stride(1) != 1:
+            raise TypeError(f"{name}: need a 2-D CUDA bf16 tensor with unit column stride")
+    if gate.shape != up.shape or gate.stride(0) != up.stride(0):
+        raise TypeError("gate and up need one shape and one row stride")
+    _need(dh, torch.bfloat16, "dh")
+    M, K = gate.shape
+    if tuple(dh.shape) != (M, K):
+        raise ValueError("dh: need the shape of gate")
+    _same_device(gate, up=up, dh=dh)
+    new = lambda rows, cols, dtype: torch.empty((rows, cols), dtype=dtype, device=gate.device)
+    dgu = new(M, 2 * K, torch.bfloat16)
+    o = dict(q_row=new(M, 2 * K, torch.uint8), s_row=new(M, max(2 * K // GROUP, 1), torch.float32),
+             q_colT=new(2 * K, M, torch.uint8), s_colT=new(2 * K, max(M // GROUP, 1), torch.float32))
+    st = jet_silu_mul_bwd_quant(_ptr(gate), _ptr(up), gate.stride(0), _ptr(dh), M, K, _ptr(dgu), _ptr(o["q_row"]),
+                                _ptr(o["s_row"]), _ptr(o["q_colT"]), _ptr(o["s_colT"]), _stream())
+    if st:
+        raise JetError(st, "jet_silu_mul_bwd_quant")
+    return dgu, o
 
 
 def quant_weight(w: torch.Tensor, transposed: bool = False, out: tuple | None = None):

@@ -13,7 +13,7 @@ PROBE_LIB = os.path.join(HERE, "libjet_probe.so")     # measurement aid of bench
 HOST_LIB = os.path.join(HERE, "_jet_host.so")         # native marshalling of the tensor helpers (host code only)
 SOURCES = ["jet_api.hip", "jet_quant.hip", "jet_fused.hip", "jet_gemm.hip"]
 PROBE_SOURCES = ["jet_probe.hip"]
-HEADERS = ["jet_internal.h", "jet_numerics.h", "jet_plan.h", os.path.join("..", "..", "include", "jet.h")]
+HEADERS = ["jet_internal.h", "jet_numerics.h", "jet_plan.h", "jet_tile_quant.h", os.path.join("..", "..", "include", "jet.h")]
 
 # No fast-math: divisions, products and fmas must be the IEEE binary32 operations.
 # Packed-fp32 instructions are switched off for the device compiler.

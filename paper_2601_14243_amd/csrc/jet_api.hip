@@ -112,6 +112,19 @@ jet_status jet_silu_mul_bwd(const void* gate, const void* up, int64_t ld, const 
     return after_launch(jet::launch_silu_mul_bwd(gate, up, ld, dh, M, K, dgate, dup, ld_out, static_cast<hipStream_t>(stream)));
 }
 
+jet_status jet_silu_mul_bwd_quant(const void* gate, const void* up, int64_t ld, const void* dh, int64_t M, int64_t K, void* dgu,
+                                  uint8_t* q_row, float* s_row, uint8_t* q_colT, float* s_colT, void* stream) {
+    if (!gate || !up || !dh || !dgu || !q_row || !s_row || !q_colT || !s_colT) return JET_ERR_NULL;
+    if (M < 1 || K < 1 || M % 128 || K % 128 || ld < K || ld % 8) return JET_ERR_SHAPE;
+    if (M > 65535LL * 128 || K > INT32_MAX / 4 || ld > INT32_MAX / 2) return JET_ERR_SHAPE;
+    if (misaligned(gate) || misaligned(up) || misaligned(dh) || misaligned(dgu) || misaligned(q_row) || misaligned(s_row) ||
+        misaligned(q_colT) || misaligned(s_colT))
+        return JET_ERR_ALIGN;
+    discard_stale_error();
+    return after_launch(jet::launch_silu_mul_bwd_quant(gate, up, ld, dh, M, K, dgu, q_row, s_row, q_colT, s_colT,
+                                                       static_cast<hipStream_t>(stream)));
+}
+
 const char* jet_status_str(jet_status st) {
     switch (st) {
         case JET_OK: return "ok";

@@ -22,6 +22,8 @@ hipError_t launch_silu_mul_quant(const void* gate, const void* up, long ld, long
 // element-wise backward of h = SiLU(gate) * up in bf16 semantics: dgate, dup from dh
 hipError_t launch_silu_mul_bwd(const void* gate, const void* up, long ld, const void* dh, long M, long K,
                                void* dgate, void* dup, long ld_out, hipStream_t st);
+hipError_t launch_silu_mul_bwd_quant(const void* gate, const void* up, long ld, const void* dh, long M, long K, void* dgu,
+                                     uint8_t* q_row, float* s_row, uint8_t* q_colT, float* s_colT, hipStream_t st);
 hipError_t launch_rmsnorm_quant(const void* x, const void* gamma, float eps, long M, long K, uint8_t* q,
                                 float* s, hipStream_t st);
 

@@ -45,6 +45,10 @@ __device__ __forceinline__ uint4 load16_nt(const void* p) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(static_cast<const u32x4*>(p)));
 }
+__device__ __forceinline__ void store16_nt(void* p, uint4 v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), static_cast<u32x4*>(p));
+}
 __device__ __forceinline__ uint2 load8_nt(const void* p) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint2, __builtin_nontemporal_load(static_cast<const u32x2*>(p)));

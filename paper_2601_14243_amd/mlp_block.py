@@ -10,12 +10,18 @@ so their output is one [M, 2 I] tensor and their backward is one DGrad and one W
     forward :  x --row quant--> (qx)  --FProp W_gu-->  gu  --SiLU*mul, row quant--> (qh)  --FProp W_d-->  y
     saved   :  qx (FP8 + scales), gu (bf16, input of the element-wise operator), qh (FP8 + scales)
     backward:  dy --row+col quant--> DGrad W_d^T --> dh ;  WGrad(dy^T, qh^T) --> dW_d
-               (gu, dh) --SiLU*mul backward--> dgu --row+col quant--> DGrad W_gu^T --> dx ;
+               (gu, dh) --SiLU*mul backward, row+col quant--> dgu, qdgu --> DGrad W_gu^T --> dx ;
                WGrad(dgu^T, qx^T) --> dW_gu
 """
 from __future__ import annotations
 
 from . import binding as jet
+
+# The gate/up gradient is quantized where it is formed from four 128x128 tiles per CU on: one pass over memory less, but half as many
+# workgroups with three times the work.  Two calls / one, us (captured): 16384x14336 907 / 760 (one by one), 4096x14336 224 / 201,
+# 1024x27648 101 / 97, 8192x3072 91 / 88; below the line 1024x14336 59.1 / 59.3, 4096x3072 52 / 46, 1024x5120 28.5 / 30.0,
+# 512x3072 14.4 / 18.8.
+QUANT_IN_BWD_FROM = 4 * 256 * 128 * 128
 
 
 class MlpWeights:
@@ -53,8 +59,11 @@ def backward(saved, dy, w: MlpWeights):
     dh = jet.fp8_linear_dgrad(qdy["q_row"], qdy["s_row"], w.d[2], w.d[3])
     qhT = jet.quant_act(qh["q_row"], qh["s_row"], row=False, col=True)
     dw_d = jet.fp8_linear_wgrad(qdy["q_colT"], qdy["s_colT"], qhT["q_colT"], qhT["s_colT"])
-    dgu = jet.silu_mul_bwd(gu[:, :I], gu[:, I:], dh)
-    qdgu = jet.quant_act(dgu, row=True, col=True)
+    if dh.numel() >= QUANT_IN_BWD_FROM:
+        dgu, qdgu = jet.silu_mul_bwd_quant(gu[:, :I], gu[:, I:], dh)
+    else:
+        dgu = jet.silu_mul_bwd(gu[:, :I], gu[:, I:], dh)
+        qdgu = jet.quant_act(dgu, row=True, col=True)
     dx = jet.fp8_linear_dgrad(qdgu["q_row"], qdgu["s_row"], w.gu[2], w.gu[3])
     qxT = jet.quant_act(qx["q_row"], qx["s_row"], row=False, col=True)
     dw_gu = jet.fp8_linear_wgrad(qdgu["q_colT"], qdgu["s_colT"], qxT["q_colT"], qxT["s_colT"])

@@ -113,6 +113,16 @@ def test_fused_producer_argument_errors(L):
     assert b.jet_silu_mul_quant(A, A + 8, 256, 4, 128, A, A, None) == ALIGN
 
 
+def test_silu_mul_bwd_quant_argument_errors(L):
+    from paper_2601_14243_amd import binding as b
+    good = [A, A, 128, A, 128, 128, A, A, A, A, A, None]
+    for i in (0, 1, 3, 6, 7, 8, 9, 10):
+        assert b.jet_silu_mul_bwd_quant(*good[:i], None, *good[i + 1:]) == NULL
+        assert b.jet_silu_mul_bwd_quant(*good[:i], A + 8, *good[i + 1:]) == ALIGN
+    for i, v in ((2, 64), (2, 132), (4, 0), (4, 64), (4, 65536 * 128), (5, 0), (5, 200)):
+        assert b.jet_silu_mul_bwd_quant(*good[:i], v, *good[i + 1:]) == SHAPE
+
+
 def test_silu_mul_bwd_argument_errors(L):
     from paper_2601_14243_amd import binding as b
     assert b.jet_silu_mul_bwd(None, A, 128, A, 4, 128, A, A, 256, None) == NULL

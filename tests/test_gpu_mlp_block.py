@@ -85,6 +85,31 @@ def test_silu_mul_bwd_shapes_and_strides(jet, M, K, fused):
     _same_or_zero("dgate", got[:, :K], want_g)
 
 
+@pytest.mark.parametrize("M,K,fused", [(128, 128, False), (128, 384, True), (384, 128, True), (256, 1152, False)])
+def test_silu_mul_bwd_quant_equals_its_parts(jet, M, K, fused):
+    """The bytes of the operator and of the two quantizations against the oracle's, with gates on both sides of |g| = 80
+    (binary64), a tile of zeros in dgate and dup, and rows whose scale leaves the plain divider."""
+    both = ji.mlp_intermediate(M, K, seed=1500 + M + K)
+    dh = ji.grads(M, K, seed=1600 + M)
+    both[:, ::13] = ji.f32_to_bf16_bits(np.linspace(-95, 95, M, dtype=np.float32))[:, None]
+    dh[:, 1:128] = ji.f32_to_bf16_bits(ji.bf16_bits_to_f32(dh[:, 1:128]) * np.float32(2.0 ** -60))
+    dh[3] = 0
+    dh[:128, K - 128:] = 0
+    want_g, want_u = orc.silu_mul_bwd(both[:, :K], both[:, K:], dh)
+    if fused:
+        t = dev_bf16(both)
+        gate, up = t[:, :K], t[:, K:]
+    else:
+        gate, up = dev_bf16(np.ascontiguousarray(both[:, :K])), dev_bf16(np.ascontiguousarray(both[:, K:]))
+    dgu, q = jet.silu_mul_bwd_quant(gate, up, dev_bf16(dh))
+    dgu = host_bits(dgu)
+    _same("dup", dgu[:, K:], want_u)
+    _same_or_zero("dgate", dgu[:, :K], want_g)
+    want = orc.quant_act(dgu, row=True, col=True)
+    for k in ("q_row", "s_row", "q_colT", "s_colT"):
+        assert np.array_equal(host(q[k]), want[k]), k
+
+
 def _oracle_block(x, w_gu, w_d, dy, I):
     """The block in the oracle's own arithmetic, end to end (its GEMM results in reference order)."""
     qx = orc.quant_act(x)
