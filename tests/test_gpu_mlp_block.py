@@ -70,6 +70,26 @@ def test_silu_mul_bwd_every_gate_value_with_every_significand(jet):
     _same("dgate", got[:, :K], want_g)
 
 
+def test_silu_mul_bwd_of_zero_and_tiny_gradients(jet):
+    """Gradients of both zeros, and products on either side of 2^-125, where binary64 takes over, with every gate value
+    whose product is formed in binary32: every bit, the sign of a zero included."""
+    bits = np.arange(0, 0x42A1, dtype=np.uint32)
+    bits = np.concatenate([bits, bits | 0x8000])
+    bits = np.concatenate([bits, np.zeros(-len(bits) % 128, np.uint32)]).astype(np.uint16)
+    K = len(bits)
+    rows = [0x0000, 0x8000] + [(127 - e) << 7 | m for e in (100, 110, 118, 122, 123, 124, 125) for m in (0x00, 0x2B, 0x7F)]
+    dh = np.tile(np.array(rows, np.uint16)[:, None], (1, K))
+    dh[2:, 1::2] |= 0x8000
+    dh[:2, 5::16] = 0x3F80                                # a lane holds zeros beside other values
+    M = len(rows)
+    gate, up = np.tile(bits, (M, 1)), np.full((M, K), 0x3F80, np.uint16)
+    up[:, 2::4] = 0xBF80
+    want_g, want_u = orc.silu_mul_bwd(gate, up, dh)
+    got = host_bits(jet.silu_mul_bwd(dev_bf16(gate), dev_bf16(up), dev_bf16(dh)))
+    _same("dup", got[:, K:], want_u)
+    _same("dgate", got[:, :K], want_g)
+
+
 @pytest.mark.parametrize("M,K,fused", [(256, 1024, True), (1, 128, False), (77, 384, True), (513, 3584, True)])
 def test_silu_mul_bwd_shapes_and_strides(jet, M, K, fused):
     both = ji.mlp_intermediate(M, K, seed=1200 + M + K)
