@@ -108,14 +108,26 @@ def test_silu_mul_bwd_shapes_and_strides(jet, M, K, fused):
 @pytest.mark.parametrize("M,K,fused", [(128, 128, False), (128, 384, True), (384, 128, True), (256, 1152, False)])
 def test_silu_mul_bwd_quant_equals_its_parts(jet, M, K, fused):
     """The bytes of the operator and of the two quantizations against the oracle's, with gates on both sides of |g| = 80
-    (binary64), a tile of zeros in dgate and dup, and rows whose scale leaves the plain divider."""
+    (binary64), a row of zeros and, where there are several tiles, a tile of them in dgate and dup, and rows and columns
+    whose scale leaves the plain divider."""
     both = ji.mlp_intermediate(M, K, seed=1500 + M + K)
     dh = ji.grads(M, K, seed=1600 + M)
-    both[:, ::13] = ji.f32_to_bf16_bits(np.linspace(-95, 95, M, dtype=np.float32))[:, None]
-    dh[:, 1:128] = ji.f32_to_bf16_bits(ji.bf16_bits_to_f32(dh[:, 1:128]) * np.float32(2.0 ** -60))
+    both[:, ::13] = ji.f32_to_bf16_bits(np.resize(np.linspace(-95, 95, 64, dtype=np.float32), M))[:, None]
+    tiny = np.zeros((M, K), bool)
+    tiny[2::9] = True
+    tiny[:, [5, 70, K - 1]] = True
+    dh[tiny] = ji.f32_to_bf16_bits(ji.bf16_bits_to_f32(dh[tiny]) * np.float32(2.0 ** -85))
     dh[3] = 0
-    dh[:128, K - 128:] = 0
+    if M * K > 128 * 128:
+        dh[:128, K - 128:] = 0
     want_g, want_u = orc.silu_mul_bwd(both[:, :K], both[:, K:], dh)
+    want_q = orc.quant_act(np.concatenate([want_g, want_u], axis=1), row=True, col=True)
+    # what the cases are there for
+    g = ji.bf16_bits_to_f32(both[:, :K])
+    assert ((want_g & 0x7FFF) != 0).mean() > 0.3 and ((want_u & 0x7FFF) != 0).mean() > 0.3
+    assert (want_q["s_row"] < 2.0 ** -80).any() and (want_q["s_row"] > 2.0 ** -40).any()
+    assert (want_q["s_colT"] < 2.0 ** -80).any() and (want_q["s_colT"] > 2.0 ** -40).any()
+    assert ((g > 80) & (dh != 0)).any() and ((g < -80) & (dh != 0)).any()
     if fused:
         t = dev_bf16(both)
         gate, up = t[:, :K], t[:, K:]
