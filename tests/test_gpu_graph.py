@@ -23,8 +23,13 @@ def _bits(t):
     return t.contiguous().view(torch.int16)
 
 
-def test_mlp_block_forward_and_backward_replayed_from_a_graph(jet):
+@pytest.mark.parametrize("one_call", [False, True])
+def test_mlp_block_forward_and_backward_replayed_from_a_graph(jet, one_call, monkeypatch):
+    """one_call: the route of large blocks, where the gradient of the element-wise operator is quantized where it is formed."""
     from paper_2601_14243_amd import mlp_block
+    if one_call:
+        monkeypatch.setattr(mlp_block, "QUANT_IN_BWD_FROM", 0)
+        monkeypatch.delattr(mlp_block.jet, "silu_mul_bwd")
     M, H, I = 256, 512, 1024
     w = mlp_block.MlpWeights(dev_bf16(ji.weights(2 * I, H, 11)), dev_bf16(ji.weights(H, I, 12)))
     inputs = [(dev_bf16(ji.activations(M, H, 20 + i)), dev_bf16(ji.grads(M, H, 30 + i))) for i in range(3)]

@@ -142,6 +142,45 @@ def test_silu_mul_bwd_quant_equals_its_parts(jet, M, K, fused):
         assert np.array_equal(host(q[k]), want[k]), k
 
 
+@pytest.mark.parametrize("M,K", [(4096, 4096), (1152, 14976)])
+def test_silu_mul_bwd_quant_of_many_tiles_equals_the_two_calls(jet, M, K):
+    """As many workgroups as the MLP block calls it with (1024 and 1053 tiles: several rounds of the CUs, an odd number of
+    tiles a row), against silu_mul_bwd and quant_act on the device, which the tests hold against the oracle."""
+    gen = torch.Generator(device="cuda").manual_seed(1700 + M)
+    gu = torch.randn((M, 2 * K), generator=gen, device="cuda").mul_(2).bfloat16()
+    dh = torch.randn((M, K), generator=gen, device="cuda").mul_(1e-3).bfloat16()
+    dh[M // 2:M // 2 + 200] = 0
+    dgu, q = jet.silu_mul_bwd_quant(gu[:, :K], gu[:, K:], dh)
+    want = jet.silu_mul_bwd(gu[:, :K], gu[:, K:], dh)
+    assert torch.equal(dgu.view(torch.int16), want.view(torch.int16))
+    want_q = jet.quant_act(want, row=True, col=True)
+    for k in ("q_row", "s_row", "q_colT", "s_colT"):
+        assert torch.equal(q[k], want_q[k]), k
+
+
+@pytest.mark.parametrize("M,one_call", [(3968, False), (4096, True)])
+def test_mlp_block_backward_is_the_same_on_either_side_of_the_line(jet, M, one_call, monkeypatch):
+    """The route that the size takes (992 and 1024 tiles of dh), and every tensor that backward returns against the other route."""
+    from paper_2601_14243_amd import mlp_block
+    H, I = 256, 4096
+    w = mlp_block.MlpWeights(dev_bf16(ji.weights(2 * I, H, 1801)), dev_bf16(ji.weights(H, I, 1802)))
+    _, saved = mlp_block.forward(dev_bf16(ji.activations(M, H, 1803)), w)
+    dy = dev_bf16(ji.grads(M, H, 1804))
+    calls, fused = [], mlp_block.jet.silu_mul_bwd_quant
+    monkeypatch.setattr(mlp_block.jet, "silu_mul_bwd_quant", lambda *a: calls.append(1) or fused(*a))
+    got = mlp_block.backward(saved, dy, w)
+    assert len(calls) == one_call
+    monkeypatch.setattr(mlp_block, "QUANT_IN_BWD_FROM", 1 << 62 if one_call else 0)
+    want = mlp_block.backward(saved, dy, w)
+    assert len(calls) == 1 and set(got) == set(want)
+    for name in got:
+        a, b = got[name], want[name]
+        assert (set(a) == set(b)) if isinstance(a, dict) else True, name
+        for k in (a if isinstance(a, dict) else [None]):
+            x, y = (a, b) if k is None else (a[k], b[k])
+            assert x.shape == y.shape and x.dtype == y.dtype and torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (name, k)
+
+
 def _oracle_block(x, w_gu, w_d, dy, I):
     """The block in the oracle's own arithmetic, end to end (its GEMM results in reference order)."""
     qx = orc.quant_act(x)
@@ -168,8 +207,13 @@ def _rel(a_bits, b):
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
-def test_mlp_block_forward_and_backward(jet):
+@pytest.mark.parametrize("one_call", [False, True])
+def test_mlp_block_forward_and_backward(jet, one_call, monkeypatch):
+    """one_call: the route of large blocks, where the gradient of the element-wise operator is quantized where it is formed."""
     from paper_2601_14243_amd import mlp_block
+    if one_call:
+        monkeypatch.setattr(mlp_block, "QUANT_IN_BWD_FROM", 0)
+        monkeypatch.delattr(mlp_block.jet, "silu_mul_bwd")
     M, H, I = 256, 512, 1024
     x = ji.activations(M, H, 1401)
     w_gu = ji.weights(2 * I, H, 1402)
