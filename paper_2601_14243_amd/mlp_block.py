@@ -17,11 +17,17 @@ from __future__ import annotations
 
 from . import binding as jet
 
-# The gate/up gradient is quantized where it is formed from four 128x128 tiles per CU on: one pass over memory less, but half as many
-# workgroups with three times the work.  Two calls / one, us (captured): 16384x14336 907 / 760 (one by one), 4096x14336 224 / 201,
-# 1024x27648 101 / 97, 8192x3072 91 / 88; below the line 1024x14336 59.1 / 59.3, 4096x3072 52 / 46, 1024x5120 28.5 / 30.0,
-# 512x3072 14.4 / 18.8.
-QUANT_IN_BWD_FROM = 4 * 256 * 128 * 128
+# The gate/up gradient is quantized where it is formed from 1024 tiles of 128x128 on: one pass over memory less, but half as many
+# workgroups with three times the work.  Two calls / one, us on 256 CUs, captured and (called one by one), by tiles:
+#   96    512x3072   13.4 / 18.8  (15.4 / 23.3)     640   2048x5120   45.1 / 43.5  (40.9 / 43.0)    1536   8192x3072   90.8 / 86.1  (85.1 / 81.0)
+#   192   1024x3072  19.3 / 20.4  (20.7 / 23.3)     768   4096x3072   51.6 / 47.1  (47.5 / 45.8)    1728   1024x27648  105 / 95.7   (98.4 / 89.3)
+#   320   1024x5120  27.9 / 29.7  (26.7 / 30.0)     864   512x27648   57.4 / 56.3  (52.3 / 55.2)    1792   2048x14336  107 / 97.6   (101 / 89.9)
+#   384   2048x3072  31.0 / 31.3  (29.4 / 31.4)     896   1024x14336  59.5 / 57.2  (54.3 / 55.1)    3584   4096x14336  220 / 190    (219 / 161)
+#   448   512x14336  33.9 / 32.4  (32.4 / 31.7)    1024   2048x8192   67.6 / 61.1  (59.3 / 59.5)   14336  16384x14336  880 / 726    (840 / 627)
+#   512   1024x8192  36.9 / 34.1  (35.0 / 33.6)    1024   16384x1024  66.7 / 60.8  (60.1 / 56.9)
+# Below 400 tiles one call loses; from there to the line it is 2 to 9 % faster in a captured block and 5 % faster to 6 % slower in one
+# that is not, where the second call's launch hides behind the first; from the line on neither loses.
+QUANT_IN_BWD_FROM = 1024 * 128 * 128
 
 
 class MlpWeights:
