@@ -411,10 +411,11 @@ void gemm_tile_kernel(const uint8_t* __restrict__ A, const float* __restrict__ s
     static_assert(kSync + kLate + (kLate > kBC ? kSchedule.gap : 0) < kTiles + kLag, "copy slots");
 
     // Vector-memory operations of a wave in step j, in their order: at the top of every fourth step the scales of chunk
-    // j / 4 + 1, the rest of the operand copies of step j + S - 1, behind the barrier the first kLate operand copies of step
-    // j + S, behind a tile's last step its stores.  The scales of chunk c (steps 4c .. 4c + 3) are first read behind
-    // the barrier of step 4c - 1, which waits for the operands of step 4c, whose last copies are issued in step
-    // 4c + 1 - S >= 4c - 3, behind the scales.  Their buffer held chunk c - 2, last read in step 4c - 5.
+    // j / 4 + 1, the rest of the operand copies of step j + S - 1 (none where all are late), behind the barrier the first kLate
+    // operand copies of step j + S, behind a tile's last step its stores.  The scales of chunk c (steps 4c .. 4c + 3) are issued at
+    // the top of step 4c - 4 and first read behind the barrier of step 4c - 1, which waits for the operands of step 4c.  The last
+    // copy of those is issued at the top of step 4c + 1 - S >= 4c - 3, or, where all are late, behind the barrier of step
+    // 4c - S >= 4c - 4: behind the scales in either case.  Their buffer held chunk c - 2, last read in step 4c - 5.
     constexpr int kYounger = (S - 2) * kCopies;      // at the barrier of step q, behind the copies of step q + 1 (at least)
     // ---- prologue: chunk 0, operands of steps 0 .. S - 1 (of the last the first kLate) ----
     int first_i0, first_j0;
