@@ -110,8 +110,14 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 // (256 registers: no room for a tail of three) 28672x4096 over 16384 tokens 1886 / 1789, 5120x5120 over 6016 183 / 172.  256x128
 // 1024x5120x27648 195 / 180, 700x7168x5120 42.6 / 40.0.  128x128 WGrad 1024x5120 over 16384 tokens 157 / 144, four stages 1024x4096
 // 94.5 / 91.  128x128 block scales, one wave per SIMD: waits for its copies and not for the LDS, so a longer tail, which shortens
-// their lead, is 1-3 % slower.  fma lag 3: a wave alone on its SIMD issues an MFMA every 34.5 cycles instead of 39 in a
-// register-only loop, two waves 3 % more of them; in the kernel nothing (one wave waits for its copies) or up to 2 % slower.
+// their lead, is 1-3 % slower.  Four late copies and not five: 8 shapes with four stages 0 to 2.6 % faster (777x4096x4096 24.5 -> 24.0).
+// Two stages, the columns' operand first: 28 shapes 2.3 % faster on average than the rows' first (3619x17280x640 77.3 -> 74.4,
+// 7645x5248x2560 135.6 -> 132.8) and none slower by more than 0.4 %, where the rows' operand is in the caches, as the operator in front leaves it; from HBM
+// too, 1.7 %, and up to 3.5 % slower where a last round of a few tiles runs alone on its CUs (4821x3456x4608 106.9 -> 110.6).
+// 128x64, two late copies and not five: 3.1 to 4.1 % faster on 7 shapes (256x8192x1024 7.82 -> 7.52), the columns' operand first alone
+// the same or 1 % slower.  256x256 on one block of rows: 256x55296x5120 91.3 -> 87.2, with its rows from HBM as well 94.3 -> 98.7.
+// fma lag 3: a wave alone on its SIMD issues an MFMA every 34.5 cycles instead of 39 in a register-only loop, two waves 3 % more of
+// them; in the kernel nothing (one wave waits for its copies) or up to 2 % slower.
 //
 // LDS: S stages [A tile BM*128][B tile BN*128], then two chunks of scales
 //   tile: 1 KB block per 8 rows, copied by one instruction that moves 8 whole 128-byte
@@ -793,7 +799,10 @@ __global__ __launch_bounds__(64 * kSkWaves) void gemm_skinny_kernel(const uint8_
 // there are fewer barriers: 2-8 % over a step of one or two groups.  The activations of a step go out in front of its weights:
 // hits in front of misses do not wait for them (28 shapes of 32 to 256 rows from HBM 1.5 % faster than behind them, us:
 // 4096x4096 32 rows 7.35 -> 7.07, 128 rows 9.29 -> 8.85; 4096x14336 128 rows 24.4 -> 23.6; 5120x27648 256 rows 75.9 -> 74.3;
-// none slower; block by block in turn as slow as the weights first).  The copying loop is
+// block by block in turn as slow as the weights first).  336 shapes of 17 to 600 rows and 16 matrices, activations in the caches:
+// 1.7 % faster on average where the weights are read past the caches (118 shapes, at worst 17x4096x4096 6.9 -> 7.2 and 48 to 90 rows
+// of 28672x4096 2 % slower), 1.7 % through them beside a partly filled row block (161, at worst 1.2 % slower), 0.5 % below 16 MB (57);
+// activations from HBM as well 2.4, 0.5 and -0.2 %, at worst 150x4096x28672 58.3 -> 59.9.  The copying loop is
 // straight-line (a compare chain for the wait and a branch per copy cost 0.3 us per step), and the fetch stays in front
 // of the MFMAs by scheduling barriers.  Every output element takes the chain of the other kernels.
 // From HBM, against the strip kernel of 64x32 and 32x32 tiles and the 128x128 tiles before it (us): 4096x14336 77 rows
