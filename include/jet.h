@@ -23,8 +23,10 @@
  *     before anything is launched; on error nothing is written.
  *   - Sizes: every dimension at most 2^30; the reduction length of a GEMM (K for
  *     FProp, N for DGrad, M for WGrad) below 2^24; the row count of a tensor that
- *     is quantized in 128x128 tiles (jet_quant_weight, and jet_quant_act whenever
- *     the colT pair is requested) at most 65535 * 128.  Otherwise: JET_ERR_SHAPE.
+ *     is quantized in 128x128 tiles (jet_quant_weight, jet_silu_mul_bwd_quant, and
+ *     jet_quant_act whenever the colT pair is requested) at most 65535 * 128; the K of
+ *     jet_silu_mul_bwd_quant, half a row of its output, below 2^29.  Otherwise:
+ *     JET_ERR_SHAPE.
  *   - JET_ERR_LAUNCH reports the status of this call's own launch only: an error
  *     left pending by the caller's earlier HIP calls is discarded first.
  *   - Inputs must be finite (NaN / Inf: no fault, result unspecified).
@@ -191,7 +193,8 @@ JET_API jet_status jet_silu_mul_bwd(const void* gate, const void* up, int64_t ld
 /*
  * The same, with the row and column quantization of dgu = [dgate | dup] formed in the same pass: dgu bf16 [M,2K] and
  * (q_row, s_row) u8 [M,2K], f32 [M,2K/128], (q_colT, s_colT) u8 [2K,M], f32 [2K,M/128] are
- * bit-identical to jet_silu_mul_bwd followed by jet_quant_act with both pairs.  M, K multiples of 128.
+ * bit-identical to jet_silu_mul_bwd followed by jet_quant_act with both pairs.  All outputs are required; M, K
+ * multiples of 128, ld as above.  From version 102 on.
  */
 JET_API jet_status jet_silu_mul_bwd_quant(const void* gate, const void* up, int64_t ld,
                                 const void* dh, int64_t M, int64_t K, void* dgu,

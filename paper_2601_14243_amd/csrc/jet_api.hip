@@ -116,7 +116,7 @@ jet_status jet_silu_mul_bwd_quant(const void* gate, const void* up, int64_t ld, 
                                   uint8_t* q_row, float* s_row, uint8_t* q_colT, float* s_colT, void* stream) {
     if (!gate || !up || !dh || !dgu || !q_row || !s_row || !q_colT || !s_colT) return JET_ERR_NULL;
     if (M < 1 || K < 1 || M % 128 || K % 128 || ld < K || ld % 8) return JET_ERR_SHAPE;
-    if (M > 65535LL * 128 || K > INT32_MAX / 4 || ld > INT32_MAX / 2) return JET_ERR_SHAPE;
+    if (M > kMaxTileRows || K > INT32_MAX / 4 || ld > INT32_MAX / 2) return JET_ERR_SHAPE;
     if (misaligned(gate) || misaligned(up) || misaligned(dh) || misaligned(dgu) || misaligned(q_row) || misaligned(s_row) ||
         misaligned(q_colT) || misaligned(s_colT))
         return JET_ERR_ALIGN;
@@ -137,6 +137,6 @@ const char* jet_status_str(jet_status st) {
     return "unknown status";
 }
 
-int jet_version(void) { return 101; }
+int jet_version(void) { return 102; }
 
 }  // extern "C"

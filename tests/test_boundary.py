@@ -115,12 +115,15 @@ def test_fused_producer_argument_errors(L):
 
 def test_silu_mul_bwd_quant_argument_errors(L):
     from paper_2601_14243_amd import binding as b
+    assert b.jet_version() >= 102                        # the first version with this call
     good = [A, A, 128, A, 128, 128, A, A, A, A, A, None]
     for i in (0, 1, 3, 6, 7, 8, 9, 10):
         assert b.jet_silu_mul_bwd_quant(*good[:i], None, *good[i + 1:]) == NULL
         assert b.jet_silu_mul_bwd_quant(*good[:i], A + 8, *good[i + 1:]) == ALIGN
-    for i, v in ((2, 64), (2, 132), (4, 0), (4, 64), (4, 65536 * 128), (5, 0), (5, 200)):
+    for i, v in ((2, 64), (2, 132), (4, 0), (4, 64), (4, 65536 * 128), (5, 0), (5, 200), (2, 1 << 30)):
         assert b.jet_silu_mul_bwd_quant(*good[:i], v, *good[i + 1:]) == SHAPE
+    K = 1 << 29                                          # a row of the output has 2 K elements
+    assert b.jet_silu_mul_bwd_quant(A, A, K, A, 128, K, A, A, A, A, A, None) == SHAPE
 
 
 def test_silu_mul_bwd_argument_errors(L):
