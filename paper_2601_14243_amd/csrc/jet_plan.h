@@ -95,10 +95,12 @@ constexpr int chunk_swap(int r) { return 16 * (r >> 3); }
 // ring fill, drain, output and half a launch gap).  The table's times were fitted to every tile on 34 matrices (128 to
 // 55296 columns, 256 to 27648 long, 17 to 4096 rows, weights from HBM and from the caches, 2366 shapes), such that the
 // choice and not the time comes out right: it was 0.7 % from the best tile on average.  They were fitted before the tile kernel's
-// scales travelled in chunks and the panels' weights past the caches.  With both (448 cases, 16 matrices of 1024 to 55296 columns,
-// 20 to 1000 rows): from HBM 0.7 % from the best on average, 10 of 224 above 5 %, worst 100x11008x2048 12 % and 140 rows of
-// 5120 columns x 5120 and 27648 9 and 10 % (48x64, not 64x64); from the caches 1.6 %, 23 above 5 %, worst 24 % where the
-// 128x112 panel reads a resident matrix past them (100x28672x4096 28.9 us, 128x128 tiles 23.3).  The cost before, rounds x
+// scales travelled in chunks and its steps took their present order, and before the panels read weights past the caches and
+// activations first.  On these kernels, activations in the caches: weights from HBM (256 cases, 16 matrices of 1024 to 55296
+// columns, 20 to 1000 rows) 1.0 % from the best on average, 10 above 5 %, worst 100x11008x2048 8 % (128x64, not 64x112) and 140 rows of
+// 5120 columns x 5120 and 27648 6 and 5 % (64x64, not 48x64), and 400 to 700 rows of 4096 to 8192 columns, where 128x128 tiles with
+// four stages are 4 to 6 % faster than 128x112 panels; from the caches (144 cases) 2.5 %, 27 above 5 %, worst 23 and 10 % where the 128x112 panel reads a resident matrix past
+// them (128x27648x5120 35.3 us, 128x128 tiles 28.6; 128x28672x4096 27.7 and 25.1).  The cost before, rounds x
 // L (L + 550) with L = rows + columns of the tile, had no time per round and took two 128x128 tiles of a CU for two
 // rounds.  It was 2.6 % from the best, and short reductions and launches of a few rounds were slower than on the kernels
 // before that (us; before, with that cost, now): from HBM 140x16384x1024 12.2, 15.6, 12.0; 280x16384x1024 17.1, 20.4, 16.1;
