@@ -373,8 +373,8 @@ __global__ __launch_bounds__(256) void silu_mul_bwd_kernel(const uint16_t* __res
 // gradient is written once and not read back.  A workgroup forms a 128x128 tile of dgate and the one of dup beside it and
 // quantizes them in turn; the arithmetic is that of silu_mul_bwd_kernel and of the tile quantizer, so the bytes are
 // theirs.  Bound by HBM: 14.1 bytes per element of dh instead of 18.1 in two launches.  All 24 loads of a thread go out
-// first; nobody reads gate, up, dh and dgu again soon, so they pass the memory-side cache.  [16384, 14336], us: two launches 907, this
-// 760 (4.4 TB/s); small calls lose by it (14.4 -> 18.8 at [512, 3072]: the caller has the line).
+// first; nobody reads gate, up, dh and dgu again soon, so they pass the memory-side cache.  Captured, us: [16384, 14336] two launches 880, this
+// 726; small calls lose by it ([512, 3072] 13.4 -> 18.8: the caller has the line).
 __global__ __launch_bounds__(256) void silu_mul_bwd_quant_kernel(const uint16_t* __restrict__ gate,
                                                                  const uint16_t* __restrict__ up, long ld,
                                                                  const uint16_t* __restrict__ dh, long M, long K,

@@ -110,12 +110,13 @@ __device__ __forceinline__ int xcd_contiguous_id(int b, int n) {
 // (256 registers: no room for a tail of three) 28672x4096 over 16384 tokens 1886 / 1789, 5120x5120 over 6016 183 / 172.  256x128
 // 1024x5120x27648 195 / 180, 700x7168x5120 42.6 / 40.0.  128x128 WGrad 1024x5120 over 16384 tokens 157 / 144, four stages 1024x4096
 // 94.5 / 91.  128x128 block scales, one wave per SIMD: waits for its copies and not for the LDS, so a longer tail, which shortens
-// their lead, is 1-3 % slower.  Four late copies and not five: 8 shapes with four stages 0 to 2.6 % faster (777x4096x4096 24.5 -> 24.0).
-// Two stages, the columns' operand first: 28 shapes 2.3 % faster on average than the rows' first (3619x17280x640 77.3 -> 74.4,
-// 7645x5248x2560 135.6 -> 132.8) and none slower by more than 0.4 %, where the rows' operand is in the caches, as the operator in front leaves it; from HBM
-// too, 1.7 %, and up to 3.5 % slower where a last round of a few tiles runs alone on its CUs (4821x3456x4608 106.9 -> 110.6).
-// 128x64, two late copies and not five: 3.1 to 4.1 % faster on 7 shapes (256x8192x1024 7.82 -> 7.52), the columns' operand first alone
-// the same or 1 % slower.  256x256 on one block of rows: 256x55296x5120 91.3 -> 87.2, with its rows from HBM as well 94.3 -> 98.7.
+// their lead, is 1-3 % slower.  Four late copies and not five: 8 shapes with four stages 0 to 2.6 % faster (777x4096x4096 24.5 ->
+// 24.0). Two stages, the columns' operand first: 28 shapes 2.3 % faster on average than the rows' first (3619x17280x640 77.3 -> 74.4,
+// 7645x5248x2560 135.6 -> 132.8) and none slower by more than 0.4 %, where the rows' operand is in the caches, as the operator in
+// front leaves it; from HBM too, 1.7 %, and up to 3.5 % slower where a last round of a few tiles runs alone on its CUs (4821x3456x4608
+// 106.9 -> 110.6). 128x64, two late copies and not five: 3.1 to 4.1 % faster on 7 shapes (256x8192x1024 7.82 -> 7.52), the columns'
+// operand first alone the same or 1 % slower.  256x256 on one block of rows: 256x55296x5120 91.3 -> 87.2, with its rows from HBM as
+// well 94.3 -> 98.7.
 // fma lag 3: a wave alone on its SIMD issues an MFMA every 34.5 cycles instead of 39 in a register-only loop, two waves 3 % more of
 // them; in the kernel nothing (one wave waits for its copies) or up to 2 % slower.
 //

@@ -97,14 +97,15 @@ constexpr int chunk_swap(int r) { return 16 * (r >> 3); }
 // choice and not the time comes out right: it was 0.7 % from the best tile on average.  They were fitted before the tile kernel's
 // scales travelled in chunks and its steps took their present order, and before the panels read weights past the caches and
 // activations first.  On these kernels, activations in the caches: weights from HBM (256 cases, 16 matrices of 1024 to 55296
-// columns, 20 to 1000 rows) 1.0 % from the best on average, 10 above 5 %, worst 100x11008x2048 8 % (128x64, not 64x112) and 140 rows of
-// 5120 columns x 5120 and 27648 6 and 5 % (64x64, not 48x64), and 400 to 700 rows of 4096 to 8192 columns, where 128x128 tiles with
-// four stages are 4 to 6 % faster than 128x112 panels; from the caches (144 cases) 2.5 %, 27 above 5 %, worst 23 and 10 % where the 128x112 panel reads a resident matrix past
-// them (128x27648x5120 35.3 us, 128x128 tiles 28.6; 128x28672x4096 27.7 and 25.1).  The cost before, rounds x
-// L (L + 550) with L = rows + columns of the tile, had no time per round and took two 128x128 tiles of a CU for two
-// rounds.  It was 2.6 % from the best, and short reductions and launches of a few rounds were slower than on the kernels
-// before that (us; before, with that cost, now): from HBM 140x16384x1024 12.2, 15.6, 12.0; 280x16384x1024 17.1, 20.4, 16.1;
-// 555x28672x4096 120, 126, 96; from the caches 440x4096x4096 17.4, 19.7, 16.7; 1000x5120x27648 195, 226, 175.
+// columns, 20 to 1000 rows) 1.0 % from the best on average, 10 above 5 %, worst 100x11008x2048 8 % (128x64, not 64x112) and 140
+// rows of 5120 columns x 5120 and 27648 6 and 5 % (64x64, not 48x64), and 400 to 700 rows of 4096 to 8192 columns, where 128x128
+// tiles with four stages are 4 to 6 % faster than 128x112 panels; from the caches (144 cases) 2.5 %, 27 above 5 %, worst 23 and
+// 10 % where the 128x112 panel reads a resident matrix past them (128x27648x5120 35.3 us, 128x128 tiles 28.6; 128x28672x4096 27.7
+// and 25.1).  The cost before, rounds x L (L + 550) with L = rows + columns of the tile, had no time per round and took two
+// 128x128 tiles of a CU for two rounds.  It was 2.6 % from the best, and short reductions and launches of a few rounds were
+// slower than on the kernels before that (us; before, with that cost, now): from HBM 140x16384x1024 12.2, 15.6, 12.0;
+// 280x16384x1024 17.1, 20.4, 16.1; 555x28672x4096 120, 126, 96; from the caches 440x4096x4096 17.4, 19.7, 16.7; 1000x5120x27648
+// 195, 226, 175.
 inline long tile_time(const GemmTile& c, long I, long J, long G, long cus) {
     const long rounds = ceil_div(ceil_div(I, c.bm) * ceil_div(J, c.bn), cus);
     if (c.kernel == kTileSmall)          // the two tiles of a CU run together

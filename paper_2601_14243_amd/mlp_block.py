@@ -25,8 +25,9 @@ from . import binding as jet
 #   384   2048x3072  31.0 / 31.3  (29.4 / 31.4)     896   1024x14336  59.5 / 57.2  (54.3 / 55.1)    3584   4096x14336  220 / 190    (219 / 161)
 #   448   512x14336  33.9 / 32.4  (32.4 / 31.7)    1024   2048x8192   67.6 / 61.1  (59.3 / 59.5)   14336  16384x14336  880 / 726    (840 / 627)
 #   512   1024x8192  36.9 / 34.1  (35.0 / 33.6)    1024   16384x1024  66.7 / 60.8  (60.1 / 56.9)
-# Below 400 tiles one call loses (captured 512x8192, 256 tiles, 23.4 / 21.7 apart); from there to the line it is 2 to 9 % faster in a captured block and 5 % faster to 6 % slower in one
-# that is not, where the second call's launch hides behind the first; from the line on neither loses.
+# Below 400 tiles one call loses (captured 512x8192, 256 tiles, 23.4 / 21.7 apart); from there to the line it is 2 to 9 % faster
+# in a captured block and 5 % faster to 6 % slower in one that is not, where the second call's launch hides behind the first; from
+# the line on neither loses.
 QUANT_IN_BWD_FROM = 1024 * 128 * 128
 
 
